@@ -1298,8 +1298,30 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
 // MCUs of one MCU row, kPixBlocks data units at most, transforms them in LDS and writes the pixel
 // rectangle they cover with row-contiguous stores.
 
-constexpr int kBlkStride = 72;  // floats per data unit in LDS: 8 rows of 9 (one pad per row)
+// Floats per data unit in LDS: 8 rows of 9 (one pad per row) and one more, so that lanes that hold the same row of
+// neighbouring units (the output loops) start in different banks (73 is odd; 72 put 64 of them into 8 banks).
+constexpr int kBlkStride = 73;
 __device__ __constant__ uint8_t c_zigzag[64] = JPGD_ZIGZAG_LITERAL;
+
+// One row of a data unit behind the column pass: its eight samples, level shift applied.
+__device__ __forceinline__ void row_samples(const float* b, float (&v)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = b[e];
+    v[0] += kLevelShiftDc;  // the level shift of +128 on all eight outputs, as one addition to the row's DC term
+    idct8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
+}
+
+// The first nbytes (at most 4 * NW) bytes of w.  Full groups leave as wide stores at any alignment.
+template <int NW>
+__device__ __forceinline__ void put_bytes(uint8_t* dst, const uint32_t (&w)[NW], uint32_t nbytes) {
+    if (nbytes == 4u * NW) {
+        __builtin_memcpy(dst, w, 4 * NW);
+        return;
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < 4u * NW; ++e)
+        if (e < nbytes) dst[e] = (uint8_t)(w[e >> 2] >> (8u * (e & 3u)));
+}
 
 __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
     __shared__ float blk[kPixBlocks * kBlkStride];
@@ -1357,7 +1379,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         tile[zo[7]] = (float)((int32_t)raw.w >> 16) * qb.w;
     }
     __syncthreads();
-    // columns, then rows
+    // columns
     for (uint32_t j = t; j < nblk * 8u; j += kWG) {
         float* b = blk + (j >> 3) * kBlkStride + (j & 7u);
         float v0 = b[0], v1 = b[9], v2 = b[18], v3 = b[27], v4 = b[36], v5 = b[45], v6 = b[54], v7 = b[63];
@@ -1365,77 +1387,61 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         b[0] = v0; b[9] = v1; b[18] = v2; b[27] = v3; b[36] = v4; b[45] = v5; b[54] = v6; b[63] = v7;
     }
     __syncthreads();
-    for (uint32_t j = t; j < nblk * 8u; j += kWG) {
-        float* b = blk + (j >> 3) * kBlkStride + (j & 7u) * 9u;
-        float v0 = b[0], v1 = b[1], v2 = b[2], v3 = b[3], v4 = b[4], v5 = b[5], v6 = b[6], v7 = b[7];
-        v0 += kLevelShiftDc;  // the level shift of +128 on all eight outputs, as one addition to the row's DC term
-        idct8(v0, v1, v2, v3, v4, v5, v6, v7);
-        b[0] = v0; b[1] = v1; b[2] = v2; b[3] = v3; b[4] = v4; b[5] = v5; b[6] = v6; b[7] = v7;
-    }
-    __syncthreads();
 
-    // output
-    // (sampling factors are 1 or 2: shifts instead of divisions; the one division by a free number, the
-    // groups per row, goes through a reciprocal that is exact for the few hundred items of a workgroup)
+    // Rows and output in one step: a lane transforms one row of a data unit and turns the eight samples into bytes,
+    // without a way back through LDS.  Only the chroma rows of subsampled images, which several lanes need, are
+    // transformed in place first.
+    // (sampling factors are 1 or 2: shifts instead of divisions; the one division by a free number, the groups per
+    // row, goes through a reciprocal that is exact for the few hundred items of a workgroup; all factors are far
+    // under 2^24: the 24-bit multiply runs at full rate, the 32-bit one at a quarter)
     const uint32_t hs = D.hs, vs = D.vs, ncomp = D.ncomp;
     const uint32_t lhs = hs >> 1, lvs = vs >> 1;          // log2 of 1 or 2
     const uint32_t mcu_w = 8u * hs, mcu_h = 8u * vs, lmw = 3u + lhs;
-    const uint32_t region_w = nm * mcu_w;
-    const uint32_t groups_per_row = region_w >> 2;
-    const float inv_gpr = 1.0f / (float)groups_per_row;
+    const uint32_t rows8 = nm * hs;                       // groups of 8 samples per luma row of the workgroup
+    const float inv_rows8 = 1.0f / (float)rows8;
     uint8_t* pix = P.pixels + D.pix_off;
     const uint32_t x_base = m0 * mcu_w, y_base = mrow * mcu_h;
-    if (P.planar) {
-        // The paper's own output (Section 3: one array per colour channel): every component at its own
+    auto pack8 = [](uint32_t (&w)[2], const float (&v)[8]) {
+        w[0] = pack_u8(v[0], 0u, 0u); w[0] = pack_u8(v[1], 1u, w[0]); w[0] = pack_u8(v[2], 2u, w[0]); w[0] = pack_u8(v[3], 3u, w[0]);
+        w[1] = pack_u8(v[4], 0u, 0u); w[1] = pack_u8(v[5], 1u, w[1]); w[1] = pack_u8(v[6], 2u, w[1]); w[1] = pack_u8(v[7], 3u, w[1]);
+    };
+    if (P.planar || ncomp == 1u) {
+        // Gray, or the paper's own output (Section 3: one array per colour channel): every component at its own
         // resolution, rounded and clamped.  Luma plane first, then Cb, then Cr.
-        auto put4 = [&](uint8_t* dst, const float* src, uint32_t left, bool word_ok) {
-            uint32_t w = pack_u8(src[0], 0u, 0u);
-            w = pack_u8(src[1], 1u, w); w = pack_u8(src[2], 2u, w); w = pack_u8(src[3], 3u, w);
-            if (left >= 4u && word_ok) {
-                *reinterpret_cast<uint32_t*>(dst) = w;
-            } else {
-                dst[0] = (uint8_t)w;
-                if (left > 1u) dst[1] = (uint8_t)(w >> 8);
-                if (left > 2u) dst[2] = (uint8_t)(w >> 16);
-                if (left > 3u) dst[3] = (uint8_t)(w >> 24);
-            }
-        };
-        const bool y_words = (D.width & 3u) == 0u && (reinterpret_cast<size_t>(pix) & 3u) == 0u;
-        for (uint32_t j = t; j < groups_per_row * mcu_h; j += kWG) {
-            const uint32_t py = (uint32_t)(((float)j + 0.5f) * inv_gpr), px0 = (j - py * groups_per_row) * 4u;
+        for (uint32_t j = t; j < rows8 * mcu_h; j += kWG) {
+            const uint32_t py = (uint32_t)(((float)j + 0.5f) * inv_rows8), px0 = (j - __umul24(py, rows8)) * 8u;
             const uint32_t gy = y_base + py, gx0 = x_base + px0;
             if (gy >= D.height || gx0 >= D.width) continue;
-            const uint32_t m = px0 >> lmw, xin = px0 & (mcu_w - 1u);
-            const float* yb = blk + (m * upm + (py >> 3) * hs + (xin >> 3)) * kBlkStride + (py & 7u) * 9u + (xin & 7u);
-            put4(pix + (size_t)gy * D.width + gx0, yb, D.width - gx0, y_words);
+            const uint32_t m = px0 >> lmw, xin = px0 & (mcu_w - 1u);  // xin: 0, or 8 in the right half of a 16-wide MCU
+            float v[8];
+            row_samples(blk + __umul24(__umul24(m, upm) + __umul24(py >> 3, hs) + (xin >> 3), (uint32_t)kBlkStride) + (py & 7u) * 9u, v);
+            uint32_t w[2];
+            pack8(w, v);
+            put_bytes<2>(pix + (size_t)gy * D.width + gx0, w, min(8u, D.width - gx0));
         }
         if (ncomp == 3u) {
             const uint32_t cw = (D.width + hs - 1u) >> lhs, ch = (D.height + vs - 1u) >> lvs;  // chroma plane size
             uint8_t* cplane = pix + (size_t)D.width * D.height;
-            const bool c_words = (cw & 3u) == 0u && (reinterpret_cast<size_t>(cplane) & 3u) == 0u && (((size_t)cw * ch) & 3u) == 0u;
-            const uint32_t gpr_c = nm * 2u;  // groups of 4 samples per chroma row of this workgroup
-            for (uint32_t j = t; j < gpr_c * 16u; j += kWG) {
-                const uint32_t c = j >= gpr_c * 8u ? 1u : 0u;
-                const uint32_t r = j - c * gpr_c * 8u;
-                const uint32_t py = (uint32_t)(((float)r + 0.5f) / (float)gpr_c), g = r - py * gpr_c;
-                const uint32_t m = g >> 1, xin = (g & 1u) * 4u;
-                const uint32_t gy = mrow * 8u + py, gx0 = (m0 + m) * 8u + xin;
+            const float inv_nm = 1.0f / (float)nm;
+            for (uint32_t j = t; j < nm * 16u; j += kWG) {
+                const uint32_t c = j >= nm * 8u ? 1u : 0u;
+                const uint32_t r = j - c * nm * 8u;
+                const uint32_t py = (uint32_t)(((float)r + 0.5f) * inv_nm), m = r - __umul24(py, nm);
+                const uint32_t gy = mrow * 8u + py, gx0 = (m0 + m) * 8u;
                 if (gy >= ch || gx0 >= cw) continue;
-                const float* cb = blk + (m * upm + hs * vs + c) * kBlkStride + py * 9u + xin;
-                put4(cplane + (size_t)c * cw * ch + (size_t)gy * cw + gx0, cb, cw - gx0, c_words);
+                float v[8];
+                row_samples(blk + __umul24(__umul24(m, upm) + hs * vs + c, (uint32_t)kBlkStride) + py * 9u, v);
+                uint32_t w[2];
+                pack8(w, v);
+                put_bytes<2>(cplane + (size_t)c * cw * ch + (size_t)gy * cw + gx0, w, min(8u, cw - gx0));
             }
         }
         return;
     }
-    // RGB or gray: a lane produces the 8 (gray) or 24 bytes of eight horizontally adjacent pixels -- one row of a
-    // luma data unit -- as whole words.  The colour terms of a chroma sample are computed once (a sample serves two
-    // of the pixels when chroma is subsampled horizontally); each output sample then costs one addition and one
-    // conversion that also puts the byte in its place.
-    // (all factors below are far under 2^24: the 24-bit multiply runs at full rate, the 32-bit one at a quarter)
-    const bool aligned = (((size_t)D.width * ncomp) & 3u) == 0u && ((reinterpret_cast<size_t>(pix)) & 3u) == 0u;
-    const uint32_t row_bytes = D.width * ncomp;  // a frame header holds the width in 16 bits
-    const uint32_t rows8 = region_w >> 3;         // groups of 8 pixels per row of the workgroup's rectangle
-    const float inv_rows8 = 1.0f / (float)rows8;
+    // RGB: a lane produces the 24 bytes of eight horizontally adjacent pixels -- one row of a luma data unit.  The
+    // colour terms of a chroma sample are computed once (a sample serves two of the pixels when chroma is subsampled
+    // horizontally); each output sample then costs one addition and one conversion that also puts the byte in its place.
+    const uint32_t row_bytes = D.width * 3u;  // a frame header holds the width in 16 bits
     // bytes in memory: R0 G0 B0 R1 | G1 B1 R2 G2 | B2 R3 G3 B3
     auto pack12 = [](uint32_t& wa, uint32_t& wb, uint32_t& wc, float y0, float y1, float y2, float y3,
                      const ChromaTerms& c0, const ChromaTerms& c1, const ChromaTerms& c2, const ChromaTerms& c3) {
@@ -1444,54 +1450,53 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         wb = pack_u8(y2 + c2.r, 2u, wb); wb = pack_u8(y2 + c2.g, 3u, wb); wc = pack_u8(y2 + c2.b, 0u, wc);
         wc = pack_u8(y3 + c3.r, 1u, wc); wc = pack_u8(y3 + c3.g, 2u, wc); wc = pack_u8(y3 + c3.b, 3u, wc);
     };
+    if (hs * vs != 1u) {
+        for (uint32_t j = t; j < nm * 16u; j += kWG) {  // j: MCU, Cb or Cr, row
+            float* b = blk + __umul24(__umul24(j >> 4, upm) + hs * vs + ((j >> 3) & 1u), (uint32_t)kBlkStride) + (j & 7u) * 9u;
+            float v[8];
+            row_samples(b, v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b[e] = v[e];
+        }
+        __syncthreads();
+    }
     for (uint32_t j = t; j < rows8 * mcu_h; j += kWG) {
         const uint32_t py = (uint32_t)(((float)j + 0.5f) * inv_rows8), px0 = (j - __umul24(py, rows8)) * 8u;
         const uint32_t gy = y_base + py, gx0 = x_base + px0;
         if (gy >= D.height || gx0 >= D.width) continue;
-        const uint32_t m = px0 >> lmw, xin = px0 & (mcu_w - 1u);  // xin: 0, or 8 in the right half of a 16-wide MCU
+        const uint32_t m = px0 >> lmw, xin = px0 & (mcu_w - 1u);
         const uint32_t mu = __umul24(m, upm);
-        const float* yb = blk + __umul24(mu + __umul24(py >> 3, hs) + (xin >> 3), (uint32_t)kBlkStride) + (py & 7u) * 9u;
-        const float y0 = yb[0], y1 = yb[1], y2 = yb[2], y3 = yb[3], y4 = yb[4], y5 = yb[5], y6 = yb[6], y7 = yb[7];
-        uint32_t w0 = 0u, w1 = 0u, w2 = 0u, w3 = 0u, w4 = 0u, w5 = 0u;
-        if (ncomp == 1u) {
-            w0 = pack_u8(y0, 0u, w0); w0 = pack_u8(y1, 1u, w0); w0 = pack_u8(y2, 2u, w0); w0 = pack_u8(y3, 3u, w0);
-            w1 = pack_u8(y4, 0u, w1); w1 = pack_u8(y5, 1u, w1); w1 = pack_u8(y6, 2u, w1); w1 = pack_u8(y7, 3u, w1);
+        float y[8];
+        row_samples(blk + __umul24(mu + __umul24(py >> 3, hs) + (xin >> 3), (uint32_t)kBlkStride) + (py & 7u) * 9u, y);
+        const float* cbb = blk + __umul24(mu + hs * vs, (uint32_t)kBlkStride) + (py >> lvs) * 9u + (xin >> lhs);
+        const float* crb = cbb + kBlkStride;
+        uint32_t w[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+        if (hs == 2u) {  // (the cases are written out so that none pays register moves for another)
+            const ChromaTerms a = chroma_terms(cbb[0], crb[0]), b = chroma_terms(cbb[1], crb[1]);
+            pack12(w[0], w[1], w[2], y[0], y[1], y[2], y[3], a, a, b, b);
+            const ChromaTerms c = chroma_terms(cbb[2], crb[2]), d = chroma_terms(cbb[3], crb[3]);
+            pack12(w[3], w[4], w[5], y[4], y[5], y[6], y[7], c, c, d, d);
         } else {
-            const float* cbb = blk + __umul24(mu + hs * vs, (uint32_t)kBlkStride) + (py >> lvs) * 9u + (xin >> lhs);
-            const float* crb = cbb + kBlkStride;
-            if (hs == 2u) {  // (the two cases are written out so that neither pays register moves for the other)
-                const ChromaTerms a = chroma_terms(cbb[0], crb[0]), b = chroma_terms(cbb[1], crb[1]);
-                pack12(w0, w1, w2, y0, y1, y2, y3, a, a, b, b);
-                const ChromaTerms c = chroma_terms(cbb[2], crb[2]), d = chroma_terms(cbb[3], crb[3]);
-                pack12(w3, w4, w5, y4, y5, y6, y7, c, c, d, d);
+            float cb[8], cr[8];
+            if (vs == 1u) {
+                row_samples(cbb, cb);
+                row_samples(crb, cr);
             } else {
-                {
-                    const ChromaTerms a = chroma_terms(cbb[0], crb[0]), b = chroma_terms(cbb[1], crb[1]);
-                    const ChromaTerms c = chroma_terms(cbb[2], crb[2]), d = chroma_terms(cbb[3], crb[3]);
-                    pack12(w0, w1, w2, y0, y1, y2, y3, a, b, c, d);
-                }
-                {
-                    const ChromaTerms a = chroma_terms(cbb[4], crb[4]), b = chroma_terms(cbb[5], crb[5]);
-                    const ChromaTerms c = chroma_terms(cbb[6], crb[6]), d = chroma_terms(cbb[7], crb[7]);
-                    pack12(w3, w4, w5, y4, y5, y6, y7, a, b, c, d);
-                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { cb[e] = cbb[e]; cr[e] = crb[e]; }
+            }
+            {
+                const ChromaTerms a = chroma_terms(cb[0], cr[0]), b = chroma_terms(cb[1], cr[1]);
+                const ChromaTerms c = chroma_terms(cb[2], cr[2]), d = chroma_terms(cb[3], cr[3]);
+                pack12(w[0], w[1], w[2], y[0], y[1], y[2], y[3], a, b, c, d);
+            }
+            {
+                const ChromaTerms a = chroma_terms(cb[4], cr[4]), b = chroma_terms(cb[5], cr[5]);
+                const ChromaTerms c = chroma_terms(cb[6], cr[6]), d = chroma_terms(cb[7], cr[7]);
+                pack12(w[3], w[4], w[5], y[4], y[5], y[6], y[7], a, b, c, d);
             }
         }
-        uint8_t* dst = pix + (size_t)gy * row_bytes + __umul24(gx0, ncomp);
-        if (gx0 + 8u <= D.width && aligned) {
-            uint32_t* d32 = reinterpret_cast<uint32_t*>(dst);
-            d32[0] = w0;
-            d32[1] = w1;
-            if (ncomp == 3u) {
-                d32[2] = w2; d32[3] = w3; d32[4] = w4; d32[5] = w5;
-            }
-        } else {
-            const uint32_t nbytes = min(8u, D.width - gx0) * ncomp;
-            for (uint32_t e = 0; e < nbytes; ++e) {
-                const uint32_t w = e < 4u ? w0 : (e < 8u ? w1 : (e < 12u ? w2 : (e < 16u ? w3 : (e < 20u ? w4 : w5))));
-                dst[e] = (uint8_t)(w >> (8u * (e & 3u)));
-            }
-        }
+        put_bytes<6>(pix + (size_t)gy * row_bytes + __umul24(gx0, 3u), w, min(8u, D.width - gx0) * 3u);
     }
 }
 
