@@ -95,13 +95,19 @@ __device__ __forceinline__ uint32_t find_image(const Params& P, uint32_t wg, F f
     return lo;
 }
 
+// v plus the value some lanes further down (data-parallel moves between the lanes of a wavefront: no LDS round trip;
+// lanes without a source add 0).  All 64 lanes must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const uint32_t lane = threadIdx.x & 63u;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t o = __shfl_up(v, d, 64);
-        if (lane >= (uint32_t)d) v += o;
-    }
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1, :2, :4, :8 inside the rows of 16 lanes
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);  // row_bcast:15: rows 1 and 3 add the last lane of the row before them
+    v = dpp_add<0x143, 0xC>(v);  // row_bcast:31: rows 2 and 3 add lane 31
     return v;
 }
 
@@ -260,41 +266,68 @@ __device__ __forceinline__ uint32_t pack_dc2(int64_t acc) {
 // bytes of such a marker are dropped too, and the byte that follows it is the first of an interval.  All
 // decisions are local (one byte back, one byte ahead).
 
+// Four bytes at a time: 0x80 in every byte of x that is zero (exact, no carry from byte to byte).
+__device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {
+    return ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
+}
+// 0x80 in the first n bytes of word k of a lane's four
+__device__ __forceinline__ uint32_t first_bytes(uint32_t n, uint32_t k) {
+    const uint32_t m = n <= 4u * k ? 0u : min(n - 4u * k, 4u);
+    return m == 4u ? 0x80808080u : 0x80808080u & ((1u << (8u * m)) - 1u);
+}
+__device__ __forceinline__ uint32_t count4(const uint32_t (&m)[4]) {
+    return (uint32_t)(__popc(m[0]) + __popc(m[1]) + __popc(m[2]) + __popc(m[3]));
+}
+
 struct UnstuffLane {
     uint32_t bytes[4];  // 16 input bytes
-    uint32_t keep_mask; // bit j set = byte j is kept
-    uint32_t mark_mask; // bit j set = byte j is the second byte of a restart marker
+    uint32_t drop[4];   // 0x80 in every byte that is not kept (bytes past the end among them)
+    uint32_t mark[4];   // 0x80 in every byte that is the second of a restart marker
     uint32_t nvalid;    // bytes of this lane that exist
 };
 
 // pos is a multiple of 16.  A lane that holds any byte loads its whole 16-byte word (the input is readable up
-// to the next multiple of 16); bytes past the end are masked out.  No private array is indexed with a variable:
+// to the next multiple of 16); bytes past the end are masked out.  The bytes are looked at four at a time, beside
+// the word that holds the byte before each of them: about 30 instructions for 16 bytes, where one byte after the
+// other took 170 and filled three quarters of the chip's issue slots.  No private array is indexed with a variable:
 // the compiler would move such an array to LDS and read the dispatch packet for the workgroup's shape, and that
 // packet lives in host memory -- measured at 2 to 11 microseconds per wavefront when a whole grid asks at once.
+// All 64 lanes of the wavefront call this together.
 __device__ __forceinline__ UnstuffLane unstuff_load(const uint8_t* scan, uint32_t n, uint32_t pos, bool restart) {
     UnstuffLane r;
     r.nvalid = pos >= n ? 0u : (n - pos < 16u ? n - pos : 16u);
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (r.nvalid) v = *reinterpret_cast<const uint4*>(scan + pos);
-    r.bytes[0] = v.x; r.bytes[1] = v.y; r.bytes[2] = v.z; r.bytes[3] = v.w;
-    uint32_t prev = (pos > 0u && r.nvalid) ? scan[pos - 1u] : 0u;
-    const uint32_t after = (restart && pos + 16u < n) ? scan[pos + 16u] : 0u;
-    uint32_t mask = 0u, marks = 0u;
-#pragma unroll
-    for (uint32_t j = 0; j < 16u; ++j) {
-        const uint32_t b = (r.bytes[j >> 2] >> (8u * (j & 3u))) & 255u;
-        const uint32_t nx = j < 15u ? (r.bytes[(j + 1u) >> 2] >> (8u * ((j + 1u) & 3u))) & 255u : after;
-        const bool exists = j < r.nvalid;
-        const bool nx_exists = j + 1u < r.nvalid || (j == 15u && pos + 16u < n);
-        const bool rst2 = restart && prev == 255u && (b & 0xF8u) == 0xD0u;                // RSTm, second byte
-        const bool rst1 = restart && b == 255u && nx_exists && (nx & 0xF8u) == 0xD0u;     // RSTm, first byte
-        const bool drop = (b == 0u && prev == 255u) || rst1 || rst2;
-        if (exists && !drop) mask |= 1u << j;
-        if (exists && rst2) marks |= 1u << j;
-        prev = b;
+    uint32_t before = 0u;
+    if (r.nvalid) {
+        v = *reinterpret_cast<const uint4*>(scan + pos);
+        if ((threadIdx.x & 63u) == 0u && pos > 0u) before = (uint32_t)scan[pos - 1u] << 24;
     }
-    r.keep_mask = mask;
-    r.mark_mask = marks;
+    r.bytes[0] = v.x; r.bytes[1] = v.y; r.bytes[2] = v.z; r.bytes[3] = v.w;
+    // the last word of the lane before (wave_shr:1); the first lane keeps what it loaded
+    before = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)v.w, 0x138, 0xF, 0xF, false);
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+        const uint32_t prev = __builtin_amdgcn_alignbyte(r.bytes[k], k ? r.bytes[k - 1u] : before, 3u);
+        r.drop[k] = zero_bytes(r.bytes[k] | ~prev);  // 0x00 behind 0xFF
+        r.mark[k] = 0u;
+    }
+    if (restart) {
+        const uint32_t after = pos + 16u < n ? scan[pos + 16u] : 0u;
+        const uint32_t nfollowed = pos + 16u < n ? 16u : (r.nvalid ? r.nvalid - 1u : 0u);  // bytes that have a next one
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t w = r.bytes[k];
+            const uint32_t prev = __builtin_amdgcn_alignbyte(w, k ? r.bytes[k - 1u] : before, 3u);
+            const uint32_t next = __builtin_amdgcn_alignbyte(k < 3u ? r.bytes[k + 1u] : after, w, 1u);
+            r.mark[k] = zero_bytes(((w ^ 0xD0D0D0D0u) & 0xF8F8F8F8u) | ~prev) & first_bytes(r.nvalid, k);   // RSTm, second byte
+            const uint32_t rst1 = zero_bytes(((next ^ 0xD0D0D0D0u) & 0xF8F8F8F8u) | ~w) & first_bytes(nfollowed, k);  // first byte
+            r.drop[k] |= r.mark[k] | rst1;
+        }
+    }
+    if (r.nvalid < 16u) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) r.drop[k] |= 0x80808080u & ~first_bytes(r.nvalid, k);
+    }
     return r;
 }
 
@@ -312,20 +345,18 @@ __global__ __launch_bounds__(kWG) void k_unstuff_count(Params P) {
     const uint8_t* scan = P.scans + D.scan_off;
     const uint32_t pos = lt * (uint32_t)kUnstuffTile + threadIdx.x * 16u;
     const bool restart = D.restart != 0u;
-    UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, restart);
-    uint32_t removed = u.nvalid - (uint32_t)__popc(u.keep_mask);
-    uint32_t total;
-    wg_excl_scan(removed, scratch, &total);
-    uint32_t marks = 0u;
+    const UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, restart);
     if (restart) {
         // this tile's share of the interval-start bitmap is cleared here, the scatter kernel sets the bits;
         // the markers are counted so that the write pass can tell whether all intervals are there
         uint32_t* bm = P.bmap + D.bmap_off + lt * 128u;
         if (threadIdx.x < 128u) bm[threadIdx.x] = 0u;
         if (lt == D.ntiles - 1u && threadIdx.x < 128u) bm[128u + threadIdx.x] = 0u;
-        wg_excl_scan((uint32_t)__popc(u.mark_mask), scratch, &marks);
     }
-    if (threadIdx.x == 0) P.tile_cnt[wg] = total | (marks << 16);  // at most 4096 and 2048
+    // bytes removed in the low half, markers in the high half: at most 4096 and 2048 in a tile
+    uint32_t total;
+    wg_excl_scan((u.nvalid + count4(u.drop) - 16u) | (count4(u.mark) << 16), scratch, &total);
+    if (threadIdx.x == 0) P.tile_cnt[wg] = total;
 }
 
 // one workgroup per image: per-tile counts -> bytes removed before each tile; unstuffed length and
@@ -366,8 +397,8 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scan(Params P) {
 }
 
 __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
-    __shared__ uint32_t scratch[8];
-    __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffTile + 16];
+    __shared__ uint32_t scratch[16];
+    __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffTile + 32];
     const uint32_t wg = blockIdx.x;
     const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.tile0; });
     const ImgDesc D = image_desc_uniform(P, ii);
@@ -375,59 +406,82 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     const uint8_t* scan = P.scans + D.scan_off;
     uint8_t* out = P.stream + D.stream_off;
     const uint32_t pos = lt * (uint32_t)kUnstuffTile + threadIdx.x * 16u;
-    UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, D.restart != 0u);
-    uint32_t kept = (uint32_t)__popc(u.keep_mask);
-    uint32_t T;
-    uint32_t off = wg_excl_scan(kept, scratch, &T);
-    const uint32_t lane_off = off;
-#pragma unroll
-    for (uint32_t j = 0; j < 16u; ++j)
-        if (u.keep_mask & (1u << j)) buf[off++] = (uint8_t)(u.bytes[j >> 2] >> (8u * (j & 3u)));
-    __syncthreads();
     // bytes removed before this tile: from the scan kernel, or, for images of up to 256 tiles, summed here
-    uint32_t before, nbytes;
-    if (D.ntiles <= (uint32_t)kWG) {
-        const uint32_t raw = threadIdx.x < D.ntiles ? P.tile_cnt[D.tile0 + threadIdx.x] : 0u;
-        const uint32_t v = raw & 0xFFFFu;
-        uint32_t all, markers = 0u;
-        wg_excl_scan(v, scratch, &all);
-        wg_excl_scan(threadIdx.x < lt ? v : 0u, scratch, &before);
-        if (D.restart != 0u && lt == 0u) wg_excl_scan(raw >> 16, scratch, &markers);
-        nbytes = D.scan_bytes - all;
-        if (lt == 0u && threadIdx.x == 0u) {
-            P.st[ii].markers = markers;
-            P.st[ii].nbytes = nbytes;
-            P.st[ii].nsub = (uint32_t)(((uint64_t)nbytes * 8u + (1u << P.logL) - 1u) >> P.logL);
-        }
+    const bool few_tiles = D.ntiles <= (uint32_t)kWG;
+    uint32_t raw = 0u, before = 0u, nbytes = 0u;
+    if (few_tiles) {
+        if (threadIdx.x < D.ntiles) raw = P.tile_cnt[D.tile0 + threadIdx.x];
     } else {
         before = P.tile_cnt[wg];
         nbytes = P.st[ii].nbytes;
     }
-    // output position of this tile's first kept byte
-    const uint32_t o = lt * (uint32_t)kUnstuffTile - before;
-    const uint32_t a = o & 3u;
-    const uint32_t nd = (a + T + 3u) >> 2;
-    uint32_t* out32 = reinterpret_cast<uint32_t*>(out + (o - a));
-    for (uint32_t d = threadIdx.x; d < nd; d += kWG) {
-        int32_t s0 = (int32_t)(4u * d) - (int32_t)a;
-        if (s0 >= 0 && (uint32_t)s0 + 4u <= T) {
-            uint32_t v = (uint32_t)buf[s0] | ((uint32_t)buf[s0 + 1] << 8) | ((uint32_t)buf[s0 + 2] << 16) |
-                         ((uint32_t)buf[s0 + 3] << 24);
-            out32[d] = v;
-        } else {
-            for (int32_t b = 0; b < 4; ++b) {
-                int32_t s = s0 + b;
-                if (s >= 0 && (uint32_t)s < T) out[o - a + 4u * d + (uint32_t)b] = buf[s];
-            }
+    const UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, D.restart != 0u);
+    const uint32_t kept = 16u - count4(u.drop);
+    const uint32_t inc = wave_incl_scan(kept), wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63u) == 63u) scratch[wave] = inc;
+    if (few_tiles) {
+        const uint32_t v = raw & 0xFFFFu;
+        const uint32_t all = wave_incl_scan(v), prior = wave_incl_scan(threadIdx.x < lt ? v : 0u), marks = wave_incl_scan(raw >> 16);
+        if ((threadIdx.x & 63u) == 63u) {
+            scratch[4u + wave] = all;
+            scratch[8u + wave] = prior;
+            scratch[12u + wave] = marks;
         }
     }
+    __syncthreads();
+    const uint32_t w0 = scratch[0], w1 = scratch[1], w2 = scratch[2];
+    const uint32_t T = w0 + w1 + w2 + scratch[3];
+    const uint32_t off = (wave > 0u ? w0 : 0u) + (wave > 1u ? w1 : 0u) + (wave > 2u ? w2 : 0u) + inc - kept;
+    if (few_tiles) {
+        before = scratch[8] + scratch[9] + scratch[10] + scratch[11];
+        nbytes = D.scan_bytes - (scratch[4] + scratch[5] + scratch[6] + scratch[7]);
+        if (lt == 0u && threadIdx.x == 0u) {
+            P.st[ii].markers = scratch[12] + scratch[13] + scratch[14] + scratch[15];
+            P.st[ii].nbytes = nbytes;
+            P.st[ii].nsub = (uint32_t)(((uint64_t)nbytes * 8u + (1u << P.logL) - 1u) >> P.logL);
+        }
+    }
+    // output position of this tile's first kept byte; in LDS the tile lies as far behind a multiple of 16
+    const uint32_t o = lt * (uint32_t)kUnstuffTile - before;
+    const uint32_t a = o & 15u;
+    uint8_t* dst = buf + a + off;
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+        const uint32_t w = u.bytes[k], d = u.drop[k];
+        if (d == 0u) {
+            __builtin_memcpy(dst, &w, 4);
+        } else {
+            uint8_t* q = dst;
+            if (!(d & 0x80u)) *q++ = (uint8_t)w;
+            if (!(d & 0x8000u)) *q++ = (uint8_t)(w >> 8);
+            if (!(d & 0x800000u)) *q++ = (uint8_t)(w >> 16);
+            if (!(d & 0x80000000u)) *q = (uint8_t)(w >> 24);
+        }
+        dst += 4u - (uint32_t)__popc(d);
+    }
+    __syncthreads();
+    // whole 16-byte words of the output; the first and the last one are shared with the neighbouring tiles
+    uint8_t* base = out + (o - a);
+    const uint32_t first16 = a ? 1u : 0u, last16 = (a + T) >> 4;
+    for (uint32_t d = first16 + threadIdx.x; d < last16; d += kWG)
+        reinterpret_cast<uint4*>(base)[d] = reinterpret_cast<const uint4*>(buf)[d];
+    if (threadIdx.x < 32u) {
+        const uint32_t at = threadIdx.x < 16u ? threadIdx.x : (last16 << 4) + (threadIdx.x & 15u);
+        const bool mine = threadIdx.x < 16u ? (a != 0u && at >= a && at < a + T) : (at < a + T && (last16 != 0u || a == 0u));
+        if (mine) base[at] = buf[at];
+    }
     // the byte after a restart marker starts an interval: its position in the output goes into the bitmap
-    if (u.mark_mask) {
+    if (D.restart) {
         uint32_t* bm = P.bmap + D.bmap_off;
-        for (uint32_t m = u.mark_mask; m; m &= m - 1u) {
-            const uint32_t j = (uint32_t)__ffs((int)m) - 1u;
-            const uint32_t at = o + lane_off + (uint32_t)__popc(u.keep_mask & ((1u << j) - 1u));
-            atomicOr(&bm[at >> 5], 1u << (at & 31u));
+        uint32_t at = o + off;
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            for (uint32_t m = u.mark[k]; m; m &= m - 1u) {
+                const uint32_t below = (m & (0u - m)) - 1u;  // bits of the bytes in front of the marker's
+                const uint32_t b = at + (uint32_t)__popc(~u.drop[k] & 0x80808080u & below);
+                atomicOr(&bm[b >> 5], 1u << (b & 31u));
+            }
+            at += 4u - (uint32_t)__popc(u.drop[k]);
         }
     }
     // the last tile clears what lanes may read past the end: one subsequence plus 64 bytes
