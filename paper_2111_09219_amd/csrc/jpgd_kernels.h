@@ -159,6 +159,13 @@ __device__ __forceinline__ Seg seg_shfl_up(const Seg& v, int d) {
     return o;
 }
 
+// The join of records without interval starts is four plain sums, which the lanes pass on without LDS.
+__device__ __forceinline__ Seg wave_incl_sums(const Seg& v) {
+    return Seg{wave_incl_scan(v.units), 0u, wave_incl_scan(v.d0), wave_incl_scan(v.d1), wave_incl_scan(v.d2)};
+}
+__device__ __forceinline__ void put_sums(uint32_t* s4, const Seg& v) { s4[0] = v.units; s4[1] = v.d0; s4[2] = v.d1; s4[3] = v.d2; }
+__device__ __forceinline__ Seg get_sums(const uint32_t* s4) { return Seg{s4[0], 0u, s4[1], s4[2], s4[3]}; }
+
 // exclusive scan of v over the 256 lanes of the workgroup under seg_join; *total gets the join of all.
 // scratch: 20 words of LDS.
 __device__ __forceinline__ Seg wg_excl_segscan(Seg v, uint32_t* scratch, Seg* total) {
@@ -1105,7 +1112,14 @@ __global__ __launch_bounds__(kWG) void k_group_totals(Params P) {
     SInfo r = {0u, 0u, 0u, 0u};
     if (i < nsub) r = P.sinfo[D.sub0 + i];
     Seg tot;
-    wg_excl_segscan(seg_of_record(r), scratch, &tot);
+    if (D.restart == 0u) {
+        const Seg inc = wave_incl_sums(seg_of_record(r));
+        if ((threadIdx.x & 63u) == 63u) put_sums(scratch + (threadIdx.x >> 6) * 4u, inc);
+        __syncthreads();
+        tot = seg_join(seg_join(get_sums(scratch), get_sums(scratch + 4)), seg_join(get_sums(scratch + 8), get_sums(scratch + 12)));
+    } else {
+        wg_excl_segscan(seg_of_record(r), scratch, &tot);
+    }
     if (threadIdx.x == 0) P.grp_tot[wg] = seg_pack(tot);
     // The records of a sequence are those of a decoder that entered it in the state `warm_x` holds for it (the
     // state its workgroup's warm-up lanes arrived in, or the one an inter-sequence lane started from).  If the
@@ -1153,7 +1167,7 @@ template <bool STAGED>
 __global__ __launch_bounds__(kWG) void k_write(Params P) {
     constexpr bool RST = true;  // (a variant without the restart code, as for k_sync_intra, was measured 2 % slower)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
-    __shared__ uint32_t scratch[20];
+    __shared__ uint32_t scratch[36];
     const uint32_t wg = blockIdx.x;
     const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.grp0; });
     const ImgDesc D = image_desc_uniform(P, ii);
@@ -1199,19 +1213,42 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     if (RST && D.restart) seen = stage_bitmap(bmap_img, first_word, nwords, bm_s, bm_lds);
     auto bword = [&](uint32_t k) { return bm_lds ? bm_s[k - bm_k0] : bmap_img[k]; };
     bool restart = false;  // interval starts in this group's stretch of the stream?
-    if (RST) restart = __syncthreads_or(seen != 0u) != 0;
-    else __syncthreads();
 
     // position of this lane's first data unit and its DC predictors: exclusive scan inside the group
-    // plus the group's prefix
-    Seg gp;
-    if (few_groups) {
-        wg_excl_segscan(seg_unpack(before), scratch, &gp);  // (all zero from lane lg on: the identity of the join)
+    // plus the group's prefix.  Both sums of a scan without restart intervals take lane-to-lane moves and the barrier
+    // that ends the staging; the segmented join of the others takes four more barriers.  The states the group's first
+    // subsequence starts from and its last one ends in travel the same way.
+    Seg gp = seg_zero(), grp_tot = seg_zero(), ex = seg_zero();
+    const uint32_t wave = t >> 6;
+    if (t == 0u) scratch[32] = xprev;
+    if (t == nloc - 1u) scratch[33] = mine.x;
+    if (D.restart == 0u) {
+        const Seg inc = wave_incl_sums(seg_of_record(mine));
+        const Seg bef = few_groups ? wave_incl_sums(seg_unpack(before)) : seg_zero();  // (zero from lane lg on)
+        if ((t & 63u) == 63u) {
+            put_sums(scratch + wave * 8u, inc);
+            put_sums(scratch + wave * 8u + 4u, bef);
+        }
+        __syncthreads();
+        Seg carry = seg_zero();
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const Seg s = get_sums(scratch + k * 8u);
+            if (k < wave) carry = seg_join(carry, s);
+            grp_tot = seg_join(grp_tot, s);
+            gp = seg_join(gp, get_sums(scratch + k * 8u + 4u));
+        }
+        if (!few_groups) gp = seg_unpack(before);
+        const Seg own = seg_of_record(mine);
+        ex = seg_join(gp, carry);
+        ex.units += inc.units - own.units;
+        ex.d0 += inc.d0 - own.d0; ex.d1 += inc.d1 - own.d1; ex.d2 += inc.d2 - own.d2;
     } else {
-        gp = seg_unpack(before);
+        restart = __syncthreads_or(seen != 0u) != 0;
+        if (few_groups) wg_excl_segscan(seg_unpack(before), scratch, &gp);  // (zero from lane lg on: the identity of the join)
+        else gp = seg_unpack(before);
+        ex = seg_join(gp, wg_excl_segscan(seg_of_record(mine), scratch, &grp_tot));
     }
-    Seg grp_tot;
-    const Seg ex = seg_join(gp, wg_excl_segscan(seg_of_record(mine), scratch, &grp_tot));
     const uint32_t grp_units = grp_tot.units;
     uint32_t unit = ex.units;
     int32_t pred0 = (int32_t)ex.d0, pred1 = (int32_t)ex.d1, pred2 = (int32_t)ex.d2;
@@ -1228,8 +1265,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const bool dense = ((uint64_t)nloc << P.logL) >= (uint64_t)kDenseBitsPerUnit * grp_units;
     if (!dense) {
         const uint64_t end_all = (uint64_t)D.total_units * 64u;
-        const uint32_t x_in = i0 > 0u ? rec[i0 - 1u].x : 0u;
-        const uint32_t x_out = rec[i0 + nloc - 1u].x;
+        const uint32_t x_in = scratch[32], x_out = scratch[33];
         uint64_t a = (uint64_t)gp.units * 64u + state_z(x_in);
         uint64_t b = i0 + nloc >= nsub ? end_all : ((uint64_t)gp.units + grp_units) * 64u + state_z(x_out);
         if (i0 == 0u) a = 0u;
@@ -1246,8 +1282,8 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
             const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
             for (uint32_t k = t; k < n16; k += kWG) body[k] = zero;
         }
+        __syncthreads();  // the cleared range is in place
     }
-    __syncthreads();  // staged tables and stream are complete; the cleared range is in place
     if (!valid) return;
 
     const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
@@ -1315,7 +1351,10 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     pred0 = (int32_t)(int16_t)pred0; pred1 = (int32_t)(int16_t)pred1; pred2 = (int32_t)(int16_t)pred2;
     uint32_t flags = 0u;
     const uint32_t total = D.total_units;
-    if (unit < total && unit % D.upm != l.u) flags |= kStUnit;
+    // unit modulo the 1, 3, 4 or 6 units of an MCU
+    const uint32_t unit3 = (D.upm == 6u ? unit >> 1 : unit) % 3u;
+    const uint32_t in_mcu = D.upm == 1u ? 0u : D.upm == 4u ? unit & 3u : D.upm == 3u ? unit3 : unit3 * 2u + (unit & 1u);
+    if (unit < total && in_mcu != l.u) flags |= kStUnit;
     const uint32_t limit = (i + 1u) << P.logL;
     if (unit < total) {
         win_init(w, l.p, (l.p >> 5) - first_word, fetch);
