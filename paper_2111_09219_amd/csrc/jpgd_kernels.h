@@ -508,12 +508,13 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
 // DC symbols.  Results are those of decode_span_sync, symbol by symbol.
 
 // lane i < upm describes data unit i of the MCU: slot of its AC table (bits 0-2), slot of the DC table of the
-// unit that follows (3-5), index of that unit (6-9), bit offset of its component's field in the DC sums (10-14)
+// unit that follows (3-5), index of that unit (6-9), and where its DC differences go in the walk's two sums: shift
+// inside the first word (10-14: 0 for component 0, 16 for component 1), or the second word (bit 15, component 2)
 __device__ __forceinline__ uint32_t coop_unit_word(const Syntax& sx, uint32_t lane) {
     if (lane >= sx.upm) return 0u;
     const UnitRow r = sx.rows[lane];
     return (r.tb_ac / (uint32_t)kLutEntries) | ((r.tb_dc_next / (uint32_t)kLutEntries) << 3) | (r.next << 6) |
-           (((uint32_t)__ffs((int)r.dcmul) - 1u) << 10);
+           (r.dcmul == 1u ? 0u : r.dcmul == (1u << 15) ? 16u << 10 : 1u << 15);
 }
 
 // second-level entry of a codeword longer than the first-level index, asked for by the whole wavefront at once
@@ -533,11 +534,114 @@ __device__ __forceinline__ uint32_t coop_resolve_lane(LutPtr lut, uint32_t slot,
                ((peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u))];
 }
 
-// A table entry as the walk adds it to its packed state (coop_span_sync): bits taken (at least one) in bits 0..4
-// and zig-zag slots covered in bits 9..14; for a first-level escape nothing but bit 16, which stops the walk.
-constexpr int kCoopUnroll = 8;
-__device__ __forceinline__ uint32_t coop_step(uint32_t e) {
-    return (e & 0x8000u) ? 0x10000u : ((e & 0x7E00u) | max(e & 31u, 1u));
+// A table entry as the walk adds it to its packed state (coop_span_sync): bits taken (every entry takes at least one)
+// in bits 0..4, zig-zag slots covered in bits 9..14, and bit 15 of a first-level escape, which stops the walk.
+__device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & 0xFE1Fu; }
+
+// The chain followed through one window: S (window position and zig-zag index, see coop_span_sync), the unit word cur,
+// the slot of the next DC symbol's table, the completed units and the DC sums are advanced until the window is
+// left or a codeword is longer than the first-level index; acv holds the lanes' entries of the current unit's AC
+// table and acs their steps.
+// In assembly, because what a lone wavefront pays for is the number of instructions and taken branches, and the
+// compiler turns the loops into its own form with a set of flags around every exit: 5 instructions per AC symbol and
+// about 75 with five taken branches per change of unit, where 4 and 47 with one or two will do.  Registers only: no
+// memory is touched, and every step moves on by at least one bit, so the loop ends after at most 64 steps.
+// dc_a holds the sums of components 0 and 1 (two 16-bit fields, the lower one's sign taken off the upper one), dc_b
+// that of component 2.
+constexpr uint32_t kCoopLeft = 0u, kCoopAcEscape = 1u, kCoopDcEscape = 2u;
+__device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32_t& dc_slot, uint32_t& nb, uint32_t& dc_a,
+                                              uint32_t& dc_b, uint32_t& acv, uint32_t& acs, uint32_t e01, uint32_t e23, uint32_t peek,
+                                              uint32_t unit_word) {
+    uint32_t why, t, t2, r, r2, v;
+    asm volatile(
+        "s_nop 4\n"
+        "s_cmp_lt_u32 %[S], 0x200\n"
+        "s_cbranch_scc0 21f\n"
+        // DC symbol at position S (its zig-zag index is 0): entry of the table, its value, the component's sum
+        "20:\n"
+        "v_readlane_b32 %[r], %[e01], %[S]\n"
+        "v_readlane_b32 %[r2], %[e23], %[S]\n"
+        "v_readlane_b32 %[v], %[peek], %[S]\n"
+        "s_bitcmp1_b32 %[dcs], 1\n"
+        "s_cselect_b32 %[r], %[r2], %[r]\n"
+        "s_lshl_b32 %[t], %[dcs], 4\n"
+        "s_lshr_b32 %[r], %[r], %[t]\n"
+        "s_movk_i32 %[why], 2\n"
+        "s_bitcmp1_b32 %[r], 15\n"
+        "s_cbranch_scc1 29f\n"
+        "s_and_b32 %[t], %[r], 31\n"
+        "s_bfe_u32 %[r2], %[r], 0x40005\n"
+        "s_sub_u32 %[t], %[t], %[r2]\n"
+        "s_lshl_b32 %[v], %[v], %[t]\n"       // value bits from the top
+        "s_ashr_i32 %[v], %[v], 1\n"
+        "s_xor_b32 %[t], %[r2], 31\n"
+        "s_ashr_i32 %[v], %[v], %[t]\n"       // the field, signed (size 0: all sign)
+        "s_ashr_i32 %[t], %[v], 31\n"
+        "s_lshl_b32 %[t2], -1, %[r2]\n"
+        "s_xor_b32 %[t], %[t], %[t2]\n"
+        "s_add_i32 %[v], %[v], %[t]\n"
+        "s_add_i32 %[v], %[v], 1\n"           // the difference, as in symbol_value
+        "s_bfe_u32 %[t], %[cur], 0x5000a\n"
+        "s_lshl_b32 %[v], %[v], %[t]\n"
+        "s_bitcmp1_b32 %[cur], 15\n"
+        "s_cselect_b32 %[t], %[v], 0\n"
+        "s_cselect_b32 %[v], 0, %[v]\n"
+        "s_add_u32 %[dcb], %[dcb], %[t]\n"
+        "s_add_u32 %[dca], %[dca], %[v]\n"
+        "s_and_b32 %[r], %[r], 0x7e1f\n"
+        "s_add_u32 %[S], %[S], %[r]\n"          // the index becomes 1; it stays 0 where no codeword starts
+        "s_movk_i32 %[why], 0\n"
+        "s_bitcmp1_b32 %[S], 6\n"
+        "s_cbranch_scc1 29f\n"
+        "s_cmp_lt_u32 %[S], 0x200\n"
+        "s_cbranch_scc1 20b\n"
+        // AC symbols, eight in a row
+        "21:\n"
+        ".rept 8\n"
+        "v_readlane_b32 %[t], %[acs], %[S]\n"
+        "s_add_u32 %[S], %[S], %[t]\n"
+        "s_and_b32 %[t2], %[S], 0x18040\n"
+        "s_cbranch_scc1 22f\n"
+        ".endr\n"
+        "s_branch 21b\n"
+        "22:\n"
+        "s_movk_i32 %[why], 1\n"
+        "s_bitcmp1_b32 %[t], 15\n"
+        "s_cbranch_scc1 28f\n"
+        "s_movk_i32 %[why], 0\n"
+        "s_bitcmp1_b32 %[S], 15\n"
+        "s_cbranch_scc0 29f\n"                   // the window ends inside the unit
+        // unit complete: the next one's word, and its AC table if that is another
+        "s_add_u32 %[nb], %[nb], 1\n"
+        "s_and_b32 %[S], %[S], 0x7f\n"
+        "s_bfe_u32 %[t], %[cur], 0x40006\n"
+        "s_bfe_u32 %[dcs], %[cur], 0x30003\n"
+        "s_and_b32 %[r], %[cur], 7\n"
+        "v_readlane_b32 %[cur], %[uw], %[t]\n"
+        "s_and_b32 %[r2], %[cur], 7\n"
+        "s_cmp_eq_u32 %[r], %[r2]\n"
+        "s_cbranch_scc1 23f\n"
+        "s_bitcmp1_b32 %[r2], 1\n"
+        "s_cselect_b64 vcc, -1, 0\n"
+        "s_lshl_b32 %[t], %[r2], 4\n"
+        "s_nop 1\n"
+        "v_cndmask_b32 %[acv], %[e01], %[e23], vcc\n"
+        "v_lshrrev_b32 %[acv], %[t], %[acv]\n"
+        "v_and_b32 %[acs], 0xfe1f, %[acv]\n"
+        "23:\n"
+        "s_bitcmp1_b32 %[S], 6\n"
+        "s_cbranch_scc0 20b\n"
+        "s_branch 29f\n"
+        "28:\n"
+        "s_sub_u32 %[S], %[S], %[t]\n"          // an escape: the step is taken back
+        "29:\n"
+        "s_nop 1\n"
+        : [S] "+&s"(S), [cur] "+&s"(cur), [dcs] "+&s"(dc_slot), [nb] "+&s"(nb), [dca] "+&s"(dc_a),
+          [dcb] "+&s"(dc_b), [acv] "+&v"(acv),
+          [acs] "+&v"(acs), [why] "=&s"(why), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v)
+        : [e01] "v"(e01), [e23] "v"(e23), [peek] "v"(peek), [uw] "v"(unit_word)
+        : "vcc", "scc");
+    return why;
 }
 
 // What the lanes know about one window of 64 bit positions: lane j holds the 32 bits that start at position j and
@@ -588,19 +692,17 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
     uint32_t p = __builtin_amdgcn_readfirstlane(p_io);
     uint32_t u = __builtin_amdgcn_readfirstlane(u_io);
     uint32_t z = __builtin_amdgcn_readfirstlane(z_io);
-    uint32_t nb = 0u;
-    int64_t dc = 0;
+    uint32_t nb = 0u, dc_a = 0u, dc_b = 0u;
     uint32_t cur = __builtin_amdgcn_readlane(unit_word, u);
-    // slots of the current unit's AC table and of the table of the DC symbol that starts it
-    uint32_t ac_slot = cur & 7u;
+    // slot of the table of the DC symbol that starts the current unit (its AC table is in bits 0..2 of its word)
     uint32_t dc_slot = (__builtin_amdgcn_readlane(unit_word, u == 0u ? upm - 1u : u - 1u) >> 3) & 7u;
     uint32_t w0 = 0u, held = 0u;
     bool have = false;
     if (p < limit) {
         uint32_t ws = p & ~63u;
         // S = window position j (bits 0..6, at most 63 + 31) and zig-zag index z (bits 9..15, at most 63 + 63);
-        // adding a symbol's step advances both.  Bit 6 set: the window is behind us; bit 15: the data unit is
-        // complete; bit 16: the entry was an escape and nothing has been advanced.
+        // adding a symbol's step advances both.  Bit 6 set: the window is behind us; bit 15 (or 16, after the step of an
+        // escape, which is taken back): the data unit is complete.
         uint32_t S = (p - ws) | (z << 9);
         CoopWindow nxt = coop_window(ws, w0, held, have, org_word, nwords, nslots, lane, fetch, lut);
         // (Without this the compiler merges these reads with the ones inside the loop into reads at the top of the
@@ -611,57 +713,29 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
             const uint32_t e01 = nxt.e0 | (nxt.e1 << 16), e23 = nxt.e2 | (nxt.e3 << 16);
             const bool more = ws + 64u < limit;
             if (more) nxt = coop_window(ws + 64u, w0, held, have, org_word, nwords, nslots, lane, fetch, lut);
+            const uint32_t ac_slot = cur & 7u;
             uint32_t acv = ((ac_slot & 2u) ? e23 : e01) >> ((ac_slot & 1u) << 4);  // the AC entry in the low 16 bits
             uint32_t acs = coop_step(acv);
             for (;;) {
-                if ((S >> 9) == 0u) {  // DC symbol (z = 0, so S is j)
+                const uint32_t why = __builtin_amdgcn_readfirstlane(coop_walk(S, cur, dc_slot, nb, dc_a, dc_b, acv, acs, e01, e23, peek, unit_word));
+                if (__builtin_expect(why == kCoopLeft, 1)) break;
+                if (why == kCoopAcEscape) {
+                    // The codeword at this position is longer than the first-level index.  Every lane whose
+                    // entry of this table is an escape follows it up now, at once: where codewords are long
+                    // (large coefficients) a window holds several on the chain, and one look-up by all lanes
+                    // costs less than one by the chain alone.  The step is then taken again.
+                    if (acv & 0x8000u) acv = coop_resolve_lane(lut, cur & 7u, acv, peek);
+                    acs = coop_step(acv);
+                } else {
                     const uint32_t pair = __builtin_amdgcn_readlane((dc_slot & 2u) ? e23 : e01, S);
                     const uint32_t pk = __builtin_amdgcn_readlane(peek, S);
-                    uint32_t r = pair >> ((dc_slot & 1u) << 4);
-                    if (r & 0x8000u) r = coop_resolve(lut, dc_slot, r, pk);
-                    const int32_t v = symbol_value(pk, lut_total(r), lut_size(r));
-                    dc += (int64_t)v * (int64_t)(1u << ((cur >> 10) & 31u));
-                    S += coop_step(r);  // z becomes 1, or stays 0 where no codeword starts
+                    const uint32_t e = coop_resolve(lut, dc_slot, (pair >> ((dc_slot & 1u) << 4)) & 0xFFFFu, pk);
+                    const int32_t d = symbol_value(pk, lut_total(e), lut_size(e));
+                    if (cur & 0x8000u) dc_b += (uint32_t)d;
+                    else dc_a += (uint32_t)d << ((cur >> 10) & 31u);
+                    S = __builtin_amdgcn_readfirstlane(S + coop_step(e));  // the index becomes 1, or stays 0 where no codeword starts
                     if (S & 0x40u) break;
-                    if ((S >> 9) == 0u) continue;
                 }
-                // AC symbols up to the end of the unit or of the window.  A taken branch costs a lone wavefront far
-                // more than the three other instructions of a step, so the steps come eight in a row with one exit
-                // test each, and everything unusual leaves through that exit.
-                for (;;) {
-                    bool out = false;
-#pragma unroll
-                    for (int k = 0; k < kCoopUnroll; ++k) {
-                        S += __builtin_amdgcn_readlane(acs, S & 63u);
-                        if (__builtin_expect((S & 0x18040u) != 0u, 0)) {
-                            out = true;
-                            break;
-                        }
-                    }
-                    if (!out) continue;
-                    if (S & 0x10000u) {
-                        // The codeword at this position is longer than the first-level index.  Every lane whose
-                        // entry of this table is an escape follows it up now, at once: where codewords are long
-                        // (large coefficients) a window holds several on the chain, and one look-up by all lanes
-                        // costs less than one by the chain alone.  The step is then taken again.
-                        S &= 0xFFFFu;
-                        if (acv & 0x8000u) acv = coop_resolve_lane(lut, ac_slot, acv, peek);
-                        acs = coop_step(acv);
-                        continue;
-                    }
-                    break;
-                }
-                if (S & 0x8000u) {  // unit complete
-                    ++nb;
-                    S &= 0x7Fu;
-                    u = (cur >> 6) & 15u;
-                    dc_slot = (cur >> 3) & 7u;
-                    cur = __builtin_amdgcn_readlane(unit_word, u);
-                    ac_slot = cur & 7u;
-                    acv = ((ac_slot & 2u) ? e23 : e01) >> ((ac_slot & 1u) << 4);
-                    acs = coop_step(acv);
-                }
-                if (S & 0x40u) break;
             }
             if (!more) break;
             S -= 64u;  // the same position, seen from the next window
@@ -669,8 +743,12 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
         }
         p = ws + (S & 0x7Fu);
         z = S >> 9;
+        const uint32_t next = (cur >> 6) & 15u;  // of the unit the chain is in now
+        u = next == 0u ? upm - 1u : next - 1u;
     }
-    p_io = p; u_io = u; z_io = z; nb_out = nb; dc_out = dc;
+    p_io = p; u_io = u; z_io = z; nb_out = nb;
+    const int32_t d0 = (int32_t)(int16_t)(dc_a & 0xFFFFu), d1 = (int32_t)(dc_a - (uint32_t)d0) >> 16;
+    dc_out = (int64_t)d0 + ((int64_t)d1 << 15) + ((int64_t)(int32_t)dc_b << 30);
 }
 
 // ---- synchronisation, intra-sequence (paper, Algorithm 3, first loop) --------------------------------
