@@ -1383,6 +1383,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     // store of zeros onto the cleared background, once per lane at most, and saves a test per chunk)
     uint32_t cur = S_chunk;
     const uint32_t shared_first = S_low != 0u ? S_chunk : 0xFFFFFFFFu;  // the first chunk, if a neighbour holds its start
+    uint64_t first = 0ull;   // what was gathered in it; it is written at the end
     auto store8 = [&](uint32_t c, uint64_t a) { *reinterpret_cast<uint64_t*>(coef + (size_t)c * 4u) = a; };
     // elements lo .. hi-1 of chunk c, zeros included (chunks shared with a neighbouring lane, dense workgroups)
     auto put_part = [&](uint32_t c, uint64_t a, uint32_t lo, uint32_t hi) {
@@ -1402,12 +1403,8 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     };
     // the lane moves on to a later chunk: the one it leaves reaches up to its end inside the lane's range
     auto leave = [&]() {
-        if (cur == shared_first) {
-            if (dense) put_part(cur, acc, S_low, 4u);
-            else put_nonzero(cur, acc);
-        } else {
-            store8(cur, acc);
-        }
+        if (cur != shared_first) store8(cur, acc);
+        else first = acc;
     };
     auto store = [&](uint32_t k, uint32_t at, int16_t v) {
         const uint32_t ck = k * 16u + (at >> 2);
@@ -1439,6 +1436,10 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         prime(l, w, sx, lut_s);
         if (restart) decode_span_write_rst(l, w, limit, unit, total, D.restart * D.upm, pred0, pred1, pred2, sx, fetch, lut_s, store, flags, bword);
         else decode_span_write(l, w, limit, unit, total, pred0, pred1, pred2, sx, fetch, lut_s, store, flags);
+    }
+    if (cur != S_chunk && S_low != 0u) {  // the first chunk, left behind
+        if (dense) put_part(S_chunk, first, S_low, 4u);
+        else put_nonzero(S_chunk, first);
     }
     if (dense) {
         // the rest of the lane's range, up to where the next lane takes over (or the image ends)

@@ -291,21 +291,22 @@ JPGD_HD void write_symbol(Lane& l, BitWin& w, uint32_t& unit, int32_t& pred0, in
                           const Syntax& sx, Fetch fetch, LutPtr lut, Store store, uint32_t& flags) {
     const Step s = step_and_request(l, w, sx, fetch, lut);
     const bool comp0 = s.dcmul == 1u, comp1 = s.dcmul == (1u << 15);
-    const int32_t value = symbol_value(s.peek, s.total, s.size);  // 0 for an escape
-    const bool real = !s.esc;
-    const bool dc = s.is_dc && real;
+    // An escape comes out as value 0, size 0, no slot; bits that start no codeword as value 0, size 0, one bit, no
+    // slot: neither changes a predictor or passes the test of the store below.
+    const int32_t value = symbol_value(s.peek, s.total, s.size);
+    const bool dc = s.is_dc;
     const int32_t pred = (comp0 ? pred0 : (comp1 ? pred1 : pred2)) + value;
     pred0 = dc && comp0 ? pred : pred0;
     pred1 = dc && comp1 ? pred : pred1;
     pred2 = dc && !comp0 && !comp1 ? pred : pred2;
-    // where the symbol ends: a coefficient sits in the last slot it covers (after its run of zeros)
+    // where the symbol ends: a coefficient sits in the last slot it covers (after its run of zeros); a DC symbol ends
+    // in slot 0, or, if it covers none, before it
     const uint32_t zn = s.z + s.adv;
-    const uint32_t at = dc ? 0u : zn - 1u;
-    const bool has_value = dc || s.size != 0u;  // a DC symbol of size 0 still yields the predictor
-    if (real && s.adv != 0u && has_value && at < 64u) store(unit, at, (int16_t)(dc ? pred : value));
+    const uint32_t at = zn - 1u;
+    if ((dc || s.size != 0u) && at < 64u) store(unit, at, (int16_t)(dc ? pred : value));  // (a DC symbol of size 0 still yields the predictor)
     // no codeword starts with these bits; or a coefficient or a run of sixteen zeros (not end-of-block,
     // which may be coded anywhere) that runs past the end of the unit
-    const bool bad = real && (s.adv == 0u || (zn > 64u && s.adv != kAdvEob));
+    const bool bad = (s.adv == 0u && !s.esc) || (zn > 64u && s.adv != kAdvEob);
     flags |= bad ? kStInvalid : 0u;
     unit += s.done ? 1u : 0u;
 }
