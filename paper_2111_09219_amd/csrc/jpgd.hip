@@ -520,13 +520,14 @@ int t_end(Call& c, int k) {
         if ((rc_ = t_end(c, K)) != JPGD_OK) return rc_;                           \
     } while (0)
 
-// inter-sequence round, group totals, prefix of the totals
-int launch_scan(Call& c) {
+// inter-sequence round, group totals, prefix of the totals.  In the first round of a call without restart intervals the
+// totals are there already (Params::fold) and the write kernel looks at the boundaries.
+int launch_scan(Call& c, bool totals) {
     if (c.pl.bnds) {
         LAUNCH(JPGD_K_SYNC_INTER, k_sync_inter, c.pl.bnds, 64, c.lds_inter);
         ++c.rounds;
     }
-    LAUNCH(JPGD_K_SCAN_TOTALS, k_group_totals, c.pl.grps, kWG, 0);
+    if (totals) LAUNCH(JPGD_K_SCAN_TOTALS, k_group_totals, c.pl.grps, kWG, 0);
     if (c.big_groups) LAUNCH(JPGD_K_SCAN_PREFIX, k_group_scan, c.pl.h.nimg, kWG, 0);
     return JPGD_OK;
 }
@@ -673,6 +674,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.sync_waves = sync_waves;
     P.coop_max = kCoopMax * sync_waves / (uint32_t)(kWG / 64);
     P.handoff = 0u;
+    P.fold = any_restart ? 0u : 1u;
     P.verdict = nullptr;
     P.ticket = 0u;
     P.up_src = (const uint4*)c.buf_dev;
@@ -718,7 +720,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     }
     // Everything is launched in one go, write pass and pixels included: nearly every call is settled by one
     // inter-sequence round, and the host need not hear from the GPU in between.
-    if ((rc = launch_scan(c)) || (rc = launch_write(c)) || (rc = launch_report(c, c.want_pixels))) return rc;
+    if ((rc = launch_scan(c, P.fold == 0u)) || (rc = launch_write(c)) || (rc = launch_report(c, c.want_pixels))) return rc;
     return JPGD_OK;
 }
 
@@ -740,7 +742,7 @@ int finish_call(Call& c, jpgd_report* report) {
         while (pending && c.rounds < c.max_rounds) {
             ++c.redo;
             hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, c.stream, (Status*)(c.ws + c.pl.h.off_status));
-            if ((rc = launch_scan(c)) || (rc = launch_report(c, false)) || (rc = wait_verdict(c))) return rc;
+            if ((rc = launch_scan(c, true)) || (rc = launch_report(c, false)) || (rc = wait_verdict(c))) return rc;
             pending = c.verdict[2] != 0u;
         }
         const bool open = pending;

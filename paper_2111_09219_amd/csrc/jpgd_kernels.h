@@ -42,6 +42,8 @@ struct Params {
     uint32_t scale_log2;    // pixel kernel: output at 1/2^scale_log2 of the size (0..3)
     uint32_t handoff;       // intra-sequence kernel, split in two: chains left at which the first hands over (at most 64)
     uint32_t coop_max;      // intra-sequence kernel: with at most this many chains left, one wavefront per chain
+    uint32_t fold;          // calls without restart intervals: the synchronisation kernels add up the group totals as they
+                            // publish records, and k_group_totals only runs in further rounds
     uint32_t sync_waves;    // wavefronts per workgroup of that kernel: kWG / 64 that hold the lanes, the rest only take chains
     // A call with one image has the last up_wgs workgroups of k_unstuff_count copy the call's parameter block
     // (up_n16 16-byte words) from pinned host memory into the workspace: that kernel does not need the block, all
@@ -165,6 +167,37 @@ __device__ __forceinline__ Seg wave_incl_sums(const Seg& v) {
 }
 __device__ __forceinline__ void put_sums(uint32_t* s4, const Seg& v) { s4[0] = v.units; s4[1] = v.d0; s4[2] = v.d1; s4[3] = v.d2; }
 __device__ __forceinline__ Seg get_sums(const uint32_t* s4) { return Seg{s4[0], 0u, s4[1], s4[2], s4[3]}; }
+
+// Group totals added up by the synchronisation kernels (Params::fold): the workgroup of tile lt, which runs before
+// them, clears the total of group lt (a group of subsequences holds at least the bits of a tile, so an image has no
+// more groups than tiles).
+__device__ __forceinline__ void clear_group_total(const Params& P, const ImgDesc& D, uint32_t lt) {
+    if (P.fold && lt < D.ngrp_max && threadIdx.x < 4u) reinterpret_cast<uint32_t*>(P.grp_tot + D.grp0 + lt)[threadIdx.x] = 0u;
+}
+__device__ __forceinline__ void add_group_total(int4* tot, const Seg& s) {
+    uint32_t* w = reinterpret_cast<uint32_t*>(tot);
+    atomicAdd(w, s.units); atomicAdd(w + 1, s.d0); atomicAdd(w + 2, s.d1); atomicAdd(w + 3, s.d2);
+}
+__device__ __forceinline__ Seg seg_minus(const Seg& a, const Seg& b) {
+    return Seg{a.units - b.units, 0u, a.d0 - b.d0, a.d1 - b.d1, a.d2 - b.d2};
+}
+// The records of a sequence are those of a decoder that entered it in the state `warm_x` holds for it (the
+// state its workgroup's warm-up lanes arrived in, or the one an inter-sequence lane started from).  If the
+// sequence before it now ends in another state - an inter-sequence lane rewrote its last record in the same
+// round, after the lane of this boundary had looked - the states further on can still be right, and the write
+// pass will find nothing wrong, but the counts and DC sums of the sequence's first records belong to the other
+// entry state.  The boundaries inside group lg are looked at here (at most four: a sequence has at least 65
+// subsequences), by the first four lanes of a kernel behind the inter-sequence kernel, and the host runs another
+// round if one is found.
+__device__ __forceinline__ void check_boundaries(const Params& P, const ImgDesc& D, uint32_t lg, uint32_t nsub) {
+    if (nsub <= P.seq_len || threadIdx.x >= 4u) return;
+    const uint32_t i0 = lg * (uint32_t)kWG;
+    const uint32_t first = (i0 + P.seq_len - 1u) / P.seq_len;  // first sequence that starts in this group
+    const uint32_t g = (first + threadIdx.x) * P.seq_len;
+    if (g > 0u && g < nsub && g < i0 + (uint32_t)kWG &&
+        P.warm_x[D.seq0 + first + threadIdx.x] != __atomic_load_n(&P.sinfo[D.sub0 + g - 1u].x, __ATOMIC_RELAXED))
+        atomicOr(&P.status->pending, 1u);
+}
 
 // exclusive scan of v over the 256 lanes of the workgroup under seg_join; *total gets the join of all.
 // scratch: 20 words of LDS.
@@ -360,6 +393,7 @@ __global__ __launch_bounds__(kWG) void k_unstuff_count(Params P) {
         if (threadIdx.x < 128u) bm[threadIdx.x] = 0u;
         if (lt == D.ntiles - 1u && threadIdx.x < 128u) bm[128u + threadIdx.x] = 0u;
     }
+    clear_group_total(P, D, lt);
     // bytes removed in the low half, markers in the high half: at most 4096 and 2048 in a tile
     uint32_t total;
     wg_excl_scan((u.nvalid + count4(u.drop) - 16u) | (count4(u.mark) << 16), scratch, &total);
@@ -1043,10 +1077,27 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
             __syncthreads();
         }
     }
-    if (valid && t >= P.overlap) {
-        SInfo r;
-        r.x = sw[t]; r.y = pnb[t]; r.z = pdc01[t]; r.w = pdc2[t];
-        P.sinfo[D.sub0 + (uint32_t)(base + (int32_t)t)] = r;
+    SInfo pub = {0u, 0u, 0u, 0u};
+    const bool own = valid && t >= P.overlap;
+    const uint32_t own_i = (uint32_t)(base + (int32_t)t);
+    if (own) {
+        pub.x = sw[t]; pub.y = pnb[t]; pub.z = pdc01[t]; pub.w = pdc2[t];
+        P.sinfo[D.sub0 + own_i] = pub;
+    }
+    // The sums of the published records go to the totals of the (at most two) groups they belong to.  A kernel of its
+    // own that reads the records again for this costs every call 4.5 microseconds.
+    if (!RST && t < (uint32_t)kWG) {
+        const uint32_t g0 = ((wg - D.seq0) * P.seq_len) >> 8;
+        static_assert(kWG == 256, "groups of 256 records");
+        const Seg all = wave_incl_sums(seg_of_record(pub));
+        const bool two = own && (own_i >> 8) != g0;
+        const bool any_two = __ballot(two) != 0ull;
+        Seg second = seg_zero();
+        if (any_two) second = wave_incl_sums(two ? seg_of_record(pub) : seg_zero());
+        if ((t & 63u) == 63u) {
+            add_group_total(P.grp_tot + D.grp0 + g0, seg_minus(all, second));
+            if (any_two) add_group_total(P.grp_tot + D.grp0 + g0 + 1u, second);
+        }
     }
     // The published records continue the state the last warm-up lane ended in.  If the previous sequence ends
     // in that very state, the two sequences already form one chain and the inter-sequence kernel has nothing
@@ -1126,9 +1177,11 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
                 const bool synced = x == __atomic_load_n(&rec[cg].x, __ATOMIC_RELAXED);
                 if (lane == 0u) {
                     if (first && !synced) atomicAdd(&P.status->inter_changed, 1u);
-                    rec[cg].y = cnb;
-                    rec[cg].z = pack_dc01(cdc);
-                    rec[cg].w = pack_dc2(cdc);
+                    const SInfo now = {x, cnb, pack_dc01(cdc), pack_dc2(cdc)};
+                    if (P.fold) add_group_total(P.grp_tot + D.grp0 + (cg >> 8), seg_minus(seg_of_record(now), seg_of_record(rec[cg])));
+                    rec[cg].y = now.y;
+                    rec[cg].z = now.z;
+                    rec[cg].w = now.w;
                     __atomic_store_n(&rec[cg].x, x, __ATOMIC_RELAXED);
                 }
                 first = false;
@@ -1166,6 +1219,7 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
         const bool synced = r.x == __atomic_load_n(&rec[g].x, __ATOMIC_RELAXED);
         if (first && !synced) atomicAdd(&P.status->inter_changed, 1u);
         first = false;
+        if (P.fold) add_group_total(P.grp_tot + D.grp0 + (g >> 8), seg_minus(seg_of_record(r), seg_of_record(rec[g])));
         rec[g].y = r.y;
         rec[g].z = r.z;
         rec[g].w = r.w;
@@ -1199,22 +1253,7 @@ __global__ __launch_bounds__(kWG) void k_group_totals(Params P) {
         wg_excl_segscan(seg_of_record(r), scratch, &tot);
     }
     if (threadIdx.x == 0) P.grp_tot[wg] = seg_pack(tot);
-    // The records of a sequence are those of a decoder that entered it in the state `warm_x` holds for it (the
-    // state its workgroup's warm-up lanes arrived in, or the one an inter-sequence lane started from).  If the
-    // sequence before it now ends in another state - an inter-sequence lane rewrote its last record in this very
-    // round, after the lane of this boundary had looked - the states further on can still be right, and the write
-    // pass will find nothing wrong, but the counts and DC sums of the sequence's first records belong to the other
-    // entry state.  The boundaries inside this group are looked at here (at most four: a sequence has at least 65
-    // subsequences), and the host runs another round if one is found.
-    {
-        const uint32_t i0 = (wg - D.grp0) * kWG;
-        const uint32_t first = (i0 + P.seq_len - 1u) / P.seq_len;  // first sequence that starts in this group
-        const uint32_t g = (first + threadIdx.x) * P.seq_len;
-        if (threadIdx.x < 4u && g > 0u && g < nsub && g < i0 + (uint32_t)kWG) {
-            const uint32_t seq = first + threadIdx.x;
-            if (P.warm_x[D.seq0 + seq] != __atomic_load_n(&P.sinfo[D.sub0 + g - 1u].x, __ATOMIC_RELAXED)) atomicOr(&P.status->pending, 1u);
-        }
-    }
+    check_boundaries(P, D, wg - D.grp0, nsub);
 }
 
 // one workgroup per image: exclusive prefix of the group totals
@@ -1457,6 +1496,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     }
     // all restart markers must have been there (the first lane of the image speaks for it)
     if (RST && D.restart && i == 0u && P.st[ii].markers != D.nint - 1u) flags |= kStInvalid;
+    if (P.fold) check_boundaries(P, D, lg, nsub);
     // every lane checks the chain: unless the image is complete it must end in the recorded state
     if (unit < total) {
         if (l.p < limit || pack_state(l.p - limit, l.z, l.u) != mine.x) flags |= kStMismatch;
