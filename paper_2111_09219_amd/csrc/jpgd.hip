@@ -692,16 +692,22 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.launched = true;
     if (n > 1)
         hipLaunchKernelGGL(k_upload, dim3(up_wgs), dim3(kWG), 0, stream, (const uint4*)c.buf_dev, (uint4*)ws, up_n16);
-    LAUNCH(JPGD_K_UNSTUFF_COUNT, k_unstuff_count, pl.tiles + P.up_wgs, kWG, 0);
-    P.up_wgs = 0u;
-    bool big_tiles = false;  // the two image-level scans are only needed beyond 256 tiles / groups
+    bool big_tiles = false, alone = n == 1 && !any_restart;  // the two image-level scans are only needed beyond 256 tiles / groups
     c.big_groups = false;
     for (int i = 0; i < n; ++i) {
+        alone = alone && pl.img[i].ntiles <= (uint32_t)kAloneTiles;
         big_tiles = big_tiles || pl.img[i].ntiles > (uint32_t)kWG;
         c.big_groups = c.big_groups || pl.img[i].ngrp_max > (uint32_t)kWG;
     }
-    if (big_tiles) LAUNCH(JPGD_K_UNSTUFF_SCAN, k_unstuff_scan, n, kWG, 0);
-    LAUNCH(JPGD_K_UNSTUFF_SCATTER, k_unstuff_scatter, pl.tiles, kWG, 0);
+    if (alone) {
+        LAUNCH(JPGD_K_UNSTUFF_SCATTER, k_unstuff_scatter<true>, pl.tiles + P.up_wgs, kWG, 0);
+        P.up_wgs = 0u;
+    } else {
+        LAUNCH(JPGD_K_UNSTUFF_COUNT, k_unstuff_count, pl.tiles + P.up_wgs, kWG, 0);
+        P.up_wgs = 0u;
+        if (big_tiles) LAUNCH(JPGD_K_UNSTUFF_SCAN, k_unstuff_scan, n, kWG, 0);
+        LAUNCH(JPGD_K_UNSTUFF_SCATTER, k_unstuff_scatter<false>, pl.tiles, kWG, 0);
+    }
     if (pl.split) {
         // first kernel: until at most kHandoff chains of a sequence are left; second kernel: the rest, four
         // wavefronts per sequence, the chains from kCoopMax down one per wavefront
@@ -1019,7 +1025,7 @@ extern "C" int jpgd_unstuff(const uint8_t* d_in, size_t n, uint8_t* d_out, size_
     P.logL = 10;
     hipLaunchKernelGGL(k_unstuff_count, dim3(tiles), dim3(kWG), 0, stream, P);
     if (tiles > (uint32_t)kWG) hipLaunchKernelGGL(k_unstuff_scan, dim3(1), dim3(kWG), 0, stream, P);
-    hipLaunchKernelGGL(k_unstuff_scatter, dim3(tiles), dim3(kWG), 0, stream, P);
+    hipLaunchKernelGGL(k_unstuff_scatter<false>, dim3(tiles), dim3(kWG), 0, stream, P);
     HIP_OK(hipGetLastError());
     HIP_OK(hipMemcpyAsync(c->verdict, ws + off_state, sizeof(ImgState), hipMemcpyDeviceToHost, stream));
     HIP_OK(hipStreamSynchronize(stream));

@@ -164,6 +164,7 @@ struct Status {
 // of the workgroup clearing its stretch of the output first
 constexpr uint32_t kDenseBitsPerUnit = 256u;
 constexpr int kUnstuffTile = 4096;  // bytes per workgroup of the unstuff kernels (256 lanes x 16 bytes)
+constexpr int kAloneTiles = 32;    // up to this many tiles in a call with one image the unstuffing is one kernel
 constexpr int kPixBlocks = 48;      // data units per workgroup of the pixel kernel
 constexpr int kPixBlocksScaled = 192;  // ... of the reduced-size pixel kernels (a unit needs 16, 4 or 1 floats of LDS there)
 

@@ -371,14 +371,24 @@ __device__ __forceinline__ UnstuffLane unstuff_load(const uint8_t* scan, uint32_
     return r;
 }
 
+// The copy of the parameter block (one image per call only), by the last workgroups of the call's first kernel.
+// WRITES_STATE: that kernel writes the image states, which lie between the block's status word and its descriptors, and
+// they are left out of the copy.
+template <bool WRITES_STATE>
+__device__ __forceinline__ bool copy_parameters(const Params& P) {
+    const uint32_t first = gridDim.x - P.up_wgs;
+    if (blockIdx.x < first) return false;
+    const uint4* const st0 = reinterpret_cast<const uint4*>(P.st);
+    const uint4* const st1 = reinterpret_cast<const uint4*>(P.img);
+    for (uint32_t k = (blockIdx.x - first) * kWG + threadIdx.x; k < P.up_n16; k += P.up_wgs * kWG)
+        if (!WRITES_STATE || P.up_dst + k < st0 || P.up_dst + k >= st1) P.up_dst[k] = P.up_src[k];
+    return true;
+}
+
 __global__ __launch_bounds__(kWG) void k_unstuff_count(Params P) {
     __shared__ uint32_t scratch[8];
     const uint32_t wg = blockIdx.x;
-    if (P.up_wgs && wg >= gridDim.x - P.up_wgs) {  // the copy of the parameter block (one image per call only)
-        const uint32_t first = gridDim.x - P.up_wgs;
-        for (uint32_t k = (wg - first) * kWG + threadIdx.x; k < P.up_n16; k += P.up_wgs * kWG) P.up_dst[k] = P.up_src[k];
-        return;
-    }
+    if (copy_parameters<false>(P)) return;
     const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.tile0; });
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t lt = wg - D.tile0;
@@ -437,10 +447,15 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scan(Params P) {
     }
 }
 
+// ALONE: the whole step in one kernel, for calls with one image of at most kAloneTiles tiles, without restart intervals:
+// a workgroup counts the bytes removed in all tiles before its own itself.  It reads them once more for that, which
+// for so few tiles takes less time than the kernel that would count them and the gap behind it.
+template <bool ALONE>
 __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     __shared__ uint32_t scratch[16];
     __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffTile + 32];
     const uint32_t wg = blockIdx.x;
+    if (ALONE && copy_parameters<true>(P)) return;
     const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.tile0; });
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t lt = wg - D.tile0;
@@ -448,19 +463,33 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     uint8_t* out = P.stream + D.stream_off;
     const uint32_t pos = lt * (uint32_t)kUnstuffTile + threadIdx.x * 16u;
     // bytes removed before this tile: from the scan kernel, or, for images of up to 256 tiles, summed here
-    const bool few_tiles = D.ntiles <= (uint32_t)kWG;
+    const bool few_tiles = !ALONE && D.ntiles <= (uint32_t)kWG;
     uint32_t raw = 0u, before = 0u, nbytes = 0u;
-    if (few_tiles) {
+    if (ALONE) {
+        clear_group_total(P, D, lt);
+#pragma unroll 4
+        for (uint32_t k = 0; k < lt; ++k) {  // (complete tiles: no byte is past the end)
+            const uint32_t at = k * (uint32_t)kUnstuffTile + threadIdx.x * 16u;
+            const uint4 v = *reinterpret_cast<const uint4*>(scan + at);
+            const uint32_t b = at ? *reinterpret_cast<const uint32_t*>(scan + at - 4u) : 0u;
+            const uint32_t drop[4] = {zero_bytes(v.x | ~__builtin_amdgcn_alignbyte(v.x, b, 3u)), zero_bytes(v.y | ~__builtin_amdgcn_alignbyte(v.y, v.x, 3u)),
+                                      zero_bytes(v.z | ~__builtin_amdgcn_alignbyte(v.z, v.y, 3u)), zero_bytes(v.w | ~__builtin_amdgcn_alignbyte(v.w, v.z, 3u))};
+            before += count4(drop);
+        }
+    } else if (few_tiles) {
         if (threadIdx.x < D.ntiles) raw = P.tile_cnt[D.tile0 + threadIdx.x];
     } else {
         before = P.tile_cnt[wg];
         nbytes = P.st[ii].nbytes;
     }
-    const UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, D.restart != 0u);
+    const UnstuffLane u = unstuff_load(scan, D.scan_bytes, pos, !ALONE && D.restart != 0u);
     const uint32_t kept = 16u - count4(u.drop);
     const uint32_t inc = wave_incl_scan(kept), wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63u) == 63u) scratch[wave] = inc;
-    if (few_tiles) {
+    if (ALONE) {
+        before = wave_incl_scan(before);
+        if ((threadIdx.x & 63u) == 63u) scratch[8u + wave] = before;
+    } else if (few_tiles) {
         const uint32_t v = raw & 0xFFFFu;
         const uint32_t all = wave_incl_scan(v), prior = wave_incl_scan(threadIdx.x < lt ? v : 0u), marks = wave_incl_scan(raw >> 16);
         if ((threadIdx.x & 63u) == 63u) {
@@ -473,7 +502,15 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     const uint32_t w0 = scratch[0], w1 = scratch[1], w2 = scratch[2];
     const uint32_t T = w0 + w1 + w2 + scratch[3];
     const uint32_t off = (wave > 0u ? w0 : 0u) + (wave > 1u ? w1 : 0u) + (wave > 2u ? w2 : 0u) + inc - kept;
-    if (few_tiles) {
+    if (ALONE) {
+        before = scratch[8] + scratch[9] + scratch[10] + scratch[11];
+        nbytes = lt * (uint32_t)kUnstuffTile - before + T;  // (of the last tile)
+        if (lt == D.ntiles - 1u && threadIdx.x == 0u) {
+            P.st[ii].markers = 0u;
+            P.st[ii].nbytes = nbytes;
+            P.st[ii].nsub = (uint32_t)(((uint64_t)nbytes * 8u + (1u << P.logL) - 1u) >> P.logL);
+        }
+    } else if (few_tiles) {
         before = scratch[8] + scratch[9] + scratch[10] + scratch[11];
         nbytes = D.scan_bytes - (scratch[4] + scratch[5] + scratch[6] + scratch[7]);
         if (lt == 0u && threadIdx.x == 0u) {
@@ -512,7 +549,7 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
         if (mine) base[at] = buf[at];
     }
     // the byte after a restart marker starts an interval: its position in the output goes into the bitmap
-    if (D.restart) {
+    if (!ALONE && D.restart) {
         uint32_t* bm = P.bmap + D.bmap_off;
         uint32_t at = o + off;
 #pragma unroll
