@@ -39,6 +39,7 @@ struct Params {
     uint32_t lut_slots;     // max tables of any image (sizes the LDS copy)
     uint32_t pair_slots;    // max AC tables of any image (sizes the LDS copy of their pair bytes)
     uint32_t planar;        // pixel kernel: component planes (no upsampling, no colour conversion) instead of RGB
+    uint32_t pix_per_wg;    // pixel kernel: runs of MCUs a workgroup takes one after the other
     uint32_t scale_log2;    // pixel kernel: output at 1/2^scale_log2 of the size (0..3)
     uint32_t handoff;       // intra-sequence kernel, split in two: chains left at which the first hands over (at most 64)
     uint32_t coop_max;      // intra-sequence kernel: with at most this many chains left, one wavefront per chain
@@ -1575,20 +1576,10 @@ __device__ __forceinline__ void put_bytes(uint8_t* dst, const uint32_t (&w)[NW],
 __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
     __shared__ float blk[kPixBlocks * kBlkStride];
     __shared__ __attribute__((aligned(16))) float qf[3 * 64];
-    const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.pix_wg0; });
-    const ImgDesc D = image_desc_uniform(P, ii);
-    const uint32_t lw = wg - D.pix_wg0;
-    const uint32_t mrow = lw / D.pix_runs, run = lw % D.pix_runs;
-    const uint32_t upm = D.upm;
-    const uint32_t M = (uint32_t)kPixBlocks / upm;
-    const uint32_t m0 = run * M;
-    const uint32_t nm = min(M, D.mcus_x - m0);
-    const uint32_t nblk = nm * upm;
-    const uint32_t t = threadIdx.x;
+    uint32_t t = threadIdx.x;
     // The write kernel is complete when this kernel starts: its verdict goes to the waiting host from here, which
     // saves the dispatch of a kernel that would do nothing else.
-    if (wg == 0u && t == 0u && P.verdict) {
+    if (blockIdx.x == 0u && t == 0u && P.verdict) {
         volatile uint32_t* host = P.verdict;
         host[0] = P.status->flags;
         host[1] = P.status->inter_changed;
@@ -1596,7 +1587,6 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         __threadfence_system();
         host[15] = P.ticket;
     }
-    if (t < 3u * 64u) qf[t] = (float)P.qts[D.qt_off + t];
     // A lane always handles the same eighth of a data unit (256 is a multiple of 8): where its 8 coefficients
     // go inside the 8x9 tile is fixed, and is kept in registers.
     const uint32_t part = t & 7u;
@@ -1606,15 +1596,35 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         const uint32_t rc = c_zigzag[part * 8u + e];
         zo[e] = (rc >> 3) * 9u + (rc & 7u);
     }
+    // A workgroup takes pix_per_wg runs of an image one after the other (Params::pix_per_wg).
+    const uint32_t ii = find_image(P, blockIdx.x, [](const ImgDesc& d) { return d.pix_wg0; });
+    const ImgDesc D = image_desc_uniform(P, ii);
+    const uint32_t upm = D.upm;
+    const uint32_t M = (uint32_t)kPixBlocks / upm;
+    const uint32_t first_run = (blockIdx.x - D.pix_wg0) * P.pix_per_wg;
+    uint32_t left = min(P.pix_per_wg, D.pix_runs * D.mcus_y - first_run);
+    uint32_t mrow = first_run / D.pix_runs, run = first_run % D.pix_runs;
+    static_assert(kPixBlocks * 8 <= 2 * kWG, "two words of coefficients per lane");
+    if (t < 3u * 64u) qf[t] = (float)P.qts[D.qt_off + t];
     __syncthreads();
+    for (;;) {
+    // (What is worked out from the lane's number inside the loop stays there: kept across it, it would take 30 more
+    // registers, and a third of the wavefronts would have no place.)
+    asm volatile("" : "+v"(t));
+    const uint32_t m0 = run * M;
+    const uint32_t nm = min(M, D.mcus_x - m0);
+    const uint32_t nblk = nm * upm;
+    // 8 coefficients (16 bytes) per lane and step
+    uint4 raw0 = make_uint4(0u, 0u, 0u, 0u), raw1 = raw0;
+    const uint4* coef = reinterpret_cast<const uint4*>(P.coef + D.coef_off + (size_t)((size_t)mrow * D.mcus_x + m0) * upm * 64u);
+    if (t < nblk * 8u) raw0 = coef[t];
+    if (t + kWG < nblk * 8u) raw1 = coef[t + kWG];
 
-    // load + dequantise + de-zigzag: 8 coefficients (16 bytes) per lane and step
-    const int16_t* coef = P.coef + D.coef_off + (size_t)((size_t)mrow * D.mcus_x + m0) * upm * 64u;
-    for (uint32_t j = t; j < nblk * 8u; j += kWG) {
+    // dequantise + de-zigzag
+    auto place = [&](uint32_t j, const uint4& raw) {
         const uint32_t k = j >> 3;
         const uint32_t ku = upm == 1u ? 0u : (upm == 3u ? k % 3u : (upm == 4u ? (k & 3u) : k % 6u));
         const uint32_t comp = (D.sched_comp >> (ku * 4u)) & 15u;
-        const uint4 raw = *reinterpret_cast<const uint4*>(coef + (size_t)j * 8u);
         const float4 qa = *reinterpret_cast<const float4*>(qf + comp * 64u + part * 8u);
         const float4 qb = *reinterpret_cast<const float4*>(qf + comp * 64u + part * 8u + 4u);
         float* tile = blk + k * kBlkStride;
@@ -1626,7 +1636,9 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         tile[zo[5]] = (float)((int32_t)raw.z >> 16) * qb.y;
         tile[zo[6]] = (float)(int16_t)(raw.w) * qb.z;
         tile[zo[7]] = (float)((int32_t)raw.w >> 16) * qb.w;
-    }
+    };
+    if (t < nblk * 8u) place(t, raw0);
+    if (t + kWG < nblk * 8u) place(t + kWG, raw1);
     __syncthreads();
     // columns
     for (uint32_t j = t; j < nblk * 8u; j += kWG) {
@@ -1685,8 +1697,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
                 put_bytes<2>(cplane + (size_t)c * cw * ch + (size_t)gy * cw + gx0, w, min(8u, cw - gx0));
             }
         }
-        return;
-    }
+    } else {
     // RGB: a lane produces the 24 bytes of eight horizontally adjacent pixels -- one row of a luma data unit.  The
     // colour terms of a chroma sample are computed once (a sample serves two of the pixels when chroma is subsampled
     // horizontally); each output sample then costs one addition and one conversion that also puts the byte in its place.
@@ -1746,6 +1757,11 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
             }
         }
         put_bytes<6>(pix + (size_t)gy * row_bytes + __umul24(gx0, 3u), w, min(8u, D.width - gx0) * 3u);
+    }
+    }
+    if (--left == 0u) break;
+    if (++run == D.pix_runs) { run = 0u; ++mrow; }
+    __syncthreads();  // the tiles are read no more
     }
 }
 
