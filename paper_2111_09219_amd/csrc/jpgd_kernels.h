@@ -71,29 +71,37 @@ __device__ __forceinline__ ImgDesc image_desc(const Params& P, uint32_t ii) {
     return P.img[ii];
 }
 
-// The same with every word passed through readfirstlane: the descriptor and what follows from it stay in scalar
-// registers and branches on it are scalar branches.  Measured per kernel: pixels 9 %, write 2 % and
-// unstuff_count 8 % faster with it; the two synchronisation kernels 2 to 4 % slower (their lane decoder is short
-// of scalar registers, not of vector ones), so they keep the plain form.
+// Descriptors are written by nobody while a kernel runs that reads them.  Read through the constant address space
+// they come by scalar loads, also behind a store, where the compiler otherwise reads lane by lane and takes the result
+// for lane-dependent.
+using ConstWords = const __attribute__((address_space(4))) uint32_t*;
+__device__ __forceinline__ ConstWords const_words(const void* p) { return (ConstWords)(uintptr_t)p; }
+
+// The same in scalar registers: what follows from the descriptor stays there and branches on it are scalar branches.
+// Measured per kernel: pixels 9 %, write 2 % and unstuff_count 8 % faster with it; the two synchronisation kernels 2 to
+// 4 % slower (their lane decoder is short of scalar registers, not of vector ones), so they keep the plain form.
 __device__ __forceinline__ ImgDesc image_desc_uniform(const Params& P, uint32_t ii) {
-    ImgDesc d = image_desc(P, ii);
     static_assert(sizeof(ImgDesc) % 4u == 0u, "descriptor is copied word by word");
+    if (P.nimg == 1u) return P.img0;
     uint32_t w[sizeof(ImgDesc) / 4u];
-    __builtin_memcpy(w, &d, sizeof d);
+    const ConstWords src = const_words(P.img + ii);
 #pragma unroll
-    for (uint32_t i = 0; i < sizeof(ImgDesc) / 4u; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    for (uint32_t i = 0; i < sizeof(ImgDesc) / 4u; ++i) w[i] = src[i];
+    ImgDesc d;
     __builtin_memcpy(&d, w, sizeof d);
     return d;
 }
 
 // ---- small helpers ------------------------------------------------------------------------------
 
-template <class F>
-__device__ __forceinline__ uint32_t find_image(const Params& P, uint32_t wg, F first_wg) {
+// The image a workgroup belongs to; first_wg: the descriptor's word with the image's first workgroup.  (In the pixel
+// kernel, whose first lane reports the verdict before this, every step of the search was a vector load and its wait: six
+// trips to L2 for 48 images.)
+__device__ __forceinline__ uint32_t find_image(const Params& P, uint32_t wg, const uint32_t ImgDesc::*first_wg) {
     uint32_t lo = 0, hi = P.nimg;  // last image whose first workgroup is <= wg
     while (hi - lo > 1) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (first_wg(P.img[mid]) <= wg) lo = mid; else hi = mid;
+        const uint32_t mid = (lo + hi) >> 1;
+        if (*const_words(&(P.img[mid].*first_wg)) <= wg) lo = mid; else hi = mid;
     }
     return lo;
 }
@@ -330,7 +338,8 @@ struct UnstuffLane {
 // pos is a multiple of 16.  A lane that holds any byte loads its whole 16-byte word (the input is readable up
 // to the next multiple of 16); bytes past the end are masked out.  The bytes are looked at four at a time, beside
 // the word that holds the byte before each of them: about 30 instructions for 16 bytes, where one byte after the
-// other took 170 and filled three quarters of the chip's issue slots.  No private array is indexed with a variable:
+// other took 170 and filled three quarters of the chip's issue slots (66 MB: count 29.6 -> 17.9 us, 3.7 TB/s; scatter
+// 53 -> 34 us, 3.9 TB/s).  No private array is indexed with a variable:
 // the compiler would move such an array to LDS and read the dispatch packet for the workgroup's shape, and that
 // packet lives in host memory -- measured at 2 to 11 microseconds per wavefront when a whole grid asks at once.
 // All 64 lanes of the wavefront call this together.
@@ -390,7 +399,7 @@ __global__ __launch_bounds__(kWG) void k_unstuff_count(Params P) {
     __shared__ uint32_t scratch[8];
     const uint32_t wg = blockIdx.x;
     if (copy_parameters<false>(P)) return;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.tile0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::tile0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t lt = wg - D.tile0;
     const uint8_t* scan = P.scans + D.scan_off;
@@ -457,7 +466,7 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffTile + 32];
     const uint32_t wg = blockIdx.x;
     if (ALONE && copy_parameters<true>(P)) return;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.tile0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::tile0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t lt = wg - D.tile0;
     const uint8_t* scan = P.scans + D.scan_off;
@@ -620,6 +629,8 @@ __device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & 0xFE1Fu; 
 // memory is touched, and every step moves on by at least one bit, so the loop ends after at most 64 steps.
 // dc_a holds the sums of components 0 and 1 (two 16-bit fields, the lower one's sign taken off the upper one), dc_b
 // that of component 2.
+// Measured, compiled loops / this (synchronisation kernels, us): 4096x4096 4:2:0 502 / 465, second kernel of 15360x8640
+// 966 / 890, 24 images of 2047x1535 362 / 335, one 1600x1200 image 218 / 201, batch of 256 251 / 243, 1920x1088 42 / 40.5.
 constexpr uint32_t kCoopLeft = 0u, kCoopAcEscape = 1u, kCoopDcEscape = 2u;
 __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32_t& dc_slot, uint32_t& nb, uint32_t& dc_a,
                                               uint32_t& dc_b, uint32_t& acv, uint32_t& acs, uint32_t e01, uint32_t e23, uint32_t peek,
@@ -853,7 +864,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     constexpr bool PAIRS = true;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.seq0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::seq0);
     const ImgDesc D = image_desc(P, ii);
     const uint32_t nsub = P.st[ii].nsub;
     const int32_t base = (int32_t)((wg - D.seq0) * P.seq_len) - (int32_t)P.overlap;
@@ -1163,7 +1174,7 @@ __global__ __launch_bounds__(kWG) void k_sync_tail(Params P) {
 __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.bnd0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::bnd0);
     const ImgDesc D = image_desc(P, ii);
     const uint32_t nsub = P.st[ii].nsub;
     const uint32_t b = (wg - D.bnd0) * 64u + threadIdx.x;
@@ -1275,7 +1286,7 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
 __global__ __launch_bounds__(kWG) void k_group_totals(Params P) {
     __shared__ uint32_t scratch[20];
     const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.grp0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::grp0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t nsub = P.st[ii].nsub;
     const uint32_t i = (wg - D.grp0) * kWG + threadIdx.x;
@@ -1324,7 +1335,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     __shared__ uint32_t scratch[36];
     const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.grp0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::grp0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t nsub = P.st[ii].nsub;
     const uint32_t lg = wg - D.grp0;
@@ -1544,9 +1555,11 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
 }
 
 // ---- pixels: de-zigzag, dequantise, 8x8 IDCT, level shift, chroma replication, YCbCr -> RGB -------------
-// (paper, Section 4.3; the colour steps are not in the paper).  A workgroup takes a run of consecutive
-// MCUs of one MCU row, kPixBlocks data units at most, transforms them in LDS and writes the pixel
-// rectangle they cover with row-contiguous stores.
+// (paper, Section 4.3; the colour steps are not in the paper).  A workgroup takes runs of consecutive
+// MCUs of one MCU row, kPixBlocks data units at most, transforms their columns in LDS and their rows on the way out, and
+// writes the pixel rectangle they cover with row-contiguous stores.  Its rate depends on the wavefronts in flight: eight
+// per SIMD with at most 64 registers (48 frames of 1920x1088 4:4:4, one run per workgroup: 307 us with 49 registers, 549
+// with 93).
 
 // Floats per data unit in LDS: 8 rows of 9 (one pad per row) and one more, so that lanes that hold the same row of
 // neighbouring units (the output loops) start in different banks (73 is odd; 72 put 64 of them into 8 banks).
@@ -1597,7 +1610,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
         zo[e] = (rc >> 3) * 9u + (rc & 7u);
     }
     // A workgroup takes pix_per_wg runs of an image one after the other (Params::pix_per_wg).
-    const uint32_t ii = find_image(P, blockIdx.x, [](const ImgDesc& d) { return d.pix_wg0; });
+    const uint32_t ii = find_image(P, blockIdx.x, &ImgDesc::pix_wg0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t upm = D.upm;
     const uint32_t M = (uint32_t)kPixBlocks / upm;
@@ -1811,7 +1824,7 @@ __global__ __launch_bounds__(kWG) void k_pixels_scaled(Params P) {
     __shared__ float smp[kPixBlocksScaled * NN];   // samples, level shift applied, [unit][y * N + x]
     __shared__ float bs[NN];
     const uint32_t wg = blockIdx.x;
-    const uint32_t ii = find_image(P, wg, [](const ImgDesc& d) { return d.pix_wg0; });
+    const uint32_t ii = find_image(P, wg, &ImgDesc::pix_wg0);
     const ImgDesc D = image_desc_uniform(P, ii);
     const uint32_t lw = wg - D.pix_wg0;
     const uint32_t mrow = lw / D.pix_runs, run = lw % D.pix_runs;
