@@ -727,12 +727,12 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     }
     if (pl.split) {
         // first kernel: until at most kHandoff chains of a sequence are left; second kernel: the rest, four
-        // wavefronts per sequence, the chains from kCoopMax down one per wavefront
+        // wavefronts per sequence, the chains from kTailCoopMax down one per wavefront
         P.handoff = kHandoff;
         if (c.staged) LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_head<true, false>), pl.seqs, kWG, c.lds_sync);
         else LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_head<false, false>), pl.seqs, kWG, c.lds_sync);
         P.sync_waves = (uint32_t)(kWG / 64);
-        P.coop_max = kCoopMax;
+        P.coop_max = kTailCoopMax;
         LAUNCH(JPGD_K_SYNC_TAIL, (k_sync_tail<false>), pl.seqs, kWG, lds_tail_bytes(pl.lut_slots, pl.pair_slots));
     } else
     switch (c.variant) {

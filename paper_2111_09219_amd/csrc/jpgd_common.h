@@ -53,6 +53,9 @@ constexpr int kLutSetEntries = kMaxSlots * kLutEntries + kMaxPairs * kPairBytes 
 // and 15360x8640 4:2:0 (1024 bits): with four wavefronts 4 to 8 chains are within noise of each other and 16 is
 // slower than never doing it on the large images; with eight wavefronts 12 is best, with sixteen 24.
 constexpr uint32_t kCoopMax = 6u;  // for the kWG / 64 wavefronts that hold the lanes
+// In the second kernel of a split synchronisation (four wavefronts): two more.  Measured per call on the 15360x8640 image for 4, 6,
+// 8, 10 and 12 chains: 2.29, 2.28, 2.25, 2.29, 2.31 ms.
+constexpr uint32_t kTailCoopMax = 8u;
 // The workgroup may have more wavefronts than those: the others do nothing but take chains in these rounds, so
 // that fewer chains share a wavefront (a CU has 32 wavefront slots and a sequence's tail leaves most of them idle).
 constexpr int kSyncWavesMax = 16;
