@@ -549,8 +549,9 @@ int launch_scan(Call& c, bool totals) {
 }
 
 int launch_write(Call& c) {
-    if (c.staged) LAUNCH(JPGD_K_WRITE, k_write<true>, c.pl.grps, kWG, c.lds_write);
-    else LAUNCH(JPGD_K_WRITE, k_write<false>, c.pl.grps, kWG, c.lds_write);
+    if (c.P.tile_bytes) LAUNCH(JPGD_K_WRITE, (k_write<true, true>), c.pl.grps, kWG, c.P.tile_off + c.P.tile_bytes);
+    else if (c.staged) LAUNCH(JPGD_K_WRITE, (k_write<true, false>), c.pl.grps, kWG, c.lds_write);
+    else LAUNCH(JPGD_K_WRITE, (k_write<false, false>), c.pl.grps, kWG, c.lds_write);
     return JPGD_OK;
 }
 
@@ -602,12 +603,15 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.lds_inter = (size_t)pl.lut_slots * kLutEntries * 2;
     if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
     c.staged = pl.L <= kStagedMaxL;
+    const bool tiled = c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups;
+    const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u), tile_bytes = tiled ? (uint32_t)kTileBytes : 0u;
     // the variants of the intra-sequence kernel: stream staged in LDS or not, call with or without restart intervals
     c.variant = (c.staged ? 0 : 1) + (any_restart ? 2 : 0);
     const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
                                          (const void*)k_sync_intra<true, true>, (const void*)k_sync_intra<false, true>};
     if ((rc = grant_lds(c.device, c.variant, sync_kernels[c.variant], c.lds_sync)) ||
-        (rc = grant_lds(c.device, c.staged ? 4 : 5, c.staged ? (const void*)k_write<true> : (const void*)k_write<false>, c.lds_write)) ||
+        (rc = grant_lds(c.device, c.staged ? 4 : 5, c.staged ? (const void*)k_write<true, false> : (const void*)k_write<false, false>, c.lds_write)) ||
+        (tiled && (rc = grant_lds(c.device, 7, (const void*)k_write<true, true>, tile_off + tile_bytes))) ||
         (rc = grant_lds(c.device, 8, (const void*)k_sync_inter, c.lds_inter)) ||
         (pl.split && c.staged && (rc = grant_lds(c.device, 6, (const void*)k_sync_head<true, false>, c.lds_sync))))
         return rc;
@@ -692,6 +696,8 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.coop_max = kCoopMax * sync_waves / (uint32_t)(kWG / 64);
     P.handoff = 0u;
     P.fold = any_restart ? 0u : 1u;
+    P.tile_off = tile_off;
+    P.tile_bytes = tile_bytes;
     P.verdict = nullptr;
     P.ticket = 0u;
     P.up_src = (const uint4*)c.buf_dev;
@@ -912,8 +918,9 @@ extern "C" int jpgd_init(void) {
     for (int v = 0; v < 4; ++v)
         if ((rc = grant_lds(dev, v, sync_kernels[v], lds_sync_bytes(2048u, kMaxSlots, kMaxPairs, v >= 2)))) break;
     if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kMaxSlots, kMaxPairs, false));
-    if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true>, lds_write_bytes(2048u, kMaxSlots, true));
-    if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false>, lds_write_bytes(2048u, kMaxSlots, true));
+    if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kMaxSlots, true));
+    if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kMaxSlots, true));
+    if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, lds_write_bytes(kTileMaxL, kMaxSlots, false) + 16 + kTileBytes);
     if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, (size_t)kMaxSlots * kLutEntries * 2);
     if (rc) return rc;
     {

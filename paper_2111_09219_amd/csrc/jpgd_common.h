@@ -167,7 +167,14 @@ struct Status {
 // of the workgroup clearing its stretch of the output first
 constexpr uint32_t kDenseBitsPerUnit = 256u;
 constexpr int kUnstuffTile = 4096;  // bytes per workgroup of the unstuff kernels (256 lanes x 16 bytes)
-constexpr int kAloneTiles = 32;    // up to this many tiles in a call with one image the unstuffing is one kernel
+// Write kernel with the output gathered in LDS: calls of at most one workgroup per CU, subsequences of up to 256 bits (of
+// longer ones a workgroup covers more coefficients than fit), and the room for them: 1024 data units.
+constexpr int kTileMaxGroups = 256;
+constexpr int kTileMaxL = 256;
+constexpr int kTileBytes = 128 * 1024;
+// Up to this many tiles in a call with one image the unstuffing is one kernel.  Whole calls, one kernel / two (us): 2.5 tiles 218 / 221,
+// 16 tiles 234 / 236, 32 tiles 313 / 311, 100 tiles 355 / 347.
+constexpr int kAloneTiles = 16;
 constexpr int kPixBlocks = 48;      // data units per workgroup of the pixel kernel
 constexpr int kPixBlocksScaled = 192;  // ... of the reduced-size pixel kernels (a unit needs 16, 4 or 1 floats of LDS there)
 

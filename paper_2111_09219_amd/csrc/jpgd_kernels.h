@@ -43,6 +43,8 @@ struct Params {
     uint32_t scale_log2;    // pixel kernel: output at 1/2^scale_log2 of the size (0..3)
     uint32_t handoff;       // intra-sequence kernel, split in two: chains left at which the first hands over (at most 64)
     uint32_t coop_max;      // intra-sequence kernel: with at most this many chains left, one wavefront per chain
+    uint32_t tile_off;      // write kernel with the output gathered in LDS: where that lies and how many bytes it has
+    uint32_t tile_bytes;
     uint32_t fold;          // calls without restart intervals: the synchronisation kernels add up the group totals as they
                             // publish records, and k_group_totals only runs in further rounds
     uint32_t sync_waves;    // wavefronts per workgroup of that kernel: kWG / 64 that hold the lanes, the rest only take chains
@@ -1329,9 +1331,13 @@ __global__ __launch_bounds__(kWG) void k_group_scan(Params P) {
 
 // ---- write pass (paper, Algorithm 1 last loop; Algorithm 2 with write = true) ---------------------------
 
-template <bool STAGED>
+// TILE: calls of few workgroups and without restart intervals (kTileMaxGroups).  Where the coefficients a workgroup covers
+// fit P.tile_bytes of LDS they are gathered there, value by value, and leave as full lines at the end: such a call
+// waits for its slowest lane, and a lane that only stores into LDS takes a quarter fewer instructions per symbol;
+// nothing is cleared in memory beforehand.
+template <bool STAGED, bool TILE>
 __global__ __launch_bounds__(kWG) void k_write(Params P) {
-    constexpr bool RST = true;  // (a variant without the restart code, as for k_sync_intra, was measured 2 % slower)
+    constexpr bool RST = !TILE;  // (a variant without the restart code, as for k_sync_intra, was measured 2 % slower)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     __shared__ uint32_t scratch[36];
     const uint32_t wg = blockIdx.x;
@@ -1429,13 +1435,20 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     // treatment of the 1920x1088 4:4:4 image, 60 bits per unit, costs the kernel a third more time; on the noise half
     // of the 15360x8640 image, 340 bits per unit, it saves 8 %).  One decision per workgroup.
     const bool dense = ((uint64_t)nloc << P.logL) >= (uint64_t)kDenseBitsPerUnit * grp_units;
-    if (!dense) {
-        const uint64_t end_all = (uint64_t)D.total_units * 64u;
-        const uint32_t x_in = scratch[32], x_out = scratch[33];
-        uint64_t a = (uint64_t)gp.units * 64u + state_z(x_in);
-        uint64_t b = i0 + nloc >= nsub ? end_all : ((uint64_t)gp.units + grp_units) * 64u + state_z(x_out);
-        if (i0 == 0u) a = 0u;
-        if (b > end_all) b = end_all;
+    const uint64_t end_all = (uint64_t)D.total_units * 64u;
+    const uint32_t x_in = scratch[32], x_out = scratch[33];
+    uint64_t a = (uint64_t)gp.units * 64u + state_z(x_in);
+    uint64_t b = i0 + nloc >= nsub ? end_all : ((uint64_t)gp.units + grp_units) * 64u + state_z(x_out);
+    if (i0 == 0u) a = 0u;
+    if (b > end_all) b = end_all;
+    const uint64_t tile_a = a & ~(uint64_t)7u;  // first slot of the tile: a 16-byte word of the output
+    const bool tiled = TILE && a < b && (b - tile_a) * 2u <= P.tile_bytes;
+    uint4* const tile16 = reinterpret_cast<uint4*>(lds_raw + P.tile_off);
+    const uint32_t tile_n = tiled ? (uint32_t)(b - tile_a) : 0u;  // slots
+    if (tiled) {
+        for (uint32_t k = t; k < (tile_n + 7u) >> 3; k += kWG) tile16[k] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    } else if (!dense) {
         if (a < b) {
             int16_t* c0 = P.coef + D.coef_off;
             uint64_t a8 = (a + 7u) & ~(uint64_t)7u;
@@ -1450,7 +1463,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         }
         __syncthreads();  // the cleared range is in place
     }
-    if (!valid) return;
+    if (!tiled && !valid) return;
 
     const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
     auto fetch = [&](uint32_t c) { return STAGED ? strm[c] : __builtin_bswap32(gwords[c]); };
@@ -1519,17 +1532,42 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const uint32_t in_mcu = D.upm == 1u ? 0u : D.upm == 4u ? unit & 3u : D.upm == 3u ? unit3 : unit3 * 2u + (unit & 1u);
     if (unit < total && in_mcu != l.u) flags |= kStUnit;
     const uint32_t limit = (i + 1u) << P.logL;
-    if (unit < total) {
+    if (TILE && tiled) {
+        if (valid && unit < total) {
+            win_init(w, l.p, (l.p >> 5) - first_word, fetch);
+            prime(l, w, sx, lut_s);
+            uint16_t* const tile = reinterpret_cast<uint16_t*>(tile16);
+            const uint32_t tile_first = (uint32_t)tile_a;
+            auto gather = [&](uint32_t k, uint32_t at, int16_t v) {
+                const uint32_t slot = k * 64u + at - tile_first;
+                if (slot < tile_n) tile[slot] = (uint16_t)v;  // (a damaged stream may leave the range)
+            };
+            decode_span_write(l, w, limit, unit, total, pred0, pred1, pred2, sx, fetch, lut_s, gather, flags);
+        }
+        __syncthreads();
+        // the first and the last word are shared with the neighbouring workgroups
+        const uint32_t lead = (uint32_t)(a - tile_a);
+        uint4* out16 = reinterpret_cast<uint4*>(coef + tile_a);
+        for (uint32_t k = (lead ? 1u : 0u) + t; k < tile_n >> 3; k += kWG) out16[k] = tile16[k];
+        if (t < 16u) {
+            const uint32_t slot = t < 8u ? t : (tile_n & ~7u) + (t & 7u);
+            const bool mine = t < 8u ? (lead != 0u && slot >= lead && slot < tile_n) : (slot < tile_n && (tile_n >= 8u || lead == 0u));
+            if (mine) coef[tile_a + slot] = reinterpret_cast<const int16_t*>(tile16)[slot];
+        }
+        if (!valid) return;
+    } else if (unit < total) {
         win_init(w, l.p, (l.p >> 5) - first_word, fetch);
         prime(l, w, sx, lut_s);
         if (restart) decode_span_write_rst(l, w, limit, unit, total, D.restart * D.upm, pred0, pred1, pred2, sx, fetch, lut_s, store, flags, bword);
         else decode_span_write(l, w, limit, unit, total, pred0, pred1, pred2, sx, fetch, lut_s, store, flags);
     }
-    if (cur != S_chunk && S_low != 0u) {  // the first chunk, left behind
+    if (!tiled && cur != S_chunk && S_low != 0u) {  // the first chunk, left behind
         if (dense) put_part(S_chunk, first, S_low, 4u);
         else put_nonzero(S_chunk, first);
     }
-    if (dense) {
+    if (tiled) {
+        // (everything is written)
+    } else if (dense) {
         // the rest of the lane's range, up to where the next lane takes over (or the image ends)
         const uint32_t E = unit < total ? unit * 64u + l.z : total * 64u;
         if (E > S) {

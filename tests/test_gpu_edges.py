@@ -47,9 +47,9 @@ def test_unstuffing_at_tile_edges(n, share):
     assert not got[k:k + 192].any() and (got[k + 192:] == 0xAA).all()
 
 
-@pytest.mark.parametrize("side", [16, 120, 176, 396, 400, 402, 404, 410, 520])
+@pytest.mark.parametrize("side", [16, 120, 176, 280, 282, 284, 286, 290, 400])
 def test_single_images_around_the_one_kernel_unstuffing(side):
-    """Calls with one image of 1 to about 50 tiles: up to 32 are unstuffed by one kernel, which also copies the parameters
+    """Calls with one image of 1 to about 32 tiles: up to 16 are unstuffed by one kernel, which also copies the parameters
     while other workgroups write the image state; twice in a row on the same buffers."""
     data = encode_jpeg(small_image(side, side, side, ncomp=1, sigma=25.0), 97, "gray").data
     batch = J.prepare_batch([data], J.Config.make())
