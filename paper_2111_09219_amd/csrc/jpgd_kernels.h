@@ -1599,9 +1599,11 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
 // per SIMD with at most 64 registers (48 frames of 1920x1088 4:4:4, one run per workgroup: 307 us with 49 registers, 549
 // with 93).
 
-// Floats per data unit in LDS: 8 rows of 9 (one pad per row) and one more, so that lanes that hold the same row of
-// neighbouring units (the output loops) start in different banks (73 is odd; 72 put 64 of them into 8 banks).
-constexpr int kBlkStride = 73;
+// Floats per data unit in LDS: 8 rows of 9 (one pad per row) and three more.  The phases ask for different strides (the
+// columns for 72, under which 64 lanes meet 64 banks; the output loops, whose lanes hold the same row of neighbouring
+// units, for an odd one), so it is a compromise, measured for 72 / 73 / 74 / 75 / 77: 48 frames of 1920x1088 4:4:4 223 /
+// 228 / 224 / 219 / 228 us, batch of 256 63.9 / 68.0 / 66.4 / 64.6 / 70.0, 15360x8640 174 / 177 / 177 / 176 / 180.
+constexpr int kBlkStride = 75;
 __device__ __constant__ uint8_t c_zigzag[64] = JPGD_ZIGZAG_LITERAL;
 
 // One row of a data unit behind the column pass: its eight samples, level shift applied.
