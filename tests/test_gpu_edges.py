@@ -159,3 +159,18 @@ def test_long_dc_and_ac_codewords(sub, L):
     assert np.array_equal(rec["u"][live], bs["u"][live]) and np.array_equal(rec["z"][live], bs["z"][live])
     assert np.array_equal(rec["units"][live], bs["units"][live])
     assert np.array_equal(rec["dcsum"][live].astype(np.int16), bs["dcsum"][live].astype(np.int16))
+
+
+@pytest.mark.parametrize("sub,L", [("gray", 128), ("444", 128), ("420", 256), ("422", 256)])
+@pytest.mark.parametrize("quality", [5, 30, 75, 95])
+def test_write_pass_below_and_above_its_room_in_lds(sub, L, quality):
+    """Small calls gather a workgroup's coefficients in LDS if they are at most 1024 data units: workgroups of 128 to about
+    10 000 units, so that both ways are taken, in one image as well (flat and noisy halves); onto a buffer that is not clear."""
+    px = small_image(quality, 416, 640, ncomp=1 if sub == "gray" else 3, sigma=14.0)
+    px[:, :300] = 120
+    data = encode_jpeg(px, quality, sub).data
+    batch = J.prepare_batch([data], J.Config.make(subseq_bits=L))
+    for _ in range(2):
+        batch.d_coef.fill_(0x1234)
+        batch.decode()
+        _check(batch, 0, data)
