@@ -35,6 +35,7 @@ struct Plan {
     std::vector<uint32_t> lut_of_img;  // index of the table set of image i
     uint32_t nsets = 0, lut_slots = 0, pair_slots = 0;
     uint32_t pix_per_wg = 1;
+    uint64_t out_bytes = 0;  // coefficients and pixels (or planes) at full size
     uint32_t tiles = 0, seqs = 0, grps = 0, bnds = 0, pixwgs = 0, nsub_total = 0;
     uint32_t bmap_words = 0;  // interval-start bitmaps of the images that have restart intervals
     uint32_t L = 0;
@@ -171,6 +172,7 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
         d.pix_runs = (d.mcus_x + M - 1) / M;
         if ((uint64_t)pl.pixwgs + (uint64_t)d.pix_runs * d.mcus_y > 0x7FFFFFFFull) return JPGD_E_ARG;  // grid size
         pl.pixwgs += d.pix_runs * d.mcus_y;
+        pl.out_bytes += (uint64_t)d.total_units * 128u + (uint64_t)d.width * d.height * d.ncomp;
         // table slots: distinct DC tables first, then distinct AC tables, in order of first use
         uint32_t dc_ids[3], ac_ids[3], ndc = 0, nac = 0, comp_dc[3], comp_ac[3];
         for (uint32_t c = 0; c < in.ncomp; ++c) {
@@ -564,7 +566,8 @@ int launch_report(Call& c, bool with_pixels) {
     if (with_pixels) {
         c.P.verdict = c.verdict_dev;
         c.P.ticket = ticket;
-        if (c.P.scale_log2 == 0u) LAUNCH(JPGD_K_PIXELS, k_pixels, c.pl.pixwgs, kWG, 0);
+        if (c.P.scale_log2 == 0u && pass_caches(c.pl.out_bytes)) LAUNCH(JPGD_K_PIXELS, k_pixels<true>, c.pl.pixwgs, kWG, 0);
+        else if (c.P.scale_log2 == 0u) LAUNCH(JPGD_K_PIXELS, k_pixels<false>, c.pl.pixwgs, kWG, 0);
         else if (c.P.scale_log2 == 1u) LAUNCH(JPGD_K_PIXELS, k_pixels_scaled<4>, c.pl.pixwgs, kWG, 0);
         else if (c.P.scale_log2 == 2u) LAUNCH(JPGD_K_PIXELS, k_pixels_scaled<2>, c.pl.pixwgs, kWG, 0);
         else LAUNCH(JPGD_K_PIXELS, k_pixels_scaled<1>, c.pl.pixwgs, kWG, 0);

@@ -179,6 +179,14 @@ constexpr int kTileBytes = 128 * 1024;
 constexpr int kAloneTiles = 16;
 constexpr int kPixBlocks = 48;      // data units per workgroup of the pixel kernel
 constexpr int kPixBlocksScaled = 192;  // ... of the reduced-size pixel kernels (a unit needs 16, 4 or 1 floats of LDS there)
+// Pixel kernel, streaming accesses (k_pixels<true>): for calls whose coefficients and pixels together do not fit the chip's
+// last-level cache of 256 MB.  Of a smaller call the coefficients are still there when the pixel kernel wants them, and
+// the pixels when the caller does.  Measured ordinary / streaming, a call alone and one followed by a kernel that reads
+// its pixels (us): 1920x1088 4:4:4 (19 MB) 73 / 73 and 80 / 83; 4096x4096 4:4:4 (151 MB) 144 / 147 and 218 / 250; frames
+// of 1920x1088 4:4:4: 12 (226 MB) 158 / 161 and 271 / 316, 14 (263 MB) 171 / 172 and 332 / 353, 16 (301 MB) 192 / 192
+// and 428 / 396, 20 (376 MB) 237 / 222 and 535 / 480; 256 images of 512x384 4:2:0 (302 MB) 329 / 328 and 683 / 642.
+constexpr uint64_t kLastLevelBytes = 256ull << 20;
+JPGD_HD bool pass_caches(uint64_t coef_and_pixel_bytes) { return coef_and_pixel_bytes > kLastLevelBytes; }
 
 JPGD_HD uint32_t align_up(uint32_t v, uint32_t a) { return (v + a - 1) / a * a; }
 

@@ -1614,24 +1614,26 @@ __device__ __forceinline__ void row_samples(const float* b, float (&v)[8]) {
     idct8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
 }
 
-// The coefficients are read for the last time here and the pixels are not read again: both pass by the caches'
-// replacement order (non-temporal), so that they do not push each other out half used.  Measured on 48 frames of 1920x1088
+// ONCE (pass_caches): the coefficients, read for the last time here, and the pixels pass by the caches' replacement order
+// (non-temporal), so that they do not push each other out half used.  Measured on 48 frames of 1920x1088
 // 4:4:4 (903 MB): 260 -> 225 us, 4.0 TB/s (reads alone 238, and the write pass of the next call slower; stores alone
 // 265), the call 538 -> 488; 15360x8640 187 -> 177.  Gray and planar rows, eight bytes to a store, keep the ordinary
 // ones (3001x2003 4:2:2 planes 13.8 / 14.6).
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
 typedef uint32_t words4_u __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t words2_u __attribute__((ext_vector_type(2), aligned(1)));
-__device__ __forceinline__ uint4 load_once(const uint4* p) {
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_coef(const uint4* p) {
+    if constexpr (!ONCE) return *p;
     const words4 v = __builtin_nontemporal_load(reinterpret_cast<const words4*>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // The first nbytes (at most 4 * NW) bytes of w.  Full groups leave as wide stores at any alignment.
-template <int NW>
+template <int NW, bool ONCE>
 __device__ __forceinline__ void put_bytes(uint8_t* dst, const uint32_t (&w)[NW], uint32_t nbytes) {
     if (nbytes == 4u * NW) {
-        if constexpr (NW == 6) {
+        if constexpr (NW == 6 && ONCE) {
             __builtin_nontemporal_store(words4_u{w[0], w[1], w[2], w[3]}, reinterpret_cast<words4_u*>(dst));
             __builtin_nontemporal_store(words2_u{w[4], w[5]}, reinterpret_cast<words2_u*>(dst + 16));
         } else {
@@ -1644,6 +1646,7 @@ __device__ __forceinline__ void put_bytes(uint8_t* dst, const uint32_t (&w)[NW],
         if (e < nbytes) dst[e] = (uint8_t)(w[e >> 2] >> (8u * (e & 3u)));
 }
 
+template <bool ONCE>
 __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
     __shared__ float blk[kPixBlocks * kBlkStride];
     __shared__ __attribute__((aligned(16))) float qf[3 * 64];
@@ -1688,8 +1691,8 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
     // 8 coefficients (16 bytes) per lane and step
     uint4 raw0 = make_uint4(0u, 0u, 0u, 0u), raw1 = raw0;
     const uint4* coef = reinterpret_cast<const uint4*>(P.coef + D.coef_off + (size_t)((size_t)mrow * D.mcus_x + m0) * upm * 64u);
-    if (t < nblk * 8u) raw0 = load_once(coef + t);
-    if (t + kWG < nblk * 8u) raw1 = load_once(coef + t + kWG);
+    if (t < nblk * 8u) raw0 = load_coef<ONCE>(coef + t);
+    if (t + kWG < nblk * 8u) raw1 = load_coef<ONCE>(coef + t + kWG);
 
     // dequantise + de-zigzag
     auto place = [&](uint32_t j, const uint4& raw) {
@@ -1749,7 +1752,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
             row_samples(blk + __umul24(__umul24(m, upm) + __umul24(py >> 3, hs) + (xin >> 3), (uint32_t)kBlkStride) + (py & 7u) * 9u, v);
             uint32_t w[2];
             pack8(w, v);
-            put_bytes<2>(pix + (size_t)gy * D.width + gx0, w, min(8u, D.width - gx0));
+            put_bytes<2, ONCE>(pix + (size_t)gy * D.width + gx0, w, min(8u, D.width - gx0));
         }
         if (ncomp == 3u) {
             const uint32_t cw = (D.width + hs - 1u) >> lhs, ch = (D.height + vs - 1u) >> lvs;  // chroma plane size
@@ -1765,7 +1768,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
                 row_samples(blk + __umul24(__umul24(m, upm) + hs * vs + c, (uint32_t)kBlkStride) + py * 9u, v);
                 uint32_t w[2];
                 pack8(w, v);
-                put_bytes<2>(cplane + (size_t)c * cw * ch + (size_t)gy * cw + gx0, w, min(8u, cw - gx0));
+                put_bytes<2, ONCE>(cplane + (size_t)c * cw * ch + (size_t)gy * cw + gx0, w, min(8u, cw - gx0));
             }
         }
     } else {
@@ -1827,7 +1830,7 @@ __global__ __launch_bounds__(kWG) void k_pixels(Params P) {
                 pack12(w[3], w[4], w[5], y[4], y[5], y[6], y[7], a, b, c, d);
             }
         }
-        put_bytes<6>(pix + (size_t)gy * row_bytes + __umul24(gx0, 3u), w, min(8u, D.width - gx0) * 3u);
+        put_bytes<6, ONCE>(pix + (size_t)gy * row_bytes + __umul24(gx0, 3u), w, min(8u, D.width - gx0) * 3u);
     }
     }
     if (--left == 0u) break;

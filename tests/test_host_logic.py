@@ -160,6 +160,7 @@ def emul():
     lib.emul_set_sync_waves.argtypes = [u32]
     lib.emul_build_lut.argtypes = [vp, vp, ctypes.c_int, vp]
     lib.emul_build_pairs.argtypes = [vp, vp]
+    lib.emul_pass_caches.argtypes = [ctypes.c_uint64]
     lib.emul_pairs_vs_single.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, vp]
     return lib
 
@@ -192,6 +193,17 @@ def test_zigzag_literal_is_the_diagonal_walk(emul):
             elif c == 0: r += 1
             else: r, c = r + 1, c - 1
     assert lit.tolist() == walk == zigzag().tolist()
+
+
+@pytest.mark.parametrize("w,h,units_per_8x8,ncomp,images,streaming", [
+    (1920, 1088, 3, 3, 1, 0), (4096, 4096, 3, 3, 1, 0), (1920, 1088, 3, 3, 14, 0),      # 19, 151 and 263 MB
+    (1920, 1088, 3, 3, 16, 1), (15360, 8640, 1.5, 3, 1, 1), (512, 384, 1.5, 3, 256, 1)])  # 301, 796 and 302 MB
+def test_only_calls_beyond_the_last_level_cache_stream_their_pixels(emul, w, h, units_per_8x8, ncomp, images, streaming):
+    """The pixel kernel leaves a call's pixels and coefficients in the caches, for whoever reads them next, unless the two
+    together are more than the 256 MB those hold."""
+    nbytes = images * (int(w * h / 64 * units_per_8x8) * 128 + w * h * ncomp)
+    assert emul.emul_pass_caches(nbytes) == streaming
+    assert emul.emul_pass_caches(256 << 20) == 0 and emul.emul_pass_caches((256 << 20) + 1) == 1
 
 
 @pytest.mark.parametrize("optimize", [False, True])
