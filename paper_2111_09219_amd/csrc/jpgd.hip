@@ -500,6 +500,12 @@ size_t lds_write_bytes(uint32_t L, uint32_t lut_slots, bool restart) {
     return (size_t)lut_slots * kLutEntries * 2 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
 }
 
+// The write kernel that gathers its output in LDS is granted the most it may ever ask for, so that calls of different
+// sizes do not each change its attribute.
+constexpr size_t kLdsTiledMax = (size_t)kMaxSlots * kLutEntries * 2 + (kWG * (kTileMaxL / 32) + 4) * 4 + kTileBytes;
+static_assert((kMaxSlots * kLutEntries * 2 + (kWG * (kTileMaxL / 32) + 4) * 4) % 16 == 0, "the tile follows at a multiple of 16");
+static_assert(kLdsTiledMax + 1024 <= 160 * 1024, "with the kernel's static LDS on one CU");
+
 // dynamic LDS beyond the default limit has to be requested per kernel and device; remember what was granted
 size_t g_lds_granted[kMaxDevices][9];
 int grant_lds(int dev, int which, const void* kernel, size_t bytes) {
@@ -606,15 +612,20 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.lds_inter = (size_t)pl.lut_slots * kLutEntries * 2;
     if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
     c.staged = pl.L <= kStagedMaxL;
-    const bool tiled = c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups;
-    const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u), tile_bytes = tiled ? (uint32_t)kTileBytes : 0u;
+    const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u);
+    uint32_t tile_bytes = 0u;
+    if (c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups)
+        for (int i = 0; i < n; ++i) {
+            const uint32_t room = tile_room(infos[i].total_units, infos[i].scan_bytes, pl.L);
+            if (room > tile_bytes) tile_bytes = room;
+        }
     // the variants of the intra-sequence kernel: stream staged in LDS or not, call with or without restart intervals
     c.variant = (c.staged ? 0 : 1) + (any_restart ? 2 : 0);
     const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
                                          (const void*)k_sync_intra<true, true>, (const void*)k_sync_intra<false, true>};
     if ((rc = grant_lds(c.device, c.variant, sync_kernels[c.variant], c.lds_sync)) ||
         (rc = grant_lds(c.device, c.staged ? 4 : 5, c.staged ? (const void*)k_write<true, false> : (const void*)k_write<false, false>, c.lds_write)) ||
-        (tiled && (rc = grant_lds(c.device, 7, (const void*)k_write<true, true>, tile_off + tile_bytes))) ||
+        (tile_bytes && (rc = grant_lds(c.device, 7, (const void*)k_write<true, true>, kLdsTiledMax))) ||
         (rc = grant_lds(c.device, 8, (const void*)k_sync_inter, c.lds_inter)) ||
         (pl.split && c.staged && (rc = grant_lds(c.device, 6, (const void*)k_sync_head<true, false>, c.lds_sync))))
         return rc;
@@ -923,7 +934,7 @@ extern "C" int jpgd_init(void) {
     if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kMaxSlots, kMaxPairs, false));
     if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kMaxSlots, true));
     if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kMaxSlots, true));
-    if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, lds_write_bytes(kTileMaxL, kMaxSlots, false) + 16 + kTileBytes);
+    if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, kLdsTiledMax);
     if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, (size_t)kMaxSlots * kLutEntries * 2);
     if (rc) return rc;
     {

@@ -167,13 +167,25 @@ struct Status {
 // of the workgroup clearing its stretch of the output first
 constexpr uint32_t kDenseBitsPerUnit = 256u;
 constexpr int kUnstuffTile = 4096;  // bytes per workgroup of the unstuff kernels (256 lanes x 16 bytes)
-// Write kernel with the output gathered in LDS: calls of at most one workgroup for every other CU (such a workgroup takes
-// nearly all of a CU's LDS, and two calls in flight shall not wait for each other), subsequences of up to 256 bits (of
-// longer ones a workgroup covers more coefficients than fit), and the room for them: 1024 data units.
+// Write kernel with the output gathered in LDS: calls of at most one workgroup for every other CU (two calls in flight
+// shall not wait for each other's LDS), subsequences of up to 256 bits (of longer ones a workgroup covers more
+// coefficients than fit), and at most this much room for them: 1024 data units.
 // Measured, in memory / in LDS: 256x256 gray 24.3 / 20.3 us of write pass; 1920x1088 4:4:4 (180 workgroups) 20.6 / 19.0.
 constexpr int kTileMaxGroups = 128;
 constexpr int kTileMaxL = 256;
 constexpr int kTileBytes = 128 * 1024;
+// Room for the groups of one image: what its average group covers and a quarter more; 0 if that average does not fit.
+// A workgroup that covers more than the room writes to memory, and one that asks for more room than it needs keeps the
+// workgroups of other calls, and itself, off a CU.  Measured with 128 KB whatever the image / this rule / no room at all
+// (us): six 640x480 4:4:4 images behind two 4096x4096 ones, on four streams 840 / 768 / 803, behind two batches of 16
+// frames of 1920x1088 1041 / 994 / 930; each alone 107.4 / 105.3 / 114.2; twice the average 830, 1030 and 106.7.
+JPGD_HD uint32_t tile_room(uint32_t total_units, uint64_t scan_bytes, uint32_t L) {
+    const uint64_t bits = scan_bytes * 8u, group = (uint64_t)kWG * L;
+    const uint64_t units = bits <= group ? total_units : (uint64_t)total_units * group / bits;
+    if (units * 128u > (uint64_t)kTileBytes) return 0u;
+    const uint64_t room = (units + units / 4u + 1u) * 128u;
+    return room < (uint64_t)kTileBytes ? (uint32_t)((room + 1023u) & ~(uint64_t)1023u) : (uint32_t)kTileBytes;
+}
 // Up to this many tiles in a call with one image the unstuffing is one kernel.  Whole calls, one kernel / two (us): 2.5 tiles 218 / 221,
 // 16 tiles 234 / 236, 32 tiles 313 / 311, 100 tiles 355 / 347.
 constexpr int kAloneTiles = 16;

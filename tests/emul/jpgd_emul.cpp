@@ -580,6 +580,9 @@ extern "C" void emul_zigzag(uint8_t out[64]) {
 // the pixel kernel's choice between ordinary and streaming accesses
 extern "C" int emul_pass_caches(uint64_t coef_and_pixel_bytes) { return pass_caches(coef_and_pixel_bytes) ? 1 : 0; }
 
+// the write kernel's room for its output in LDS
+extern "C" uint32_t emul_tile_room(uint32_t total_units, uint64_t scan_bytes, uint32_t L) { return tile_room(total_units, scan_bytes, L); }
+
 // one table built by jpgd_lut.h
 extern "C" int emul_build_lut(const uint8_t* bits, const uint8_t* vals, int is_dc, uint16_t* out) {
     return build_lut(bits, vals, is_dc != 0, out) ? 0 : JPGD_E_TABLE;

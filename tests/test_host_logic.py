@@ -161,6 +161,8 @@ def emul():
     lib.emul_build_lut.argtypes = [vp, vp, ctypes.c_int, vp]
     lib.emul_build_pairs.argtypes = [vp, vp]
     lib.emul_pass_caches.argtypes = [ctypes.c_uint64]
+    lib.emul_tile_room.argtypes = [u32, ctypes.c_uint64, u32]
+    lib.emul_tile_room.restype = u32
     lib.emul_pairs_vs_single.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, vp]
     return lib
 
@@ -204,6 +206,23 @@ def test_only_calls_beyond_the_last_level_cache_stream_their_pixels(emul, w, h, 
     nbytes = images * (int(w * h / 64 * units_per_8x8) * 128 + w * h * ncomp)
     assert emul.emul_pass_caches(nbytes) == streaming
     assert emul.emul_pass_caches(256 << 20) == 0 and emul.emul_pass_caches((256 << 20) + 1) == 1
+
+
+def test_room_for_gathered_output_follows_the_image(emul):
+    """The write kernel asks for as much LDS as the image's average workgroup of 256 subsequences covers and a quarter
+    more, in 1 KB steps; for none where that average does not fit 128 KB, and never for more than those."""
+    assert emul.emul_tile_room(97920, 740_000, 128) == 85 * 1024     # 1920x1088 4:4:4 at 60 bits a unit: (542 * 5/4 + 1) * 128 bytes
+    assert emul.emul_tile_room(1024, 5_000, 256) == 128 * 1024       # one workgroup, all of its units
+    assert emul.emul_tile_room(1, 20, 128) == 1024                   # 8x8 pixels
+    rng = np.random.default_rng(0)
+    for _ in range(2000):
+        L, units, nbytes = int(rng.choice([128, 256])), int(rng.integers(1, 1 << 20)), int(rng.integers(1, 1 << 22))
+        need = 128.0 * units * min(1.0, 256.0 * L / (8.0 * nbytes))
+        room = emul.emul_tile_room(units, nbytes, L)
+        if need >= 128 * 1024 + 128:
+            assert room == 0
+        elif need <= 128 * 1024:
+            assert need - 128 <= room <= min(128 * 1024, 1.25 * need + 1280) and room % 1024 == 0
 
 
 @pytest.mark.parametrize("optimize", [False, True])
