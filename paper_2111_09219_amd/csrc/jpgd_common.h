@@ -68,10 +68,10 @@ constexpr uint32_t kHandoff = 48u;
 // wavefront, one after the other (the walk takes about half the time of a lane's loop per subsequence).
 constexpr int kInterCoopMax = 2;
 
-JPGD_HD bool lut_esc(uint32_t e) { return e >= 0x8000u; }
-JPGD_HD uint32_t lut_total(uint32_t e) { return e & 31u; }
-JPGD_HD uint32_t lut_size(uint32_t e) { return (e >> 5) & 15u; }
-JPGD_HD uint32_t lut_adv(uint32_t e) { return (e >> 9) & 63u; }
+JPGD_HD constexpr bool lut_esc(uint32_t e) { return e >= 0x8000u; }
+JPGD_HD constexpr uint32_t lut_total(uint32_t e) { return e & 31u; }
+JPGD_HD constexpr uint32_t lut_size(uint32_t e) { return (e >> 5) & 15u; }
+JPGD_HD constexpr uint32_t lut_adv(uint32_t e) { return (e >> 9) & 63u; }
 JPGD_HD uint32_t lut_esc_bits(uint32_t e) { return e & 7u; }
 JPGD_HD uint32_t lut_esc_offset(uint32_t e) { return ((e >> 3) & 255u) << 1; }
 

@@ -593,11 +593,12 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
 // lane i < upm describes data unit i of the MCU: slot of its AC table (bits 0-2), slot of the DC table of the
 // unit that follows (3-5), index of that unit (6-9), and where its DC differences go in the walk's two sums: shift
 // inside the first word (10-14: 0 for component 0, 16 for component 1), or the second word (bit 15, component 2)
+constexpr uint32_t kUwDcNext = 3u, kUwNext = 6u, kUwShift = 10u, kUwSecond = 15u;
 __device__ __forceinline__ uint32_t coop_unit_word(const Syntax& sx, uint32_t lane) {
     if (lane >= sx.upm) return 0u;
     const UnitRow r = sx.rows[lane];
-    return (r.tb_ac / (uint32_t)kLutEntries) | ((r.tb_dc_next / (uint32_t)kLutEntries) << 3) | (r.next << 6) |
-           (r.dcmul == 1u ? 0u : r.dcmul == (1u << 15) ? 16u << 10 : 1u << 15);
+    return (r.tb_ac / (uint32_t)kLutEntries) | ((r.tb_dc_next / (uint32_t)kLutEntries) << kUwDcNext) | (r.next << kUwNext) |
+           (r.dcmul == 1u ? 0u : r.dcmul == (1u << 15) ? 16u << kUwShift : 1u << kUwSecond);
 }
 
 // second-level entry of a codeword longer than the first-level index, asked for by the whole wavefront at once
@@ -619,7 +620,15 @@ __device__ __forceinline__ uint32_t coop_resolve_lane(LutPtr lut, uint32_t slot,
 
 // A table entry as the walk adds it to its packed state (coop_span_sync): bits taken (every entry takes at least one)
 // in bits 0..4, zig-zag slots covered in bits 9..14, and bit 15 of a first-level escape, which stops the walk.
-__device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & 0xFE1Fu; }
+constexpr uint32_t kCoopStep = 0xFE1Fu;
+__device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & kCoopStep; }
+// What the packed state (coop_span_sync) and the walk's instructions take for granted of a table entry: 5 bits of
+// length, 4 of value bits, 6 of slots, the escape's flag on top, and an end of block that completes any unit; of a unit
+// word: three bits of a table slot, four of a unit.
+static_assert(lut_total(kCoopStep) == 31u && lut_total(~31u) == 0u && lut_size(0x1E0u) == 15u && lut_size(~0x1E0u) == 0u);
+static_assert(lut_adv(kCoopStep) == 63u && lut_adv(~0x7E00u) == 0u && lut_esc(0x8000u) && !lut_esc(0x7FFFu) && kAdvEob == 63u);
+static_assert(kUwDcNext >= 3u && kUwNext == kUwDcNext + 3u && kUwShift == kUwNext + 4u && kUwSecond == kUwShift + 5u);
+constexpr uint32_t bit_field(uint32_t at, uint32_t bits) { return (bits << 16) | at; }  // operand of s_bfe
 
 // The chain followed through one window: S (window position and zig-zag index, see coop_span_sync), the unit word cur,
 // the slot of the next DC symbol's table, the completed units and the DC sums are advanced until the window is
@@ -630,7 +639,9 @@ __device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & 0xFE1Fu; 
 // about 75 with five taken branches per change of unit, where 4 and 47 with one or two will do.  Registers only: no
 // memory is touched, and every step moves on by at least one bit, so the loop ends after at most 64 steps.
 // dc_a holds the sums of components 0 and 1 (two 16-bit fields, the lower one's sign taken off the upper one), dc_b
-// that of component 2.
+// that of component 2.  (Sums that leave 16 bits come out otherwise than from the lanes' loop in the components behind; the
+// sums of a chain that is in step do so only where DC values leave the range of 8-bit samples, and the 15-bit fields
+// of the lanes do not hold those either.)
 // Measured, compiled loops / this (synchronisation kernels, us): 4096x4096 4:2:0 502 / 465, second kernel of 15360x8640
 // 966 / 890, 24 images of 2047x1535 362 / 335, one 1600x1200 image 218 / 201, batch of 256 251 / 243, 1920x1088 42 / 40.5.
 constexpr uint32_t kCoopLeft = 0u, kCoopAcEscape = 1u, kCoopDcEscape = 2u;
@@ -655,7 +666,7 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         "s_bitcmp1_b32 %[r], 15\n"
         "s_cbranch_scc1 29f\n"
         "s_and_b32 %[t], %[r], 31\n"
-        "s_bfe_u32 %[r2], %[r], 0x40005\n"
+        "s_bfe_u32 %[r2], %[r], %[f_size]\n"
         "s_sub_u32 %[t], %[t], %[r2]\n"
         "s_lshl_b32 %[v], %[v], %[t]\n"       // value bits from the top
         "s_ashr_i32 %[v], %[v], 1\n"
@@ -666,14 +677,14 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         "s_xor_b32 %[t], %[t], %[t2]\n"
         "s_add_i32 %[v], %[v], %[t]\n"
         "s_add_i32 %[v], %[v], 1\n"           // the difference, as in symbol_value
-        "s_bfe_u32 %[t], %[cur], 0x5000a\n"
+        "s_bfe_u32 %[t], %[cur], %[f_shift]\n"
         "s_lshl_b32 %[v], %[v], %[t]\n"
-        "s_bitcmp1_b32 %[cur], 15\n"
+        "s_bitcmp1_b32 %[cur], %[b_second]\n"
         "s_cselect_b32 %[t], %[v], 0\n"
         "s_cselect_b32 %[v], 0, %[v]\n"
         "s_add_u32 %[dcb], %[dcb], %[t]\n"
         "s_add_u32 %[dca], %[dca], %[v]\n"
-        "s_and_b32 %[r], %[r], 0x7e1f\n"
+        "s_and_b32 %[r], %[r], %[step]\n"
         "s_add_u32 %[S], %[S], %[r]\n"          // the index becomes 1; it stays 0 where no codeword starts
         "s_movk_i32 %[why], 0\n"
         "s_bitcmp1_b32 %[S], 6\n"
@@ -699,8 +710,8 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         // unit complete: the next one's word, and its AC table if that is another
         "s_add_u32 %[nb], %[nb], 1\n"
         "s_and_b32 %[S], %[S], 0x7f\n"
-        "s_bfe_u32 %[t], %[cur], 0x40006\n"
-        "s_bfe_u32 %[dcs], %[cur], 0x30003\n"
+        "s_bfe_u32 %[t], %[cur], %[f_next]\n"
+        "s_bfe_u32 %[dcs], %[cur], %[f_dcs]\n"
         "s_and_b32 %[r], %[cur], 7\n"
         "v_readlane_b32 %[cur], %[uw], %[t]\n"
         "s_and_b32 %[r2], %[cur], 7\n"
@@ -712,7 +723,7 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         "s_nop 1\n"
         "v_cndmask_b32 %[acv], %[e01], %[e23], vcc\n"
         "v_lshrrev_b32 %[acv], %[t], %[acv]\n"
-        "v_and_b32 %[acs], 0xfe1f, %[acv]\n"
+        "v_and_b32 %[acs], %[step], %[acv]\n"
         "23:\n"
         "s_bitcmp1_b32 %[S], 6\n"
         "s_cbranch_scc0 20b\n"
@@ -724,7 +735,9 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         : [S] "+&s"(S), [cur] "+&s"(cur), [dcs] "+&s"(dc_slot), [nb] "+&s"(nb), [dca] "+&s"(dc_a),
           [dcb] "+&s"(dc_b), [acv] "+&v"(acv),
           [acs] "+&v"(acs), [why] "=&s"(why), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v)
-        : [e01] "v"(e01), [e23] "v"(e23), [peek] "v"(peek), [uw] "v"(unit_word)
+        : [e01] "v"(e01), [e23] "v"(e23), [peek] "v"(peek), [uw] "v"(unit_word),
+          [step] "i"(kCoopStep), [f_size] "i"(bit_field(5u, 4u)), [f_dcs] "i"(bit_field(kUwDcNext, 3u)),
+          [f_next] "i"(bit_field(kUwNext, 4u)), [f_shift] "i"(bit_field(kUwShift, 5u)), [b_second] "i"(kUwSecond)
         : "vcc", "scc");
     return why;
 }
@@ -780,7 +793,7 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
     uint32_t nb = 0u, dc_a = 0u, dc_b = 0u;
     uint32_t cur = __builtin_amdgcn_readlane(unit_word, u);
     // slot of the table of the DC symbol that starts the current unit (its AC table is in bits 0..2 of its word)
-    uint32_t dc_slot = (__builtin_amdgcn_readlane(unit_word, u == 0u ? upm - 1u : u - 1u) >> 3) & 7u;
+    uint32_t dc_slot = (__builtin_amdgcn_readlane(unit_word, u == 0u ? upm - 1u : u - 1u) >> kUwDcNext) & 7u;
     uint32_t w0 = 0u, held = 0u;
     bool have = false;
     if (p < limit) {
@@ -816,8 +829,8 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
                     const uint32_t pk = __builtin_amdgcn_readlane(peek, S);
                     const uint32_t e = coop_resolve(lut, dc_slot, (pair >> ((dc_slot & 1u) << 4)) & 0xFFFFu, pk);
                     const int32_t d = symbol_value(pk, lut_total(e), lut_size(e));
-                    if (cur & 0x8000u) dc_b += (uint32_t)d;
-                    else dc_a += (uint32_t)d << ((cur >> 10) & 31u);
+                    if (cur & (1u << kUwSecond)) dc_b += (uint32_t)d;
+                    else dc_a += (uint32_t)d << ((cur >> kUwShift) & 31u);
                     S = __builtin_amdgcn_readfirstlane(S + coop_step(e));  // the index becomes 1, or stays 0 where no codeword starts
                     if (S & 0x40u) break;
                 }
@@ -828,7 +841,7 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
         }
         p = ws + (S & 0x7Fu);
         z = S >> 9;
-        const uint32_t next = (cur >> 6) & 15u;  // of the unit the chain is in now
+        const uint32_t next = (cur >> kUwNext) & 15u;  // of the unit the chain is in now
         u = next == 0u ? upm - 1u : next - 1u;
     }
     p_io = p; u_io = u; z_io = z; nb_out = nb;
