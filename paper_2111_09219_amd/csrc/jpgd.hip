@@ -117,7 +117,7 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
     pl = Plan();  // (a slot's plan is used again by the slot's next call)
     const bool scaled = cfg && ((cfg->flags >> 2) & 3u) != 0u;  // reduced-size pixels: larger runs per workgroup
     uint32_t L = cfg && cfg->subseq_bits ? cfg->subseq_bits : choose_subseq_bits(infos, n);
-    if (L < 128u || L > 2048u || (L & (L - 1u))) return JPGD_E_ARG;
+    if (L < kMinSubseqBits || L > kMaxSubseqBits || (L & (L - 1u))) return JPGD_E_ARG;
     // default overlap: enough warm-up lanes that the chain entering a sequence is almost always synchronised,
     // which leaves the inter-sequence kernel one subsequence per boundary
     uint32_t H = (!cfg || cfg->overlap == 0xFFFFFFFFu) ? (L <= 256u ? 16u : 32u) : cfg->overlap;

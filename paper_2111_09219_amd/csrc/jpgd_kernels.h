@@ -182,6 +182,7 @@ __device__ __forceinline__ Seg get_sums(const uint32_t* s4) { return Seg{s4[0], 
 // Group totals added up by the synchronisation kernels (Params::fold): the workgroup of tile lt, which runs before
 // them, clears the total of group lt (a group of subsequences holds at least the bits of a tile, so an image has no
 // more groups than tiles).
+static_assert((uint64_t)kWG * kMinSubseqBits >= 8ull * kUnstuffTile, "every group's total is cleared by a tile of its own number");
 __device__ __forceinline__ void clear_group_total(const Params& P, const ImgDesc& D, uint32_t lt) {
     if (P.fold && lt < D.ngrp_max && threadIdx.x < 4u) reinterpret_cast<uint32_t*>(P.grp_tot + D.grp0 + lt)[threadIdx.x] = 0u;
 }
