@@ -112,7 +112,11 @@ typedef struct {
 #define JPGD_F_SCALE_4 8u   /* the same at 1/4: 2 x 2 lowest frequencies, 2-point transform */
 #define JPGD_F_SCALE_8 12u  /* the same at 1/8: one sample per data unit, DC * Q / 8 + 128 */
 
-/* kernels of the pipeline, in launch order */
+/* Kernels of the pipeline, in launch order.  Not every call launches all of them: UNSTUFF_COUNT is left out for a
+   single image of at most 64 KB without restart intervals, whose UNSTUFF_SCATTER counts itself; UNSTUFF_SCAN and
+   SCAN_PREFIX where every image has at most 256 tiles or groups; SYNC_TAIL unless the synchronisation is split;
+   SYNC_INTER where every image is a single sequence; SCAN_TOTALS in calls without restart intervals, but for
+   further rounds (jpgd_report.redo); PIXELS where no pixels are asked for. */
 enum {
     JPGD_K_UNSTUFF_COUNT = 0, /* unstuff: bytes to drop per tile                                   */
     JPGD_K_UNSTUFF_SCAN,      /* unstuff: exclusive scan of the tile counts, unstuffed length      */
@@ -256,7 +260,9 @@ int jpgd_decode(const jpgd_info* info, const uint8_t* d_scan, int16_t* d_coef, u
  *
  * jpgd_init: once per device, with that device current, before the first jpgd_decode_static there (calling it
  * again is harmless).  It looks up the array's device address, allocates the pinned parameter and verdict blocks
- * of the fixed slot and asks for the kernels' dynamic LDS.  Not needed by the other entry points.
+ * of the fixed slot and asks for the kernels' dynamic LDS.  Not needed by the other entry points: they ask for it
+ * in the first call that uses a kernel on a device (one function attribute each, small beside the few milliseconds the
+ * loading of the kernels costs the first call of a process).
  *
  * jpgd_decode_static: arguments as jpgd_decode.  JPGD_E_WORKSPACE if the image needs more workspace than the
  * array holds (jpgd_workspace_bytes(info, 1, cfg) > JPGD_STATIC_WORKSPACE_BYTES: roughly, scans beyond 1.8 MB),

@@ -768,14 +768,15 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
 }
 
 // Waits for the verdict of a call and, if the boundaries between sequences are not settled yet, settles them first
-// (rounds of the inter-sequence kernel and the totals kernel, which says whether a boundary is still open; paper: the
-// host repeats the phase until all sequences are synchronised) and runs the write pass and the pixels once more.
+// (rounds of the inter-sequence kernel and the totals kernel, which says whether a boundary is still open, as the write
+// kernel does in the first round of a call without restart intervals; paper: the host repeats the phase until all
+// sequences are synchronised) and runs the write pass and the pixels once more.
 int finish_call(Call& c, jpgd_report* report) {
     int rc = wait_verdict(c);
     if (rc) return rc;
     uint32_t flags = c.verdict[0];
     // pending: a sequence whose records were made for another entry state than the one the sequence before it
-    // now ends in (k_group_totals).  Its states may all be right, so that the write pass finds nothing, while the
+    // now ends in (check_boundaries).  Its states may all be right, so that the write pass finds nothing, while the
     // counts and DC sums of its first records are not.
     bool pending = c.verdict[2] != 0u;
     // A broken chain (a write lane that did not end in the recorded state) with more than one sequence, or an open

@@ -132,7 +132,7 @@ struct ImgDesc {
     uint32_t hs, vs;       // luma sampling factors
     uint32_t mcus_x, mcus_y;
     uint32_t pix_wg0;      // first workgroup of the pixel kernel
-    uint32_t pix_runs;     // workgroups per MCU row
+    uint32_t pix_runs;     // runs of MCUs per MCU row (a workgroup takes Params::pix_per_wg of the image's runs)
     uint32_t qt_off;       // element (uint16) offset of 3 x 64 quantisation values (per component, zig-zag)
     // restart intervals (0 = the scan has none)
     uint32_t restart;      // MCUs per interval
@@ -190,7 +190,7 @@ JPGD_HD uint32_t tile_room(uint32_t total_units, uint64_t scan_bytes, uint32_t L
 // Up to this many tiles in a call with one image the unstuffing is one kernel.  Whole calls, one kernel / two (us): 2.5 tiles 218 / 221,
 // 16 tiles 234 / 236, 32 tiles 313 / 311, 100 tiles 355 / 347.
 constexpr int kAloneTiles = 16;
-constexpr int kPixBlocks = 48;      // data units per workgroup of the pixel kernel
+constexpr int kPixBlocks = 48;      // data units per run of MCUs of the pixel kernel
 constexpr int kPixBlocksScaled = 192;  // ... of the reduced-size pixel kernels (a unit needs 16, 4 or 1 floats of LDS there)
 // Pixel kernel, streaming accesses (k_pixels<true>): for calls whose coefficients and pixels together do not fit the chip's
 // last-level cache of 256 MB.  Of a smaller call the coefficients are still there when the pixel kernel wants them, and

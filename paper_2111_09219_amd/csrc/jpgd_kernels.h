@@ -48,9 +48,10 @@ struct Params {
     uint32_t fold;          // calls without restart intervals: the synchronisation kernels add up the group totals as they
                             // publish records, and k_group_totals only runs in further rounds
     uint32_t sync_waves;    // wavefronts per workgroup of that kernel: kWG / 64 that hold the lanes, the rest only take chains
-    // A call with one image has the last up_wgs workgroups of k_unstuff_count copy the call's parameter block
-    // (up_n16 16-byte words) from pinned host memory into the workspace: that kernel does not need the block, all
-    // later ones do, and a kernel of its own for the copy would cost a dispatch.  up_wgs = 0: nothing to copy.
+    // A call with one image has the last up_wgs workgroups of its first kernel (k_unstuff_count, or k_unstuff_scatter<true>,
+    // which leaves out the image states it writes itself) copy the call's parameter block (up_n16 16-byte words) from
+    // pinned host memory into the workspace: that kernel does not need the block, all later ones do, and a kernel of
+    // its own for the copy would cost a dispatch.  up_wgs = 0: nothing to copy.
     const uint4* up_src;
     uint4* up_dst;
     uint32_t up_n16;
@@ -1201,8 +1202,8 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     uint32_t g = 0u, x0 = 0u;
     bool work = false;
     // The state words of records at a boundary are read here while the lane of the boundary before may be rewriting
-    // them (and read again by the totals kernel, which opens another round if the two did not agree): single
-    // 32-bit accesses, marked as such, with the rest of a record written before its state word.
+    // them (and read again by check_boundaries, in the write or the totals kernel, which opens another round if the two
+    // did not agree): single 32-bit accesses, marked as such, with the rest of a record written before its state word.
     if (gfirst < nsub) {
         g = (uint32_t)gfirst;
         x0 = __atomic_load_n(&rec[g - 1u].x, __ATOMIC_RELAXED);
