@@ -33,7 +33,7 @@ struct Plan {
     WsHeader h;
     std::vector<ImgDesc> img;
     std::vector<uint32_t> lut_of_img;  // index of the table set of image i
-    uint32_t nsets = 0, lut_slots = 0, pair_slots = 0;
+    uint32_t nsets = 0, lut_slots = 0;
     uint32_t pix_per_wg = 1;
     uint64_t out_bytes = 0;  // coefficients and pixels (or planes) at full size
     uint32_t tiles = 0, seqs = 0, grps = 0, bnds = 0, pixwgs = 0, nsub_total = 0;
@@ -189,7 +189,6 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
         }
         d.nslots = ndc + nac;
         d.ndc = ndc;
-        if (nac > pl.pair_slots) pl.pair_slots = nac;
         d.sched_dc = d.sched_ac = d.sched_comp = 0;
         uint32_t u = 0;
         for (uint32_t c = 0; c < in.ncomp; ++c) {
@@ -399,14 +398,16 @@ struct LutCacheEntry {
     uint64_t stamp;
     uint16_t lut[kLutEntries];
     uint8_t pairs[kPairBytes];  // AC tables
+    uint32_t sub_words;         // sync_sub_words
 };
 std::mutex g_lut_mu;
 std::vector<LutCacheEntry> g_lut_cache;
 uint64_t g_lut_clock = 0;
 constexpr size_t kLutCacheMax = 32;
 
-// pairs: where the pair bytes of an AC table go (null for a DC table)
-bool cached_lut(const uint8_t bits[16], const uint8_t* vals, bool is_dc, uint16_t* out, uint8_t* pairs) {
+// pairs: where the pair bytes of an AC table go (null for a DC table); sub_words: words of subtables it needs in the
+// synchronisation kernels
+bool cached_lut(const uint8_t bits[16], const uint8_t* vals, bool is_dc, uint16_t* out, uint8_t* pairs, uint32_t* sub_words) {
     uint32_t nvals = 0;
     for (int k = 0; k < 16; ++k) nvals += bits[k];
     if (nvals > 256u) return false;
@@ -416,10 +417,12 @@ bool cached_lut(const uint8_t bits[16], const uint8_t* vals, bool is_dc, uint16_
             e.stamp = ++g_lut_clock;
             memcpy(out, e.lut, sizeof e.lut);
             if (pairs) memcpy(pairs, e.pairs, sizeof e.pairs);
+            *sub_words = e.sub_words;
             return true;
         }
     if (!build_lut(bits, vals, is_dc, out)) return false;
     if (pairs) build_pairs(out, pairs);
+    *sub_words = sync_sub_words(out, is_dc);
     LutCacheEntry* victim;
     if (g_lut_cache.size() < kLutCacheMax) {
         g_lut_cache.emplace_back();
@@ -436,6 +439,7 @@ bool cached_lut(const uint8_t bits[16], const uint8_t* vals, bool is_dc, uint16_
     victim->stamp = ++g_lut_clock;
     memcpy(victim->lut, out, sizeof victim->lut);
     if (pairs) memcpy(victim->pairs, pairs, sizeof victim->pairs);
+    victim->sub_words = *sub_words;
     return true;
 }
 
@@ -486,15 +490,15 @@ uint32_t staged_max_bits() {
 size_t lds_bitmap_bytes(uint32_t L, bool restart) {
     return restart && L <= (uint32_t)kBitmapLdsMaxL ? ((size_t)(kWG * (L / 32) + 4 + 7) / 8 + 2) * 4 : 0;
 }
-size_t lds_sync_bytes(uint32_t L, uint32_t lut_slots, uint32_t pair_slots, bool restart) {
+size_t lds_sync_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
     uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + 4 : 4;
-    return (size_t)lut_slots * kLutEntries * 2 + (size_t)pair_slots * kPairBytes + 6 * kWG * 4 + (size_t)nwords * 4 +
-           lds_bitmap_bytes(L, restart);
+    return (size_t)tab_bytes + kSyncFixedWords * 4 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
 }
 // the second of the two synchronisation kernels keeps the tables and the records, not the stream
-size_t lds_tail_bytes(uint32_t lut_slots, uint32_t pair_slots) {
-    return (size_t)lut_slots * kLutEntries * 2 + (size_t)pair_slots * kPairBytes + 4 * kWG * 4 + 2 * kHandMax * 4 + 16;
-}
+size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + kSyncFixedWords * 4 + 16; }
+// most bytes that any image's tables take there
+constexpr uint32_t kSyncTabMax = kMaxPairs * (kSyncDcBytes + kSyncAcBytes) + kMaxPairs * 4 * (1022u + kLutL2);
+static_assert(kSyncTabMax <= 8u << 13, "an escape has 13 bits for its subtable");
 size_t lds_write_bytes(uint32_t L, uint32_t lut_slots, bool restart) {
     uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + 4 : 4;
     return (size_t)lut_slots * kLutEntries * 2 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
@@ -607,10 +611,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.stream = stream;
     c.ws = (uint8_t*)d_workspace;
     const bool any_restart = pl.bmap_words != 0u;
-    c.lds_sync = lds_sync_bytes(pl.L, pl.lut_slots, pl.pair_slots, any_restart);
     c.lds_write = lds_write_bytes(pl.L, pl.lut_slots, any_restart);
-    c.lds_inter = (size_t)pl.lut_slots * kLutEntries * 2;
-    if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
     c.staged = pl.L <= kStagedMaxL;
     const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u);
     uint32_t tile_bytes = 0u;
@@ -619,6 +620,52 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
             const uint32_t room = tile_room(infos[i].total_units, infos[i].scan_bytes, pl.L);
             if (room > tile_bytes) tile_bytes = room;
         }
+    rc = call_reserve(c, pl.h.upload_bytes + 16);
+    if (rc) return rc;
+    uint8_t* up = c.buf;
+    memset(up, 0, pl.h.upload_bytes);
+    memcpy(up, &pl.h, sizeof pl.h);
+    uint16_t* luts = (uint16_t*)(up + pl.h.off_lut);
+    uint16_t* qts = (uint16_t*)(up + pl.h.off_qt);
+    uint32_t tab_bytes = 0u;  // of the tables in the synchronisation kernels
+    for (int i = 0; i < n; ++i) {
+        const jpgd_info& in = infos[i];
+        ImgDesc& d = pl.img[i];
+        if (i == 0 || pl.lut_of_img[i] != pl.lut_of_img[i - 1]) {
+            uint16_t* set = luts + d.lut_off;
+            uint32_t built = 0u;  // slots of this set already filled
+            uint32_t words[kMaxSlots] = {0}, all = 0u;
+            for (uint32_t u = 0; u < d.upm; ++u) {
+                uint32_t cc = (d.sched_comp >> (4 * u)) & 15u;
+                uint32_t sd = (d.sched_dc >> (4 * u)) & 15u, sa = (d.sched_ac >> (4 * u)) & 15u;
+                if (!(built & (1u << sd)) &&
+                    !cached_lut(in.dht_bits[0][in.td[cc]], in.dht_vals[0][in.td[cc]], true, set + sd * kLutEntries, nullptr,
+                                words + sd))
+                    return JPGD_E_TABLE;
+                built |= 1u << sd;
+                if (!(built & (1u << sa)) &&
+                    !cached_lut(in.dht_bits[1][in.ta[cc]], in.dht_vals[1][in.ta[cc]], false, set + sa * kLutEntries,
+                                (uint8_t*)(set + kMaxSlots * kLutEntries) + (sa - d.ndc) * kPairBytes, words + sa))
+                    return JPGD_E_TABLE;
+                built |= 1u << sa;
+            }
+            d.sub_words = 0u;
+            for (uint32_t k = 0; k < d.nslots; ++k) {
+                all += words[k];
+                if (k >= d.ndc) d.sub_words |= words[k] << (10u * (k - d.ndc));
+            }
+            const uint32_t bytes = (d.ndc * kSyncDcBytes + (d.nslots - d.ndc) * kSyncAcBytes + all * 4u + 15u) & ~15u;
+            if (bytes > tab_bytes) tab_bytes = bytes;
+        } else {
+            d.sub_words = pl.img[i - 1].sub_words;
+        }
+        for (uint32_t cc = 0; cc < in.ncomp; ++cc)
+            for (int k = 0; k < 64; ++k) qts[d.qt_off + cc * 64 + k] = in.qt[in.tq[cc]][k];
+    }
+    memcpy(up + pl.h.off_img, pl.img.data(), sizeof(ImgDesc) * (size_t)n);
+    c.lds_sync = lds_sync_bytes(pl.L, tab_bytes, any_restart);
+    c.lds_inter = tab_bytes;
+    if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
     // the variants of the intra-sequence kernel: stream staged in LDS or not, call with or without restart intervals
     c.variant = (c.staged ? 0 : 1) + (any_restart ? 2 : 0);
     const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
@@ -629,37 +676,6 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
         (rc = grant_lds(c.device, 8, (const void*)k_sync_inter, c.lds_inter)) ||
         (pl.split && c.staged && (rc = grant_lds(c.device, 6, (const void*)k_sync_head<true, false>, c.lds_sync))))
         return rc;
-    rc = call_reserve(c, pl.h.upload_bytes + 16);
-    if (rc) return rc;
-    uint8_t* up = c.buf;
-    memset(up, 0, pl.h.upload_bytes);
-    memcpy(up, &pl.h, sizeof pl.h);
-    memcpy(up + pl.h.off_img, pl.img.data(), sizeof(ImgDesc) * (size_t)n);
-    uint16_t* luts = (uint16_t*)(up + pl.h.off_lut);
-    uint16_t* qts = (uint16_t*)(up + pl.h.off_qt);
-    for (int i = 0; i < n; ++i) {
-        const jpgd_info& in = infos[i];
-        const ImgDesc& d = pl.img[i];
-        if (i == 0 || pl.lut_of_img[i] != pl.lut_of_img[i - 1]) {
-            uint16_t* set = luts + d.lut_off;
-            uint32_t built = 0u;  // slots of this set already filled
-            for (uint32_t u = 0; u < d.upm; ++u) {
-                uint32_t cc = (d.sched_comp >> (4 * u)) & 15u;
-                uint32_t sd = (d.sched_dc >> (4 * u)) & 15u, sa = (d.sched_ac >> (4 * u)) & 15u;
-                if (!(built & (1u << sd)) &&
-                    !cached_lut(in.dht_bits[0][in.td[cc]], in.dht_vals[0][in.td[cc]], true, set + sd * kLutEntries, nullptr))
-                    return JPGD_E_TABLE;
-                built |= 1u << sd;
-                if (!(built & (1u << sa)) &&
-                    !cached_lut(in.dht_bits[1][in.ta[cc]], in.dht_vals[1][in.ta[cc]], false, set + sa * kLutEntries,
-                                (uint8_t*)(set + kMaxSlots * kLutEntries) + (sa - d.ndc) * kPairBytes))
-                    return JPGD_E_TABLE;
-                built |= 1u << sa;
-            }
-        }
-        for (uint32_t cc = 0; cc < in.ncomp; ++cc)
-            for (int k = 0; k < 64; ++k) qts[d.qt_off + cc * 64 + k] = in.qt[in.tq[cc]][k];
-    }
     uint8_t* ws = c.ws;
     // The parameter block goes from the pinned buffer into the workspace: for a batch by a kernel of its own (the
     // first kernel of the path already looks its image up in the block), for a single image by extra workgroups of
@@ -690,7 +706,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.overlap = pl.h.overlap;
     P.seq_len = kWG - pl.h.overlap;
     P.lut_slots = pl.lut_slots;
-    P.pair_slots = pl.pair_slots;
+    P.tab_bytes = tab_bytes;
     P.planar = (flags_in & JPGD_F_PLANAR) ? 1u : 0u;
     P.scale_log2 = scale_log2;
     P.pix_per_wg = pl.pix_per_wg;
@@ -753,7 +769,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
         else LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_head<false, false>), pl.seqs, kWG, c.lds_sync);
         P.sync_waves = (uint32_t)(kWG / 64);
         P.coop_max = kTailCoopMax;
-        LAUNCH(JPGD_K_SYNC_TAIL, (k_sync_tail<false>), pl.seqs, kWG, lds_tail_bytes(pl.lut_slots, pl.pair_slots));
+        LAUNCH(JPGD_K_SYNC_TAIL, (k_sync_tail<false>), pl.seqs, kWG, lds_tail_bytes(tab_bytes));
     } else
     switch (c.variant) {
         case 0: LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_intra<true, false>), pl.seqs, 64u * P.sync_waves, c.lds_sync); break;
@@ -931,12 +947,12 @@ extern "C" int jpgd_init(void) {
     const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
                                          (const void*)k_sync_intra<true, true>, (const void*)k_sync_intra<false, true>};
     for (int v = 0; v < 4; ++v)
-        if ((rc = grant_lds(dev, v, sync_kernels[v], lds_sync_bytes(2048u, kMaxSlots, kMaxPairs, v >= 2)))) break;
-    if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kMaxSlots, kMaxPairs, false));
+        if ((rc = grant_lds(dev, v, sync_kernels[v], lds_sync_bytes(2048u, kSyncTabMax, v >= 2)))) break;
+    if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kSyncTabMax, false));
     if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kMaxSlots, true));
     if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kMaxSlots, true));
     if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, kLdsTiledMax);
-    if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, (size_t)kMaxSlots * kLutEntries * 2);
+    if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, kSyncTabMax);
     if (rc) return rc;
     {
         std::lock_guard<std::mutex> lock(g_mu);

@@ -140,7 +140,7 @@ struct ImgDesc {
     uint32_t bmap_off;     // word offset of this image's interval-start bitmap (one bit per unstuffed byte,
                            // 128 words per unstuff tile plus 128 of slack)
     uint32_t ndc;          // DC tables of this image: slots 0 .. ndc-1; its AC tables follow, AC table k with pair bytes k
-    uint32_t pad_;
+    uint32_t sub_words;    // words of subtables of its AC tables in the synchronisation kernels, 10 bits each
 };
 
 // written by the unstuff kernels

@@ -37,7 +37,7 @@ struct Params {
     uint32_t overlap;       // H: warm-up lanes in front of each sequence
     uint32_t seq_len;       // kWG - H: subsequences a sequence owns
     uint32_t lut_slots;     // max tables of any image (sizes the LDS copy)
-    uint32_t pair_slots;    // max AC tables of any image (sizes the LDS copy of their pair bytes)
+    uint32_t tab_bytes;     // max bytes of any image's tables in the layout of the synchronisation kernels (a multiple of 16)
     uint32_t planar;        // pixel kernel: component planes (no upsampling, no colour conversion) instead of RGB
     uint32_t pix_per_wg;    // pixel kernel: runs of MCUs a workgroup takes one after the other
     uint32_t scale_log2;    // pixel kernel: output at 1/2^scale_log2 of the size (0..3)
@@ -249,14 +249,62 @@ __device__ __forceinline__ void stage_luts(const Params& P, const ImgDesc& D, ui
     for (uint32_t k = threadIdx.x; k < n16 / 8u; k += blockDim.x) dst[k] = src[k];
 }
 
-// pair bytes of the image's AC tables, behind its table slots in memory; pair_of_unit: 8 words of LDS
-__device__ __forceinline__ void stage_pairs(const Params& P, const ImgDesc& D, uint8_t* pair_s, uint32_t* pair_of_unit) {
-    const uint32_t n16 = (D.nslots - D.ndc) * (uint32_t)(kPairBytes / 16);
-    const uint4* src = reinterpret_cast<const uint4*>(P.luts + D.lut_off + (uint32_t)(kMaxSlots * kLutEntries));
-    uint4* dst = reinterpret_cast<uint4*>(pair_s);
-    for (uint32_t k = threadIdx.x; k < n16; k += blockDim.x) dst[k] = src[k];
-    if (threadIdx.x < D.upm)
-        pair_of_unit[threadIdx.x] = (((D.sched_ac >> (4u * threadIdx.x)) & 15u) - D.ndc) * (uint32_t)kPairBytes;
+// The image's tables as the synchronisation kernels read them (sync_entry), at the start of the dynamic LDS: DC tables, AC
+// tables, subtables of the AC tables, subtables of the DC tables in any order.  dc_fill: a word of LDS, zero since the
+// last barrier; all of it is complete after the next one.  What points into the tables (the rows, escapes) counts its bytes
+// from the start of LDS: a lane then has its addresses without an addition.
+using LdsBytes = const __attribute__((address_space(3))) uint8_t*;
+using LdsWords = const __attribute__((address_space(3))) uint32_t*;
+__device__ __forceinline__ uint32_t lds_at(const void* p) { return (uint32_t)(uintptr_t)(LdsBytes)p; }
+__device__ __forceinline__ uint32_t lds_word(uint32_t at) { return *(LdsWords)(uintptr_t)at; }
+__device__ __forceinline__ uint32_t sync_ac_at(const ImgDesc& D) { return D.ndc * kSyncDcBytes; }
+__device__ __forceinline__ void stage_sync_tables(const Params& P, const ImgDesc& D, uint8_t* lds, uint32_t* dc_fill) {
+    uint32_t* const tab = reinterpret_cast<uint32_t*>(lds);
+    const uint16_t* luts = P.luts + D.lut_off;
+    const uint8_t* pairs = reinterpret_cast<const uint8_t*>(luts + kMaxSlots * kLutEntries);
+    const uint32_t nac = D.nslots - D.ndc;
+    const uint32_t ac = sync_ac_at(D), l2 = ac + nac * kSyncAcBytes, lds0 = lds_at(lds);
+    const uint32_t n0 = D.sub_words & 1023u, n1 = (D.sub_words >> 10) & 1023u, n2 = D.sub_words >> 20;
+    static_assert(kMaxPairs == 3, "sub_words holds three counts");
+    for (uint32_t k = threadIdx.x; k < nac * (uint32_t)(kLutL1 / 8); k += blockDim.x) {  // eight entries
+        const uint32_t a = k / (uint32_t)(kLutL1 / 8), i = (k % (uint32_t)(kLutL1 / 8)) * 8u;
+        const uint4 e = *reinterpret_cast<const uint4*>(luts + (D.ndc + a) * (uint32_t)kLutEntries + i);
+        const uint2 pb = *reinterpret_cast<const uint2*>(pairs + a * (uint32_t)kPairBytes + i);
+        const uint32_t at = lds0 + l2 + (a > 0u ? n0 * 4u : 0u) + (a > 1u ? n1 * 4u : 0u);
+        uint4* dst = reinterpret_cast<uint4*>(tab + (ac >> 2) + a * (uint32_t)kLutL1 + i);
+        dst[0] = make_uint4(sync_ac_entry(0u, e.x & 0xFFFFu, pb.x & 255u, at), sync_ac_entry(1u, e.x >> 16, (pb.x >> 8) & 255u, at),
+                            sync_ac_entry(0u, e.y & 0xFFFFu, (pb.x >> 16) & 255u, at), sync_ac_entry(1u, e.y >> 16, pb.x >> 24, at));
+        dst[1] = make_uint4(sync_ac_entry(0u, e.z & 0xFFFFu, pb.y & 255u, at), sync_ac_entry(1u, e.z >> 16, (pb.y >> 8) & 255u, at),
+                            sync_ac_entry(0u, e.w & 0xFFFFu, (pb.y >> 16) & 255u, at), sync_ac_entry(1u, e.w >> 16, pb.y >> 24, at));
+    }
+    for (uint32_t k = threadIdx.x; k < (n0 + n1 + n2) >> 1; k += blockDim.x) {  // two entries
+        uint32_t j = 2u * k, a = 0u;
+        if (j >= n0) { j -= n0; a = 1u; if (j >= n1) { j -= n1; a = 2u; } }
+        const uint32_t e = *reinterpret_cast<const uint32_t*>(luts + (D.ndc + a) * (uint32_t)kLutEntries + (uint32_t)kLutL1 + j);
+        reinterpret_cast<uint2*>(tab + (l2 >> 2))[k] = make_uint2(sync_entry(e & 0xFFFFu, false, 0u), sync_entry(e >> 16, false, 0u));
+    }
+    const uint32_t dc_sub = l2 + (n0 + n1 + n2) * 4u;
+    for (uint32_t k = threadIdx.x; k < D.ndc << kSyncDcK; k += blockDim.x) {
+        const uint16_t* lut = luts + (k >> kSyncDcK) * (uint32_t)kLutEntries;
+        const uint32_t e = *reinterpret_cast<const uint32_t*>(lut + (k & ((1u << kSyncDcK) - 1u)) * 2u);
+        const uint32_t a = e & 0xFFFFu, b = e >> 16, n = sync_dc_sub(a, b);
+        if (n == 0xFFFFFFFFu) {
+            tab[k] = sync_dc_direct(a);
+        } else {
+            const uint32_t at = dc_sub + atomicAdd(dc_fill, 8u << n);  // (a multiple of 8)
+            for (uint32_t j = 0u; j < 2u << n; ++j) tab[(at >> 2) + j] = sync_dc_sub_entry(a, b, n, j, lut + kLutL1);
+            tab[k] = sync_escape(n + 1u, lds0 + at);
+        }
+    }
+}
+
+// rows: 8 entries of LDS, complete after the next barrier
+__device__ __forceinline__ void stage_sync_rows(const ImgDesc& D, SyncRow* rows, uint32_t tab) {
+    const uint32_t u = threadIdx.x, un = u + 1u == D.upm ? 0u : u + 1u;
+    if (u < D.upm)
+        rows[u] = SyncRow{tab + sync_ac_at(D) + (((D.sched_ac >> (4u * u)) & 15u) - D.ndc) * kSyncAcBytes,
+                          tab + ((D.sched_dc >> (4u * un)) & 15u) * kSyncDcBytes, 1u << (15u * ((D.sched_comp >> (4u * u)) & 15u)),
+                          un * (uint32_t)sizeof(SyncRow)};
 }
 
 // rows: 8 entries of LDS, complete after the next barrier
@@ -596,28 +644,29 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
 // unit that follows (3-5), index of that unit (6-9), and where its DC differences go in the walk's two sums: shift
 // inside the first word (10-14: 0 for component 0, 16 for component 1), or the second word (bit 15, component 2)
 constexpr uint32_t kUwDcNext = 3u, kUwNext = 6u, kUwShift = 10u, kUwSecond = 15u;
-__device__ __forceinline__ uint32_t coop_unit_word(const Syntax& sx, uint32_t lane) {
-    if (lane >= sx.upm) return 0u;
-    const UnitRow r = sx.rows[lane];
-    return (r.tb_ac / (uint32_t)kLutEntries) | ((r.tb_dc_next / (uint32_t)kLutEntries) << kUwDcNext) | (r.next << kUwNext) |
-           (r.dcmul == 1u ? 0u : r.dcmul == (1u << 15) ? 16u << kUwShift : 1u << kUwSecond);
+__device__ __forceinline__ uint32_t coop_unit_word(const ImgDesc& D, uint32_t lane) {
+    if (lane >= D.upm) return 0u;
+    const uint32_t next = lane + 1u == D.upm ? 0u : lane + 1u, comp = (D.sched_comp >> (4u * lane)) & 15u;
+    return ((D.sched_ac >> (4u * lane)) & 15u) | (((D.sched_dc >> (4u * next)) & 15u) << kUwDcNext) | (next << kUwNext) |
+           (comp == 2u ? 1u << kUwSecond : comp * 16u << kUwShift);
 }
 
-// second-level entry of a codeword longer than the first-level index, asked for by the whole wavefront at once
-template <class LutPtr>
-__device__ __forceinline__ uint32_t coop_resolve(LutPtr lut, uint32_t slot, uint32_t e, uint32_t peek) {
-    const uint32_t nb2 = lut_esc_bits(e);
-    const uint32_t at = slot * (uint32_t)kLutEntries + (uint32_t)kLutL1 + lut_esc_offset(e) +
-                        ((peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u));
-    return __builtin_amdgcn_readfirstlane((uint32_t)lut[at]);
-}
-
-// the same for every lane's own entry and bits
-template <class LutPtr>
-__device__ __forceinline__ uint32_t coop_resolve_lane(LutPtr lut, uint32_t slot, uint32_t e, uint32_t peek) {
-    const uint32_t nb2 = lut_esc_bits(e);
-    return lut[slot * (uint32_t)kLutEntries + (uint32_t)kLutL1 + lut_esc_offset(e) +
-               ((peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u))];
+// Where the tables of the image's (at most four) slots lie and how their indices are made, the same in every lane.  A slot
+// the image does not have is asked as the last one it has.
+struct CoopTables {
+    uint32_t base[4], shift[4], dc[4];  // dc: the bits of an entry of the walk that are a DC symbol's value bits
+};
+__device__ __forceinline__ CoopTables coop_tables(uint32_t nslots, uint32_t ndc, uint32_t tab) {
+    CoopTables c;
+#pragma unroll
+    for (uint32_t i = 0; i < 4u; ++i) {
+        const uint32_t s = min(i, nslots - 1u);
+        const bool is_dc = s < ndc;
+        c.base[i] = tab + (is_dc ? s * kSyncDcBytes : ndc * kSyncDcBytes + (s - ndc) * kSyncAcBytes);
+        c.shift[i] = 32u - (is_dc ? kSyncDcK : kSyncAcK);
+        c.dc[i] = is_dc ? 0x1E0u : 0u;
+    }
+    return c;
 }
 
 // A table entry as the walk adds it to its packed state (coop_span_sync): bits taken (every entry takes at least one)
@@ -745,17 +794,21 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
 }
 
 // What the lanes know about one window of 64 bit positions: lane j holds the 32 bits that start at position j and
-// the first-level entry of each table for them (a table the image does not have is asked as the last one it has).
+// the first-level entry of each table for them.
 struct CoopWindow {
     uint32_t peek, e0, e1, e2, e3;
+    __device__ __forceinline__ uint32_t of_slot(uint32_t slot) const {
+        const uint32_t a = (slot & 1u) ? 0u + e1 : 0u + e0, b = (slot & 1u) ? 0u + e3 : 0u + e2;
+        return (slot & 2u) ? 0u + b : 0u + a;
+    }
 };
 
 // The window that starts at bit ws (a multiple of 64).  The wavefront keeps 64 consecutive stream words, one per
 // lane, from word w0 on, and reloads them when a window needs words beyond them (org_word: stream word with cursor
 // 0 of `fetch`; cursors from nwords on are not read).  The table reads are only issued here.
-template <class Fetch, class LutPtr>
+template <class Fetch, class Tab>
 __device__ __forceinline__ CoopWindow coop_window(uint32_t ws, uint32_t& w0, uint32_t& held, bool& have, uint32_t org_word,
-                                                  uint32_t nwords, uint32_t nslots, uint32_t lane, Fetch fetch, LutPtr lut) {
+                                                  uint32_t nwords, const CoopTables& ct, uint32_t lane, Fetch fetch, Tab tab) {
     uint32_t wb = (ws >> 5) - w0;
     if (!have || wb + 2u > 63u) {
         w0 = ws >> 5;
@@ -769,25 +822,24 @@ __device__ __forceinline__ CoopWindow coop_window(uint32_t ws, uint32_t& w0, uin
     const uint32_t hi = lane < 32u ? s0 : s1, lo = lane < 32u ? s1 : s2;
     CoopWindow w;
     w.peek = (uint32_t)(((((uint64_t)hi << 32) | (uint64_t)lo) << (lane & 31u)) >> 32);
-    const uint32_t idx = w.peek >> (32 - kLutK);
-    w.e0 = lut[idx];
-    w.e1 = lut[min(1u, nslots - 1u) * (uint32_t)kLutEntries + idx];
-    w.e2 = lut[min(2u, nslots - 1u) * (uint32_t)kLutEntries + idx];
-    w.e3 = lut[min(3u, nslots - 1u) * (uint32_t)kLutEntries + idx];
+    w.e0 = tab(ct.base[0] + ((w.peek >> ct.shift[0]) << 2));
+    w.e1 = tab(ct.base[1] + ((w.peek >> ct.shift[1]) << 2));
+    w.e2 = tab(ct.base[2] + ((w.peek >> ct.shift[2]) << 2));
+    w.e3 = tab(ct.base[3] + ((w.peek >> ct.shift[3]) << 2));
     return w;
 }
 
 // p, u, z: wave-uniform state of the chain, advanced until p >= limit (limit a multiple of 64).  org_word, nwords:
-// see coop_window.  1 <= nslots <= 4 tables.
+// see coop_window.
 // The windows lie on a 64-bit grid of the stream (a subsequence is a whole number of them, and a chain enters a
 // subsequence at most 31 bits behind its start, so no window is wasted): the window after the current one is known
 // before the chain has been followed through this one, and its table reads are issued first and answered
 // meanwhile.  Escapes are followed up in the walk, where only those on the chain matter.
-template <class Fetch, class LutPtr>
+template <class Fetch, class Tab>
 __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, uint32_t& z_io, uint32_t& nb_out,
                                                int64_t& dc_out, uint32_t limit, uint32_t org_word, uint32_t nwords,
-                                               uint32_t unit_word, uint32_t upm, uint32_t nslots, Fetch fetch,
-                                               LutPtr lut) {
+                                               uint32_t unit_word, uint32_t upm, const CoopTables& ct, Fetch fetch,
+                                               Tab tab) {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t p = __builtin_amdgcn_readfirstlane(p_io);
     uint32_t u = __builtin_amdgcn_readfirstlane(u_io);
@@ -804,15 +856,18 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
         // adding a symbol's step advances both.  Bit 6 set: the window is behind us; bit 15 (or 16, after the step of an
         // escape, which is taken back): the data unit is complete.
         uint32_t S = (p - ws) | (z << 9);
-        CoopWindow nxt = coop_window(ws, w0, held, have, org_word, nwords, nslots, lane, fetch, lut);
+        CoopWindow nxt = coop_window(ws, w0, held, have, org_word, nwords, ct, lane, fetch, tab);
         // (Without this the compiler merges these reads with the ones inside the loop into reads at the top of the
         // loop, where every window would wait for them.)
         asm volatile("" : "+v"(nxt.e0), "+v"(nxt.e1), "+v"(nxt.e2), "+v"(nxt.e3));
         for (;;) {
-            const uint32_t peek = nxt.peek;
-            const uint32_t e01 = nxt.e0 | (nxt.e1 << 16), e23 = nxt.e2 | (nxt.e3 << 16);
+            const CoopWindow now = nxt;
+            const uint32_t peek = now.peek;
+            // (the walk finds a DC symbol's value bits in bits 5..8)
+            const uint32_t e01 = (now.e0 & 0xFFFFu) | ((now.e0 >> 15) & ct.dc[0]) | ((now.e1 | ((now.e1 >> 15) & ct.dc[1])) << 16);
+            const uint32_t e23 = (now.e2 & 0xFFFFu) | ((now.e2 >> 15) & ct.dc[2]) | ((now.e3 | ((now.e3 >> 15) & ct.dc[3])) << 16);
             const bool more = ws + 64u < limit;
-            if (more) nxt = coop_window(ws + 64u, w0, held, have, org_word, nwords, nslots, lane, fetch, lut);
+            if (more) nxt = coop_window(ws + 64u, w0, held, have, org_word, nwords, ct, lane, fetch, tab);
             const uint32_t ac_slot = cur & 7u;
             uint32_t acv = ((ac_slot & 2u) ? e23 : e01) >> ((ac_slot & 1u) << 4);  // the AC entry in the low 16 bits
             uint32_t acs = coop_step(acv);
@@ -824,13 +879,12 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
                     // entry of this table is an escape follows it up now, at once: where codewords are long
                     // (large coefficients) a window holds several on the chain, and one look-up by all lanes
                     // costs less than one by the chain alone.  The step is then taken again.
-                    if (acv & 0x8000u) acv = coop_resolve_lane(lut, cur & 7u, acv, peek);
+                    if (acv & 0x8000u) acv = tab(sync_escape_at(now.of_slot(cur & 7u), peek));
                     acs = coop_step(acv);
                 } else {
-                    const uint32_t pair = __builtin_amdgcn_readlane((dc_slot & 2u) ? e23 : e01, S);
                     const uint32_t pk = __builtin_amdgcn_readlane(peek, S);
-                    const uint32_t e = coop_resolve(lut, dc_slot, (pair >> ((dc_slot & 1u) << 4)) & 0xFFFFu, pk);
-                    const int32_t d = symbol_value(pk, lut_total(e), lut_size(e));
+                    const uint32_t e = __builtin_amdgcn_readfirstlane(tab(sync_escape_at(__builtin_amdgcn_readlane(now.of_slot(dc_slot), S), pk)));
+                    const int32_t d = symbol_value(pk, lut_total(e), (e >> 20) & 15u);
                     if (cur & (1u << kUwSecond)) dc_b += (uint32_t)d;
                     else dc_a += (uint32_t)d << ((cur >> kUwShift) & 31u);
                     S = __builtin_amdgcn_readfirstlane(S + coop_step(e));  // the index becomes 1, or stays 0 where no codeword starts
@@ -868,17 +922,12 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
 // wavefront per chain, and what keeps the chip busy then is the number of sequences in flight: without the staged
 // stream a workgroup needs a third of the LDS, and a CU holds eight of them instead of three.
 constexpr int kSyncAll = 0, kSyncHead = 1, kSyncTail = 2;
-constexpr uint32_t kHandMax = 128u;       // most chains a sequence may hand over
-constexpr uint32_t kHandWords = 6u * kWG;  // per sequence: 4 x kWG record words, 3 x kHandMax chain words, the chain count
+constexpr uint32_t kHandWords = 4u * kWG;  // per sequence: 3 x kWG record words, the chains, in the last word their number
+constexpr uint32_t kSyncFixedWords = 7u * kWG / 2u;  // of LDS: records and chains
+static_assert(kHandoff < kWG, "chains and their number in kWG words");
 template <bool STAGED, bool RST, int PHASE>
 __device__ __forceinline__ void sync_intra_body(const Params& P) {
     static_assert(PHASE != kSyncTail || !STAGED, "the second kernel reads the stream from memory");
-    // Two symbols per step where the tables allow it (sync_symbol_pair); a workgroup whose stretch of the stream holds
-    // the start of a restart interval takes the loop that knows their rules instead, one symbol per step.  Measured
-    // on the 15360x8640 image: first kernel 0.85 -> 0.75 ms, second 1.00 -> 0.87 ms; 4096x4096 0.67 -> 0.59 ms; the
-    // 256-image batch 0.40 -> 0.36 ms; nothing on images whose rounds are mostly walked by whole wavefronts
-    // (1920x1088 with 128-bit subsequences).
-    constexpr bool PAIRS = true;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     const uint32_t wg = blockIdx.x;
     const uint32_t ii = find_image(P, wg, &ImgDesc::seq0);
@@ -887,18 +936,15 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     const int32_t base = (int32_t)((wg - D.seq0) * P.seq_len) - (int32_t)P.overlap;
     if (base >= (int32_t)nsub || (int32_t)((wg - D.seq0) * P.seq_len) >= (int32_t)nsub) return;  // nothing owned
 
-    uint16_t* lut_s = reinterpret_cast<uint16_t*>(lds_raw);
-    uint8_t* pair_s = reinterpret_cast<uint8_t*>(lut_s + P.lut_slots * (uint32_t)kLutEntries);
-    uint32_t* sw = reinterpret_cast<uint32_t*>(pair_s + (PAIRS ? P.pair_slots * (uint32_t)kPairBytes : 0u));
-    uint32_t* pnb = sw + kWG;
-    uint32_t* pdc01 = pnb + kWG;
-    uint32_t* pdc2 = pdc01 + kWG;
-    // staging for packing the running chains: position; z (bits 0..7), u (8..11), target subsequence (12..).
-    // The second kernel never has more than kHandMax chains.
-    constexpr uint32_t kMv = PHASE == kSyncTail ? kHandMax : (uint32_t)kWG;
-    uint32_t* mv_p = pdc2 + kWG;
-    uint32_t* mv_s = mv_p + kMv;
-    uint32_t* strm = mv_s + kMv;
+    // A record: the state after the subsequence (16 bits, pack_state), completed units (15 bits) and "an interval began"
+    // (bit 31), the DC sums of components 0 and 1, that of component 2.
+    uint32_t* rec = reinterpret_cast<uint32_t*>(lds_raw + P.tab_bytes);
+    uint32_t* pdc01 = rec + kWG;
+    uint16_t* pdc2 = reinterpret_cast<uint16_t*>(pdc01 + kWG);
+    // chains on their way to another lane or wavefront: state before the target subsequence, target subsequence << 16
+    uint32_t* mv = reinterpret_cast<uint32_t*>(pdc2 + kWG);
+    static_assert(kSyncFixedWords == 2u * kWG + kWG / 2u + kWG, "what lies between the tables and the stream");
+    uint32_t* strm = mv + kWG;
     __shared__ uint32_t scratch[8];
 
     const uint32_t L = 1u << P.logL, wps = L >> 5;  // words per subsequence
@@ -907,14 +953,12 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     const uint32_t t1 = min((uint32_t)kWG, (uint32_t)((int32_t)nsub - base));  // one past the last such lane
     const uint32_t first_word = first * wps;
     const uint32_t nwords = (t1 - t0) * wps + 4u;
-    __shared__ UnitRow rows[8];
-    __shared__ uint32_t pair_of_unit[8];
-    stage_luts(P, D, lut_s);
-    Syntax sx = stage_syntax(D, rows);
-    if (PAIRS) {
-        stage_pairs(P, D, pair_s, pair_of_unit);
-        sx.pair_of_unit = pair_of_unit;
-    }
+    __shared__ SyncRow rows_s[8];
+    __shared__ uint32_t dc_fill;
+    if (threadIdx.x == 0u) dc_fill = 0u;
+    stage_sync_rows(D, rows_s, lds_at(lds_raw));
+    __syncthreads();
+    stage_sync_tables(P, D, lds_raw, &dc_fill);
     if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
     // scans with restart intervals: the bitmap of interval starts, for the bytes staged above
     uint32_t* bm_s = strm + (STAGED ? kWG * wps + 4u : 4u);
@@ -931,48 +975,51 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
     // cursor = word index inside the workgroup's window
     auto fetch = [&](uint32_t c) { return STAGED ? strm[c] : __builtin_bswap32(gwords[c]); };
+    // The lanes' bits count from the start of LDS, or of the stretch in memory: position in the image's stream plus org.
+    const uint32_t org = (STAGED ? 8u * lds_at(strm) : 0u) - (first_word << 5);
+    auto word = [&](uint32_t b) { return STAGED ? lds_word(b >> 3) : __builtin_bswap32(gwords[b >> 5]); };
+    auto tab = [&](uint32_t k) { return lds_word(k); };
+    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
     const uint32_t t = threadIdx.x;
     const bool valid = t >= t0 && t < t1;
-    Lane l;
-    BitWin w;
-    int64_t dcacc = 0;
+    SyncLane l;
+    l.nb = 0u;
     uint32_t* handed = P.seq_rec + (size_t)wg * kHandWords;
     bool active = false;
     uint32_t tt = t + 1u;
     uint32_t waves_used = kWG / 64u;
+    // bit of the stream at which subsequence k of the workgroup starts
+    auto start_of = [&](uint32_t k) { return (uint32_t)(base + (int32_t)k) << P.logL; };
+    // chain and target as one word, and back
+    auto state_of = [&](uint32_t end) { return pack_state(sync_pos(l) - org - end, (l.S >> 9) & 63u, l.row / (uint32_t)sizeof(SyncRow)); };
+    auto take_chain = [&](uint32_t m) {
+        tt = m >> 16;
+        sync_start(l, start_of(tt) + state_prel(m) + org, state_u(m), state_z(m), D.upm, word, tab, rows);
+    };
+    auto put_record = [&](uint32_t k, uint32_t x, uint32_t units, uint32_t crossed, int64_t dc) {
+        rec[k] = x | (units << 16) | (crossed << 31);
+        pdc01[k] = pack_dc01(dc);
+        pdc2[k] = (uint16_t)pack_dc2(dc);
+    };
     if (PHASE == kSyncTail) {
         // the records the first kernel left, and the chains that were still running
         if (valid) {
-            sw[t] = handed[t];
-            pnb[t] = handed[kWG + t];
-            pdc01[t] = handed[2 * kWG + t];
-            pdc2[t] = handed[3 * kWG + t];
+            rec[t] = handed[t];
+            pdc01[t] = handed[kWG + t];
+            pdc2[t] = (uint16_t)handed[2 * kWG + t];
         }
-        const uint32_t n = handed[4u * kWG + 384u];
+        const uint32_t n = handed[4u * kWG - 1u];
         active = t < n;
-        if (active) {
-            l.p = handed[4u * kWG + t];
-            const uint32_t uz = handed[4u * kWG + 128u + t];
-            l.u = uz >> 8;
-            l.z = uz & 255u;
-            l.nb = 0u;
-            tt = handed[4u * kWG + 256u + t];
-        }
+        if (active) take_chain(handed[3u * kWG + t]);
         waves_used = (n + 63u) >> 6; if (waves_used == 0u) waves_used = 1u;
     } else if (valid) {
-        const uint32_t i = (uint32_t)(base + (int32_t)t);
-        l.p = i << P.logL; l.u = 0u; l.z = 0u; l.nb = 0u;
-        win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-        prime(l, w, sx, lut_s);
-        const uint32_t limit = (i + 1u) << P.logL;
+        const uint32_t limit = start_of(t + 1u);
+        sync_start(l, start_of(t) + org, 0u, 0u, D.upm, word, tab, rows);
         uint32_t crossed = 0u;
-        if (restart) decode_span_sync_rst(l, w, limit, dcacc, crossed, sx, fetch, lut_s, bword);
-        else if (PAIRS) decode_span_sync_pairs(l, w, limit, dcacc, sx, fetch, lut_s, pair_s);
-        else decode_span_sync(l, w, limit, dcacc, sx, fetch, lut_s);
-        sw[t] = pack_state(l.p - limit, l.z, l.u);
-        pnb[t] = l.nb | (crossed << 31);
-        pdc01[t] = pack_dc01(dcacc);
-        pdc2[t] = pack_dc2(dcacc);
+        int64_t dcacc = 0;
+        if (restart) sync_span_rst(l, limit + org, dcacc, crossed, org, D.upm, word, tab, rows, bword);
+        else sync_span(l, limit + org, dcacc, word, tab, rows);
+        put_record(t, state_of(limit), l.nb, crossed, dcacc);
         active = t + 1u < t1;
     }
     // Overflow rounds: in round r the chain that started at subsequence c decodes subsequence c+r from its own
@@ -986,7 +1033,6 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     // such rounds never take longer than the packed ones they replace.
     const uint32_t coop_max = P.lut_slots > 4u ? 0u : (restart ? min(P.coop_max, P.sync_waves) : P.coop_max);
     uint32_t coop_n = 0u;
-    bool first_tail_round = PHASE == kSyncTail;
     for (uint32_t round = 0u;; ++round) {
         const uint64_t bal = __ballot(active);
         uint32_t* cnt = scratch + ((round & 1u) << 2);
@@ -998,17 +1044,12 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
             const uint32_t wave = t >> 6;
             const uint32_t before = wave == 0u ? 0u : wave == 1u ? c0 : wave == 2u ? c0 + c1 : c0 + c1 + c2;
             const uint32_t rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            if (active) {
-                handed[4u * kWG + rank] = l.p;
-                handed[4u * kWG + 128u + rank] = (l.u << 8) | l.z;
-                handed[4u * kWG + 256u + rank] = tt;
-            }
-            if (t == 0u) handed[4u * kWG + 384u] = now;
+            if (active) handed[3u * kWG + rank] = state_of(start_of(tt)) | (tt << 16);
+            if (t == 0u) handed[4u * kWG - 1u] = now;
             if (valid) {
-                handed[t] = sw[t];
-                handed[kWG + t] = pnb[t];
-                handed[2 * kWG + t] = pdc01[t];
-                handed[3 * kWG + t] = pdc2[t];
+                handed[t] = rec[t];
+                handed[kWG + t] = pdc01[t];
+                handed[2 * kWG + t] = pdc2[t];
             }
             return;
         }
@@ -1017,10 +1058,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
             const uint32_t wave = t >> 6;
             const uint32_t before = wave == 0u ? 0u : wave == 1u ? c0 : wave == 2u ? c0 + c1 : c0 + c1 + c2;
             const uint32_t rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            if (active) {
-                mv_p[rank] = l.p;
-                mv_s[rank] = (tt << 12) | (l.u << 8) | l.z;
-            }
+            if (active) mv[rank] = state_of(start_of(tt)) | (tt << 16);
             coop_n = now;
             __syncthreads();
             break;
@@ -1029,48 +1067,28 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
             const uint32_t wave = t >> 6;
             const uint32_t before = wave == 0u ? 0u : wave == 1u ? c0 : wave == 2u ? c0 + c1 : c0 + c1 + c2;
             const uint32_t rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            if (active) {
-                mv_p[rank] = l.p;
-                mv_s[rank] = (tt << 12) | (l.u << 8) | l.z;
-            }
+            if (active) mv[rank] = state_of(start_of(tt)) | (tt << 16);
             __syncthreads();
             active = t < now;
-            if (active) {
-                l.p = mv_p[t];
-                const uint32_t ms = mv_s[t];
-                l.u = (ms >> 8) & 15u;
-                l.z = ms & 255u;
-                tt = ms >> 12;
-                win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-                prime(l, w, sx, lut_s);
-            }
+            if (active) take_chain(mv[t]);
             waves_used = (now + 63u) >> 6;
         }
         if (active) {
             l.nb = 0u;
-            dcacc = 0;
-            const uint32_t limit = ((uint32_t)(base + (int32_t)tt) + 1u) << P.logL;
+            int64_t dcacc = 0;
+            const uint32_t limit = start_of(tt + 1u);
             uint32_t crossed = 0u;
-            if (PHASE == kSyncTail && first_tail_round) {
-                win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-                prime(l, w, sx, lut_s);
-            }
-            if (restart) decode_span_sync_rst(l, w, limit, dcacc, crossed, sx, fetch, lut_s, bword);
-            else if (PAIRS) decode_span_sync_pairs(l, w, limit, dcacc, sx, fetch, lut_s, pair_s);
-            else decode_span_sync(l, w, limit, dcacc, sx, fetch, lut_s);
-            const uint32_t x = pack_state(l.p - limit, l.z, l.u);
-            const bool synced = x == sw[tt];
-            sw[tt] = x;
-            pnb[tt] = l.nb | (crossed << 31);
-            pdc01[tt] = pack_dc01(dcacc);
-            pdc2[tt] = pack_dc2(dcacc);
+            if (restart) sync_span_rst(l, limit + org, dcacc, crossed, org, D.upm, word, tab, rows, bword);
+            else sync_span(l, limit + org, dcacc, word, tab, rows);
+            const uint32_t x = state_of(limit);
+            const bool synced = x == (rec[tt] & 0xFFFFu);
+            put_record(tt, x, l.nb, crossed, dcacc);
             ++tt;
             active = !synced && tt < t1;
         }
-        first_tail_round = false;
     }
     // The same rounds with one chain per wavefront.  The chains keep their slot k < coop_n in a list held twice
-    // (read from one copy, written to the other, swapped every round; mv_s = kCoopDone once a chain has
+    // (read from one copy, written to the other, swapped every round; kCoopDone once a chain has
     // synchronised or reached the end of the sequence).  Every wavefront reads the whole list and takes the
     // running chains whose rank among them is its own number modulo the number of wavefronts (the four that hold
     // the lanes and the ones that are only here for this), so the work stays spread as chains drop out;
@@ -1082,43 +1100,42 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
         const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
         const uint32_t u_n = __builtin_amdgcn_readfirstlane(coop_n), u_t1 = __builtin_amdgcn_readfirstlane(t1);
         const uint32_t u_first = __builtin_amdgcn_readfirstlane(first_word), u_nwords = __builtin_amdgcn_readfirstlane(nwords);
-        const uint32_t u_upm = __builtin_amdgcn_readfirstlane(sx.upm);
+        const uint32_t u_upm = __builtin_amdgcn_readfirstlane(D.upm);
+        const CoopTables ct = coop_tables(__builtin_amdgcn_readfirstlane(D.nslots), __builtin_amdgcn_readfirstlane(D.ndc), lds_at(lds_raw));
         const uint32_t u_waves = P.sync_waves;  // a power of two
         const int32_t u_base = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
-        const uint32_t unit_word = coop_unit_word(sx, lane);
+        const uint32_t unit_word = coop_unit_word(D, lane);
         for (uint32_t par = 0u;; par ^= 1u) {
             const uint32_t rd = par << 6, wr = (par ^ 1u) << 6;
-            const uint32_t mine = lane < u_n ? mv_s[rd + lane] : kCoopDone;
+            const uint32_t mine = lane < u_n ? mv[rd + lane] : kCoopDone;
             const uint64_t running = __ballot(mine != kCoopDone);
             if (running == 0ull) break;
-            if (wave == 0u && lane < u_n && mine == kCoopDone) mv_s[wr + lane] = kCoopDone;
+            if (wave == 0u && lane < u_n && mine == kCoopDone) mv[wr + lane] = kCoopDone;
             uint32_t rank = 0u;
             for (uint64_t m = running; m; m &= m - 1ull, ++rank) {
                 if ((rank & (u_waves - 1u)) != wave) continue;
                 const uint32_t k = (uint32_t)__ffsll((long long)m) - 1u;
-                uint32_t cp = mv_p[rd + k];
-                const uint32_t ms = __builtin_amdgcn_readfirstlane(mv_s[rd + k]);
-                uint32_t cu = (ms >> 8) & 15u, cz = ms & 255u, cnb = 0u;
-                const uint32_t ctt = ms >> 12;
+                const uint32_t ms = __builtin_amdgcn_readfirstlane(mv[rd + k]);
+                const uint32_t ctt = ms >> 16;
+                uint32_t cu = state_u(ms), cz = state_z(ms), cnb = 0u;
+                uint32_t cp = ((uint32_t)(u_base + (int32_t)ctt) << P.logL) + state_prel(ms);
                 int64_t cdc = 0;
-                const uint32_t limit = ((uint32_t)(u_base + (int32_t)ctt) + 1u) << P.logL;
+                const uint32_t limit = (uint32_t)(u_base + (int32_t)ctt + 1) << P.logL;
                 // The wavefront's decoder does not know the rules of restart intervals.  A chain whose stretch holds
                 // no interval start does not need them (decode_span_sync_rst is the plain loop then); one whose
                 // stretch does is decoded by a single lane for this round.
                 uint32_t crossed = 0u;
                 uint32_t B = kNoBoundary;
-                if (restart) B = __builtin_amdgcn_readfirstlane(next_boundary(__builtin_amdgcn_readfirstlane(cp), limit + 64u, bword));
+                if (restart) B = __builtin_amdgcn_readfirstlane(next_boundary(cp, limit + 64u, bword));
                 if (B == kNoBoundary) {
-                    coop_span_sync(cp, cu, cz, cnb, cdc, limit, u_first, u_nwords, unit_word, u_upm, P.lut_slots, fetch, lut_s);
+                    coop_span_sync(cp, cu, cz, cnb, cdc, limit, u_first, u_nwords, unit_word, u_upm, ct, fetch, tab);
                 } else {
                     if (lane == 0u) {
-                        Lane cl;
-                        BitWin cw;
-                        cl.p = cp; cl.u = cu; cl.z = cz; cl.nb = 0u;
-                        win_init(cw, cl.p, (cl.p >> 5) - first_word, fetch);
-                        prime(cl, cw, sx, lut_s);
-                        decode_span_sync_rst(cl, cw, limit, cdc, crossed, sx, fetch, lut_s, bword);
-                        cp = cl.p; cu = cl.u; cz = cl.z; cnb = cl.nb;
+                        SyncLane cl;
+                        cl.nb = 0u;
+                        sync_start(cl, cp + org, cu, cz, D.upm, word, tab, rows);
+                        sync_span_rst(cl, limit + org, cdc, crossed, org, D.upm, word, tab, rows, bword);
+                        cp = sync_pos(cl) - org; cu = cl.row / (uint32_t)sizeof(SyncRow); cz = (cl.S >> 9) & 63u; cnb = cl.nb;
                     }
                     cp = __builtin_amdgcn_readfirstlane(cp);
                     cu = __builtin_amdgcn_readfirstlane(cu);
@@ -1130,14 +1147,10 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
                     cdc = (int64_t)(((uint64_t)dhi << 32) | (uint64_t)dlo);
                 }
                 const uint32_t x = pack_state(cp - limit, cz, cu);
-                const bool synced = x == sw[ctt];
+                const bool synced = x == (rec[ctt] & 0xFFFFu);
                 if (lane == 0u) {
-                    sw[ctt] = x;
-                    pnb[ctt] = cnb | (crossed << 31);
-                    pdc01[ctt] = pack_dc01(cdc);
-                    pdc2[ctt] = pack_dc2(cdc);
-                    mv_p[wr + k] = cp;
-                    mv_s[wr + k] = (synced || ctt + 1u >= u_t1) ? kCoopDone : ((ctt + 1u) << 12) | (cu << 8) | cz;
+                    put_record(ctt, x, cnb, crossed, cdc);
+                    mv[wr + k] = (synced || ctt + 1u >= u_t1) ? kCoopDone : ((ctt + 1u) << 16) | x;
                 }
             }
             __syncthreads();
@@ -1147,7 +1160,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     const bool own = valid && t >= P.overlap;
     const uint32_t own_i = (uint32_t)(base + (int32_t)t);
     if (own) {
-        pub.x = sw[t]; pub.y = pnb[t]; pub.z = pdc01[t]; pub.w = pdc2[t];
+        pub.x = rec[t] & 0xFFFFu; pub.y = (rec[t] >> 16 & 0x7FFFu) | (rec[t] & 0x80000000u); pub.z = pdc01[t]; pub.w = pdc2[t];
         P.sinfo[D.sub0 + own_i] = pub;
     }
     // The sums of the published records go to the totals of the (at most two) groups they belong to.  A kernel of its
@@ -1168,7 +1181,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     // The published records continue the state the last warm-up lane ended in.  If the previous sequence ends
     // in that very state, the two sequences already form one chain and the inter-sequence kernel has nothing
     // to decode at this boundary.
-    if (t == 0u) P.warm_x[wg] = (P.overlap > 0u && P.overlap - 1u >= t0) ? sw[P.overlap - 1u] : 0xFFFFFFFFu;
+    if (t == 0u) P.warm_x[wg] = (P.overlap > 0u && P.overlap - 1u >= t0) ? rec[P.overlap - 1u] & 0xFFFFu : 0xFFFFFFFFu;
 }
 
 template <bool STAGED, bool RST>
@@ -1210,21 +1223,27 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
         work = *warm != x0;
     }
     if (!__syncthreads_or(work)) return;
-    uint16_t* lut_s = reinterpret_cast<uint16_t*>(lds_raw);
-    __shared__ UnitRow rows[8];
-    stage_luts(P, D, lut_s);
-    const Syntax sx = stage_syntax(D, rows);
+    __shared__ SyncRow rows_s[8];
+    __shared__ uint32_t dc_fill;
+    if (threadIdx.x == 0u) dc_fill = 0u;
+    stage_sync_rows(D, rows_s, lds_at(lds_raw));
+    __syncthreads();
+    stage_sync_tables(P, D, lds_raw, &dc_fill);
     __syncthreads();
     const uint32_t* words = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off);
     auto fetch = [&](uint32_t w) { return __builtin_bswap32(words[w]); };
+    auto word = [&](uint32_t b) { return __builtin_bswap32(words[b >> 5]); };
+    auto tab = [&](uint32_t k) { return lds_word(k); };
+    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
     // Usually a handful of boundaries in a whole image have something to decode, and the kernel lasts as long as
     // the slowest of them.  With few in this workgroup, each is walked by the whole wavefront, one after the other
     // (same results as the lane's loop below; the wavefront's decoder does not know restart intervals).
     const uint64_t workers = __ballot(work);
     if (!D.restart && P.lut_slots <= 4u && __popcll(workers) <= kInterCoopMax) {
         const uint32_t lane = threadIdx.x;
-        const uint32_t unit_word = coop_unit_word(sx, lane);
-        const uint32_t u_upm = __builtin_amdgcn_readfirstlane(sx.upm);
+        const uint32_t unit_word = coop_unit_word(D, lane);
+        const uint32_t u_upm = __builtin_amdgcn_readfirstlane(D.upm);
+        const CoopTables ct = coop_tables(__builtin_amdgcn_readfirstlane(D.nslots), __builtin_amdgcn_readfirstlane(D.ndc), lds_at(lds_raw));
         const uint32_t u_nsub = __builtin_amdgcn_readfirstlane(nsub);
         const uint32_t u_nwords = (u_nsub << (P.logL - 5u)) + 4u;
         for (uint64_t m = workers; m; m &= m - 1ull) {
@@ -1238,7 +1257,7 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
                 uint32_t cnb = 0u;
                 int64_t cdc = 0;
                 const uint32_t limit = (cg + 1u) << P.logL;
-                coop_span_sync(cp, cu, cz, cnb, cdc, limit, 0u, u_nwords, unit_word, u_upm, P.lut_slots, fetch, lut_s);
+                coop_span_sync(cp, cu, cz, cnb, cdc, limit, 0u, u_nwords, unit_word, u_upm, ct, fetch, tab);
                 const uint32_t x = pack_state(cp - limit, cz, cu);
                 const bool synced = x == __atomic_load_n(&rec[cg].x, __ATOMIC_RELAXED);
                 if (lane == 0u) {
@@ -1262,23 +1281,18 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     const uint32_t gend = min(nsub, g + P.seq_len);
     const uint32_t* bmap_img = P.bmap + D.bmap_off;
     auto bword = [&](uint32_t k) { return bmap_img[k]; };
-    Lane l;
-    BitWin w;
-    l.p = (g << P.logL) + state_prel(x0);
-    l.z = state_z(x0);
-    l.u = state_u(x0);
-    win_init(w, l.p, l.p >> 5, fetch);  // cursor = word index in the image's stream
-    prime(l, w, sx, lut_s);
+    SyncLane l;
+    sync_start(l, (g << P.logL) + state_prel(x0), state_u(x0), state_z(x0), D.upm, word, tab, rows);
     bool first = true;
     for (;;) {
         l.nb = 0u;
         int64_t dcacc = 0;
         const uint32_t limit = (g + 1u) << P.logL;
         uint32_t crossed = 0u;
-        if (D.restart) decode_span_sync_rst(l, w, limit, dcacc, crossed, sx, fetch, lut_s, bword);
-        else decode_span_sync(l, w, limit, dcacc, sx, fetch, lut_s);
+        if (D.restart) sync_span_rst(l, limit, dcacc, crossed, 0u, D.upm, word, tab, rows, bword);
+        else sync_span(l, limit, dcacc, word, tab, rows);
         SInfo r;
-        r.x = pack_state(l.p - limit, l.z, l.u);
+        r.x = pack_state(sync_pos(l) - limit, (l.S >> 9) & 63u, l.row / (uint32_t)sizeof(SyncRow));
         r.y = l.nb | (crossed << 31);
         r.z = pack_dc01(dcacc);
         r.w = pack_dc2(dcacc);

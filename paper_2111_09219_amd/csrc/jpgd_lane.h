@@ -102,6 +102,10 @@ JPGD_HD void prime(Lane& l, const BitWin& w, const Syntax& sx, LutPtr lut) {
 // Section 2): a leading 1 means the bits are the value itself, a leading 0 means value = bits - (2^size - 1);
 // size 0 gives 0.  peek holds the symbol from its most significant bit on.  With the field read as a signed
 // number s (leading 1 = negative): value = s + 2^size if s < 0, else s - 2^size + 1.
+JPGD_HD int32_t value_of_field(int32_t s, uint32_t size) {
+    // s + 2^size if s < 0, s - (2^size - 1) otherwise: subtract 2^size - 1 with all its bits flipped in the first case
+    return s - (int32_t)(((1u << size) - 1u) ^ (uint32_t)(s >> 31));
+}
 JPGD_HD int32_t symbol_value(uint32_t peek, uint32_t total, uint32_t size) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const int32_t s = __builtin_amdgcn_sbfe((int32_t)peek, (32u - total) & 31u, size);
@@ -109,8 +113,7 @@ JPGD_HD int32_t symbol_value(uint32_t peek, uint32_t total, uint32_t size) {
     const uint32_t raw = (peek >> ((32u - total) & 31u)) & ((1u << size) - 1u);
     const int32_t s = size ? (int32_t)(raw << (32u - size)) >> (32u - size) : 0;
 #endif
-    // s + 2^size if s < 0, s - (2^size - 1) otherwise: subtract 2^size - 1 with all its bits flipped in the first case
-    return s - (int32_t)(((1u << size) - 1u) ^ (uint32_t)(s >> 31));
+    return value_of_field(s, size);
 }
 
 // DC-difference sums of the three components, kept in one 64-bit accumulator with 15-bit fields
@@ -211,6 +214,9 @@ JPGD_HD void decode_span_sync(Lane& l, BitWin& w, uint32_t limit, int64_t& dcacc
 }
 
 // ---- two symbols per step ---------------------------------------------------------------------------------
+// (The kernels' lanes take two symbols per step from tables of their own, sync_span below.  decode_span_sync,
+// decode_span_sync_pairs and decode_span_sync_rst say the same on the tables of jpgd_lut.h; the host walk-through runs
+// them, and sync_span is held to them.)
 // The synchronisation pass needs the state, the unit count and the DC sums, not the coefficients.  So where the
 // first-level index of an AC symbol also holds the whole codeword of the AC symbol after it, one step may take
 // both: the pair byte of that index (build_pairs) says how many bits the second symbol takes and how many slots it
@@ -280,6 +286,201 @@ JPGD_HD void decode_span_sync_pairs(Lane& l, BitWin& w, uint32_t limit, int64_t&
     while (w.next + 1u < stop) sync_symbol_pair(l, w, dcacc, sx, fetch, lut, pairs);
     while (w.next < stop) sync_symbol(l, w, dcacc, sx, fetch, lut);
     l.p = win_pos(w);
+}
+
+// ---- the lanes of the synchronisation pass -----------------------------------------------------------------
+// The same walk as decode_span_sync, on tables laid out for it in LDS (SyncTables): a 32-bit entry per first-level index
+// says at once what its symbol takes, what the symbol behind it takes where the index holds that one's whole codeword
+// too (build_pairs), and how many value bits a DC symbol has.  Position and zig-zag index are one register that an entry
+// is added to.
+//
+// What bounds it: a lane's next look-up waits for the one before (about 130 cycles of LDS), and behind that for the
+// instructions between an entry's arrival and the next request, 4 cycles each; with several wavefronts on a SIMD, for
+// all instructions of a step.  So the words on the way from entry to request are kept few, everything else stands behind
+// the request, and an escape (a codeword longer than the index) is followed up without a branch, which would cost a
+// lone wavefront more than the instructions it skips: 46 vector instructions and three LDS reads a step where
+// sync_symbol_pair takes 62 and five, two thirds of them in front of the request.
+// Measured, decode_span_sync_pairs / this (kernels, us): 15360x8640 first kernel 697 / 611, second 890 / 848; 256 images of
+// 512x384 240 / 213; 24 images of 2047x1535 337 / 305; one 1001x667 image 104 / 89; 3001x2003 with an interval per MCU row
+// (single symbols before) 122 / 97.
+//
+//   entry, bits 0..4   bits the symbol takes
+//          bits 9..14  zig-zag slots it covers
+//          bit  15     set, with bit 31, in an escape: bits 0..4 and 9..14 are zero, bits 6..8 = n, bits 18..30 = 8-byte
+//                      word of the tables from which on the subtable lies that the n bits from the last bit of a 10-bit
+//                      index on point into
+//          bits 16..19 bits that the symbol behind it takes, bits 25..30 the slots that one covers (0: no second symbol;
+//                      an end of block covers kAdvEob like any other)
+//          bits 20..23 DC tables: value bits of the symbol
+constexpr uint32_t kSyncDcK = 9u;              // bits of a first-level index: DC tables (half the size; their codes are short),
+constexpr uint32_t kSyncAcK = (uint32_t)kLutK; // AC tables
+constexpr uint32_t kSyncDcBytes = 4u << kSyncDcK, kSyncAcBytes = 4u << kSyncAcK;
+constexpr uint32_t kSyncEsc = 0x8000u;         // also: the carry out of the zig-zag index, "data unit complete"
+constexpr uint32_t kSyncStep = 0x7E1Fu;        // position and slots
+constexpr uint32_t kSyncSecond = 0x7E0Fu;      // the same of the second symbol, in the upper half
+constexpr uint32_t kSyncPairBits = 9u;         // most bits a first symbol with a second one behind it takes
+static_assert(kSyncDcK == kSyncAcK - 1u, "subtables of both kinds are indexed from the last bit of a 10-bit index on");
+
+// second-level entry (or first-level one that is no escape) of build_lut, with pair byte pb (0: none)
+JPGD_HD uint32_t sync_entry(uint32_t e, bool is_dc, uint32_t pb) {
+    const uint32_t slots = pb >> 4;
+    return (e & kSyncStep) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
+}
+// escape into a subtable indexed by n bits, from byte `at` of the tables on (a multiple of 8)
+JPGD_HD uint32_t sync_escape(uint32_t n, uint32_t at) { return 0x80000000u | kSyncEsc | (n << 6) | ((at >> 3) << 18); }
+// byte of the tables at which the entry lies that escape e leads to
+JPGD_HD uint32_t sync_escape_at(uint32_t e, uint32_t peek) {
+    const uint32_t n = (e >> 6) & 7u;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const uint32_t i = __builtin_amdgcn_ubfe(peek, 23u - n, n);
+#else
+    const uint32_t i = (peek >> (23u - n)) & ((1u << n) - 1u);
+#endif
+    return ((e >> 15) & 0xFFF8u) + (i << 2);
+}
+// first-level entry i of an AC table; l2: byte of the tables from which on the table's second level lies, entry by entry
+JPGD_HD uint32_t sync_ac_entry(uint32_t i, uint32_t e, uint32_t pb, uint32_t l2) {
+    if (!lut_esc(e)) return sync_entry(e, false, pb);
+    const uint32_t n = lut_esc_bits(e);
+    return sync_escape(n + 1u, l2 + 4u * lut_esc_offset(e) - (n ? (i & 1u) << (n + 2u) : 0u));
+}
+// Entry i of a DC table from entries 2i and 2i+1 of build_lut's: n such that they need a subtable of 2^(n+1) entries, or
+// 0xFFFFFFFF if both are the same symbol (or no codeword).
+JPGD_HD uint32_t sync_dc_sub(uint32_t a, uint32_t b) {
+    if (a == b && !(lut_esc(a) && lut_esc_bits(a) != 0u)) return 0xFFFFFFFFu;
+    const uint32_t na = lut_esc(a) ? lut_esc_bits(a) : 0u, nb = lut_esc(b) ? lut_esc_bits(b) : 0u;
+    return na > nb ? na : nb;
+}
+// entry j of that subtable; l2: second level of build_lut's table.  (An escape without further bits stands for "no
+// codeword", the first entry there.)
+template <class L2>
+JPGD_HD uint32_t sync_dc_sub_entry(uint32_t a, uint32_t b, uint32_t n, uint32_t j, L2 l2) {
+    const uint32_t e = j >> n ? b : a;
+    if (!lut_esc(e)) return sync_entry(e, true, 0u);
+    const uint32_t k = lut_esc_bits(e);
+    return sync_entry(l2[lut_esc_offset(e) + ((j & ((1u << n) - 1u)) >> (n - k))], true, 0u);
+}
+JPGD_HD uint32_t sync_dc_direct(uint32_t a) { return sync_entry(lut_esc(a) ? 1u : a, true, 0u); }
+
+// Words of subtables that a table of build_lut needs in this layout (at most 1022).
+inline uint32_t sync_sub_words(const uint16_t* lut, bool is_dc) {
+    uint32_t words = 0u;
+    if (is_dc) {
+        for (uint32_t i = 0; i < (uint32_t)kLutL1; i += 2u) {
+            const uint32_t n = sync_dc_sub(lut[i], lut[i + 1u]);
+            if (n != 0xFFFFFFFFu) words += 2u << n;
+        }
+        return words;
+    }
+    words = 2u;
+    for (uint32_t i = 0; i < (uint32_t)kLutL1; ++i)
+        if (lut_esc(lut[i])) {
+            const uint32_t end = lut_esc_offset(lut[i]) + (1u << lut_esc_bits(lut[i]));
+            if (end > words) words = end;
+        }
+    return (words + 1u) & ~1u;
+}
+
+// One row per data unit of the MCU: bytes of the tables at which its AC table and the next unit's DC table start, the
+// factor of its component in the DC sums, and the byte of the rows at which the next unit's row lies.
+struct alignas(16) SyncRow {
+    uint32_t ac, dc_next, dcmul, next;
+};
+
+// A lane between two symbols.  The window is two words and the offset of the next bit in them, 1 to 32 (so that one
+// funnel shift by 0 to 31 gives the next 32 bits); S holds the offset less one in bits 0..4 and the zig-zag index in bits
+// 9..14.
+struct SyncLane {
+    uint32_t S;
+    uint32_t row;        // byte of the current unit's row
+    uint32_t e;          // entry of the symbol that comes next, already asked for
+    uint32_t hi, lo, ahead;
+    uint32_t at;         // bit at which `ahead` starts, in the bits of the Word functor
+    uint32_t nb;         // data units completed since it was last cleared
+};
+
+JPGD_HD uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t s) {  // by s & 31 to the right
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_alignbit(hi, lo, s);
+#else
+    return (uint32_t)(((((uint64_t)hi) << 32) | lo) >> (s & 31u));
+#endif
+}
+// position of the next bit, less one, plus 64 (the two words before `at`)
+JPGD_HD uint32_t sync_at(const SyncLane& l) { return (l.S & 31u) | l.at; }
+constexpr uint32_t kSyncBias = 63u;
+JPGD_HD uint32_t sync_pos(const SyncLane& l) { return sync_at(l) - kSyncBias; }
+
+JPGD_HD uint32_t sync_peek(const SyncLane& l) { return funnel(l.hi, l.lo, ~l.S); }
+
+// word(b): the stream word that starts at bit b (a multiple of 32); tab(k): 32-bit entry at byte k of the tables; rows(k):
+// the SyncRow at byte k of the rows, upm of them.  p: bit to start at, in the bits of `word`; z, u: zig-zag index and data
+// unit.
+template <class Word, class Tab, class Row>
+JPGD_HD void sync_start(SyncLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, Word word, Tab tab, Row rows) {
+    const uint32_t w = (p + 31u) & ~31u;
+    l.hi = (p & 31u) ? word(w - 32u) : 0u;  // (at the first bit of a word the offset is 32: nothing of it is used)
+    l.lo = word(w);
+    l.ahead = word(w + 32u);
+    l.at = w + 32u;
+    l.S = ((p + 31u) & 31u) | (z << 9);
+    l.row = u * (uint32_t)sizeof(SyncRow);
+    const uint32_t dc = rows(((u ? u : upm) - 1u) * (uint32_t)sizeof(SyncRow)).dc_next;
+    const uint32_t peek = sync_peek(l);
+    l.e = tab(z == 0u ? dc + ((peek >> (32u - kSyncDcK)) << 2) : rows(l.row).ac + ((peek >> (32u - kSyncAcK)) << 2));
+}
+
+// Decodes while the next symbol starts before bit `limit` (of `word`).  A second symbol is left to the next step where
+// it might start behind `limit`.
+template <class Word, class Tab, class Row>
+JPGD_HD void sync_span(SyncLane& l, uint32_t limit, int64_t& dcacc, Word word, Tab tab, Row rows) {
+    const uint32_t stop = limit + kSyncBias, last_pair = stop - kSyncPairBits;
+    uint32_t pos = sync_at(l);
+    if (pos >= stop) return;
+    uint32_t peek = sync_peek(l);
+    SyncRow row = rows(l.row);
+#if defined(__HIP_DEVICE_COMPILE__)
+    // (Keeps the compiler from merging this read with the one at the end of a step into one at the top of the loop, where
+    // every step would wait for it.)
+    asm volatile("" : "+v"(row.ac), "+v"(row.dc_next), "+v"(row.dcmul), "+v"(row.next));
+#endif
+    do {
+        const bool late = pos >= last_pair;
+        const uint32_t e = l.e, before = peek;
+        const bool esc = (int32_t)e < 0;
+        const uint32_t s1 = l.S + (e & 0xFFFFu);
+        const bool one = late || s1 >= kSyncEsc;  // (an escape has no second symbol either)
+        const uint32_t s2 = s1 + (one ? 0u : (e >> 16) & kSyncSecond);
+        const bool ends = s2 >= kSyncEsc;         // the unit is complete, or an escape
+        const uint32_t word_on = s2 & 32u;
+        l.hi = word_on ? l.lo : l.hi;
+        l.lo = word_on ? l.ahead : l.lo;
+        peek = funnel(l.hi, l.lo, ~s2);
+        const uint32_t next = (ends ? row.dc_next : row.ac) + ((peek >> (ends ? 32u - kSyncDcK : 32u - kSyncAcK)) << 2);
+        const uint32_t sub = sync_escape_at(e, peek);
+        uint32_t size = (e >> 20) & 15u, total = e & 31u;
+#if defined(__HIP_DEVICE_COMPILE__)
+        total = 0u - e;  // (the offset of the value's bits, taken modulo 32)
+        asm volatile("" : "+v"(size), "+v"(total));  // (the entry's register is free for the next one from here on)
+#endif
+        l.e = tab(esc ? sub : next);
+        l.at += word_on;
+        l.ahead = word(l.at);
+        const bool done = ends && !esc;
+        l.S = s2 & (done ? 31u : kSyncStep);
+        l.nb += done ? 1u : 0u;
+        l.row = done ? row.next : l.row;
+        pos = sync_at(l);
+        // value of a DC symbol (0 with the 0 value bits that every other entry has)
+        const int32_t mul = (int32_t)(esc ? 0u : row.dcmul);
+        row = rows(l.row);
+#if defined(__HIP_DEVICE_COMPILE__)
+        const int32_t v = value_of_field(__builtin_amdgcn_sbfe((int32_t)before, total, size), size);
+#else
+        const int32_t v = symbol_value(before, total, size);
+#endif
+        dcacc += (int64_t)v * (int64_t)mul;
+    } while (pos < stop);
 }
 
 // One symbol of the write pass (write = true in Algorithm 2): every non-zero coefficient goes to
@@ -416,6 +617,42 @@ JPGD_HD void decode_span_sync_rst(Lane& l, BitWin& w, uint32_t limit, int64_t& d
         if (!next_interval) break;
     }
     l.p = win_pos(w);
+}
+
+// The same over a stream with restart intervals (rules: decode_span_sync_rst below, which this follows step by step).
+// Boundaries are positions in the image's stream: a position there plus `org` is a bit of `word`.
+template <class Word, class Tab, class Row, class BWord>
+JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t& crossed, uint32_t org, uint32_t upm, Word word,
+                           Tab tab, Row rows, BWord bword) {
+    const uint32_t end = limit - org;
+    uint32_t from = sync_pos(l) - org;
+    for (;;) {
+        const uint32_t B = next_boundary(from, end + 64u, bword);
+        // a symbol that starts 40 bits before B ends more than 7 bits before it
+        uint32_t calm = end;
+        if (B != kNoBoundary && B < end + 39u) calm = B >= 39u ? B - 39u : 0u;
+        if (from < calm) sync_span(l, calm + org, dcacc, word, tab, rows);
+        if (B == kNoBoundary) break;
+        uint32_t pos = sync_pos(l) - org;
+        bool next_interval = false;
+        while (pos < end) {
+            if (pos == B) {  // this symbol starts the interval
+                dcacc = 0;
+                crossed = 1u;
+                from = B + 1u;
+                next_interval = true;
+                break;
+            }
+            sync_span(l, pos + org + 1u, dcacc, word, tab, rows);  // one symbol
+            pos = sync_pos(l) - org;
+            const uint32_t r = B - pos;
+            if (pos >= B || (r <= 7u && (~sync_peek(l) >> (32u - r)) == 0u)) {
+                sync_start(l, B + org, 0u, 0u, upm, word, tab, rows);
+                pos = B;
+            }
+        }
+        if (!next_interval) break;
+    }
 }
 
 // Write pass over a stream with restart intervals: the predictors return to zero where an interval starts.

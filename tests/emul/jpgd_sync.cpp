@@ -1,0 +1,209 @@
+// Host build of the synchronisation pass's lanes (sync_span, sync_span_rst) on tables laid out as the kernels lay them out in
+// LDS, beside the plain lanes that decode symbol by symbol from the tables of jpgd_lut.h.  Test code: the library never
+// calls it.
+//
+// Build: g++ -O2 -std=c++17 -shared -fPIC -o libjpgd_sync.so jpgd_sync.cpp ../../paper_2111_09219_amd/csrc/jpgd_parse.cpp
+#include <string.h>
+
+#include <map>
+#include <utility>
+#include <vector>
+
+#include "../../include/jpgd.h"
+#include "../../paper_2111_09219_amd/csrc/jpgd_common.h"
+#include "../../paper_2111_09219_amd/csrc/jpgd_lane.h"
+#include "../../paper_2111_09219_amd/csrc/jpgd_lut.h"
+
+using namespace jpgd;
+
+namespace {
+
+struct Tables {
+    std::vector<uint16_t> lut;       // build_lut, DC slots first
+    std::vector<uint32_t> sync;      // the kernels' layout
+    uint32_t ndc = 0, nslots = 0;
+    uint32_t words[6] = {0};         // sync_sub_words
+};
+
+// as stage_sync_tables fills them, DC subtables in the order of their entries
+bool lay_out(Tables& t, uint32_t base) {
+    const uint32_t nac = t.nslots - t.ndc;
+    std::vector<uint8_t> pairs(kPairBytes);
+    uint32_t sub = t.ndc * kSyncDcBytes + nac * kSyncAcBytes, all = 0;
+    for (uint32_t s = 0; s < t.nslots; ++s) all += t.words[s] = sync_sub_words(&t.lut[s * kLutEntries], s < t.ndc);
+    t.sync.assign(sub / 4 + all, 0xDEADBEEFu);
+    for (uint32_t a = 0; a < nac; ++a) {
+        const uint16_t* lut = &t.lut[(t.ndc + a) * kLutEntries];
+        build_pairs(lut, pairs.data());
+        for (uint32_t i = 0; i < (uint32_t)kLutL1; ++i)
+            t.sync[(t.ndc * kSyncDcBytes + a * kSyncAcBytes) / 4 + i] = sync_ac_entry(i, lut[i], pairs[i], base + sub);
+        for (uint32_t k = 0; k < t.words[t.ndc + a]; ++k) t.sync[sub / 4 + k] = sync_entry(lut[kLutL1 + k], false, 0u);
+        sub += 4u * t.words[t.ndc + a];
+    }
+    for (uint32_t s = 0; s < t.ndc; ++s) {
+        const uint16_t* lut = &t.lut[s * kLutEntries];
+        for (uint32_t i = 0; i < 1u << kSyncDcK; ++i) {
+            const uint32_t a = lut[2 * i], b = lut[2 * i + 1], n = sync_dc_sub(a, b);
+            uint32_t& e = t.sync[s * kSyncDcBytes / 4 + i];
+            if (n == 0xFFFFFFFFu) { e = sync_dc_direct(a); continue; }
+            e = sync_escape(n + 1u, base + sub);
+            for (uint32_t j = 0; j < 2u << n; ++j, sub += 4)
+                t.sync.at(sub / 4) = sync_dc_sub_entry(a, b, n, j, lut + kLutL1);
+        }
+    }
+    return sub / 4 == t.sync.size();
+}
+
+struct Scan {
+    jpgd_info in;
+    Tables t;
+    std::vector<uint8_t> stream;
+    std::vector<uint32_t> bmap;
+    uint32_t nbits = 0;
+    UnitRow rows[8];
+    SyncRow srows[8];
+};
+
+// build_lut's tables for the plain lanes; remembers whether an entry of a DC table stood for "no codeword"
+struct Lut {
+    const Tables* t;
+    bool* no_dc_code;
+    uint32_t operator[](uint32_t k) const {
+        const uint32_t e = t->lut.at(k);
+        if (k < t->ndc * (uint32_t)kLutEntries && !lut_esc(e) && lut_adv(e) == 0u) *no_dc_code = true;
+        return e;
+    }
+};
+
+constexpr uint32_t kBase = 176;   // where the tables start
+
+int open_scan(const uint8_t* file, size_t len, Scan& S) {
+    const int rc = jpgd_parse(file, len, &S.in);
+    if (rc) return rc;
+    const jpgd_info& in = S.in;
+    uint32_t slot_dc[3], slot_ac[3];
+    std::map<uint32_t, uint32_t> dc, ac;
+    for (uint32_t c = 0; c < in.ncomp; ++c) slot_dc[c] = dc.emplace(in.td[c], (uint32_t)dc.size()).first->second;
+    for (uint32_t c = 0; c < in.ncomp; ++c) slot_ac[c] = ac.emplace(in.ta[c], (uint32_t)ac.size()).first->second;
+    S.t.ndc = (uint32_t)dc.size();
+    S.t.nslots = (uint32_t)(dc.size() + ac.size());
+    S.t.lut.assign(S.t.nslots * kLutEntries, 0);
+    for (auto& d : dc) if (!build_lut(in.dht_bits[0][d.first], in.dht_vals[0][d.first], true, &S.t.lut[d.second * kLutEntries])) return JPGD_E_TABLE;
+    for (auto& a : ac) if (!build_lut(in.dht_bits[1][a.first], in.dht_vals[1][a.first], false, &S.t.lut[(S.t.ndc + a.second) * kLutEntries])) return JPGD_E_TABLE;
+    if (!lay_out(S.t, kBase)) return JPGD_E_TABLE;
+    uint32_t sched_dc = 0, sched_ac = 0, sched_comp = 0, u = 0;
+    for (uint32_t c = 0; c < in.ncomp; ++c)
+        for (uint32_t k = 0, nu = in.ncomp == 3 && c == 0 ? (uint32_t)in.hsamp[0] * in.vsamp[0] : 1u; k < nu; ++k, ++u) {
+            sched_dc |= slot_dc[c] << (4 * u);
+            sched_ac |= (S.t.ndc + slot_ac[c]) << (4 * u);
+            sched_comp |= c << (4 * u);
+        }
+    for (uint32_t k = 0; k < u; ++k) {
+        S.rows[k] = make_unit_row(k, u, sched_dc, sched_ac, sched_comp);
+        S.srows[k] = SyncRow{kBase + S.t.ndc * kSyncDcBytes + (((sched_ac >> (4 * k)) & 15) - S.t.ndc) * kSyncAcBytes,
+                             kBase + ((sched_dc >> (4 * ((k + 1) % u))) & 15) * kSyncDcBytes, S.rows[k].dcmul,
+                             S.rows[k].next * (uint32_t)sizeof(SyncRow)};
+    }
+    const uint8_t* p = file + in.scan_offset;
+    S.bmap.assign(in.scan_bytes / 32 + 80, 0);
+    for (size_t k = 0; k < in.scan_bytes; ++k) {
+        if (p[k] == 0xFF && k + 1 < in.scan_bytes && p[k + 1] >= 0xD0 && p[k + 1] <= 0xD7) {
+            S.bmap[S.stream.size() >> 5] |= 1u << (S.stream.size() & 31);
+            ++k;
+            continue;
+        }
+        S.stream.push_back(p[k]);
+        if (p[k] == 0xFF) ++k;   // the stuffed zero
+    }
+    S.nbits = (uint32_t)S.stream.size() * 8;
+    S.stream.resize(S.stream.size() + 1024, 0);
+    return JPGD_OK;
+}
+
+}  // namespace
+
+// `tries` random states, each decoded over `spans` subsequences of L bits by both: mismatches in state, unit count, DC sums or
+// "an interval began".  org: added to the positions the lanes of sync_span see (a multiple of 32).  *compared: spans compared.
+// Where bits start no codeword of a DC table (only off the true chain of an intact file) the next entry comes from the AC
+// table, and the plain lane adds that symbol's value to its DC sums: from there on the sums are not compared.
+extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32_t tries, uint32_t spans, uint32_t org,
+                             uint32_t seed, uint32_t* compared) {
+    Scan S;
+    const int rc = open_scan(file, len, S);
+    if (rc) return -rc;
+    const uint32_t* words = (const uint32_t*)S.stream.data();
+    auto fetch = [&](uint32_t c) { return c < S.stream.size() / 4 ? __builtin_bswap32(words[c]) : 0u; };
+    auto word = [&](uint32_t b) {
+        if ((b & 31u) || b - org > S.nbits + 4096u) __builtin_trap();
+        return fetch((b - org) >> 5);
+    };
+    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.sync.at((k - kBase) / 4); };
+    auto rows = [&](uint32_t k) { if (k % sizeof(SyncRow) || k / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.srows[k / sizeof(SyncRow)]; };
+    auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
+    Syntax sx;
+    sx.rows = S.rows;
+    sx.upm = S.in.units_per_mcu;
+    const bool restart = S.in.restart_interval != 0;
+    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
+    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    int bad = 0;
+    *compared = 0;
+    for (uint32_t k = 0; k < tries; ++k) {
+        const uint32_t nsub = (S.nbits + L - 1) / L, i0 = rnd(nsub);
+        bool no_dc_code = false;
+        const Lut lut{&S.t, &no_dc_code};
+        Lane a;
+        BitWin w;
+        a.p = i0 * L + (rnd(4) ? rnd(31) : 0u);
+        if (a.p >= S.nbits || (org >> 31 && a.p + org >= org)) continue;   // (a negative org: the stretch starts at bit -org)
+        a.u = rnd(sx.upm); a.z = rnd(3) ? rnd(64) : 0u;
+        SyncLane b;
+        win_init(w, a.p, a.p >> 5, fetch);
+        prime(a, w, sx, lut);
+        sync_start(b, a.p + org, a.u, a.z, sx.upm, word, tab, rows);
+        for (uint32_t i = i0; i < i0 + spans && i < nsub; ++i) {
+            const uint32_t limit = (i + 1) * L;
+            int64_t da = 0, db = 0;
+            uint32_t ca = 0, cb = 0;
+            a.nb = b.nb = 0;
+            if (restart) {
+                decode_span_sync_rst(a, w, limit, da, ca, sx, fetch, lut, bword);
+                sync_span_rst(b, limit + org, db, cb, org, sx.upm, word, tab, rows, bword);
+            } else {
+                decode_span_sync(a, w, limit, da, sx, fetch, lut);
+                sync_span(b, limit + org, db, word, tab, rows);
+            }
+            ++*compared;
+            const uint32_t u = b.row / (uint32_t)sizeof(SyncRow), z = (b.S >> 9) & 63u;
+            if (sync_pos(b) - org != a.p || u != a.u || z != a.z || a.nb != b.nb || (da != db && !no_dc_code) || ca != cb) { ++bad; break; }
+        }
+    }
+    return bad;
+}
+
+// Every 16-bit stretch looked up in a table of build_lut and in its layout for the synchronisation kernels: mismatches.
+extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int is_dc) {
+    Tables t;
+    t.ndc = is_dc ? 1u : 0u;
+    t.nslots = 1u;
+    t.lut.assign(kLutEntries, 0);
+    if (!build_lut(bits, vals, is_dc != 0, t.lut.data())) return -1;
+    if (!lay_out(t, kBase)) return -2;
+    int bad = 0;
+    for (uint32_t v = 0; v < 65536u; ++v) {
+        const uint32_t peek = v << 16 | 0x5A5Au;
+        uint32_t e = t.lut[peek >> (32 - kLutK)];
+        if (lut_esc(e)) {
+            const uint32_t n = lut_esc_bits(e);
+            e = t.lut[kLutL1 + lut_esc_offset(e) + ((peek >> (32 - kLutK - n)) & ((1u << n) - 1u))];
+        }
+        uint32_t s = t.sync.at(peek >> (32u - (is_dc ? kSyncDcK : kSyncAcK)));
+        if (s & kSyncEsc) {
+            const uint32_t k = sync_escape_at(s, peek);
+            if (k < kBase || (k & 3u)) return -3;
+            s = t.sync.at((k - kBase) / 4);
+        }
+        bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != lut_adv(e) || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
+    }
+    return bad;
+}
