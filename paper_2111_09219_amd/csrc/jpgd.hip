@@ -201,6 +201,18 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
             }
         }
         if (u != d.upm) return JPGD_E_ARG;
+        // kinds of data units (component 0 is of kind 0)
+        uint32_t kind[3] = {0, 0, 0}, kinds = 1, slots[2] = {comp_dc[0] | (ndc + comp_ac[0]) << 3, 0};
+        for (uint32_t c = 1; c < in.ncomp; ++c) {
+            const uint32_t mine = comp_dc[c] | (ndc + comp_ac[c]) << 3;
+            uint32_t k = 0;
+            while (k < kinds && k < 2u && slots[k] != mine) ++k;
+            if (k == kinds && kinds++ < 2u) slots[k] = mine;
+            kind[c] = k;
+        }
+        if (kinds == 1) slots[1] = slots[0];
+        d.walk = kinds > 2u ? 0u : 0x80000000u | slots[0] << kWalkSlots | slots[1] << (kWalkSlots + 6u);
+        for (uint32_t k = 0; d.walk && k < d.upm; ++k) d.walk |= kind[(d.sched_comp >> (4 * k)) & 15u] << k;
         if (i > 0 && same_tables(infos[i - 1], in)) {
             pl.lut_of_img[i] = pl.lut_of_img[i - 1];
         } else {
@@ -491,11 +503,11 @@ size_t lds_bitmap_bytes(uint32_t L, bool restart) {
     return restart && L <= (uint32_t)kBitmapLdsMaxL ? ((size_t)(kWG * (L / 32) + 4 + 7) / 8 + 2) * 4 : 0;
 }
 size_t lds_sync_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
-    uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + 4 : 4;
+    uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + kSyncPadWords : kSyncWavesMax * kCoopBufWords;
     return (size_t)tab_bytes + kSyncFixedWords * 4 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
 }
 // the second of the two synchronisation kernels keeps the tables and the records, not the stream
-size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + kSyncFixedWords * 4 + 16; }
+size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + (kSyncFixedWords + kWG / 64 * kCoopBufWords) * 4; }
 // most bytes that any image's tables take there
 constexpr uint32_t kSyncTabMax = kMaxPairs * (kSyncDcBytes + kSyncAcBytes) + kMaxPairs * 4 * (1022u + kLutL2);
 static_assert(kSyncTabMax <= 8u << 13, "an escape has 13 bits for its subtable");

@@ -632,97 +632,159 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
 }
 
 // ---- one chain decoded by a whole wavefront -----------------------------------------------------------
-// The last overflow rounds of a sequence have a handful of chains left, and a lane that decodes one symbol
-// after the other spends some fifty dependent instructions on each.  So when few chains remain, each goes to a
-// wavefront of its own: lane j looks up the symbol that WOULD start j bits after the chain's position, in every
+// The last overflow rounds of a sequence have a handful of chains left, and a lane that decodes one step
+// after the other spends over two hundred cycles on each.  So when few chains remain, each goes to a
+// wavefront of its own: lane j looks up the symbol that WOULD start j bits into a window of 64, in every
 // table of the image at once, and the chain is then followed through those 64 answers with scalar code (a
-// readlane and a few scalar operations per symbol) until it leaves the 64-bit window.  The synchronisation pass
+// readlane and a few scalar operations per symbol) until it leaves the window.  The synchronisation pass
 // only needs (p, u, z), the count of completed units and the DC sums, so a symbol's value bits matter only for
-// DC symbols.  Results are those of decode_span_sync, symbol by symbol.
+// DC symbols.  Results are those of sync_span, symbol by symbol.
+//
+// What bounds it is the number of instructions and taken branches of a lone wavefront: a step of an AC symbol is four
+// instructions, some 30 cycles, and everything else used to be four times that.  So the whole loop over the windows is
+// assembly: the compiler's form of it set and tested flags around every exit, moved the next window's answers from
+// register to register and spent six taken branches a window outside the walk.  Here a window costs 27 instructions and
+// one taken branch, a unit's end and the DC symbol behind it 45 and three.  An image may have two kinds of data units, by
+// their tables (ImgDesc::walk); each kind has its own loop over AC symbols, so that nothing is selected per symbol.
+// Measured, window loop compiled around an assembly walk / this (kernels, us): second kernel of 15360x8640 848 / 705, 24
+// images of 2047x1535 305 / 270, one 1600x1200 image 190 / 158, 256 images of 512x384 213 / 186, 1001x667 89 / 80; a round
+// of 1024 bits with up to 23 chains on 16 wavefronts 28 000 / 19 800 cycles.  (An image with three kinds of units keeps to
+// the lanes.)
 
-// lane i < upm describes data unit i of the MCU: slot of its AC table (bits 0-2), slot of the DC table of the
-// unit that follows (3-5), index of that unit (6-9), and where its DC differences go in the walk's two sums: shift
-// inside the first word (10-14: 0 for component 0, 16 for component 1), or the second word (bit 15, component 2)
-constexpr uint32_t kUwDcNext = 3u, kUwNext = 6u, kUwShift = 10u, kUwSecond = 15u;
+// lane i < upm describes data unit i of the MCU: index of the unit that follows (bits 0..3), the kind of unit (4), and
+// where its DC differences go in the walk's two sums: shift inside the first word (10-14: 0 for component 0, 16 for
+// component 1), or the second word (bit 15, component 2)
+constexpr uint32_t kUwKind = 4u, kUwShift = 10u, kUwSecond = 15u;
 __device__ __forceinline__ uint32_t coop_unit_word(const ImgDesc& D, uint32_t lane) {
     if (lane >= D.upm) return 0u;
     const uint32_t next = lane + 1u == D.upm ? 0u : lane + 1u, comp = (D.sched_comp >> (4u * lane)) & 15u;
-    return ((D.sched_ac >> (4u * lane)) & 15u) | (((D.sched_dc >> (4u * next)) & 15u) << kUwDcNext) | (next << kUwNext) |
-           (comp == 2u ? 1u << kUwSecond : comp * 16u << kUwShift);
+    return next | (((D.walk >> lane) & 1u) << kUwKind) | (comp == 2u ? 1u << kUwSecond : comp * 16u << kUwShift);
 }
 
-// Where the tables of the image's (at most four) slots lie and how their indices are made, the same in every lane.  A slot
-// the image does not have is asked as the last one it has.
+// Where the tables of the two kinds of units lie: bytes of LDS, the same in every lane.
 struct CoopTables {
-    uint32_t base[4], shift[4], dc[4];  // dc: the bits of an entry of the walk that are a DC symbol's value bits
+    uint32_t dc0, ac0, dc1, ac1;
 };
-__device__ __forceinline__ CoopTables coop_tables(uint32_t nslots, uint32_t ndc, uint32_t tab) {
-    CoopTables c;
-#pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {
-        const uint32_t s = min(i, nslots - 1u);
-        const bool is_dc = s < ndc;
-        c.base[i] = tab + (is_dc ? s * kSyncDcBytes : ndc * kSyncDcBytes + (s - ndc) * kSyncAcBytes);
-        c.shift[i] = 32u - (is_dc ? kSyncDcK : kSyncAcK);
-        c.dc[i] = is_dc ? 0x1E0u : 0u;
-    }
-    return c;
+__device__ __forceinline__ CoopTables coop_tables(const ImgDesc& D, uint32_t tab) {
+    const uint32_t walk = __builtin_amdgcn_readfirstlane(D.walk), ndc = __builtin_amdgcn_readfirstlane(D.ndc);
+    auto dc = [&](uint32_t at) { return tab + ((walk >> at) & 7u) * kSyncDcBytes; };
+    auto ac = [&](uint32_t at) { return tab + ndc * kSyncDcBytes + (((walk >> at) & 7u) - ndc) * kSyncAcBytes; };
+    return CoopTables{dc(kWalkSlots), ac(kWalkSlots + 3u), dc(kWalkSlots + 6u), ac(kWalkSlots + 9u)};
 }
 
-// A table entry as the walk adds it to its packed state (coop_span_sync): bits taken (every entry takes at least one)
-// in bits 0..4, zig-zag slots covered in bits 9..14, and bit 15 of a first-level escape, which stops the walk.
-constexpr uint32_t kCoopStep = 0xFE1Fu;
-__device__ __forceinline__ uint32_t coop_step(uint32_t e) { return e & kCoopStep; }
-// What the packed state (coop_span_sync) and the walk's instructions take for granted of a table entry: 5 bits of
-// length, 4 of value bits, 6 of slots, the escape's flag on top, and an end of block that completes any unit; of a unit
-// word: three bits of a table slot, four of a unit.
-static_assert(lut_total(kCoopStep) == 31u && lut_total(~31u) == 0u && lut_size(0x1E0u) == 15u && lut_size(~0x1E0u) == 0u);
-static_assert(lut_adv(kCoopStep) == 63u && lut_adv(~0x7E00u) == 0u && lut_esc(0x8000u) && !lut_esc(0x7FFFu) && kAdvEob == 63u);
-static_assert(kUwDcNext >= 3u && kUwNext == kUwDcNext + 3u && kUwShift == kUwNext + 4u && kUwSecond == kUwShift + 5u);
+// What the walk's instructions take for granted of an entry (sync_entry), beside what the lanes do.
+static_assert(kSyncStep == 0x7E1Fu && kSyncEsc == 0x8000u && kSyncDcK == 9u && kSyncAcK == 10u && kAdvEob == 63u);
 constexpr uint32_t bit_field(uint32_t at, uint32_t bits) { return (bits << 16) | at; }  // operand of s_bfe
 
-// The chain followed through one window: S (window position and zig-zag index, see coop_span_sync), the unit word cur,
-// the slot of the next DC symbol's table, the completed units and the DC sums are advanced until the window is
-// left or a codeword is longer than the first-level index; acv holds the lanes' entries of the current unit's AC
-// table and acs their steps.
-// In assembly, because what a lone wavefront pays for is the number of instructions and taken branches, and the
-// compiler turns the loops into its own form with a set of flags around every exit: 5 instructions per AC symbol and
-// about 75 with five taken branches per change of unit, where 4 and 47 with one or two will do.  Registers only: no
-// memory is touched, and every step moves on by at least one bit, so the loop ends after at most 64 steps.
+// p, u, z: state of the chain, the same in every lane, advanced until p >= limit (limit a multiple of 64; a subsequence is
+// a whole number of 64-bit windows, and a chain enters it at most 31 bits behind its start, so no window is wasted).
+// words: byte of LDS at which the stream's word with the window of bit p begins, big-endian words; the walk looks at 24
+// bytes behind the last window.  All 64 lanes are active.
+// S = window position j (bits 0..6, at most 63 + 31) and zig-zag index z (bits 9..15, at most 63 + 63); adding an entry
+// advances both.  Bit 6 set: the window is behind us; bit 15: the data unit is complete; an escape sets bit 15 or carries
+// out of it, and its step is taken back.  The answers for the next window and the words of the one after that are asked for
+// before the chain is followed through this one.  At the first escape of a kind of units in a window all lanes follow up
+// their own at once.  Every step moves on by at least one bit.
 // dc_a holds the sums of components 0 and 1 (two 16-bit fields, the lower one's sign taken off the upper one), dc_b
 // that of component 2.  (Sums that leave 16 bits come out otherwise than from the lanes' loop in the components behind; the
 // sums of a chain that is in step do so only where DC values leave the range of 8-bit samples, and the 15-bit fields
 // of the lanes do not hold those either.)
-// Measured, compiled loops / this (synchronisation kernels, us): 4096x4096 4:2:0 502 / 465, second kernel of 15360x8640
-// 966 / 890, 24 images of 2047x1535 362 / 335, one 1600x1200 image 218 / 201, batch of 256 251 / 243, 1920x1088 42 / 40.5.
-constexpr uint32_t kCoopLeft = 0u, kCoopAcEscape = 1u, kCoopDcEscape = 2u;
-__device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32_t& dc_slot, uint32_t& nb, uint32_t& dc_a,
-                                              uint32_t& dc_b, uint32_t& acv, uint32_t& acs, uint32_t e01, uint32_t e23, uint32_t peek,
-                                              uint32_t unit_word) {
-    uint32_t why, t, t2, r, r2, v;
+__device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, uint32_t& z_io, uint32_t& nb_out, int64_t& dc_out,
+                                               uint32_t limit, uint32_t words, uint32_t unit_word, uint32_t upm,
+                                               const CoopTables& ct) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t p = __builtin_amdgcn_readfirstlane(p_io), u = __builtin_amdgcn_readfirstlane(u_io);
+    const uint32_t ws = p & ~63u;
+    uint32_t S = (p - ws) | (__builtin_amdgcn_readfirstlane(z_io) << 9);
+    uint32_t left = (limit - ws) >> 6;  // windows; at least one
+    uint32_t nb = 0u, dc_a = 0u, dc_b = 0u;
+    uint32_t cur = __builtin_amdgcn_readlane(unit_word, u);
+    // the lane's 32 bits start behind the first 1 to 32 bits of two words
+    uint32_t at = words + ((lane + 31u) >> 5) * 4u - 4u;
+    const uint32_t shift = 0u - lane;
+    uint32_t d0, d1, a0, a1, c0, c1, peek, nd0, nd1, na0, na1, npeek, x0, x1;
+    uint32_t t, t2, r, r2, v;
+    uint64_t all;
     asm volatile(
-        "s_nop 4\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "ds_read_b32 %[x0], %[at]\n"
+        "ds_read_b32 %[x1], %[at] offset:4\n"
+        "s_bitset1_b32 %[left], 31\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "s_branch 2f\n"
+        // the next window's answers become this one's
+        "1:\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "v_mov_b32 %[peek], %[npeek]\n"
+        "v_mov_b32 %[d0], %[nd0]\n"
+        "v_mov_b32 %[d1], %[nd1]\n"
+        "v_mov_b32 %[a0], %[na0]\n"
+        "v_mov_b32 %[a1], %[na1]\n"
+        "v_and_b32 %[c0], 0xfe1f, %[na0]\n"
+        "v_and_b32 %[c1], 0xfe1f, %[na1]\n"
+        // ask for those of the window behind it, and for the words of the one after that
+        "2:\n"
+        "v_alignbit_b32 %[npeek], %[x0], %[x1], %[shift]\n"
+        "v_lshrrev_b32 %[x0], 23, %[npeek]\n"
+        "v_lshrrev_b32 %[x1], 22, %[npeek]\n"
+        "v_lshl_add_u32 %[nd0], %[x0], 2, %[bd0]\n"
+        "v_lshl_add_u32 %[nd1], %[x0], 2, %[bd1]\n"
+        "v_lshl_add_u32 %[na0], %[x1], 2, %[ba0]\n"
+        "v_lshl_add_u32 %[na1], %[x1], 2, %[ba1]\n"
+        "ds_read_b32 %[nd0], %[nd0]\n"
+        "ds_read_b32 %[nd1], %[nd1]\n"
+        "ds_read_b32 %[na0], %[na0]\n"
+        "ds_read_b32 %[na1], %[na1]\n"
+        "ds_read_b32 %[x0], %[at] offset:8\n"
+        "ds_read_b32 %[x1], %[at] offset:12\n"
+        "v_add_u32 %[at], 8, %[at]\n"
+        "s_bitcmp1_b32 %[left], 31\n"   // (the first time round there is no window to walk through yet)
+        "s_cbranch_scc0 3f\n"
+        "s_bitset0_b32 %[left], 31\n"
+        "s_branch 1b\n"
+        "3:\n"
         "s_cmp_lt_u32 %[S], 0x200\n"
-        "s_cbranch_scc0 21f\n"
+        "s_cbranch_scc1 20f\n"
+        "s_bitcmp1_b32 %[cur], %[kind]\n"
+        "s_cbranch_scc1 31f\n"
+        // AC symbols of a unit of kind 0, eight in a row
+        "21:\n"
+        ".rept 8\n"
+        "v_readlane_b32 %[t], %[c0], %[S]\n"
+        "s_add_u32 %[S], %[S], %[t]\n"
+        "s_and_b32 %[t2], %[S], 0x18040\n"
+        "s_cbranch_scc1 22f\n"
+        ".endr\n"
+        "s_branch 21b\n"
+        "22:\n"
+        "s_bitcmp1_b32 %[t], 15\n"
+        "s_cbranch_scc1 27f\n"
+        "s_bitcmp1_b32 %[S], 15\n"
+        "s_cbranch_scc0 29f\n"
+        // unit complete
+        "23:\n"
+        "s_add_u32 %[nb], %[nb], 1\n"
+        "s_and_b32 %[S], %[S], 0x7f\n"
+        "s_and_b32 %[t], %[cur], 15\n"
+        "s_bitcmp1_b32 %[S], 6\n"
+        "v_readlane_b32 %[cur], %[uw], %[t]\n"
+        "s_cbranch_scc1 29f\n"
         // DC symbol at position S (its zig-zag index is 0): entry of the table, its value, the component's sum
         "20:\n"
-        "v_readlane_b32 %[r], %[e01], %[S]\n"
-        "v_readlane_b32 %[r2], %[e23], %[S]\n"
+        "v_readlane_b32 %[r], %[d0], %[S]\n"
+        "v_readlane_b32 %[r2], %[d1], %[S]\n"
         "v_readlane_b32 %[v], %[peek], %[S]\n"
-        "s_bitcmp1_b32 %[dcs], 1\n"
+        "s_bitcmp1_b32 %[cur], %[kind]\n"
         "s_cselect_b32 %[r], %[r2], %[r]\n"
-        "s_lshl_b32 %[t], %[dcs], 4\n"
-        "s_lshr_b32 %[r], %[r], %[t]\n"
-        "s_movk_i32 %[why], 2\n"
-        "s_bitcmp1_b32 %[r], 15\n"
-        "s_cbranch_scc1 29f\n"
+        "s_bitcmp1_b32 %[r], 31\n"
+        "s_cbranch_scc1 28f\n"
+        "24:\n"
         "s_and_b32 %[t], %[r], 31\n"
         "s_bfe_u32 %[r2], %[r], %[f_size]\n"
-        "s_sub_u32 %[t], %[t], %[r2]\n"
-        "s_lshl_b32 %[v], %[v], %[t]\n"       // value bits from the top
-        "s_ashr_i32 %[v], %[v], 1\n"
-        "s_xor_b32 %[t], %[r2], 31\n"
-        "s_ashr_i32 %[v], %[v], %[t]\n"       // the field, signed (size 0: all sign)
+        "s_sub_u32 %[t], 32, %[t]\n"
+        "s_lshl_b32 %[t2], %[r2], 16\n"
+        "s_or_b32 %[t], %[t], %[t2]\n"
+        "s_bfe_i32 %[v], %[v], %[t]\n"        // the value's bits, signed (none: 0)
         "s_ashr_i32 %[t], %[v], 31\n"
         "s_lshl_b32 %[t2], -1, %[r2]\n"
         "s_xor_b32 %[t], %[t], %[t2]\n"
@@ -735,174 +797,114 @@ __device__ __forceinline__ uint32_t coop_walk(uint32_t& S, uint32_t& cur, uint32
         "s_cselect_b32 %[v], 0, %[v]\n"
         "s_add_u32 %[dcb], %[dcb], %[t]\n"
         "s_add_u32 %[dca], %[dca], %[v]\n"
-        "s_and_b32 %[r], %[r], %[step]\n"
-        "s_add_u32 %[S], %[S], %[r]\n"          // the index becomes 1; it stays 0 where no codeword starts
-        "s_movk_i32 %[why], 0\n"
+        "s_and_b32 %[r], %[r], 0x7e1f\n"
+        "s_add_u32 %[S], %[S], %[r]\n"        // the index becomes 1; it stays 0 where no codeword starts
         "s_bitcmp1_b32 %[S], 6\n"
         "s_cbranch_scc1 29f\n"
         "s_cmp_lt_u32 %[S], 0x200\n"
         "s_cbranch_scc1 20b\n"
-        // AC symbols, eight in a row
-        "21:\n"
+        "s_bitcmp1_b32 %[cur], %[kind]\n"
+        "s_cbranch_scc0 21b\n"
+        // AC symbols of a unit of kind 1
+        "31:\n"
         ".rept 8\n"
-        "v_readlane_b32 %[t], %[acs], %[S]\n"
+        "v_readlane_b32 %[t], %[c1], %[S]\n"
         "s_add_u32 %[S], %[S], %[t]\n"
         "s_and_b32 %[t2], %[S], 0x18040\n"
-        "s_cbranch_scc1 22f\n"
+        "s_cbranch_scc1 32f\n"
         ".endr\n"
-        "s_branch 21b\n"
-        "22:\n"
-        "s_movk_i32 %[why], 1\n"
+        "s_branch 31b\n"
+        "32:\n"
         "s_bitcmp1_b32 %[t], 15\n"
-        "s_cbranch_scc1 28f\n"
-        "s_movk_i32 %[why], 0\n"
+        "s_cbranch_scc1 37f\n"
         "s_bitcmp1_b32 %[S], 15\n"
-        "s_cbranch_scc0 29f\n"                   // the window ends inside the unit
-        // unit complete: the next one's word, and its AC table if that is another
-        "s_add_u32 %[nb], %[nb], 1\n"
-        "s_and_b32 %[S], %[S], 0x7f\n"
-        "s_bfe_u32 %[t], %[cur], %[f_next]\n"
-        "s_bfe_u32 %[dcs], %[cur], %[f_dcs]\n"
-        "s_and_b32 %[r], %[cur], 7\n"
-        "v_readlane_b32 %[cur], %[uw], %[t]\n"
-        "s_and_b32 %[r2], %[cur], 7\n"
-        "s_cmp_eq_u32 %[r], %[r2]\n"
-        "s_cbranch_scc1 23f\n"
-        "s_bitcmp1_b32 %[r2], 1\n"
-        "s_cselect_b64 vcc, -1, 0\n"
-        "s_lshl_b32 %[t], %[r2], 4\n"
-        "s_nop 1\n"
-        "v_cndmask_b32 %[acv], %[e01], %[e23], vcc\n"
-        "v_lshrrev_b32 %[acv], %[t], %[acv]\n"
-        "v_and_b32 %[acs], %[step], %[acv]\n"
-        "23:\n"
-        "s_bitcmp1_b32 %[S], 6\n"
-        "s_cbranch_scc0 20b\n"
-        "s_branch 29f\n"
-        "28:\n"
-        "s_sub_u32 %[S], %[S], %[t]\n"          // an escape: the step is taken back
+        "s_cbranch_scc1 23b\n"
+        // the window ends
         "29:\n"
+        "s_sub_u32 %[S], %[S], 64\n"          // the same position, seen from the next window
+        "s_sub_u32 %[left], %[left], 1\n"
+        "s_cmp_lg_u32 %[left], 0\n"
+        "s_cbranch_scc1 1b\n"
+        "s_branch 40f\n"
+        // escapes of the AC table of kind 0, of kind 1, of either DC table; the step is taken (again) with what they lead to
+        "27:\n"
+        "s_sub_u32 %[S], %[S], %[t]\n"
+        "v_cmp_gt_i32 vcc, 0, %[a0]\n"
+        "s_and_saveexec_b64 %[all], vcc\n"
+        "v_bfe_u32 %[c0], %[a0], 6, 3\n"
+        "v_sub_u32 %[c1], 23, %[c0]\n"
+        "v_bfe_u32 %[c0], %[peek], %[c1], %[c0]\n"
+        "v_lshrrev_b32 %[a0], 15, %[a0]\n"
+        "v_and_b32 %[a0], 0xfff8, %[a0]\n"
+        "v_lshl_add_u32 %[a0], %[c0], 2, %[a0]\n"
+        "ds_read_b32 %[a0], %[a0]\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "s_mov_b64 exec, %[all]\n"
+        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
+        "v_and_b32 %[c1], 0xfe1f, %[a1]\n"
         "s_nop 1\n"
-        : [S] "+&s"(S), [cur] "+&s"(cur), [dcs] "+&s"(dc_slot), [nb] "+&s"(nb), [dca] "+&s"(dc_a),
-          [dcb] "+&s"(dc_b), [acv] "+&v"(acv),
-          [acs] "+&v"(acs), [why] "=&s"(why), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v)
-        : [e01] "v"(e01), [e23] "v"(e23), [peek] "v"(peek), [uw] "v"(unit_word),
-          [step] "i"(kCoopStep), [f_size] "i"(bit_field(5u, 4u)), [f_dcs] "i"(bit_field(kUwDcNext, 3u)),
-          [f_next] "i"(bit_field(kUwNext, 4u)), [f_shift] "i"(bit_field(kUwShift, 5u)), [b_second] "i"(kUwSecond)
-        : "vcc", "scc");
-    return why;
+        "s_branch 21b\n"
+        "37:\n"
+        "s_sub_u32 %[S], %[S], %[t]\n"
+        "v_cmp_gt_i32 vcc, 0, %[a1]\n"
+        "s_and_saveexec_b64 %[all], vcc\n"
+        "v_bfe_u32 %[c1], %[a1], 6, 3\n"
+        "v_sub_u32 %[c0], 23, %[c1]\n"
+        "v_bfe_u32 %[c1], %[peek], %[c0], %[c1]\n"
+        "v_lshrrev_b32 %[a1], 15, %[a1]\n"
+        "v_and_b32 %[a1], 0xfff8, %[a1]\n"
+        "v_lshl_add_u32 %[a1], %[c1], 2, %[a1]\n"
+        "ds_read_b32 %[a1], %[a1]\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "s_mov_b64 exec, %[all]\n"
+        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
+        "v_and_b32 %[c1], 0xfe1f, %[a1]\n"
+        "s_nop 1\n"
+        "s_branch 31b\n"
+        "28:\n"
+        "s_bfe_u32 %[t], %[r], %[f_n]\n"
+        "s_sub_u32 %[t2], 23, %[t]\n"
+        "s_lshl_b32 %[t], %[t], 16\n"
+        "s_or_b32 %[t], %[t], %[t2]\n"
+        "s_bfe_u32 %[t], %[v], %[t]\n"
+        "s_lshl_b32 %[t], %[t], 2\n"
+        "s_lshr_b32 %[r], %[r], 15\n"
+        "s_and_b32 %[r], %[r], 0xfff8\n"
+        "s_add_u32 %[t], %[t], %[r]\n"
+        "v_mov_b32 %[c0], %[t]\n"
+        "ds_read_b32 %[c0], %[c0]\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        "v_readfirstlane_b32 %[r], %[c0]\n"
+        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
+        "s_branch 24b\n"
+        "40:\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        : [S] "+&s"(S), [cur] "+&s"(cur), [left] "+&s"(left), [nb] "+&s"(nb), [dca] "+&s"(dc_a), [dcb] "+&s"(dc_b), [at] "+&v"(at),
+          [d0] "=&v"(d0), [d1] "=&v"(d1), [a0] "=&v"(a0), [a1] "=&v"(a1), [c0] "=&v"(c0), [c1] "=&v"(c1), [peek] "=&v"(peek),
+          [nd0] "=&v"(nd0), [nd1] "=&v"(nd1), [na0] "=&v"(na0), [na1] "=&v"(na1), [npeek] "=&v"(npeek), [x0] "=&v"(x0),
+          [x1] "=&v"(x1), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v), [all] "=&s"(all)
+        : [shift] "v"(shift), [uw] "v"(unit_word), [bd0] "s"(ct.dc0), [ba0] "s"(ct.ac0), [bd1] "s"(ct.dc1), [ba1] "s"(ct.ac1),
+          [kind] "i"(kUwKind), [f_size] "i"(bit_field(20u, 4u)), [f_shift] "i"(bit_field(kUwShift, 5u)),
+          [b_second] "i"(kUwSecond), [f_n] "i"(bit_field(6u, 3u))
+        : "vcc", "scc", "memory");
+    p_io = limit + (S & 0x7Fu);
+    z_io = S >> 9;
+    const uint32_t next = cur & 15u;  // of the unit the chain is in now
+    u_io = next == 0u ? upm - 1u : next - 1u;
+    nb_out = nb;
+    const int32_t s0 = (int32_t)(int16_t)(dc_a & 0xFFFFu), s1 = (int32_t)(dc_a - (uint32_t)s0) >> 16;
+    dc_out = (int64_t)s0 + ((int64_t)s1 << 15) + ((int64_t)(int32_t)dc_b << 30);
 }
 
-// What the lanes know about one window of 64 bit positions: lane j holds the 32 bits that start at position j and
-// the first-level entry of each table for them.
-struct CoopWindow {
-    uint32_t peek, e0, e1, e2, e3;
-    __device__ __forceinline__ uint32_t of_slot(uint32_t slot) const {
-        const uint32_t a = (slot & 1u) ? 0u + e1 : 0u + e0, b = (slot & 1u) ? 0u + e3 : 0u + e2;
-        return (slot & 2u) ? 0u + b : 0u + a;
-    }
-};
-
-// The window that starts at bit ws (a multiple of 64).  The wavefront keeps 64 consecutive stream words, one per
-// lane, from word w0 on, and reloads them when a window needs words beyond them (org_word: stream word with cursor
-// 0 of `fetch`; cursors from nwords on are not read).  The table reads are only issued here.
-template <class Fetch, class Tab>
-__device__ __forceinline__ CoopWindow coop_window(uint32_t ws, uint32_t& w0, uint32_t& held, bool& have, uint32_t org_word,
-                                                  uint32_t nwords, const CoopTables& ct, uint32_t lane, Fetch fetch, Tab tab) {
-    uint32_t wb = (ws >> 5) - w0;
-    if (!have || wb + 2u > 63u) {
-        w0 = ws >> 5;
-        const uint32_t c = w0 - org_word + lane;
-        held = c < nwords ? fetch(c) : 0u;
-        wb = 0u;
-        have = true;
-    }
-    const uint32_t s0 = __builtin_amdgcn_readlane(held, wb), s1 = __builtin_amdgcn_readlane(held, wb + 1u);
-    const uint32_t s2 = __builtin_amdgcn_readlane(held, wb + 2u);
-    const uint32_t hi = lane < 32u ? s0 : s1, lo = lane < 32u ? s1 : s2;
-    CoopWindow w;
-    w.peek = (uint32_t)(((((uint64_t)hi << 32) | (uint64_t)lo) << (lane & 31u)) >> 32);
-    w.e0 = tab(ct.base[0] + ((w.peek >> ct.shift[0]) << 2));
-    w.e1 = tab(ct.base[1] + ((w.peek >> ct.shift[1]) << 2));
-    w.e2 = tab(ct.base[2] + ((w.peek >> ct.shift[2]) << 2));
-    w.e3 = tab(ct.base[3] + ((w.peek >> ct.shift[3]) << 2));
-    return w;
-}
-
-// p, u, z: wave-uniform state of the chain, advanced until p >= limit (limit a multiple of 64).  org_word, nwords:
-// see coop_window.
-// The windows lie on a 64-bit grid of the stream (a subsequence is a whole number of them, and a chain enters a
-// subsequence at most 31 bits behind its start, so no window is wasted): the window after the current one is known
-// before the chain has been followed through this one, and its table reads are issued first and answered
-// meanwhile.  Escapes are followed up in the walk, where only those on the chain matter.
-template <class Fetch, class Tab>
-__device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, uint32_t& z_io, uint32_t& nb_out,
-                                               int64_t& dc_out, uint32_t limit, uint32_t org_word, uint32_t nwords,
-                                               uint32_t unit_word, uint32_t upm, const CoopTables& ct, Fetch fetch,
-                                               Tab tab) {
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t p = __builtin_amdgcn_readfirstlane(p_io);
-    uint32_t u = __builtin_amdgcn_readfirstlane(u_io);
-    uint32_t z = __builtin_amdgcn_readfirstlane(z_io);
-    uint32_t nb = 0u, dc_a = 0u, dc_b = 0u;
-    uint32_t cur = __builtin_amdgcn_readlane(unit_word, u);
-    // slot of the table of the DC symbol that starts the current unit (its AC table is in bits 0..2 of its word)
-    uint32_t dc_slot = (__builtin_amdgcn_readlane(unit_word, u == 0u ? upm - 1u : u - 1u) >> kUwDcNext) & 7u;
-    uint32_t w0 = 0u, held = 0u;
-    bool have = false;
-    if (p < limit) {
-        uint32_t ws = p & ~63u;
-        // S = window position j (bits 0..6, at most 63 + 31) and zig-zag index z (bits 9..15, at most 63 + 63);
-        // adding a symbol's step advances both.  Bit 6 set: the window is behind us; bit 15 (or 16, after the step of an
-        // escape, which is taken back): the data unit is complete.
-        uint32_t S = (p - ws) | (z << 9);
-        CoopWindow nxt = coop_window(ws, w0, held, have, org_word, nwords, ct, lane, fetch, tab);
-        // (Without this the compiler merges these reads with the ones inside the loop into reads at the top of the
-        // loop, where every window would wait for them.)
-        asm volatile("" : "+v"(nxt.e0), "+v"(nxt.e1), "+v"(nxt.e2), "+v"(nxt.e3));
-        for (;;) {
-            const CoopWindow now = nxt;
-            const uint32_t peek = now.peek;
-            // (the walk finds a DC symbol's value bits in bits 5..8)
-            const uint32_t e01 = (now.e0 & 0xFFFFu) | ((now.e0 >> 15) & ct.dc[0]) | ((now.e1 | ((now.e1 >> 15) & ct.dc[1])) << 16);
-            const uint32_t e23 = (now.e2 & 0xFFFFu) | ((now.e2 >> 15) & ct.dc[2]) | ((now.e3 | ((now.e3 >> 15) & ct.dc[3])) << 16);
-            const bool more = ws + 64u < limit;
-            if (more) nxt = coop_window(ws + 64u, w0, held, have, org_word, nwords, ct, lane, fetch, tab);
-            const uint32_t ac_slot = cur & 7u;
-            uint32_t acv = ((ac_slot & 2u) ? e23 : e01) >> ((ac_slot & 1u) << 4);  // the AC entry in the low 16 bits
-            uint32_t acs = coop_step(acv);
-            for (;;) {
-                const uint32_t why = __builtin_amdgcn_readfirstlane(coop_walk(S, cur, dc_slot, nb, dc_a, dc_b, acv, acs, e01, e23, peek, unit_word));
-                if (__builtin_expect(why == kCoopLeft, 1)) break;
-                if (why == kCoopAcEscape) {
-                    // The codeword at this position is longer than the first-level index.  Every lane whose
-                    // entry of this table is an escape follows it up now, at once: where codewords are long
-                    // (large coefficients) a window holds several on the chain, and one look-up by all lanes
-                    // costs less than one by the chain alone.  The step is then taken again.
-                    if (acv & 0x8000u) acv = tab(sync_escape_at(now.of_slot(cur & 7u), peek));
-                    acs = coop_step(acv);
-                } else {
-                    const uint32_t pk = __builtin_amdgcn_readlane(peek, S);
-                    const uint32_t e = __builtin_amdgcn_readfirstlane(tab(sync_escape_at(__builtin_amdgcn_readlane(now.of_slot(dc_slot), S), pk)));
-                    const int32_t d = symbol_value(pk, lut_total(e), (e >> 20) & 15u);
-                    if (cur & (1u << kUwSecond)) dc_b += (uint32_t)d;
-                    else dc_a += (uint32_t)d << ((cur >> kUwShift) & 31u);
-                    S = __builtin_amdgcn_readfirstlane(S + coop_step(e));  // the index becomes 1, or stays 0 where no codeword starts
-                    if (S & 0x40u) break;
-                }
-            }
-            if (!more) break;
-            S -= 64u;  // the same position, seen from the next window
-            ws += 64u;
-        }
-        p = ws + (S & 0x7Fu);
-        z = S >> 9;
-        const uint32_t next = (cur >> kUwNext) & 15u;  // of the unit the chain is in now
-        u = next == 0u ? upm - 1u : next - 1u;
-    }
-    p_io = p; u_io = u; z_io = z; nb_out = nb;
-    const int32_t d0 = (int32_t)(int16_t)(dc_a & 0xFFFFu), d1 = (int32_t)(dc_a - (uint32_t)d0) >> 16;
-    dc_out = (int64_t)d0 + ((int64_t)d1 << 15) + ((int64_t)(int32_t)dc_b << 30);
+// The words the walk reads, for kernels that do not keep the stream in LDS: those from the window of bit p on, copied to `buf`
+// (kCoopBufWords words, the wavefront's own) by the whole wavefront.  Returns what coop_span_sync calls words.  cursors of
+// `fetch` from nwords on are not read.
+constexpr uint32_t kCoopBufWords = kMaxSubseqBits / 32u + 16u;
+template <class Fetch>
+__device__ __forceinline__ uint32_t coop_words(uint32_t* buf, uint32_t p, uint32_t limit, uint32_t org_word, uint32_t nwords, Fetch fetch) {
+    const uint32_t w0 = ((p & ~63u) >> 5) - org_word, n = ((limit - (p & ~63u)) >> 5) + 7u;
+    for (uint32_t k = threadIdx.x & 63u; k < n; k += 64u) buf[1u + k] = w0 + k < nwords ? fetch(w0 + k) : 0u;
+    return lds_at(buf + 1);
 }
 
 // ---- synchronisation, intra-sequence (paper, Algorithm 3, first loop) --------------------------------
@@ -924,6 +926,7 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
 constexpr int kSyncAll = 0, kSyncHead = 1, kSyncTail = 2;
 constexpr uint32_t kHandWords = 4u * kWG;  // per sequence: 3 x kWG record words, the chains, in the last word their number
 constexpr uint32_t kSyncFixedWords = 7u * kWG / 2u;  // of LDS: records and chains
+constexpr uint32_t kSyncPadWords = 12u;   // behind the stream in LDS: what lanes, and the walk of a whole wavefront, look at
 static_assert(kHandoff < kWG, "chains and their number in kWG words");
 template <bool STAGED, bool RST, int PHASE>
 __device__ __forceinline__ void sync_intra_body(const Params& P) {
@@ -961,7 +964,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     stage_sync_tables(P, D, lds_raw, &dc_fill);
     if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
     // scans with restart intervals: the bitmap of interval starts, for the bytes staged above
-    uint32_t* bm_s = strm + (STAGED ? kWG * wps + 4u : 4u);
+    uint32_t* bm_s = strm + (STAGED ? kWG * wps + kSyncPadWords : (uint32_t)kSyncWavesMax * kCoopBufWords);
     const uint32_t bm_k0 = first_word >> 3;
     uint32_t seen = 0u;
     const bool bm_lds = (1u << P.logL) <= (uint32_t)kBitmapLdsMaxL;
@@ -1028,10 +1031,10 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     // that frees a whole wavefront: a chain is (p, u, z, target), everything else is rebuilt from the staged
     // stream, so moving one costs two LDS words.  Between packings a round costs one barrier: the count of
     // running chains goes through one LDS word per wavefront, double-buffered by the parity of the round.
-    // The wavefront-per-chain code does not know more than four tables.  In a workgroup that sees restart intervals
+    // The wavefront-per-chain code does not know more than two kinds of data units.  In a workgroup that sees restart intervals
     // a chain may fall back to a single lane for a round (below): at most one chain per wavefront then, so that
     // such rounds never take longer than the packed ones they replace.
-    const uint32_t coop_max = P.lut_slots > 4u ? 0u : (restart ? min(P.coop_max, P.sync_waves) : P.coop_max);
+    const uint32_t coop_max = D.walk == 0u ? 0u : (restart ? min(P.coop_max, P.sync_waves) : P.coop_max);
     uint32_t coop_n = 0u;
     for (uint32_t round = 0u;; ++round) {
         const uint64_t bal = __ballot(active);
@@ -1099,9 +1102,9 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
         // the thread index); saying so keeps the chain's state in scalar registers
         const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63u;
         const uint32_t u_n = __builtin_amdgcn_readfirstlane(coop_n), u_t1 = __builtin_amdgcn_readfirstlane(t1);
-        const uint32_t u_first = __builtin_amdgcn_readfirstlane(first_word), u_nwords = __builtin_amdgcn_readfirstlane(nwords);
+        const uint32_t u_org = __builtin_amdgcn_readfirstlane(org);
         const uint32_t u_upm = __builtin_amdgcn_readfirstlane(D.upm);
-        const CoopTables ct = coop_tables(__builtin_amdgcn_readfirstlane(D.nslots), __builtin_amdgcn_readfirstlane(D.ndc), lds_at(lds_raw));
+        const CoopTables ct = coop_tables(D, lds_at(lds_raw));
         const uint32_t u_waves = P.sync_waves;  // a power of two
         const int32_t u_base = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
         const uint32_t unit_word = coop_unit_word(D, lane);
@@ -1128,7 +1131,8 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
                 uint32_t B = kNoBoundary;
                 if (restart) B = __builtin_amdgcn_readfirstlane(next_boundary(cp, limit + 64u, bword));
                 if (B == kNoBoundary) {
-                    coop_span_sync(cp, cu, cz, cnb, cdc, limit, u_first, u_nwords, unit_word, u_upm, ct, fetch, tab);
+                    const uint32_t at = STAGED ? (u_org + (cp & ~63u)) >> 3 : coop_words(strm + wave * kCoopBufWords, cp, limit, first_word, nwords, fetch);
+                    coop_span_sync(cp, cu, cz, cnb, cdc, limit, __builtin_amdgcn_readfirstlane(at), unit_word, u_upm, ct);
                 } else {
                     if (lane == 0u) {
                         SyncLane cl;
@@ -1239,11 +1243,12 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     // the slowest of them.  With few in this workgroup, each is walked by the whole wavefront, one after the other
     // (same results as the lane's loop below; the wavefront's decoder does not know restart intervals).
     const uint64_t workers = __ballot(work);
-    if (!D.restart && P.lut_slots <= 4u && __popcll(workers) <= kInterCoopMax) {
+    if (!D.restart && D.walk != 0u && __popcll(workers) <= kInterCoopMax) {
         const uint32_t lane = threadIdx.x;
         const uint32_t unit_word = coop_unit_word(D, lane);
         const uint32_t u_upm = __builtin_amdgcn_readfirstlane(D.upm);
-        const CoopTables ct = coop_tables(__builtin_amdgcn_readfirstlane(D.nslots), __builtin_amdgcn_readfirstlane(D.ndc), lds_at(lds_raw));
+        const CoopTables ct = coop_tables(D, lds_at(lds_raw));
+        __shared__ uint32_t buf[kCoopBufWords];
         const uint32_t u_nsub = __builtin_amdgcn_readfirstlane(nsub);
         const uint32_t u_nwords = (u_nsub << (P.logL - 5u)) + 4u;
         for (uint64_t m = workers; m; m &= m - 1ull) {
@@ -1257,7 +1262,7 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
                 uint32_t cnb = 0u;
                 int64_t cdc = 0;
                 const uint32_t limit = (cg + 1u) << P.logL;
-                coop_span_sync(cp, cu, cz, cnb, cdc, limit, 0u, u_nwords, unit_word, u_upm, ct, fetch, tab);
+                coop_span_sync(cp, cu, cz, cnb, cdc, limit, coop_words(buf, cp, limit, 0u, u_nwords, fetch), unit_word, u_upm, ct);
                 const uint32_t x = pack_state(cp - limit, cz, cu);
                 const bool synced = x == __atomic_load_n(&rec[cg].x, __ATOMIC_RELAXED);
                 if (lane == 0u) {
