@@ -36,6 +36,7 @@ struct Plan {
     uint32_t nsets = 0, lut_slots = 0;
     uint32_t pix_per_wg = 1;
     uint64_t out_bytes = 0;  // coefficients and pixels (or planes) at full size
+    uint64_t coef_bytes = 0;
     uint32_t tiles = 0, seqs = 0, grps = 0, bnds = 0, pixwgs = 0, nsub_total = 0;
     uint32_t bmap_words = 0;  // interval-start bitmaps of the images that have restart intervals
     uint32_t L = 0;
@@ -172,6 +173,7 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
         d.pix_runs = (d.mcus_x + M - 1) / M;
         if ((uint64_t)pl.pixwgs + (uint64_t)d.pix_runs * d.mcus_y > 0x7FFFFFFFull) return JPGD_E_ARG;  // grid size
         pl.pixwgs += d.pix_runs * d.mcus_y;
+        pl.coef_bytes += (uint64_t)d.total_units * 128u;
         pl.out_bytes += (uint64_t)d.total_units * 128u + (uint64_t)d.width * d.height * d.ncomp;
         // table slots: distinct DC tables first, then distinct AC tables, in order of first use
         uint32_t dc_ids[3], ac_ids[3], ndc = 0, nac = 0, comp_dc[3], comp_ac[3];
@@ -511,16 +513,16 @@ size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + (kSyncFix
 // most bytes that any image's tables take there
 constexpr uint32_t kSyncTabMax = kMaxPairs * (kSyncDcBytes + kSyncAcBytes) + kMaxPairs * 4 * (1022u + kLutL2);
 static_assert(kSyncTabMax <= 8u << 13, "an escape has 13 bits for its subtable");
-size_t lds_write_bytes(uint32_t L, uint32_t lut_slots, bool restart) {
+size_t lds_write_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
     uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + 4 : 4;
-    return (size_t)lut_slots * kLutEntries * 2 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
+    return (size_t)tab_bytes + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
 }
 
 // The write kernel that gathers its output in LDS is granted the most it may ever ask for, so that calls of different
-// sizes do not each change its attribute.
-constexpr size_t kLdsTiledMax = (size_t)kMaxSlots * kLutEntries * 2 + (kWG * (kTileMaxL / 32) + 4) * 4 + kTileBytes;
-static_assert((kMaxSlots * kLutEntries * 2 + (kWG * (kTileMaxL / 32) + 4) * 4) % 16 == 0, "the tile follows at a multiple of 16");
-static_assert(kLdsTiledMax + 1024 <= 160 * 1024, "with the kernel's static LDS on one CU");
+// sizes do not each change its attribute.  (With an image of six tables that are full of long codes there is not the most
+// room behind them.)
+constexpr size_t kLdsTiledMax = 160 * 1024 - 2048;
+static_assert(2u * (kSyncDcBytes + kSyncAcBytes + 4u * kLutL2) + (kWG * (kTileMaxL / 32) + 4) * 4 + kTileBytes <= kLdsTiledMax, "with the kernel's static LDS on one CU");
 
 // dynamic LDS beyond the default limit has to be requested per kernel and device; remember what was granted
 size_t g_lds_granted[kMaxDevices][9];
@@ -623,15 +625,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.stream = stream;
     c.ws = (uint8_t*)d_workspace;
     const bool any_restart = pl.bmap_words != 0u;
-    c.lds_write = lds_write_bytes(pl.L, pl.lut_slots, any_restart);
     c.staged = pl.L <= kStagedMaxL;
-    const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u);
-    uint32_t tile_bytes = 0u;
-    if (c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups)
-        for (int i = 0; i < n; ++i) {
-            const uint32_t room = tile_room(infos[i].total_units, infos[i].scan_bytes, pl.L);
-            if (room > tile_bytes) tile_bytes = room;
-        }
     rc = call_reserve(c, pl.h.upload_bytes + 16);
     if (rc) return rc;
     uint8_t* up = c.buf;
@@ -676,7 +670,16 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     }
     memcpy(up + pl.h.off_img, pl.img.data(), sizeof(ImgDesc) * (size_t)n);
     c.lds_sync = lds_sync_bytes(pl.L, tab_bytes, any_restart);
+    c.lds_write = lds_write_bytes(pl.L, tab_bytes, any_restart);
     c.lds_inter = tab_bytes;
+    const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u);
+    uint32_t tile_bytes = 0u;
+    if (c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups)
+        for (int i = 0; i < n; ++i) {
+            const uint32_t room = tile_room(infos[i].total_units, infos[i].scan_bytes, pl.L);
+            if (room > tile_bytes) tile_bytes = room;
+        }
+    if (tile_bytes > kLdsTiledMax - tile_off) tile_bytes = (uint32_t)(kLdsTiledMax - tile_off) & ~15u;
     if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
     // the variants of the intra-sequence kernel: stream staged in LDS or not, call with or without restart intervals
     c.variant = (c.staged ? 0 : 1) + (any_restart ? 2 : 0);
@@ -717,7 +720,6 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.logL = pl.h.logL;
     P.overlap = pl.h.overlap;
     P.seq_len = kWG - pl.h.overlap;
-    P.lut_slots = pl.lut_slots;
     P.tab_bytes = tab_bytes;
     P.planar = (flags_in & JPGD_F_PLANAR) ? 1u : 0u;
     P.scale_log2 = scale_log2;
@@ -740,6 +742,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.fold = any_restart ? 0u : 1u;
     P.tile_off = tile_off;
     P.tile_bytes = tile_bytes;
+    P.clear = tile_bytes == 0u && pl.coef_bytes <= kClearAheadBytes ? 1u : 0u;
     P.verdict = nullptr;
     P.ticket = 0u;
     P.up_src = (const uint4*)c.buf_dev;
@@ -818,6 +821,7 @@ int finish_call(Call& c, jpgd_report* report) {
             pending = c.verdict[2] != 0u;
         }
         const bool open = pending;
+        if (c.P.clear) hipLaunchKernelGGL(k_clear_coefficients, dim3(c.pl.grps), dim3(kWG), 0, c.stream, c.P);
         if ((rc = launch_write(c)) || (rc = launch_report(c, c.want_pixels)) || (rc = wait_verdict(c))) return rc;
         flags = c.verdict[0];
         if (open) flags |= kStMismatch;  // out of rounds: the result is not to be trusted
@@ -961,8 +965,8 @@ extern "C" int jpgd_init(void) {
     for (int v = 0; v < 4; ++v)
         if ((rc = grant_lds(dev, v, sync_kernels[v], lds_sync_bytes(2048u, kSyncTabMax, v >= 2)))) break;
     if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kSyncTabMax, false));
-    if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kMaxSlots, true));
-    if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kMaxSlots, true));
+    if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kSyncTabMax, true));
+    if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kSyncTabMax, true));
     if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, kLdsTiledMax);
     if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, kSyncTabMax);
     if (rc) return rc;

@@ -169,9 +169,6 @@ struct Status {
     uint32_t pad;
 };
 
-// write kernel: from this many bits of stream per data unit on, a workgroup's lanes lay down their own zeros instead
-// of the workgroup clearing its stretch of the output first
-constexpr uint32_t kDenseBitsPerUnit = 256u;
 constexpr int kUnstuffTile = 4096;  // bytes per workgroup of the unstuff kernels (256 lanes x 16 bytes)
 // Write kernel with the output gathered in LDS: calls of at most one workgroup for every other CU (two calls in flight
 // shall not wait for each other's LDS), subsequences of up to 256 bits (of longer ones a workgroup covers more
@@ -205,6 +202,13 @@ constexpr int kPixBlocksScaled = 192;  // ... of the reduced-size pixel kernels 
 // and 428 / 396, 20 (376 MB) 237 / 222 and 535 / 480; 256 images of 512x384 4:2:0 (302 MB) 329 / 328 and 683 / 642.
 constexpr uint64_t kLastLevelBytes = 256ull << 20;
 JPGD_HD bool pass_caches(uint64_t coef_and_pixel_bytes) { return coef_and_pixel_bytes > kLastLevelBytes; }
+
+// Calls of up to this many bytes of coefficients have them cleared by the synchronisation kernels, ahead of the write pass;
+// beyond, the lines are out of the last-level cache again when the values come, and the write pass clears its own
+// stretch.  Measured ahead / in the write pass, a call (us): frames of 1920x1088 4:4:4: 8 (100 MB) 118 / 124, 18 (226 MB)
+// 190 / 200, 24 (301 MB) 254 / 255, 32 (401 MB) 368 / 329, 48 (602 MB) 609 / 479; images of 512x384 4:2:0: 256 (151 MB)
+// 374 / 385, 512 (302 MB) 644 / 652; images of 2047x1535: 24 (227 MB) 456 / 464, 36 (340 MB) 520 / 543.
+constexpr uint64_t kClearAheadBytes = 320ull << 20;
 
 JPGD_HD uint32_t align_up(uint32_t v, uint32_t a) { return (v + a - 1) / a * a; }
 

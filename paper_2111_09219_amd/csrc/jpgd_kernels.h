@@ -36,8 +36,7 @@ struct Params {
     uint32_t logL;          // log2 of the subsequence size in bits
     uint32_t overlap;       // H: warm-up lanes in front of each sequence
     uint32_t seq_len;       // kWG - H: subsequences a sequence owns
-    uint32_t lut_slots;     // max tables of any image (sizes the LDS copy)
-    uint32_t tab_bytes;     // max bytes of any image's tables in the layout of the synchronisation kernels (a multiple of 16)
+    uint32_t tab_bytes;     // max bytes of any image's tables in LDS (stage_tables; a multiple of 16)
     uint32_t planar;        // pixel kernel: component planes (no upsampling, no colour conversion) instead of RGB
     uint32_t pix_per_wg;    // pixel kernel: runs of MCUs a workgroup takes one after the other
     uint32_t scale_log2;    // pixel kernel: output at 1/2^scale_log2 of the size (0..3)
@@ -45,6 +44,7 @@ struct Params {
     uint32_t coop_max;      // intra-sequence kernel: with at most this many chains left, one wavefront per chain
     uint32_t tile_off;      // write kernel with the output gathered in LDS: where that lies and how many bytes it has
     uint32_t tile_bytes;
+    uint32_t clear;         // the synchronisation kernels clear the coefficients (kClearAheadBytes), not the write kernel
     uint32_t fold;          // calls without restart intervals: the synchronisation kernels add up the group totals as they
                             // publish records, and k_group_totals only runs in further rounds
     uint32_t sync_waves;    // wavefronts per workgroup of that kernel: kWG / 64 that hold the lanes, the rest only take chains
@@ -242,15 +242,8 @@ __device__ __forceinline__ Seg wg_excl_segscan(Seg v, uint32_t* scratch, Seg* to
     return seg_join(carry, before);
 }
 
-__device__ __forceinline__ void stage_luts(const Params& P, const ImgDesc& D, uint16_t* lut_s) {
-    const uint32_t n16 = D.nslots * (uint32_t)kLutEntries;       // uint16 count, multiple of 8
-    const uint4* src = reinterpret_cast<const uint4*>(P.luts + D.lut_off);
-    uint4* dst = reinterpret_cast<uint4*>(lut_s);
-    for (uint32_t k = threadIdx.x; k < n16 / 8u; k += blockDim.x) dst[k] = src[k];
-}
-
-// The image's tables as the synchronisation kernels read them (sync_entry), at the start of the dynamic LDS: DC tables, AC
-// tables, subtables of the AC tables, subtables of the DC tables in any order.  dc_fill: a word of LDS, zero since the
+// The image's tables as the synchronisation kernels (sync_entry) or the write kernel (write_entry) read them, at the start of
+// the dynamic LDS: DC tables, AC tables, subtables of the AC tables, subtables of the DC tables in any order.  dc_fill: a word of LDS, zero since the
 // last barrier; all of it is complete after the next one.  What points into the tables (the rows, escapes) counts its bytes
 // from the start of LDS: a lane then has its addresses without an addition.
 using LdsBytes = const __attribute__((address_space(3))) uint8_t*;
@@ -258,7 +251,8 @@ using LdsWords = const __attribute__((address_space(3))) uint32_t*;
 __device__ __forceinline__ uint32_t lds_at(const void* p) { return (uint32_t)(uintptr_t)(LdsBytes)p; }
 __device__ __forceinline__ uint32_t lds_word(uint32_t at) { return *(LdsWords)(uintptr_t)at; }
 __device__ __forceinline__ uint32_t sync_ac_at(const ImgDesc& D) { return D.ndc * kSyncDcBytes; }
-__device__ __forceinline__ void stage_sync_tables(const Params& P, const ImgDesc& D, uint8_t* lds, uint32_t* dc_fill) {
+template <bool WRITE>
+__device__ __forceinline__ void stage_tables(const Params& P, const ImgDesc& D, uint8_t* lds, uint32_t* dc_fill) {
     uint32_t* const tab = reinterpret_cast<uint32_t*>(lds);
     const uint16_t* luts = P.luts + D.lut_off;
     const uint8_t* pairs = reinterpret_cast<const uint8_t*>(luts + kMaxSlots * kLutEntries);
@@ -269,19 +263,20 @@ __device__ __forceinline__ void stage_sync_tables(const Params& P, const ImgDesc
     for (uint32_t k = threadIdx.x; k < nac * (uint32_t)(kLutL1 / 8); k += blockDim.x) {  // eight entries
         const uint32_t a = k / (uint32_t)(kLutL1 / 8), i = (k % (uint32_t)(kLutL1 / 8)) * 8u;
         const uint4 e = *reinterpret_cast<const uint4*>(luts + (D.ndc + a) * (uint32_t)kLutEntries + i);
-        const uint2 pb = *reinterpret_cast<const uint2*>(pairs + a * (uint32_t)kPairBytes + i);
+        uint2 pb = make_uint2(0u, 0u);
+        if (!WRITE) pb = *reinterpret_cast<const uint2*>(pairs + a * (uint32_t)kPairBytes + i);
         const uint32_t at = lds0 + l2 + (a > 0u ? n0 * 4u : 0u) + (a > 1u ? n1 * 4u : 0u);
         uint4* dst = reinterpret_cast<uint4*>(tab + (ac >> 2) + a * (uint32_t)kLutL1 + i);
-        dst[0] = make_uint4(sync_ac_entry(0u, e.x & 0xFFFFu, pb.x & 255u, at), sync_ac_entry(1u, e.x >> 16, (pb.x >> 8) & 255u, at),
-                            sync_ac_entry(0u, e.y & 0xFFFFu, (pb.x >> 16) & 255u, at), sync_ac_entry(1u, e.y >> 16, pb.x >> 24, at));
-        dst[1] = make_uint4(sync_ac_entry(0u, e.z & 0xFFFFu, pb.y & 255u, at), sync_ac_entry(1u, e.z >> 16, (pb.y >> 8) & 255u, at),
-                            sync_ac_entry(0u, e.w & 0xFFFFu, (pb.y >> 16) & 255u, at), sync_ac_entry(1u, e.w >> 16, pb.y >> 24, at));
+        dst[0] = make_uint4(sync_ac_entry<WRITE>(0u, e.x & 0xFFFFu, pb.x & 255u, at), sync_ac_entry<WRITE>(1u, e.x >> 16, (pb.x >> 8) & 255u, at),
+                            sync_ac_entry<WRITE>(0u, e.y & 0xFFFFu, (pb.x >> 16) & 255u, at), sync_ac_entry<WRITE>(1u, e.y >> 16, pb.x >> 24, at));
+        dst[1] = make_uint4(sync_ac_entry<WRITE>(0u, e.z & 0xFFFFu, pb.y & 255u, at), sync_ac_entry<WRITE>(1u, e.z >> 16, (pb.y >> 8) & 255u, at),
+                            sync_ac_entry<WRITE>(0u, e.w & 0xFFFFu, (pb.y >> 16) & 255u, at), sync_ac_entry<WRITE>(1u, e.w >> 16, pb.y >> 24, at));
     }
     for (uint32_t k = threadIdx.x; k < (n0 + n1 + n2) >> 1; k += blockDim.x) {  // two entries
         uint32_t j = 2u * k, a = 0u;
         if (j >= n0) { j -= n0; a = 1u; if (j >= n1) { j -= n1; a = 2u; } }
         const uint32_t e = *reinterpret_cast<const uint32_t*>(luts + (D.ndc + a) * (uint32_t)kLutEntries + (uint32_t)kLutL1 + j);
-        reinterpret_cast<uint2*>(tab + (l2 >> 2))[k] = make_uint2(sync_entry(e & 0xFFFFu, false, 0u), sync_entry(e >> 16, false, 0u));
+        reinterpret_cast<uint2*>(tab + (l2 >> 2))[k] = make_uint2(pass_entry<WRITE>(e & 0xFFFFu, false, 0u), pass_entry<WRITE>(e >> 16, false, 0u));
     }
     const uint32_t dc_sub = l2 + (n0 + n1 + n2) * 4u;
     for (uint32_t k = threadIdx.x; k < D.ndc << kSyncDcK; k += blockDim.x) {
@@ -289,31 +284,26 @@ __device__ __forceinline__ void stage_sync_tables(const Params& P, const ImgDesc
         const uint32_t e = *reinterpret_cast<const uint32_t*>(lut + (k & ((1u << kSyncDcK) - 1u)) * 2u);
         const uint32_t a = e & 0xFFFFu, b = e >> 16, n = sync_dc_sub(a, b);
         if (n == 0xFFFFFFFFu) {
-            tab[k] = sync_dc_direct(a);
+            tab[k] = sync_dc_direct<WRITE>(a);
         } else {
             const uint32_t at = dc_sub + atomicAdd(dc_fill, 8u << n);  // (a multiple of 8)
-            for (uint32_t j = 0u; j < 2u << n; ++j) tab[(at >> 2) + j] = sync_dc_sub_entry(a, b, n, j, lut + kLutL1);
+            for (uint32_t j = 0u; j < 2u << n; ++j) tab[(at >> 2) + j] = sync_dc_sub_entry<WRITE>(a, b, n, j, lut + kLutL1);
             tab[k] = sync_escape(n + 1u, lds0 + at);
         }
     }
 }
 
 // rows: 8 entries of LDS, complete after the next barrier
-__device__ __forceinline__ void stage_sync_rows(const ImgDesc& D, SyncRow* rows, uint32_t tab) {
+template <bool WRITE>
+__device__ __forceinline__ void stage_rows(const ImgDesc& D, SyncRow* rows, uint32_t tab) {
     const uint32_t u = threadIdx.x, un = u + 1u == D.upm ? 0u : u + 1u;
-    if (u < D.upm)
+    if (u >= D.upm) return;
+    const uint32_t comp = (D.sched_comp >> (4u * u)) & 15u, comp_next = (D.sched_comp >> (4u * un)) & 15u;
+    {
         rows[u] = SyncRow{tab + sync_ac_at(D) + (((D.sched_ac >> (4u * u)) & 15u) - D.ndc) * kSyncAcBytes,
-                          tab + ((D.sched_dc >> (4u * un)) & 15u) * kSyncDcBytes, 1u << (15u * ((D.sched_comp >> (4u * u)) & 15u)),
-                          un * (uint32_t)sizeof(SyncRow)};
-}
-
-// rows: 8 entries of LDS, complete after the next barrier
-__device__ __forceinline__ Syntax stage_syntax(const ImgDesc& D, UnitRow* rows) {
-    if (threadIdx.x < D.upm) rows[threadIdx.x] = make_unit_row(threadIdx.x, D.upm, D.sched_dc, D.sched_ac, D.sched_comp);
-    Syntax sx;
-    sx.rows = rows;
-    sx.upm = D.upm;
-    return sx;
+                          tab + ((D.sched_dc >> (4u * un)) & 15u) * kSyncDcBytes,
+                          WRITE ? (comp != comp_next ? 1u : 0u) : 1u << (15u * comp), un * (uint32_t)sizeof(SyncRow)};
+    }
 }
 
 // LDS copy of a stretch of the stream as big-endian 32-bit words.  No padding: lanes start a power of two
@@ -907,6 +897,14 @@ __device__ __forceinline__ uint32_t coop_words(uint32_t* buf, uint32_t p, uint32
     return lds_at(buf + 1);
 }
 
+// Part k of n of an image's coefficients is cleared by `lanes` lanes of a workgroup, this one being number `lane`.
+__device__ __forceinline__ void clear_coefficients(const Params& P, const ImgDesc& D, uint32_t k, uint32_t n, uint32_t lane, uint32_t lanes) {
+    const uint32_t u0 = (uint32_t)((uint64_t)D.total_units * k / n), u1 = (uint32_t)((uint64_t)D.total_units * (k + 1u) / n);
+    uint4* out = reinterpret_cast<uint4*>(P.coef + D.coef_off + (size_t)u0 * 64u);
+    const uint32_t n16 = (u1 - u0) * 8u;
+    for (uint32_t j = lane; j < n16; j += lanes) out[j] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // ---- synchronisation, intra-sequence (paper, Algorithm 3, first loop) --------------------------------
 // Workgroup w of an image covers the kWG subsequences base .. base+kWG-1, base = w*seq_len - overlap, and
 // publishes the records of the last seq_len of them; the first `overlap` lanes only warm the chain up.
@@ -959,9 +957,9 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     __shared__ SyncRow rows_s[8];
     __shared__ uint32_t dc_fill;
     if (threadIdx.x == 0u) dc_fill = 0u;
-    stage_sync_rows(D, rows_s, lds_at(lds_raw));
+    stage_rows<false>(D, rows_s, lds_at(lds_raw));
     __syncthreads();
-    stage_sync_tables(P, D, lds_raw, &dc_fill);
+    stage_tables<false>(P, D, lds_raw, &dc_fill);
     if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
     // scans with restart intervals: the bitmap of interval starts, for the bytes staged above
     uint32_t* bm_s = strm + (STAGED ? kWG * wps + kSyncPadWords : (uint32_t)kSyncWavesMax * kCoopBufWords);
@@ -974,6 +972,17 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     bool restart = false;
     if (RST) restart = __syncthreads_or(seen != 0u) != 0;
     else __syncthreads();  // staged tables and stream are complete
+
+    // The write pass only stores values that are not zero: the coefficients are cleared here, a sequence's share of them
+    // by each workgroup (calls of moderate size, kClearAheadBytes): this kernel waits for chains of dependent symbols and leaves the memory idle, and the wavefronts
+    // that are only here for single chains have nothing else to do yet.  Where the write pass cleared its own stretch, all
+    // its workgroups did so first and waited for it: 24 images of 2047x1535 50 000 of 160 000 cycles a workgroup, batch of
+    // 256 20 000 of 190 000, 4963x7013 gray 13 000 of 50 000.  (No barrier waits for these stores.)
+    if (PHASE != kSyncTail && P.clear) {
+        const uint32_t lanes0 = blockDim.x > (uint32_t)kWG ? (uint32_t)kWG : 0u;
+        if (threadIdx.x >= lanes0)
+            clear_coefficients(P, D, wg - D.seq0, (nsub + P.seq_len - 1u) / P.seq_len, threadIdx.x - lanes0, blockDim.x - lanes0);
+    }
 
     const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
     // cursor = word index inside the workgroup's window
@@ -1230,9 +1239,9 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     __shared__ SyncRow rows_s[8];
     __shared__ uint32_t dc_fill;
     if (threadIdx.x == 0u) dc_fill = 0u;
-    stage_sync_rows(D, rows_s, lds_at(lds_raw));
+    stage_rows<false>(D, rows_s, lds_at(lds_raw));
     __syncthreads();
-    stage_sync_tables(P, D, lds_raw, &dc_fill);
+    stage_tables<false>(P, D, lds_raw, &dc_fill);
     __syncthreads();
     const uint32_t* words = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off);
     auto fetch = [&](uint32_t w) { return __builtin_bswap32(words[w]); };
@@ -1363,6 +1372,13 @@ __global__ __launch_bounds__(kWG) void k_group_scan(Params P) {
     }
 }
 
+// further rounds: what the write pass left from states that were not settled goes before it runs again
+__global__ __launch_bounds__(kWG) void k_clear_coefficients(Params P) {
+    const uint32_t ii = find_image(P, blockIdx.x, &ImgDesc::grp0);
+    const ImgDesc D = image_desc_uniform(P, ii);
+    clear_coefficients(P, D, blockIdx.x - D.grp0, D.ngrp_max, threadIdx.x, kWG);
+}
+
 // ---- write pass (paper, Algorithm 1 last loop; Algorithm 2 with write = true) ---------------------------
 
 // TILE: calls of few workgroups and without restart intervals (kTileMaxGroups).  Where the coefficients a workgroup covers
@@ -1381,14 +1397,16 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const uint32_t lg = wg - D.grp0;
     const uint32_t i0 = lg * kWG;
     if (i0 >= nsub) return;
-    uint16_t* lut_s = reinterpret_cast<uint16_t*>(lds_raw);
-    uint32_t* strm = reinterpret_cast<uint32_t*>(lut_s + P.lut_slots * (uint32_t)kLutEntries);
+    uint32_t* strm = reinterpret_cast<uint32_t*>(lds_raw + P.tab_bytes);
 
     const uint32_t L = 1u << P.logL, wps = L >> 5;
     const uint32_t nloc = min((uint32_t)kWG, nsub - i0);
     const uint32_t first_word = i0 * wps;
     const uint32_t nwords = nloc * wps + 4u;
-    __shared__ UnitRow rows[8];
+    __shared__ SyncRow rows_s[8];
+    __shared__ uint32_t dc_fill;
+    if (threadIdx.x == 0u) dc_fill = 0u;
+    stage_rows<true>(D, rows_s, lds_at(lds_raw));
     // the lane's record, its predecessor's state and the totals of the groups before this one are asked for
     // first: their way from memory overlaps the staging below
     const uint32_t t = threadIdx.x;
@@ -1408,9 +1426,9 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     } else {
         before = P.grp_pref[wg];
     }
-    stage_luts(P, D, lut_s);
-    const Syntax sx = stage_syntax(D, rows);
     if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
+    __syncthreads();
+    stage_tables<true>(P, D, lds_raw, &dc_fill);
     uint32_t* bm_s = strm + (STAGED ? kWG * wps + 4u : 4u);
     const uint32_t bm_k0 = first_word >> 3;
     uint32_t seen = 0u;
@@ -1459,16 +1477,9 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     uint32_t unit = ex.units;
     int32_t pred0 = (int32_t)ex.d0, pred1 = (int32_t)ex.d1, pred2 = (int32_t)ex.d2;
 
-    // The group clears the coefficients it is about to fill: those from where its first subsequence takes
-    // over (data unit and zig-zag index) to where the next group's does; the last group goes on to the end of
-    // the image.  The ranges of the groups tile the image, and a lane only stores inside its group's range.
-    // Where the data units are dense (kDenseBitsPerUnit bits of stream or more per unit: most of their 64 slots hold a
-    // value), the lanes lay down the few zeros of their own ranges as they go, chunk after chunk in address order,
-    // and nothing is cleared up front: the clear would write every line a second time.  Where they are sparse, the
-    // cooperative clear with full-width stores is far cheaper than one store per chunk and lane (measured: dense
-    // treatment of the 1920x1088 4:4:4 image, 60 bits per unit, costs the kernel a third more time; on the noise half
-    // of the 15360x8640 image, 340 bits per unit, it saves 8 %).  One decision per workgroup.
-    const bool dense = ((uint64_t)nloc << P.logL) >= (uint64_t)kDenseBitsPerUnit * grp_units;
+    // The group's slots: from where its first subsequence takes over (data unit and zig-zag index) to where the next
+    // group's does; the last group goes on to the end of the image.  The ranges of the groups tile the image, and a lane
+    // only stores inside its group's range.
     const uint64_t end_all = (uint64_t)D.total_units * 64u;
     const uint32_t x_in = scratch[32], x_out = scratch[33];
     uint64_t a = (uint64_t)gp.units * 64u + state_z(x_in);
@@ -1482,7 +1493,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     if (tiled) {
         for (uint32_t k = t; k < (tile_n + 7u) >> 3; k += kWG) tile16[k] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-    } else if (!dense) {
+    } else if (!P.clear) {
         if (a < b) {
             int16_t* c0 = P.coef + D.coef_off;
             uint64_t a8 = (a + 7u) & ~(uint64_t)7u;
@@ -1500,7 +1511,11 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     if (!tiled && !valid) return;
 
     const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
-    auto fetch = [&](uint32_t c) { return STAGED ? strm[c] : __builtin_bswap32(gwords[c]); };
+    // The lanes' bits: as in the synchronisation kernels.
+    const uint32_t org = (STAGED ? 8u * lds_at(strm) : 0u) - (first_word << 5);
+    auto word = [&](uint32_t b) { return STAGED ? lds_word(b >> 3) : __builtin_bswap32(gwords[b >> 5]); };
+    auto tab = [&](uint32_t k) { return lds_word(k); };
+    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
     int16_t* coef = P.coef + D.coef_off;
     // Coefficients leave the lane four at a time.  Every value as a store of its own makes 64 two-byte requests per
     // dense data unit, and the number of requests, not of bytes, is what the memory system charges for: the values
@@ -1513,20 +1528,12 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const uint32_t S = unit * 64u + state_z(xprev);  // first slot of this lane's range
     const uint32_t S_chunk = S >> 2, S_low = S & 3u;
     uint64_t acc = 0ull;
-    // chunk being gathered: 16 * data unit + (slot >> 2), from the chunk the lane's range starts in on (in a dense
-    // workgroup zeros are laid down from the first slot on; in a sparse one a chunk left without a value costs a
-    // store of zeros onto the cleared background, once per lane at most, and saves a test per chunk)
+    // chunk being gathered: 16 * data unit + (slot >> 2), from the chunk the lane's range starts in on (a chunk left
+    // without a value costs a store of zeros onto the cleared background, once per lane at most, and saves a test per chunk)
     uint32_t cur = S_chunk;
     const uint32_t shared_first = S_low != 0u ? S_chunk : 0xFFFFFFFFu;  // the first chunk, if a neighbour holds its start
     uint64_t first = 0ull;   // what was gathered in it; it is written at the end
     auto store8 = [&](uint32_t c, uint64_t a) { *reinterpret_cast<uint64_t*>(coef + (size_t)c * 4u) = a; };
-    // elements lo .. hi-1 of chunk c, zeros included (chunks shared with a neighbouring lane, dense workgroups)
-    auto put_part = [&](uint32_t c, uint64_t a, uint32_t lo, uint32_t hi) {
-        int16_t* dst = coef + (size_t)c * 4u;
-#pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e)
-            if (e >= lo && e < hi) dst[e] = (int16_t)(uint16_t)(a >> (16u * e));
-    };
     // the non-zero elements of chunk c (chunks shared with a neighbouring lane, onto the cleared background)
     auto put_nonzero = [&](uint32_t c, uint64_t a) {
         int16_t* dst = coef + (size_t)c * 4u;
@@ -1545,38 +1552,34 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         const uint32_t ck = k * 16u + (at >> 2);
         if (ck != cur) {
             leave();
-            if (dense)
-                for (uint32_t c = cur + 1u; c < ck; ++c) store8(c, 0ull);
             acc = 0ull;
             cur = ck;
         }
         acc |= (uint64_t)(uint16_t)v << ((at & 3u) * 16u);
     };
-    Lane l;
-    BitWin w;
-    l.p = (i << P.logL) + state_prel(xprev);
-    l.z = state_z(xprev);
-    l.u = state_u(xprev);
-    l.nb = 0u;
-    pred0 = (int32_t)(int16_t)pred0; pred1 = (int32_t)(int16_t)pred1; pred2 = (int32_t)(int16_t)pred2;
+    WriteLane l;
+    l.unit = unit;
+    l.seen = 0u;
+    const uint32_t u_in = state_u(xprev);
+    write_predictors(l, (D.sched_comp >> (4u * u_in)) & 15u, (int32_t)(int16_t)pred0, (int32_t)(int16_t)pred1, (int32_t)(int16_t)pred2);
+    auto start = [&]() { write_start(l, (i << P.logL) + state_prel(xprev) + org, u_in, state_z(xprev), D.upm, word, tab, rows); };
     uint32_t flags = 0u;
     const uint32_t total = D.total_units;
     // unit modulo the 1, 3, 4 or 6 units of an MCU
     const uint32_t unit3 = (D.upm == 6u ? unit >> 1 : unit) % 3u;
     const uint32_t in_mcu = D.upm == 1u ? 0u : D.upm == 4u ? unit & 3u : D.upm == 3u ? unit3 : unit3 * 2u + (unit & 1u);
-    if (unit < total && in_mcu != l.u) flags |= kStUnit;
+    if (unit < total && in_mcu != u_in) flags |= kStUnit;
     const uint32_t limit = (i + 1u) << P.logL;
     if (TILE && tiled) {
         if (valid && unit < total) {
-            win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-            prime(l, w, sx, lut_s);
+            start();
             uint16_t* const tile = reinterpret_cast<uint16_t*>(tile16);
             const uint32_t tile_first = (uint32_t)tile_a;
             auto gather = [&](uint32_t k, uint32_t at, int16_t v) {
                 const uint32_t slot = k * 64u + at - tile_first;
                 if (slot < tile_n) tile[slot] = (uint16_t)v;  // (a damaged stream may leave the range)
             };
-            decode_span_write(l, w, limit, unit, total, pred0, pred1, pred2, sx, fetch, lut_s, gather, flags);
+            write_span(l, limit + org, total, word, tab, rows, gather);
         }
         __syncthreads();
         // the first and the last word are shared with the neighbouring workgroups
@@ -1590,37 +1593,23 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         }
         if (!valid) return;
     } else if (unit < total) {
-        win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-        prime(l, w, sx, lut_s);
-        if (restart) decode_span_write_rst(l, w, limit, unit, total, D.restart * D.upm, pred0, pred1, pred2, sx, fetch, lut_s, store, flags, bword);
-        else decode_span_write(l, w, limit, unit, total, pred0, pred1, pred2, sx, fetch, lut_s, store, flags);
+        start();
+        if (restart) write_span_rst(l, limit + org, total, D.restart * D.upm, org, D.upm, word, tab, rows, store, bword, &flags);
+        else write_span(l, limit + org, total, word, tab, rows, store);
     }
-    if (!tiled && cur != S_chunk && S_low != 0u) {  // the first chunk, left behind
-        if (dense) put_part(S_chunk, first, S_low, 4u);
-        else put_nonzero(S_chunk, first);
-    }
-    if (tiled) {
-        // (everything is written)
-    } else if (dense) {
-        // the rest of the lane's range, up to where the next lane takes over (or the image ends)
-        const uint32_t E = unit < total ? unit * 64u + l.z : total * 64u;
-        if (E > S) {
-            const uint32_t E_chunk = E >> 2, E_low = E & 3u;
-            const uint32_t lo = cur == S_chunk ? S_low : 0u, hi = cur == E_chunk ? E_low : 4u;
-            if (lo == 0u && hi == 4u) store8(cur, acc);
-            else put_part(cur, acc, lo, hi);
-            for (uint32_t c = cur + 1u; c < E_chunk; ++c) store8(c, 0ull);
-            if (E_low != 0u && E_chunk > cur) put_part(E_chunk, 0ull, 0u, E_low);
-        }
-    } else {
-        put_nonzero(cur, acc);  // the last chunk may be shared with the next lane
-    }
+    // (in a workgroup with nothing to decode the lane stays where it was: behind the last unit)
+    unit = l.unit;
+    const uint32_t z_out = unit < total ? (l.s.S >> 9) & 63u : 0u;
+    if (l.seen & kWriteBad) flags |= kStInvalid;
+    if (!tiled && cur != S_chunk && S_low != 0u) put_nonzero(S_chunk, first);  // the first chunk, left behind
+    if (!tiled) put_nonzero(cur, acc);  // the last chunk may be shared with the next lane
     // all restart markers must have been there (the first lane of the image speaks for it)
     if (RST && D.restart && i == 0u && P.st[ii].markers != D.nint - 1u) flags |= kStInvalid;
     if (P.fold) check_boundaries(P, D, lg, nsub);
     // every lane checks the chain: unless the image is complete it must end in the recorded state
     if (unit < total) {
-        if (l.p < limit || pack_state(l.p - limit, l.z, l.u) != mine.x) flags |= kStMismatch;
+        const uint32_t p = sync_pos(l.s) - org;
+        if (p < limit || pack_state(p - limit, z_out, l.s.row / (uint32_t)sizeof(SyncRow)) != mine.x) flags |= kStMismatch;
         if (i == nsub - 1u) flags |= kStShort;
     }
     if (flags) atomicOr(&P.status->flags, flags);

@@ -312,6 +312,9 @@ JPGD_HD void decode_span_sync_pairs(Lane& l, BitWin& w, uint32_t limit, int64_t&
 //          bits 16..19 bits that the symbol behind it takes, bits 25..30 the slots that one covers (0: no second symbol;
 //                      an end of block covers kAdvEob like any other)
 //          bits 20..23 DC tables: value bits of the symbol
+// The write pass's tables differ in that nothing is said of a second symbol: bits 20..23 are the value bits of an AC
+// symbol too, bit 16 is set for coefficients and runs of sixteen zeros, which must not reach past the end of the unit, and
+// bit 17 where no codeword starts.
 constexpr uint32_t kSyncDcK = 9u;              // bits of a first-level index: DC tables (half the size; their codes are short),
 constexpr uint32_t kSyncAcK = (uint32_t)kLutK; // AC tables
 constexpr uint32_t kSyncDcBytes = 4u << kSyncDcK, kSyncAcBytes = 4u << kSyncAcK;
@@ -326,6 +329,14 @@ JPGD_HD uint32_t sync_entry(uint32_t e, bool is_dc, uint32_t pb) {
     const uint32_t slots = pb >> 4;
     return (e & kSyncStep) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
 }
+constexpr uint32_t kWriteInside = 1u << 16, kWriteNoCode = 1u << 17;
+JPGD_HD uint32_t write_entry(uint32_t e, bool is_dc) {
+    const uint32_t slots = lut_adv(e);
+    return (e & kSyncStep) | (lut_size(e) << 20) | (slots == 0u ? kWriteNoCode : !is_dc && slots != kAdvEob ? kWriteInside : 0u);
+}
+// either, as the tables of the pass need it
+template <bool WRITE>
+JPGD_HD uint32_t pass_entry(uint32_t e, bool is_dc, uint32_t pb) { return WRITE ? write_entry(e, is_dc) : sync_entry(e, is_dc, pb); }
 // escape into a subtable indexed by n bits, from byte `at` of the tables on (a multiple of 8)
 JPGD_HD uint32_t sync_escape(uint32_t n, uint32_t at) { return 0x80000000u | kSyncEsc | (n << 6) | ((at >> 3) << 18); }
 // byte of the tables at which the entry lies that escape e leads to
@@ -339,8 +350,9 @@ JPGD_HD uint32_t sync_escape_at(uint32_t e, uint32_t peek) {
     return ((e >> 15) & 0xFFF8u) + (i << 2);
 }
 // first-level entry i of an AC table; l2: byte of the tables from which on the table's second level lies, entry by entry
+template <bool WRITE = false>
 JPGD_HD uint32_t sync_ac_entry(uint32_t i, uint32_t e, uint32_t pb, uint32_t l2) {
-    if (!lut_esc(e)) return sync_entry(e, false, pb);
+    if (!lut_esc(e)) return pass_entry<WRITE>(e, false, pb);
     const uint32_t n = lut_esc_bits(e);
     return sync_escape(n + 1u, l2 + 4u * lut_esc_offset(e) - (n ? (i & 1u) << (n + 2u) : 0u));
 }
@@ -353,14 +365,15 @@ JPGD_HD uint32_t sync_dc_sub(uint32_t a, uint32_t b) {
 }
 // entry j of that subtable; l2: second level of build_lut's table.  (An escape without further bits stands for "no
 // codeword", the first entry there.)
-template <class L2>
+template <bool WRITE = false, class L2>
 JPGD_HD uint32_t sync_dc_sub_entry(uint32_t a, uint32_t b, uint32_t n, uint32_t j, L2 l2) {
     const uint32_t e = j >> n ? b : a;
-    if (!lut_esc(e)) return sync_entry(e, true, 0u);
+    if (!lut_esc(e)) return pass_entry<WRITE>(e, true, 0u);
     const uint32_t k = lut_esc_bits(e);
-    return sync_entry(l2[lut_esc_offset(e) + ((j & ((1u << n) - 1u)) >> (n - k))], true, 0u);
+    return pass_entry<WRITE>(l2[lut_esc_offset(e) + ((j & ((1u << n) - 1u)) >> (n - k))], true, 0u);
 }
-JPGD_HD uint32_t sync_dc_direct(uint32_t a) { return sync_entry(lut_esc(a) ? 1u : a, true, 0u); }
+template <bool WRITE = false>
+JPGD_HD uint32_t sync_dc_direct(uint32_t a) { return pass_entry<WRITE>(lut_esc(a) ? 1u : a, true, 0u); }
 
 // Words of subtables that a table of build_lut needs in this layout (at most 1022).
 inline uint32_t sync_sub_words(const uint16_t* lut, bool is_dc) {
@@ -481,6 +494,90 @@ JPGD_HD void sync_span(SyncLane& l, uint32_t limit, int64_t& dcacc, Word word, T
 #endif
         dcacc += (int64_t)v * (int64_t)mul;
     } while (pos < stop);
+}
+
+// ---- the lanes of the write pass ---------------------------------------------------------------------------
+// The same walk, one symbol per step (write = true in Algorithm 2), on tables in the same layout: every non-zero coefficient
+// goes to 64*unit + zig-zag index, DC values un-differenced.  Without branches except around the store itself: a
+// wavefront holds lanes in every kind of symbol at once, so each arm of a branch would be walked anyway.
+// What bounds it is the length of a step in a wavefront that has its SIMD nearly to itself: 680 cycles on the 4096x4096
+// image where the stores are scattered over 64 lines, 450 of them without any store; a loop for the zeros between two
+// values, for stretches of dense units, was 100 more and is gone since the coefficients are always cleared first.
+// Kernel before / now, cleared ahead (us): 24 images of 2047x1535 104 / 82, 4963x7013 gray 31 / 21, 1001x667 28 / 23, one
+// 1600x1200 image 46 / 38, 3001x2003 41 / 36; 15360x8640 (cleared here) 412 / 384.
+// The predictors are kept in the order in which the components come next: the current unit's in p0, so that a DC symbol need
+// not choose; they move up where the component changes (`dcmul` of a write pass's row: 1 if the unit behind it is of another
+// component, else 0).
+struct WriteLane {
+    SyncLane s;
+    SyncRow row;         // the current unit's
+    uint32_t peek;
+    uint32_t unit;       // index of the data unit being decoded
+    int32_t p0, p1, p2;
+    uint32_t seen;       // bit 16: a symbol ran past the end of its unit; bit 17: bits that start no codeword
+};
+constexpr uint32_t kWriteBad = 3u << 16;
+// the predictors of components 0, 1 and 2 in the order for a unit of component comp
+JPGD_HD void write_predictors(WriteLane& l, uint32_t comp, int32_t d0, int32_t d1, int32_t d2) {
+    l.p0 = comp == 0u ? d0 : comp == 1u ? d1 : d2;
+    l.p1 = comp == 0u ? d1 : comp == 1u ? d2 : d0;
+    l.p2 = comp == 0u ? d2 : comp == 1u ? d0 : d1;
+}
+template <class Word, class Tab, class Row>
+JPGD_HD void write_start(WriteLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, Word word, Tab tab, Row rows) {
+    sync_start(l.s, p, u, z, upm, word, tab, rows);
+    l.row = rows(l.s.row);
+    l.peek = sync_peek(l.s);
+}
+template <class Word, class Tab, class Row, class Store>
+JPGD_HD void write_step(WriteLane& l, Word word, Tab tab, Row rows, Store store) {
+    const uint32_t e = l.s.e, before = l.peek;
+    const bool esc = (int32_t)e < 0;
+    const bool dc = l.s.S < 0x200u && !esc;
+    const uint32_t s2 = l.s.S + (e & 0xFFFFu);
+    const bool ends = s2 >= kSyncEsc;  // the unit is complete, or an escape
+    const uint32_t word_on = s2 & 32u;
+    l.s.hi = word_on ? l.s.lo : l.s.hi;
+    l.s.lo = word_on ? l.s.ahead : l.s.lo;
+    l.peek = funnel(l.s.hi, l.s.lo, ~s2);
+    const uint32_t next = (ends ? l.row.dc_next : l.row.ac) + ((l.peek >> (ends ? 32u - kSyncDcK : 32u - kSyncAcK)) << 2);
+    const uint32_t sub = sync_escape_at(e, l.peek);
+    uint32_t size = (e >> 20) & 15u, total = e & 31u;
+    // (bit 16 of the sum is set from 65 slots on, bit 17 always)
+    l.seen |= e & (s2 + (kWriteNoCode + kWriteInside - (65u << 9)));
+#if defined(__HIP_DEVICE_COMPILE__)
+    total = 0u - e;  // (the offset of the value's bits, taken modulo 32)
+    asm volatile("" : "+v"(size), "+v"(total), "+v"(l.seen));  // (the entry's register is free for the next one from here on)
+#endif
+    l.s.e = tab(esc ? sub : next);
+    l.s.at += word_on;
+    l.s.ahead = word(l.s.at);
+    const bool done = ends && !esc;
+    l.s.S = s2 & (done ? 31u : kSyncStep);
+    l.s.row = done ? l.row.next : l.s.row;
+    const bool other = done && l.row.dcmul != 0u;
+    l.row = rows(l.s.row);
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int32_t v = value_of_field(__builtin_amdgcn_sbfe((int32_t)before, total, size), size);
+#else
+    const int32_t v = symbol_value(before, total, size);
+#endif
+    l.p0 += dc ? v : 0;
+    // where the symbol ends: a coefficient sits in the last slot it covers (after its run of zeros); a DC symbol ends
+    // in slot 0, or, where no codeword starts, before it; a DC symbol without value bits still yields the predictor
+    if ((dc || (size != 0u && !esc)) && s2 - 0x200u < (64u << 9)) store(l.unit, (s2 >> 9) - 1u, (int16_t)(dc ? l.p0 : v));
+    const int32_t q = l.p0;
+    l.p0 = other ? l.p1 : l.p0;
+    l.p1 = other ? l.p2 : l.p1;
+    l.p2 = other ? q : l.p2;
+    l.unit += done ? 1u : 0u;
+}
+
+// Decodes while the next symbol starts before bit `limit` (of `word`), up to the image's last data unit.
+template <class Word, class Tab, class Row, class Store>
+JPGD_HD void write_span(WriteLane& l, uint32_t limit, uint32_t total_units, Word word, Tab tab, Row rows, Store store) {
+    const uint32_t stop = limit + kSyncBias;
+    while (sync_at(l.s) < stop && l.unit < total_units) write_step(l, word, tab, rows, store);
 }
 
 // One symbol of the write pass (write = true in Algorithm 2): every non-zero coefficient goes to
@@ -652,6 +749,37 @@ JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t
             }
         }
         if (!next_interval) break;
+    }
+}
+
+// The write pass's lanes over a stream with restart intervals (rules: decode_span_write_rst below).  `org` as in
+// sync_span_rst; *flags: kStInvalid where an interval starts at another unit than it should.
+template <class Word, class Tab, class Row, class Store, class BWord>
+JPGD_HD void write_span_rst(WriteLane& l, uint32_t limit, uint32_t total_units, uint32_t units_per_interval, uint32_t org,
+                            uint32_t upm, Word word, Tab tab, Row rows, Store store, BWord bword, uint32_t* flags) {
+    const uint32_t end = limit - org;
+    auto calm_until = [&](uint32_t B) { return B != kNoBoundary && B < end + 39u ? (B >= 39u ? B - 39u : 0u) : end; };
+    uint32_t pos = sync_pos(l.s) - org;
+    uint32_t B = next_boundary(pos, end + 64u, bword);
+    uint32_t calm = calm_until(B);
+    while (l.unit < total_units) {
+        const bool near = pos >= calm;
+        if (near) {
+            if (B == kNoBoundary || pos >= end) break;
+            if (pos == B) {
+                l.p0 = l.p1 = l.p2 = 0;
+                if (l.unit % units_per_interval != 0u) *flags |= kStInvalid;
+                B = next_boundary(B + 1u, end + 64u, bword);
+                calm = calm_until(B);
+                continue;
+            }
+        }
+        write_step(l, word, tab, rows, store);
+        pos = sync_pos(l.s) - org;
+        if (near && (pos >= B || (B - pos <= 7u && (~l.peek >> (32u - (B - pos))) == 0u))) {
+            write_start(l, B + org, 0u, 0u, upm, word, tab, rows);
+            pos = B;
+        }
     }
 }
 

@@ -1,6 +1,6 @@
-// Host build of the synchronisation pass's lanes (sync_span, sync_span_rst) on tables laid out as the kernels lay them out in
-// LDS, beside the plain lanes that decode symbol by symbol from the tables of jpgd_lut.h.  Test code: the library never
-// calls it.
+// Host build of the kernels' lanes (sync_span, write_span and their _rst forms) on tables laid out as the kernels lay them out
+// in LDS, beside the plain lanes that decode symbol by symbol from the tables of jpgd_lut.h.  Test code: the library
+// never calls it.
 //
 // Build: g++ -O2 -std=c++17 -shared -fPIC -o libjpgd_sync.so jpgd_sync.cpp ../../paper_2111_09219_amd/csrc/jpgd_parse.cpp
 #include <string.h>
@@ -20,38 +20,40 @@ namespace {
 
 struct Tables {
     std::vector<uint16_t> lut;       // build_lut, DC slots first
-    std::vector<uint32_t> sync;      // the kernels' layout
+    std::vector<uint32_t> sync;      // the kernels' layout: synchronisation pass,
+    std::vector<uint32_t> write;     // write pass
     uint32_t ndc = 0, nslots = 0;
     uint32_t words[6] = {0};         // sync_sub_words
 };
 
-// as stage_sync_tables fills them, DC subtables in the order of their entries
-bool lay_out(Tables& t, uint32_t base) {
+// as stage_tables fills them, DC subtables in the order of their entries
+template <bool WRITE>
+bool lay_out(Tables& t, uint32_t base, std::vector<uint32_t>& out) {
     const uint32_t nac = t.nslots - t.ndc;
     std::vector<uint8_t> pairs(kPairBytes);
     uint32_t sub = t.ndc * kSyncDcBytes + nac * kSyncAcBytes, all = 0;
     for (uint32_t s = 0; s < t.nslots; ++s) all += t.words[s] = sync_sub_words(&t.lut[s * kLutEntries], s < t.ndc);
-    t.sync.assign(sub / 4 + all, 0xDEADBEEFu);
+    out.assign(sub / 4 + all, 0xDEADBEEFu);
     for (uint32_t a = 0; a < nac; ++a) {
         const uint16_t* lut = &t.lut[(t.ndc + a) * kLutEntries];
         build_pairs(lut, pairs.data());
         for (uint32_t i = 0; i < (uint32_t)kLutL1; ++i)
-            t.sync[(t.ndc * kSyncDcBytes + a * kSyncAcBytes) / 4 + i] = sync_ac_entry(i, lut[i], pairs[i], base + sub);
-        for (uint32_t k = 0; k < t.words[t.ndc + a]; ++k) t.sync[sub / 4 + k] = sync_entry(lut[kLutL1 + k], false, 0u);
+            out[(t.ndc * kSyncDcBytes + a * kSyncAcBytes) / 4 + i] = sync_ac_entry<WRITE>(i, lut[i], pairs[i], base + sub);
+        for (uint32_t k = 0; k < t.words[t.ndc + a]; ++k) out[sub / 4 + k] = pass_entry<WRITE>(lut[kLutL1 + k], false, 0u);
         sub += 4u * t.words[t.ndc + a];
     }
     for (uint32_t s = 0; s < t.ndc; ++s) {
         const uint16_t* lut = &t.lut[s * kLutEntries];
         for (uint32_t i = 0; i < 1u << kSyncDcK; ++i) {
             const uint32_t a = lut[2 * i], b = lut[2 * i + 1], n = sync_dc_sub(a, b);
-            uint32_t& e = t.sync[s * kSyncDcBytes / 4 + i];
-            if (n == 0xFFFFFFFFu) { e = sync_dc_direct(a); continue; }
+            uint32_t& e = out[s * kSyncDcBytes / 4 + i];
+            if (n == 0xFFFFFFFFu) { e = sync_dc_direct<WRITE>(a); continue; }
             e = sync_escape(n + 1u, base + sub);
             for (uint32_t j = 0; j < 2u << n; ++j, sub += 4)
-                t.sync.at(sub / 4) = sync_dc_sub_entry(a, b, n, j, lut + kLutL1);
+                out.at(sub / 4) = sync_dc_sub_entry<WRITE>(a, b, n, j, lut + kLutL1);
         }
     }
-    return sub / 4 == t.sync.size();
+    return sub / 4 == out.size();
 }
 
 struct Scan {
@@ -61,7 +63,8 @@ struct Scan {
     std::vector<uint32_t> bmap;
     uint32_t nbits = 0;
     UnitRow rows[8];
-    SyncRow srows[8];
+    SyncRow srows[8], wrows[8];
+    uint32_t sched_comp = 0;
 };
 
 // build_lut's tables for the plain lanes; remembers whether an entry of a DC table stood for "no codeword"
@@ -90,7 +93,7 @@ int open_scan(const uint8_t* file, size_t len, Scan& S) {
     S.t.lut.assign(S.t.nslots * kLutEntries, 0);
     for (auto& d : dc) if (!build_lut(in.dht_bits[0][d.first], in.dht_vals[0][d.first], true, &S.t.lut[d.second * kLutEntries])) return JPGD_E_TABLE;
     for (auto& a : ac) if (!build_lut(in.dht_bits[1][a.first], in.dht_vals[1][a.first], false, &S.t.lut[(S.t.ndc + a.second) * kLutEntries])) return JPGD_E_TABLE;
-    if (!lay_out(S.t, kBase)) return JPGD_E_TABLE;
+    if (!lay_out<false>(S.t, kBase, S.t.sync) || !lay_out<true>(S.t, kBase, S.t.write)) return JPGD_E_TABLE;
     uint32_t sched_dc = 0, sched_ac = 0, sched_comp = 0, u = 0;
     for (uint32_t c = 0; c < in.ncomp; ++c)
         for (uint32_t k = 0, nu = in.ncomp == 3 && c == 0 ? (uint32_t)in.hsamp[0] * in.vsamp[0] : 1u; k < nu; ++k, ++u) {
@@ -103,7 +106,10 @@ int open_scan(const uint8_t* file, size_t len, Scan& S) {
         S.srows[k] = SyncRow{kBase + S.t.ndc * kSyncDcBytes + (((sched_ac >> (4 * k)) & 15) - S.t.ndc) * kSyncAcBytes,
                              kBase + ((sched_dc >> (4 * ((k + 1) % u))) & 15) * kSyncDcBytes, S.rows[k].dcmul,
                              S.rows[k].next * (uint32_t)sizeof(SyncRow)};
+        S.wrows[k] = S.srows[k];
+        S.wrows[k].dcmul = ((sched_comp >> (4 * k)) & 15) != ((sched_comp >> (4 * ((k + 1) % u))) & 15) ? 1u : 0u;
     }
+    S.sched_comp = sched_comp;
     const uint8_t* p = file + in.scan_offset;
     S.bmap.assign(in.scan_bytes / 32 + 80, 0);
     for (size_t k = 0; k < in.scan_bytes; ++k) {
@@ -181,6 +187,89 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
     return bad;
 }
 
+// The write pass's lanes from `tries` states: what they store, unit, position, state, predictors and flags must be those of
+// decode_span_write (_rst).  States: random ones, and with `chain` those the true chain passes through (both flag
+// nothing there).  Predictors are compared in scans without intervals: a lane that has moved to the start of one has yet to
+// clear them.  total: units after which they stop (0: all of the image).
+extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32_t tries, int chain, uint32_t org, uint32_t total,
+                              uint32_t seed, uint32_t* stored) {
+    Scan S;
+    const int rc = open_scan(file, len, S);
+    if (rc) return -rc;
+    const uint32_t* words = (const uint32_t*)S.stream.data();
+    auto fetch = [&](uint32_t c) { return c < S.stream.size() / 4 ? __builtin_bswap32(words[c]) : 0u; };
+    auto word = [&](uint32_t b) {
+        if ((b & 31u) || b - org > S.nbits + 4096u) __builtin_trap();
+        return fetch((b - org) >> 5);
+    };
+    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.write.at((k - kBase) / 4); };
+    auto rows = [&](uint32_t k) { if (k % sizeof(SyncRow) || k / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.wrows[k / sizeof(SyncRow)]; };
+    auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
+    Syntax sx;
+    sx.rows = S.rows;
+    const uint32_t upm = sx.upm = S.in.units_per_mcu;
+    const bool restart = S.in.restart_interval != 0;
+    const uint32_t upi = S.in.restart_interval * upm;
+    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
+    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    int bad = 0;
+    *stored = 0;
+    Lane c;   // the true chain
+    BitWin cw;
+    c.p = c.u = c.z = c.nb = 0;
+    win_init(cw, 0, 0, fetch);
+    prime(c, cw, sx, S.t.lut.data());
+    const uint32_t nsub = (S.nbits + L - 1) / L;
+    if (!total) total = S.in.total_units;
+    for (uint32_t k = 0; k < tries && (!chain || k < nsub); ++k) {
+        const uint32_t i = chain ? k : rnd(nsub), limit = (i + 1) * L;
+        Lane a;
+        BitWin w;
+        a.p = chain ? c.p : i * L + rnd(31);
+        a.u = chain ? c.u : rnd(upm);
+        a.z = chain ? c.z : rnd(3) ? rnd(64) : 0u;
+        a.nb = 0;
+        const Lane in = a;
+        // (no lane starts in the padding in front of an interval)
+        const bool padding = restart && next_boundary(a.p, a.p + 8u, bword) != kNoBoundary && next_boundary(a.p, a.p + 8u, bword) > a.p;
+        if (a.p < S.nbits && !(org >> 31 && a.p + org >= org) && !padding) {
+            const uint32_t unit = chain ? c.nb : rnd(S.in.total_units) / upm * upm + a.u;
+            const int32_t d[3] = {(int32_t)rnd(4096) - 2048, (int32_t)rnd(4096) - 2048, (int32_t)rnd(4096) - 2048};
+            std::vector<std::pair<uint64_t, int>> sa, sb;
+            uint32_t ua = unit, fa = 0, fb = 0;
+            int32_t p0 = d[0], p1 = d[1], p2 = d[2];
+            win_init(w, a.p, a.p >> 5, fetch);
+            prime(a, w, sx, S.t.lut.data());
+            auto store_a = [&](uint32_t u, uint32_t at, int16_t v) { sa.push_back({(uint64_t)u * 64 + at, v}); };
+            if (restart) decode_span_write_rst(a, w, limit, ua, total, upi, p0, p1, p2, sx, fetch, S.t.lut.data(), store_a, fa, bword);
+            else decode_span_write(a, w, limit, ua, total, p0, p1, p2, sx, fetch, S.t.lut.data(), store_a, fa);
+            WriteLane b;
+            b.unit = unit;
+            b.seen = 0;
+            auto store_b = [&](uint32_t u, uint32_t at, int16_t v) { if (at > 63u) __builtin_trap(); sb.push_back({(uint64_t)u * 64 + at, v}); };
+            write_predictors(b, (S.sched_comp >> (4 * in.u)) & 15, d[0], d[1], d[2]);
+            write_start(b, in.p + org, in.u, in.z, upm, word, tab, rows);
+            if (restart) write_span_rst(b, limit + org, total, upi, org, upm, word, tab, rows, store_b, bword, &fb);
+            else write_span(b, limit + org, total, word, tab, rows, store_b);
+            if (b.seen & kWriteBad) fb |= kStInvalid;
+            const uint32_t u = b.s.row / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
+            WriteLane want = b;
+            write_predictors(want, (S.sched_comp >> (4 * a.u)) & 15, p0, p1, p2);
+            if (sa != sb || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
+                (!restart && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
+                ++bad;
+            *stored += (uint32_t)sb.size();
+        }
+        if (chain) {
+            int64_t dc = 0;
+            uint32_t crossed = 0;
+            if (restart) decode_span_sync_rst(c, cw, limit, dc, crossed, sx, fetch, S.t.lut.data(), bword);
+            else decode_span_sync(c, cw, limit, dc, sx, fetch, S.t.lut.data());
+        }
+    }
+    return bad;
+}
+
 // Every 16-bit stretch looked up in a table of build_lut and in its layout for the synchronisation kernels: mismatches.
 extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int is_dc) {
     Tables t;
@@ -188,7 +277,7 @@ extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int i
     t.nslots = 1u;
     t.lut.assign(kLutEntries, 0);
     if (!build_lut(bits, vals, is_dc != 0, t.lut.data())) return -1;
-    if (!lay_out(t, kBase)) return -2;
+    if (!lay_out<false>(t, kBase, t.sync) || !lay_out<true>(t, kBase, t.write)) return -2;
     int bad = 0;
     for (uint32_t v = 0; v < 65536u; ++v) {
         const uint32_t peek = v << 16 | 0x5A5Au;
@@ -203,6 +292,10 @@ extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int i
             if (k < kBase || (k & 3u)) return -3;
             s = t.sync.at((k - kBase) / 4);
         }
+        uint32_t w = t.write.at(peek >> (32u - (is_dc ? kSyncDcK : kSyncAcK)));
+        if (w & kSyncEsc) w = t.write.at((sync_escape_at(w, peek) - kBase) / 4);
+        const bool inside = !is_dc && lut_adv(e) != 0u && lut_adv(e) != kAdvEob;
+        bad += w != ((e & kSyncStep) | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u));
         bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != lut_adv(e) || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
     }
     return bad;

@@ -1,5 +1,5 @@
-"""The lanes of the synchronisation pass on the kernels' own tables (sync_span, sync_span_rst) against the plain lanes that
-take one symbol after the other from the tables of jpgd_lut.h, on the CPU: exact."""
+"""The lanes of the synchronisation and the write pass on the kernels' own tables (sync_span, write_span and their _rst forms)
+against the plain lanes that take one symbol after the other from the tables of jpgd_lut.h, on the CPU: exact."""
 import ctypes
 import os
 import subprocess
@@ -25,6 +25,7 @@ def lanes():
     lib = ctypes.CDLL(lib_path)
     vp, u32 = ctypes.c_void_p, ctypes.c_uint32
     lib.sync_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, u32, vp]
+    lib.write_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, ctypes.c_int, u32, u32, u32, vp]
     lib.sync_table_vs_lut.argtypes = [vp, vp, ctypes.c_int]
     return lib
 
@@ -42,6 +43,21 @@ def test_lanes_equal_the_plain_ones_from_any_state(lanes, sub, opt, q, shape, L,
     n = ctypes.c_uint32()
     assert lanes.sync_vs_plain(data.ctypes.data, data.size, L, 4000, 5, org, 3, ctypes.byref(n)) == 0
     assert n.value > 3000
+
+
+@pytest.mark.parametrize("sub,opt,q,shape,L,ri,org,total", [
+    ("420", False, 92, (137, 251), 128, 0, 0, 0), ("444", True, 75, (96, 120), 1024, 0, 4096, 0), ("gray", False, 30, (200, 64), 256, 0, 32, 100),
+    ("422", True, 98, (64, 80), 512, 0, 1 << 20, 0), ("444", False, 100, (64, 64), 2048, 0, 64, 0), ("420", True, 10, (160, 160), 128, 0, 0, 301),
+    ("420", True, 95, (96, 160), 256, 1, 0, 0), ("422", False, 60, (120, 96), 128, 3, 1 << 20, 0), ("gray", True, 90, (64, 200), 1024, 25, 96, 0),
+    ("444", True, 85, (96, 160), 128, 5, (1 << 32) - 512, 250)])
+@pytest.mark.parametrize("chain", [1, 0])
+def test_write_lanes_equal_the_plain_ones(lanes, sub, opt, q, shape, L, ri, org, total, chain):
+    """Stores in their order, unit, position, state, predictors and flags, on the true chain and from random states (where
+    symbols run past their unit and bits start no codeword); also where the image's units end inside a subsequence."""
+    data = encode_jpeg(small_image(21, shape[0], shape[1], sigma=14.0), q, sub, opt, ri).data
+    n = ctypes.c_uint32()
+    assert lanes.write_vs_plain(data.ctypes.data, data.size, L, 4000, chain, org, total, 3, ctypes.byref(n)) == 0
+    assert n.value > 200
 
 
 def test_tables_hold_what_the_first_ones_hold(lanes):
