@@ -250,6 +250,11 @@ using LdsBytes = const __attribute__((address_space(3))) uint8_t*;
 using LdsWords = const __attribute__((address_space(3))) uint32_t*;
 __device__ __forceinline__ uint32_t lds_at(const void* p) { return (uint32_t)(uintptr_t)(LdsBytes)p; }
 __device__ __forceinline__ uint32_t lds_word(uint32_t at) { return *(LdsWords)(uintptr_t)at; }
+typedef uint32_t lds_quad __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ SyncRow lds_row(uint32_t at) {
+    const lds_quad q = *(const __attribute__((address_space(3))) lds_quad*)(uintptr_t)at;
+    return SyncRow{q.x, q.y, q.z, q.w};
+}
 __device__ __forceinline__ uint32_t sync_ac_at(const ImgDesc& D) { return D.ndc * kSyncDcBytes; }
 template <bool WRITE>
 __device__ __forceinline__ void stage_tables(const Params& P, const ImgDesc& D, uint8_t* lds, uint32_t* dc_fill) {
@@ -295,14 +300,14 @@ __device__ __forceinline__ void stage_tables(const Params& P, const ImgDesc& D, 
 
 // rows: 8 entries of LDS, complete after the next barrier
 template <bool WRITE>
-__device__ __forceinline__ void stage_rows(const ImgDesc& D, SyncRow* rows, uint32_t tab) {
+__device__ __forceinline__ void stage_rows(const ImgDesc& D, SyncRow* rows, uint32_t tab) {  // (rows, too, by their bytes of LDS)
     const uint32_t u = threadIdx.x, un = u + 1u == D.upm ? 0u : u + 1u;
     if (u >= D.upm) return;
     const uint32_t comp = (D.sched_comp >> (4u * u)) & 15u, comp_next = (D.sched_comp >> (4u * un)) & 15u;
     {
         rows[u] = SyncRow{tab + sync_ac_at(D) + (((D.sched_ac >> (4u * u)) & 15u) - D.ndc) * kSyncAcBytes,
                           tab + ((D.sched_dc >> (4u * un)) & 15u) * kSyncDcBytes,
-                          WRITE ? (comp != comp_next ? 1u : 0u) : 1u << (15u * comp), un * (uint32_t)sizeof(SyncRow)};
+                          WRITE ? (comp != comp_next ? 1u : 0u) : 1u << (15u * comp), lds_at(rows) + un * (uint32_t)sizeof(SyncRow)};
     }
 }
 
@@ -897,6 +902,127 @@ __device__ __forceinline__ uint32_t coop_words(uint32_t* buf, uint32_t p, uint32
     return lds_at(buf + 1);
 }
 
+// sync_span as the kernels run it (jpgd_lane.h has the same in C++, which says what every value is; the host tests hold that
+// one to the plain lanes, the GPU's records are compared with the oracle's).
+// In assembly, because of what a wavefront on its own on a SIMD pays for (measured, cycles): a vector instruction 4, also
+// behind the one it depends on; a mask from a compare to a select 8 more, if nothing else stands between them; a scalar
+// instruction on a mask 16 more; a taken branch 20; a read from LDS 64.  The compiler's loop takes three scalar
+// instructions on fresh masks a step (a second symbol or none, unit complete or escape, lanes that are done), stalls for
+// two selects and branches once: 300 cycles for 46 vector instructions.  Here other work stands behind every compare,
+// lanes that are done leave through v_cmpx, one branch serves two steps, and whether a second symbol may be taken is a
+// threshold worked out in the step before.
+// Measured against the compiler's loop: 15360x8640 head 622 -> 573 us and tail 705 -> 661, eight calls of 1600x1200 160 ->
+// 149, 1001x753 83 -> 77, 3001x2003 with restart intervals 91 -> 89; a lane round of 4096x4096 (L = 1024) 33.5k -> 28.3k
+// cycles.
+// `ahead` is asked for when the window may have moved on and looked at a step later.  STAGED: big-endian words in LDS; else
+// the stream in memory, bytes swapped when the word is used.
+template <bool STAGED>
+__device__ __forceinline__ void sync_span_device(SyncLane& l, uint32_t limit, int64_t& dcacc, const uint32_t* words) {
+    const uint32_t stop = limit + kSyncBias, last_pair = stop - kSyncPairBits;
+    uint32_t pos = sync_at(l);
+    if (pos >= stop) return;
+    uint32_t threshold = pos < last_pair ? kSyncEsc : 0u, peek = sync_peek(l);
+    const uint32_t keep = kSyncStep, carry = kSyncEsc;
+    uint32_t t0, t1, t2, t3, t4, t5;
+    uint64_t ends, esc, done, all;
+    if (!STAGED) l.ahead = __builtin_bswap32(l.ahead);
+    const uint64_t base = (uint64_t)(uintptr_t)words;  // (the same in every lane)
+    const uint32_t base_hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)), base_lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+    const uint64_t from = ((uint64_t)base_hi << 32) | base_lo;
+#define JPGD_STEP(WAIT_ENTRY, WAIT_AHEAD, AHEAD, LOAD_AHEAD)                                              \
+    WAIT_ENTRY                                                                                             \
+    "v_add_u32_sdwa %[t0], %[S], %[e] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n" \
+    "v_and_b32_sdwa %[t1], %[second], %[e] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n" \
+    "v_cmp_lt_u32 vcc, %[t0], %[thr]\n"        /* one symbol completes nothing and is not late */          \
+    "v_bfe_u32 %[t2], %[e], 20, 4\n"           /* value bits of a DC symbol */                             \
+    "v_sub_u32 %[t3], 0, %[e]\n"                                                                           \
+    "v_cndmask_b32 %[t1], 0, %[t1], vcc\n"                                                                 \
+    "v_bfe_i32 %[t3], %[peek], %[t3], %[t2]\n" /* they, signed */                                          \
+    "v_add_u32 %[t0], %[t0], %[t1]\n"                                                                      \
+    "v_bfe_u32 %[t4], %[e], 6, 3\n"            /* escape: bits of the subtable's index */                  \
+    "v_and_b32 %[t1], 32, %[t0]\n"             /* the window moves on by a word */                         \
+    "v_cmp_lt_u32 %[ends], %[top], %[t0]\n"                                                                \
+    "v_cmp_ne_u32 vcc, 0, %[t1]\n"                                                                         \
+    "v_cmp_gt_i32 %[esc], 0, %[e]\n"                                                                       \
+    "v_not_b32 %[t5], %[t0]\n"                                                                             \
+    WAIT_AHEAD                                                                                             \
+    "v_cndmask_b32 %[hi], %[hi], %[lo], vcc\n"                                                             \
+    "v_cndmask_b32 %[lo], %[lo], " AHEAD ", vcc\n"                                                         \
+    "v_alignbit_b32 %[peek], %[hi], %[lo], %[t5]\n"                                                        \
+    "v_sub_u32 v59, 23, %[t4]\n"                                                                           \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "v_cndmask_b32 %[t5], 22, 23, %[ends]\n"                                                               \
+    "v_cndmask_b32 v60, v60, v61, %[ends]\n"   /* table of the next symbol */                              \
+    "v_lshrrev_b32 v61, 15, %[e]\n"                                                                        \
+    "v_lshrrev_b32 %[t5], %[t5], %[peek]\n"                                                                \
+    "v_bfe_u32 %[t4], %[peek], v59, %[t4]\n"                                                               \
+    "v_and_b32 v61, 0xfff8, v61\n"                                                                         \
+    "v_lshl_add_u32 v60, %[t5], 2, v60\n"                                                                  \
+    "v_lshl_add_u32 v61, %[t4], 2, v61\n"                                                                  \
+    "v_cndmask_b32 v60, v60, v61, %[esc]\n"                                                                \
+    "ds_read_b32 %[e], v60\n"                                                                              \
+    "v_add_u32 %[at], %[at], %[t1]\n"                                                                      \
+    "s_andn2_b64 %[done], %[ends], %[esc]\n"                                                               \
+    "v_lshrrev_b32 v60, 3, %[at]\n"                                                                        \
+    LOAD_AHEAD                                                                                             \
+    "v_cndmask_b32 %[row], %[row], v63, %[done]\n"                                                         \
+    "v_cndmask_b32 %[t4], v62, 0, %[esc]\n"                                                                \
+    "ds_read_b128 v[60:63], %[row]\n"                                                                      \
+    "v_cndmask_b32 %[t5], %[keep], 31, %[done]\n"                                                          \
+    "v_and_b32 %[S], %[t5], %[t0]\n"                                                                       \
+    "v_addc_co_u32 %[nb], vcc, 0, %[nb], %[done]\n"                                                        \
+    "v_lshlrev_b32 %[t2], %[t2], -1\n"                                                                     \
+    "v_ashrrev_i32 %[t1], 31, %[t3]\n"                                                                     \
+    "v_and_or_b32 %[pos], %[S], 31, %[at]\n"                                                               \
+    "v_xor_b32 %[t2], %[t2], %[t1]\n"                                                                      \
+    "v_cmp_lt_u32 vcc, %[pos], %[last]\n"                                                                  \
+    "v_add3_u32 %[t3], %[t3], %[t2], 1\n"      /* a DC symbol's value, else 0 */                           \
+    "v_mad_i64_i32 %[dc], %[done], %[t3], %[t4], %[dc]\n"                                                  \
+    "v_cndmask_b32 %[thr], 0, %[carry], vcc\n"                                                             \
+    "v_cmpx_lt_u32 vcc, %[pos], %[stop]\n"
+#define JPGD_SPAN_OPERANDS                                                                                 \
+    [S] "+&v"(l.S), [row] "+&v"(l.row), [e] "+&v"(l.e), [hi] "+&v"(l.hi), [lo] "+&v"(l.lo), [ahead] "+&v"(l.ahead), [at] "+&v"(l.at), \
+        [nb] "+&v"(l.nb), [dc] "+&v"(dcacc), [pos] "+&v"(pos), [thr] "+&v"(threshold), [peek] "+&v"(peek), [t0] "=&v"(t0),   \
+        [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [ends] "=&s"(ends), [esc] "=&s"(esc), \
+        [done] "=&s"(done), [all] "=&s"(all)                                                               \
+        : [stop] "v"(stop), [last] "v"(last_pair), [keep] "v"(keep), [carry] "v"(carry), [second] "s"(kSyncSecond), \
+          [top] "s"(kSyncEsc - 1u)
+#define JPGD_SPAN_CLOBBERS "vcc", "scc", "memory", "v59", "v60", "v61", "v62", "v63"
+    static_assert(sizeof(SyncRow) == 16 && kSyncDcK == 9u && kSyncAcK == 10u);
+    if constexpr (STAGED) {
+        asm volatile(
+            "s_mov_b64 %[all], exec\n"
+            "ds_read_b128 v[60:63], %[row]\n"
+            "1:\n"
+            // in the order they were asked for: entry, word, row
+            JPGD_STEP("s_waitcnt lgkmcnt(2)\n", "s_waitcnt lgkmcnt(1)\n", "%[ahead]", "ds_read_b32 %[ahead], v60\n")
+            JPGD_STEP("s_waitcnt lgkmcnt(2)\n", "s_waitcnt lgkmcnt(1)\n", "%[ahead]", "ds_read_b32 %[ahead], v60\n")
+            "s_cbranch_execnz 1b\n"
+            "s_mov_b64 exec, %[all]\n"
+            "s_waitcnt lgkmcnt(0)\n"
+            : JPGD_SPAN_OPERANDS
+            : JPGD_SPAN_CLOBBERS);
+    } else {
+        asm volatile(
+            "s_mov_b64 %[all], exec\n"
+            "ds_read_b128 v[60:63], %[row]\n"
+            "1:\n"
+            JPGD_STEP("s_waitcnt lgkmcnt(1)\n", "s_waitcnt vmcnt(0)\nv_perm_b32 %[ahead], %[ahead], %[ahead], %[swap]\n", "%[ahead]",
+                      "global_load_dword %[ahead], v60, %[words]\n")
+            JPGD_STEP("s_waitcnt lgkmcnt(1)\n", "s_waitcnt vmcnt(0)\nv_perm_b32 %[ahead], %[ahead], %[ahead], %[swap]\n", "%[ahead]",
+                      "global_load_dword %[ahead], v60, %[words]\n")
+            "s_cbranch_execnz 1b\n"
+            "s_mov_b64 exec, %[all]\n"
+            "s_waitcnt vmcnt(0) lgkmcnt(0)\n"
+            "v_perm_b32 %[ahead], %[ahead], %[ahead], %[swap]\n"
+            : JPGD_SPAN_OPERANDS, [words] "s"(from), [swap] "s"(0x00010203u)
+            : JPGD_SPAN_CLOBBERS);
+    }
+#undef JPGD_STEP
+#undef JPGD_SPAN_OPERANDS
+#undef JPGD_SPAN_CLOBBERS
+}
+
 // Part k of n of an image's coefficients is cleared by `lanes` lanes of a workgroup, this one being number `lane`.
 __device__ __forceinline__ void clear_coefficients(const Params& P, const ImgDesc& D, uint32_t k, uint32_t n, uint32_t lane, uint32_t lanes) {
     const uint32_t u0 = (uint32_t)((uint64_t)D.total_units * k / n), u1 = (uint32_t)((uint64_t)D.total_units * (k + 1u) / n);
@@ -991,7 +1117,8 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     const uint32_t org = (STAGED ? 8u * lds_at(strm) : 0u) - (first_word << 5);
     auto word = [&](uint32_t b) { return STAGED ? lds_word(b >> 3) : __builtin_bswap32(gwords[b >> 5]); };
     auto tab = [&](uint32_t k) { return lds_word(k); };
-    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
+    const uint32_t row0 = lds_at(rows_s);
+    auto rows = [&](uint32_t k) { return lds_row(k); };
     const uint32_t t = threadIdx.x;
     const bool valid = t >= t0 && t < t1;
     SyncLane l;
@@ -1003,10 +1130,19 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     // bit of the stream at which subsequence k of the workgroup starts
     auto start_of = [&](uint32_t k) { return (uint32_t)(base + (int32_t)k) << P.logL; };
     // chain and target as one word, and back
-    auto state_of = [&](uint32_t end) { return pack_state(sync_pos(l) - org - end, (l.S >> 9) & 63u, l.row / (uint32_t)sizeof(SyncRow)); };
+    auto state_of = [&](uint32_t end) { return pack_state(sync_pos(l) - org - end, (l.S >> 9) & 63u, (l.row - row0) / (uint32_t)sizeof(SyncRow)); };
     auto take_chain = [&](uint32_t m) {
         tt = m >> 16;
-        sync_start(l, start_of(tt) + state_prel(m) + org, state_u(m), state_z(m), D.upm, word, tab, rows);
+        sync_start(l, start_of(tt) + state_prel(m) + org, state_u(m), state_z(m), D.upm, row0, word, tab, rows);
+    };
+    auto span = [&](SyncLane& a, uint32_t to, int64_t& dc) { sync_span_device<STAGED>(a, to, dc, gwords); };
+    auto decode_rst = [&](SyncLane& a, uint32_t limit, int64_t& dc, uint32_t& crossed) {
+        sync_span_rst(a, limit + org, dc, crossed, org, [&](uint32_t p) { sync_start(a, p, 0u, 0u, D.upm, row0, word, tab, rows); },
+                      [&](uint32_t to) { span(a, to, dc); }, bword);
+    };
+    auto decode = [&](SyncLane& a, uint32_t limit, int64_t& dc, uint32_t& crossed) {
+        if (restart) decode_rst(a, limit, dc, crossed);
+        else span(a, limit + org, dc);
     };
     auto put_record = [&](uint32_t k, uint32_t x, uint32_t units, uint32_t crossed, int64_t dc) {
         rec[k] = x | (units << 16) | (crossed << 31);
@@ -1026,11 +1162,10 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
         waves_used = (n + 63u) >> 6; if (waves_used == 0u) waves_used = 1u;
     } else if (valid) {
         const uint32_t limit = start_of(t + 1u);
-        sync_start(l, start_of(t) + org, 0u, 0u, D.upm, word, tab, rows);
+        sync_start(l, start_of(t) + org, 0u, 0u, D.upm, row0, word, tab, rows);
         uint32_t crossed = 0u;
         int64_t dcacc = 0;
-        if (restart) sync_span_rst(l, limit + org, dcacc, crossed, org, D.upm, word, tab, rows, bword);
-        else sync_span(l, limit + org, dcacc, word, tab, rows);
+        decode(l, limit, dcacc, crossed);
         put_record(t, state_of(limit), l.nb, crossed, dcacc);
         active = t + 1u < t1;
     }
@@ -1090,8 +1225,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
             int64_t dcacc = 0;
             const uint32_t limit = start_of(tt + 1u);
             uint32_t crossed = 0u;
-            if (restart) sync_span_rst(l, limit + org, dcacc, crossed, org, D.upm, word, tab, rows, bword);
-            else sync_span(l, limit + org, dcacc, word, tab, rows);
+            decode(l, limit, dcacc, crossed);
             const uint32_t x = state_of(limit);
             const bool synced = x == (rec[tt] & 0xFFFFu);
             put_record(tt, x, l.nb, crossed, dcacc);
@@ -1146,9 +1280,9 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
                     if (lane == 0u) {
                         SyncLane cl;
                         cl.nb = 0u;
-                        sync_start(cl, cp + org, cu, cz, D.upm, word, tab, rows);
-                        sync_span_rst(cl, limit + org, cdc, crossed, org, D.upm, word, tab, rows, bword);
-                        cp = sync_pos(cl) - org; cu = cl.row / (uint32_t)sizeof(SyncRow); cz = (cl.S >> 9) & 63u; cnb = cl.nb;
+                        sync_start(cl, cp + org, cu, cz, D.upm, row0, word, tab, rows);
+                        decode_rst(cl, limit, cdc, crossed);
+                        cp = sync_pos(cl) - org; cu = (cl.row - row0) / (uint32_t)sizeof(SyncRow); cz = (cl.S >> 9) & 63u; cnb = cl.nb;
                     }
                     cp = __builtin_amdgcn_readfirstlane(cp);
                     cu = __builtin_amdgcn_readfirstlane(cu);
@@ -1247,7 +1381,8 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     auto fetch = [&](uint32_t w) { return __builtin_bswap32(words[w]); };
     auto word = [&](uint32_t b) { return __builtin_bswap32(words[b >> 5]); };
     auto tab = [&](uint32_t k) { return lds_word(k); };
-    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
+    const uint32_t row0 = lds_at(rows_s);
+    auto rows = [&](uint32_t k) { return lds_row(k); };
     // Usually a handful of boundaries in a whole image have something to decode, and the kernel lasts as long as
     // the slowest of them.  With few in this workgroup, each is walked by the whole wavefront, one after the other
     // (same results as the lane's loop below; the wavefront's decoder does not know restart intervals).
@@ -1296,17 +1431,19 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     const uint32_t* bmap_img = P.bmap + D.bmap_off;
     auto bword = [&](uint32_t k) { return bmap_img[k]; };
     SyncLane l;
-    sync_start(l, (g << P.logL) + state_prel(x0), state_u(x0), state_z(x0), D.upm, word, tab, rows);
+    sync_start(l, (g << P.logL) + state_prel(x0), state_u(x0), state_z(x0), D.upm, row0, word, tab, rows);
     bool first = true;
     for (;;) {
         l.nb = 0u;
         int64_t dcacc = 0;
         const uint32_t limit = (g + 1u) << P.logL;
         uint32_t crossed = 0u;
-        if (D.restart) sync_span_rst(l, limit, dcacc, crossed, 0u, D.upm, word, tab, rows, bword);
-        else sync_span(l, limit, dcacc, word, tab, rows);
+        auto span = [&](uint32_t to) { sync_span_device<false>(l, to, dcacc, words); };
+        if (D.restart)
+            sync_span_rst(l, limit, dcacc, crossed, 0u, [&](uint32_t p) { sync_start(l, p, 0u, 0u, D.upm, row0, word, tab, rows); }, span, bword);
+        else span(limit);
         SInfo r;
-        r.x = pack_state(sync_pos(l) - limit, (l.S >> 9) & 63u, l.row / (uint32_t)sizeof(SyncRow));
+        r.x = pack_state(sync_pos(l) - limit, (l.S >> 9) & 63u, (l.row - row0) / (uint32_t)sizeof(SyncRow));
         r.y = l.nb | (crossed << 31);
         r.z = pack_dc01(dcacc);
         r.w = pack_dc2(dcacc);
@@ -1515,7 +1652,8 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const uint32_t org = (STAGED ? 8u * lds_at(strm) : 0u) - (first_word << 5);
     auto word = [&](uint32_t b) { return STAGED ? lds_word(b >> 3) : __builtin_bswap32(gwords[b >> 5]); };
     auto tab = [&](uint32_t k) { return lds_word(k); };
-    auto rows = [&](uint32_t k) { return *reinterpret_cast<const SyncRow*>(reinterpret_cast<const uint8_t*>(rows_s) + k); };
+    const uint32_t row0 = lds_at(rows_s);
+    auto rows = [&](uint32_t k) { return lds_row(k); };
     int16_t* coef = P.coef + D.coef_off;
     // Coefficients leave the lane four at a time.  Every value as a store of its own makes 64 two-byte requests per
     // dense data unit, and the number of requests, not of bytes, is what the memory system charges for: the values
@@ -1562,7 +1700,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     l.seen = 0u;
     const uint32_t u_in = state_u(xprev);
     write_predictors(l, (D.sched_comp >> (4u * u_in)) & 15u, (int32_t)(int16_t)pred0, (int32_t)(int16_t)pred1, (int32_t)(int16_t)pred2);
-    auto start = [&]() { write_start(l, (i << P.logL) + state_prel(xprev) + org, u_in, state_z(xprev), D.upm, word, tab, rows); };
+    auto start = [&]() { write_start(l, (i << P.logL) + state_prel(xprev) + org, u_in, state_z(xprev), D.upm, row0, word, tab, rows); };
     uint32_t flags = 0u;
     const uint32_t total = D.total_units;
     // unit modulo the 1, 3, 4 or 6 units of an MCU
@@ -1594,7 +1732,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         if (!valid) return;
     } else if (unit < total) {
         start();
-        if (restart) write_span_rst(l, limit + org, total, D.restart * D.upm, org, D.upm, word, tab, rows, store, bword, &flags);
+        if (restart) write_span_rst(l, limit + org, total, D.restart * D.upm, org, D.upm, row0, word, tab, rows, store, bword, &flags);
         else write_span(l, limit + org, total, word, tab, rows, store);
     }
     // (in a workgroup with nothing to decode the lane stays where it was: behind the last unit)
@@ -1609,7 +1747,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     // every lane checks the chain: unless the image is complete it must end in the recorded state
     if (unit < total) {
         const uint32_t p = sync_pos(l.s) - org;
-        if (p < limit || pack_state(p - limit, z_out, l.s.row / (uint32_t)sizeof(SyncRow)) != mine.x) flags |= kStMismatch;
+        if (p < limit || pack_state(p - limit, z_out, (l.s.row - row0) / (uint32_t)sizeof(SyncRow)) != mine.x) flags |= kStMismatch;
         if (i == nsub - 1u) flags |= kStShort;
     }
     if (flags) atomicOr(&P.status->flags, flags);

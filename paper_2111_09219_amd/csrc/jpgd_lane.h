@@ -405,7 +405,7 @@ struct alignas(16) SyncRow {
 // 9..14.
 struct SyncLane {
     uint32_t S;
-    uint32_t row;        // byte of the current unit's row
+    uint32_t row;        // byte of the current unit's row, in the bytes of the Row functor
     uint32_t e;          // entry of the symbol that comes next, already asked for
     uint32_t hi, lo, ahead;
     uint32_t at;         // bit at which `ahead` starts, in the bits of the Word functor
@@ -427,18 +427,18 @@ JPGD_HD uint32_t sync_pos(const SyncLane& l) { return sync_at(l) - kSyncBias; }
 JPGD_HD uint32_t sync_peek(const SyncLane& l) { return funnel(l.hi, l.lo, ~l.S); }
 
 // word(b): the stream word that starts at bit b (a multiple of 32); tab(k): 32-bit entry at byte k of the tables; rows(k):
-// the SyncRow at byte k of the rows, upm of them.  p: bit to start at, in the bits of `word`; z, u: zig-zag index and data
-// unit.
+// the SyncRow at byte k; the rows of the upm units lie from byte row0 on.  p: bit to start at, in the bits of `word`; z, u:
+// zig-zag index and data unit.
 template <class Word, class Tab, class Row>
-JPGD_HD void sync_start(SyncLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, Word word, Tab tab, Row rows) {
+JPGD_HD void sync_start(SyncLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, uint32_t row0, Word word, Tab tab, Row rows) {
     const uint32_t w = (p + 31u) & ~31u;
     l.hi = (p & 31u) ? word(w - 32u) : 0u;  // (at the first bit of a word the offset is 32: nothing of it is used)
     l.lo = word(w);
     l.ahead = word(w + 32u);
     l.at = w + 32u;
     l.S = ((p + 31u) & 31u) | (z << 9);
-    l.row = u * (uint32_t)sizeof(SyncRow);
-    const uint32_t dc = rows(((u ? u : upm) - 1u) * (uint32_t)sizeof(SyncRow)).dc_next;
+    l.row = row0 + u * (uint32_t)sizeof(SyncRow);
+    const uint32_t dc = rows(row0 + ((u ? u : upm) - 1u) * (uint32_t)sizeof(SyncRow)).dc_next;
     const uint32_t peek = sync_peek(l);
     l.e = tab(z == 0u ? dc + ((peek >> (32u - kSyncDcK)) << 2) : rows(l.row).ac + ((peek >> (32u - kSyncAcK)) << 2));
 }
@@ -524,8 +524,8 @@ JPGD_HD void write_predictors(WriteLane& l, uint32_t comp, int32_t d0, int32_t d
     l.p2 = comp == 0u ? d2 : comp == 1u ? d0 : d1;
 }
 template <class Word, class Tab, class Row>
-JPGD_HD void write_start(WriteLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, Word word, Tab tab, Row rows) {
-    sync_start(l.s, p, u, z, upm, word, tab, rows);
+JPGD_HD void write_start(WriteLane& l, uint32_t p, uint32_t u, uint32_t z, uint32_t upm, uint32_t row0, Word word, Tab tab, Row rows) {
+    sync_start(l.s, p, u, z, upm, row0, word, tab, rows);
     l.row = rows(l.s.row);
     l.peek = sync_peek(l.s);
 }
@@ -717,10 +717,11 @@ JPGD_HD void decode_span_sync_rst(Lane& l, BitWin& w, uint32_t limit, int64_t& d
 }
 
 // The same over a stream with restart intervals (rules: decode_span_sync_rst below, which this follows step by step).
-// Boundaries are positions in the image's stream: a position there plus `org` is a bit of `word`.
-template <class Word, class Tab, class Row, class BWord>
-JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t& crossed, uint32_t org, uint32_t upm, Word word,
-                           Tab tab, Row rows, BWord bword) {
+// Boundaries are positions in the image's stream: a position there plus `org` is a bit of `word`.  start(p): sync_start at
+// bit p with u = z = 0; span(limit): sync_span.
+template <class Start, class Span, class BWord>
+JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t& crossed, uint32_t org, Start start, Span span,
+                           BWord bword) {
     const uint32_t end = limit - org;
     uint32_t from = sync_pos(l) - org;
     for (;;) {
@@ -728,7 +729,7 @@ JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t
         // a symbol that starts 40 bits before B ends more than 7 bits before it
         uint32_t calm = end;
         if (B != kNoBoundary && B < end + 39u) calm = B >= 39u ? B - 39u : 0u;
-        if (from < calm) sync_span(l, calm + org, dcacc, word, tab, rows);
+        if (from < calm) span(calm + org);
         if (B == kNoBoundary) break;
         uint32_t pos = sync_pos(l) - org;
         bool next_interval = false;
@@ -740,11 +741,11 @@ JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t
                 next_interval = true;
                 break;
             }
-            sync_span(l, pos + org + 1u, dcacc, word, tab, rows);  // one symbol
+            span(pos + org + 1u);  // one symbol
             pos = sync_pos(l) - org;
             const uint32_t r = B - pos;
             if (pos >= B || (r <= 7u && (~sync_peek(l) >> (32u - r)) == 0u)) {
-                sync_start(l, B + org, 0u, 0u, upm, word, tab, rows);
+                start(B + org);
                 pos = B;
             }
         }
@@ -756,7 +757,7 @@ JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t
 // sync_span_rst; *flags: kStInvalid where an interval starts at another unit than it should.
 template <class Word, class Tab, class Row, class Store, class BWord>
 JPGD_HD void write_span_rst(WriteLane& l, uint32_t limit, uint32_t total_units, uint32_t units_per_interval, uint32_t org,
-                            uint32_t upm, Word word, Tab tab, Row rows, Store store, BWord bword, uint32_t* flags) {
+                            uint32_t upm, uint32_t row0, Word word, Tab tab, Row rows, Store store, BWord bword, uint32_t* flags) {
     const uint32_t end = limit - org;
     auto calm_until = [&](uint32_t B) { return B != kNoBoundary && B < end + 39u ? (B >= 39u ? B - 39u : 0u) : end; };
     uint32_t pos = sync_pos(l.s) - org;
@@ -777,7 +778,7 @@ JPGD_HD void write_span_rst(WriteLane& l, uint32_t limit, uint32_t total_units, 
         write_step(l, word, tab, rows, store);
         pos = sync_pos(l.s) - org;
         if (near && (pos >= B || (B - pos <= 7u && (~l.peek >> (32u - (B - pos))) == 0u))) {
-            write_start(l, B + org, 0u, 0u, upm, word, tab, rows);
+            write_start(l, B + org, 0u, 0u, upm, row0, word, tab, rows);
             pos = B;
         }
     }

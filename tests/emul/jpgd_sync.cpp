@@ -78,7 +78,7 @@ struct Lut {
     }
 };
 
-constexpr uint32_t kBase = 176;   // where the tables start
+constexpr uint32_t kBase = 176, kRow0 = 48;   // where the tables and the rows start
 
 int open_scan(const uint8_t* file, size_t len, Scan& S) {
     const int rc = jpgd_parse(file, len, &S.in);
@@ -105,7 +105,7 @@ int open_scan(const uint8_t* file, size_t len, Scan& S) {
         S.rows[k] = make_unit_row(k, u, sched_dc, sched_ac, sched_comp);
         S.srows[k] = SyncRow{kBase + S.t.ndc * kSyncDcBytes + (((sched_ac >> (4 * k)) & 15) - S.t.ndc) * kSyncAcBytes,
                              kBase + ((sched_dc >> (4 * ((k + 1) % u))) & 15) * kSyncDcBytes, S.rows[k].dcmul,
-                             S.rows[k].next * (uint32_t)sizeof(SyncRow)};
+                             kRow0 + S.rows[k].next * (uint32_t)sizeof(SyncRow)};
         S.wrows[k] = S.srows[k];
         S.wrows[k].dcmul = ((sched_comp >> (4 * k)) & 15) != ((sched_comp >> (4 * ((k + 1) % u))) & 15) ? 1u : 0u;
     }
@@ -144,7 +144,7 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
         return fetch((b - org) >> 5);
     };
     auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.sync.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { if (k % sizeof(SyncRow) || k / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.srows[k / sizeof(SyncRow)]; };
+    auto rows = [&](uint32_t k) { if (k < kRow0 || k % sizeof(SyncRow) || (k - kRow0) / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
     auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
     Syntax sx;
     sx.rows = S.rows;
@@ -166,7 +166,7 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
         SyncLane b;
         win_init(w, a.p, a.p >> 5, fetch);
         prime(a, w, sx, lut);
-        sync_start(b, a.p + org, a.u, a.z, sx.upm, word, tab, rows);
+        sync_start(b, a.p + org, a.u, a.z, sx.upm, kRow0, word, tab, rows);
         for (uint32_t i = i0; i < i0 + spans && i < nsub; ++i) {
             const uint32_t limit = (i + 1) * L;
             int64_t da = 0, db = 0;
@@ -174,13 +174,14 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
             a.nb = b.nb = 0;
             if (restart) {
                 decode_span_sync_rst(a, w, limit, da, ca, sx, fetch, lut, bword);
-                sync_span_rst(b, limit + org, db, cb, org, sx.upm, word, tab, rows, bword);
+                sync_span_rst(b, limit + org, db, cb, org, [&](uint32_t p) { sync_start(b, p, 0u, 0u, sx.upm, kRow0, word, tab, rows); },
+                              [&](uint32_t to) { sync_span(b, to, db, word, tab, rows); }, bword);
             } else {
                 decode_span_sync(a, w, limit, da, sx, fetch, lut);
                 sync_span(b, limit + org, db, word, tab, rows);
             }
             ++*compared;
-            const uint32_t u = b.row / (uint32_t)sizeof(SyncRow), z = (b.S >> 9) & 63u;
+            const uint32_t u = (b.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.S >> 9) & 63u;
             if (sync_pos(b) - org != a.p || u != a.u || z != a.z || a.nb != b.nb || (da != db && !no_dc_code) || ca != cb) { ++bad; break; }
         }
     }
@@ -203,7 +204,7 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
         return fetch((b - org) >> 5);
     };
     auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.write.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { if (k % sizeof(SyncRow) || k / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.wrows[k / sizeof(SyncRow)]; };
+    auto rows = [&](uint32_t k) { if (k < kRow0 || k % sizeof(SyncRow) || (k - kRow0) / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.wrows[(k - kRow0) / sizeof(SyncRow)]; };
     auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
     Syntax sx;
     sx.rows = S.rows;
@@ -248,11 +249,11 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             b.seen = 0;
             auto store_b = [&](uint32_t u, uint32_t at, int16_t v) { if (at > 63u) __builtin_trap(); sb.push_back({(uint64_t)u * 64 + at, v}); };
             write_predictors(b, (S.sched_comp >> (4 * in.u)) & 15, d[0], d[1], d[2]);
-            write_start(b, in.p + org, in.u, in.z, upm, word, tab, rows);
-            if (restart) write_span_rst(b, limit + org, total, upi, org, upm, word, tab, rows, store_b, bword, &fb);
+            write_start(b, in.p + org, in.u, in.z, upm, kRow0, word, tab, rows);
+            if (restart) write_span_rst(b, limit + org, total, upi, org, upm, kRow0, word, tab, rows, store_b, bword, &fb);
             else write_span(b, limit + org, total, word, tab, rows, store_b);
             if (b.seen & kWriteBad) fb |= kStInvalid;
-            const uint32_t u = b.s.row / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
+            const uint32_t u = (b.s.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
             WriteLane want = b;
             write_predictors(want, (S.sched_comp >> (4 * a.u)) & 15, p0, p1, p2);
             if (sa != sb || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
