@@ -1023,6 +1023,193 @@ __device__ __forceinline__ void sync_span_device(SyncLane& l, uint32_t limit, in
 #undef JPGD_SPAN_CLOBBERS
 }
 
+// write_span (jpgd_lane.h, which says what every value is) as the kernels run it where the stream lies in LDS and the image
+// has no restart intervals; in assembly for the reasons given at sync_span_device.  Entry and first predictor change places
+// from one step to the next, so that neither has to be copied; lanes without a value are switched off for the store instead of
+// branched around.  Calls with the compiler's loop / with this one (us, each against the same older tree beside it): 24 images
+// of 2047x1535 419 / 405, batch of 256 395 / 375, 15360x8640 1877 / 1750, eight of 1600x1200 1116 / 1060, 256x256 gray
+// 56.6 / 53.2.
+// Memory: chunk_value, from `out` on, which is where slot0 goes.  A first loop runs until no lane is left in a chunk that it
+// shares with the lane before; the second need not look for it.
+// Tile: every value goes to its place in LDS on its own.  first: place of slot0 there, tile_n: slots there are room for.
+// l.unit in, l.s, l.unit and l.seen out.
+template <bool TILE>
+__device__ __forceinline__ void write_span_device(WriteLane& l, uint32_t limit, uint32_t total_units, uint32_t slot0, uint32_t first,
+                                                  uint32_t tile_n, const int16_t* out, WriteChunk& c) {
+    const uint32_t stop = limit + kSyncBias;
+    uint32_t pos = sync_at(l.s);
+    if (pos >= stop || l.unit >= total_units) return;
+    // slot of a symbol: the unit's first one, less one, from slot0 on (below zero in a unit that began before it), plus the
+    // symbol's last zig-zag index plus one
+    const uint32_t unit0 = l.unit;
+    uint32_t unit = l.unit * 64u - slot0 - 1u;
+    const uint32_t unit_end = min(total_units * 64u - slot0 - 1u, 0x7FFFFFFFu), unit_now = unit;
+    const uint32_t keep = kSyncStep;
+    uint32_t t0, t1, t2, t3, t4, t5, e2 = 0u, q0 = 0u;
+    uint64_t ends, esc, done, other, run, all;
+    const uint64_t base = (uint64_t)(uintptr_t)out;  // (the same in every lane)
+    const uint32_t base_hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)), base_lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+    const uint64_t to = ((uint64_t)base_hi << 32) | base_lo;
+    static_assert(sizeof(SyncRow) == 16 && kSyncDcK == 9u && kSyncAcK == 10u && kWriteValue == 0x40000000 && kWriteDc == 0x60000000);
+#define JPGD_STEP(E, NEXT, P, PNEXT, W1, W2, W3, STORE)                                                    \
+    "s_waitcnt lgkmcnt(" W1 ")\n"              /* the entry */                                             \
+    "v_add_u32_sdwa %[t0], %[S], " E " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n" \
+    "v_bfe_u32 %[t2], " E ", 20, 4\n"                                                                      \
+    "v_sub_u32 %[t3], 0, " E "\n"                                                                          \
+    "v_and_b32 %[t1], 32, %[t0]\n"                                                                         \
+    "v_bfe_i32 %[t3], %[peek], %[t3], %[t2]\n" /* value bits, signed */                                    \
+    "v_cmp_ne_u32 vcc, 0, %[t1]\n"                                                                         \
+    "v_cmp_lt_u32 %[ends], %[top], %[t0]\n"                                                                \
+    "v_cmp_gt_i32 %[esc], 0, " E "\n"                                                                      \
+    "v_not_b32 %[t5], %[t0]\n"                                                                             \
+    "v_bfe_u32 %[t4], " E ", 6, 3\n"                                                                       \
+    "s_waitcnt lgkmcnt(" W2 ")\n"              /* the word */                                              \
+    "v_cndmask_b32 %[hi], %[hi], %[lo], vcc\n"                                                             \
+    "v_cndmask_b32 %[lo], %[lo], %[ahead], vcc\n"                                                          \
+    "v_alignbit_b32 %[peek], %[hi], %[lo], %[t5]\n"                                                        \
+    "v_sub_u32 v59, 23, %[t4]\n"                                                                           \
+    "s_waitcnt lgkmcnt(" W3 ")\n"              /* the row */                                               \
+    "v_cndmask_b32 %[t5], 22, 23, %[ends]\n"                                                               \
+    "v_cndmask_b32 v60, v60, v61, %[ends]\n"                                                               \
+    "v_lshrrev_b32 v61, 15, " E "\n"                                                                       \
+    "v_lshrrev_b32 %[t5], %[t5], %[peek]\n"                                                                \
+    "v_bfe_u32 %[t4], %[peek], v59, %[t4]\n"                                                               \
+    "v_and_b32 v61, 0xfff8, v61\n"                                                                         \
+    "v_lshl_add_u32 v60, %[t5], 2, v60\n"                                                                  \
+    "v_lshl_add_u32 v61, %[t4], 2, v61\n"                                                                  \
+    "v_cndmask_b32 v60, v60, v61, %[esc]\n"                                                                \
+    "ds_read_b32 " NEXT ", v60\n"                                                                          \
+    "v_add_u32 %[at], %[at], %[t1]\n"                                                                      \
+    "s_andn2_b64 %[done], %[ends], %[esc]\n"                                                               \
+    "v_lshrrev_b32 v60, 3, %[at]\n"                                                                        \
+    "ds_read_b32 %[ahead], v60\n"                                                                          \
+    "v_cndmask_b32 %[row], %[row], v63, %[done]\n"                                                         \
+    "v_cmp_ne_u32 %[other], 0, v62\n"                                                                      \
+    "ds_read_b128 v[60:63], %[row]\n"                                                                      \
+    "v_cndmask_b32 %[t5], %[keep], 31, %[done]\n"                                                          \
+    "v_lshlrev_b32 %[t2], %[t2], -1\n"                                                                     \
+    "v_ashrrev_i32 v59, 31, %[t3]\n"                                                                       \
+    "v_and_b32 %[S], %[t5], %[t0]\n"                                                                       \
+    "v_xor_b32 %[t2], %[t2], v59\n"                                                                        \
+    "s_and_b64 %[other], %[other], %[done]\n" /* the next unit is another component's */                   \
+    "v_cmp_le_i32 vcc, 0x60000000, " E "\n"   /* a DC value */                                             \
+    "v_add3_u32 %[t3], %[t3], %[t2], 1\n"     /* the value */                                              \
+    "v_lshrrev_b32 %[t5], 9, %[t0]\n"                                                                      \
+    "v_add_u32 %[t4], " P ", %[t3]\n"                                                                      \
+    "v_add_u32 %[t5], %[unit], %[t5]\n"       /* its slot */                                               \
+    "v_cndmask_b32_sdwa v58, %[t3], %[t4], vcc dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n" \
+    "v_cndmask_b32 %[t4], " P ", %[t4], vcc\n"                                                             \
+    "v_cndmask_b32 %[t1], 0, 64, %[done]\n"                                                                \
+    "v_add_u32 %[unit], %[unit], %[t1]\n"                                                                  \
+    "v_add_u32 %[t1], %[late], %[t0]\n"                                                                    \
+    "v_cndmask_b32 " PNEXT ", %[t4], %[p1], %[other]\n"                                                    \
+    "v_cndmask_b32 %[p1], %[p1], %[p2], %[other]\n"                                                        \
+    "v_cndmask_b32 %[p2], %[p2], %[t4], %[other]\n"                                                        \
+    "v_and_or_b32 %[seen], " E ", %[t1], %[seen]\n"                                                        \
+    "v_and_or_b32 %[pos], %[S], 31, %[at]\n"                                                               \
+    STORE(E)                                                                                               \
+    "s_mov_b64 exec, %[run]\n"                                                                             \
+    "v_cmpx_lt_i32 vcc, %[unit], %[unit_end]\n"                                                            \
+    "v_cmpx_lt_u32 %[run], %[pos], %[stop]\n"
+// (lanes that have no value are switched off)
+#define JPGD_TO_TILE(E)                                                                                    \
+    "v_lshl_add_u32 %[t1], %[t5], 1, %[first]\n"                                                           \
+    "v_cmpx_le_i32 vcc, 0x40000000, " E "\n"                                                               \
+    "v_cmpx_gt_u32 vcc, %[room], %[t5]\n"                                                                  \
+    "v_cmpx_gt_u32 vcc, %[beyond], %[t0]\n"                                                                \
+    "ds_write_b16 %[t1], v58\n"
+// (done: lanes with a value, those among them that move on to another chunk store the one they leave, or keep it)
+#define JPGD_CHUNK(E, FIRST)                                                                               \
+    "v_cmpx_le_i32 vcc, 0x40000000, " E "\n"                                                               \
+    "v_lshlrev_b32 %[t4], 4, %[t5]\n"                                                                      \
+    "v_cmpx_gt_u32 %[done], %[beyond], %[t0]\n"                                                            \
+    "v_mov_b32 v59, 0\n"                                                                                   \
+    "v_and_b32 %[t5], -4, %[t5]\n"                                                                         \
+    "v_lshlrev_b32 %[t1], 1, %[cur]\n"                                                                     \
+    "v_lshlrev_b64 v[58:59], %[t4], v[58:59]\n"                                                            \
+    "v_cmpx_ne_u32 %[other], %[t5], %[cur]\n"                                                              \
+    FIRST                                                                                                  \
+    "global_store_dwordx2 %[t1], v[56:57], %[to]\n"                                                        \
+    "s_mov_b64 exec, %[other]\n"                                                                           \
+    "v_mov_b32 %[cur], %[t5]\n"                                                                            \
+    "v_mov_b32 v56, 0\n"                                                                                   \
+    "v_mov_b32 v57, 0\n"                                                                                   \
+    "s_mov_b64 exec, %[done]\n"                                                                            \
+    "v_or_b32 v56, v56, v58\n"                                                                             \
+    "v_or_b32 v57, v57, v59\n"
+#define JPGD_TO_MEMORY(E) JPGD_CHUNK(E, "")
+#define JPGD_TO_MEMORY_FIRST(E)                                                                            \
+    JPGD_CHUNK(E, "v_cmp_ne_u32 vcc, %[cur], %[shared]\n"                                                  \
+                  "s_nop 1\n"                                                                              \
+                  "v_cndmask_b32 %[f0], v56, %[f0], vcc\n"                                                 \
+                  "v_cndmask_b32 %[f1], v57, %[f1], vcc\n"                                                 \
+                  "v_cmpx_ne_u32 vcc, %[cur], %[shared]\n")
+#define JPGD_WRITE_OPERANDS                                                                                \
+    [S] "+&v"(l.s.S), [row] "+&v"(l.s.row), [e] "+&v"(l.s.e), [e2] "+&v"(e2), [hi] "+&v"(l.s.hi), [lo] "+&v"(l.s.lo),     \
+        [ahead] "+&v"(l.s.ahead), [at] "+&v"(l.s.at), [peek] "+&v"(l.peek), [unit] "+&v"(unit), [p0] "+&v"(l.p0),         \
+        [q0] "+&v"(q0), [p1] "+&v"(l.p1), [p2] "+&v"(l.p2), [seen] "+&v"(l.seen), [pos] "+&v"(pos), [t0] "=&v"(t0),       \
+        [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [t4] "=&v"(t4), [t5] "=&v"(t5), [ends] "=&s"(ends),               \
+        [esc] "=&s"(esc), [done] "=&s"(done), [other] "=&s"(other), [run] "=&s"(run), [all] "=&s"(all)
+#define JPGD_WRITE_INPUTS                                                                                  \
+    [stop] "v"(stop), [keep] "v"(keep), [unit_end] "v"(unit_end), [top] "s"(kSyncEsc - 1u),           \
+        [beyond] "s"(65u << 9), [late] "s"(kWriteNoCode + kWriteInside - (65u << 9))
+#define JPGD_WRITE_CLOBBERS "vcc", "scc", "memory", "v58", "v59", "v60", "v61", "v62", "v63"
+    if constexpr (TILE) {
+        // in the order they were asked for: entry, word, row, and the store of the step before
+        asm volatile(
+            "s_mov_b64 %[all], exec\n"
+            "s_mov_b64 %[run], exec\n"
+            "ds_read_b128 v[60:63], %[row]\n"
+            "s_waitcnt lgkmcnt(0)\n"
+            "1:\n"
+            JPGD_STEP("%[e]", "%[e2]", "%[p0]", "%[q0]", "3", "2", "1", JPGD_TO_TILE)
+            JPGD_STEP("%[e2]", "%[e]", "%[q0]", "%[p0]", "3", "2", "1", JPGD_TO_TILE)
+            "s_cbranch_execnz 1b\n"
+            "s_mov_b64 exec, %[all]\n"
+            "s_waitcnt lgkmcnt(0)\n"
+            : JPGD_WRITE_OPERANDS
+            : JPGD_WRITE_INPUTS, [first] "v"(first), [room] "v"(tile_n)
+            : JPGD_WRITE_CLOBBERS);
+    } else {
+        uint32_t a0 = (uint32_t)c.acc, a1 = (uint32_t)(c.acc >> 32), f0 = (uint32_t)c.first, f1 = (uint32_t)(c.first >> 32);
+        asm volatile(
+            "s_mov_b64 %[all], exec\n"
+            "s_mov_b64 %[run], exec\n"
+            "v_mov_b32 v56, %[a0]\n"
+            "v_mov_b32 v57, %[a1]\n"
+            "ds_read_b128 v[60:63], %[row]\n"
+            "1:\n"
+            JPGD_STEP("%[e]", "%[e2]", "%[p0]", "%[q0]", "2", "1", "0", JPGD_TO_MEMORY_FIRST)
+            JPGD_STEP("%[e2]", "%[e]", "%[q0]", "%[p0]", "2", "1", "0", JPGD_TO_MEMORY_FIRST)
+            "v_cmp_eq_u32 vcc, %[cur], %[shared]\n"   /* (none where no lane is left) */
+            "s_cbranch_vccnz 1b\n"
+            "s_cbranch_execz 3f\n"
+            "2:\n"
+            JPGD_STEP("%[e]", "%[e2]", "%[p0]", "%[q0]", "2", "1", "0", JPGD_TO_MEMORY)
+            JPGD_STEP("%[e2]", "%[e]", "%[q0]", "%[p0]", "2", "1", "0", JPGD_TO_MEMORY)
+            "s_cbranch_execnz 2b\n"
+            "3:\n"
+            "s_mov_b64 exec, %[all]\n"
+            "v_mov_b32 %[a0], v56\n"
+            "v_mov_b32 %[a1], v57\n"
+            "s_waitcnt lgkmcnt(0)\n"
+            : JPGD_WRITE_OPERANDS, [cur] "+&v"(c.cur), [a0] "+&v"(a0), [a1] "+&v"(a1), [f0] "+&v"(f0), [f1] "+&v"(f1)
+            : JPGD_WRITE_INPUTS, [to] "s"(to), [shared] "v"(c.shared)
+            : JPGD_WRITE_CLOBBERS, "v56", "v57");
+        c.acc = ((uint64_t)a1 << 32) | a0;
+        c.first = ((uint64_t)f1 << 32) | f0;
+    }
+    l.unit = unit0 + ((unit - unit_now) >> 6);
+#undef JPGD_STEP
+#undef JPGD_TO_TILE
+#undef JPGD_CHUNK
+#undef JPGD_TO_MEMORY
+#undef JPGD_TO_MEMORY_FIRST
+#undef JPGD_WRITE_OPERANDS
+#undef JPGD_WRITE_INPUTS
+#undef JPGD_WRITE_CLOBBERS
+}
+
 // Part k of n of an image's coefficients is cleared by `lanes` lanes of a workgroup, this one being number `lane`.
 __device__ __forceinline__ void clear_coefficients(const Params& P, const ImgDesc& D, uint32_t k, uint32_t n, uint32_t lane, uint32_t lanes) {
     const uint32_t u0 = (uint32_t)((uint64_t)D.total_units * k / n), u1 = (uint32_t)((uint64_t)D.total_units * (k + 1u) / n);
@@ -1524,6 +1711,7 @@ __global__ __launch_bounds__(kWG) void k_clear_coefficients(Params P) {
 // nothing is cleared in memory beforehand.
 template <bool STAGED, bool TILE>
 __global__ __launch_bounds__(kWG) void k_write(Params P) {
+    static_assert(STAGED || !TILE);
     constexpr bool RST = !TILE;  // (a variant without the restart code, as for k_sync_intra, was measured 2 % slower)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     __shared__ uint32_t scratch[36];
@@ -1655,45 +1843,12 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     const uint32_t row0 = lds_at(rows_s);
     auto rows = [&](uint32_t k) { return lds_row(k); };
     int16_t* coef = P.coef + D.coef_off;
-    // Coefficients leave the lane four at a time.  Every value as a store of its own makes 64 two-byte requests per
-    // dense data unit, and the number of requests, not of bytes, is what the memory system charges for: the values
-    // of four neighbouring slots (one aligned 8-byte chunk of the output) are gathered in a register pair and
-    // stored together when the lane moves on to another chunk.  The zeros among them are the lane's own (the chunk
-    // lies inside the range of slots this lane covers), except in the chunk the lane starts in, if it starts in
-    // the middle of one, and in the chunk it ends in: those are shared with the neighbouring lanes and get their
-    // values one by one.  (Eight slots per store were measured too: no faster on dense units, slower on sparse
-    // ones.)
-    const uint32_t S = unit * 64u + state_z(xprev);  // first slot of this lane's range
-    const uint32_t S_chunk = S >> 2, S_low = S & 3u;
-    uint64_t acc = 0ull;
-    // chunk being gathered: 16 * data unit + (slot >> 2), from the chunk the lane's range starts in on (a chunk left
-    // without a value costs a store of zeros onto the cleared background, once per lane at most, and saves a test per chunk)
-    uint32_t cur = S_chunk;
-    const uint32_t shared_first = S_low != 0u ? S_chunk : 0xFFFFFFFFu;  // the first chunk, if a neighbour holds its start
-    uint64_t first = 0ull;   // what was gathered in it; it is written at the end
-    auto store8 = [&](uint32_t c, uint64_t a) { *reinterpret_cast<uint64_t*>(coef + (size_t)c * 4u) = a; };
-    // the non-zero elements of chunk c (chunks shared with a neighbouring lane, onto the cleared background)
-    auto put_nonzero = [&](uint32_t c, uint64_t a) {
-        int16_t* dst = coef + (size_t)c * 4u;
-#pragma unroll
-        for (uint32_t e = 0; e < 4u; ++e) {
-            const int16_t v = (int16_t)(uint16_t)(a >> (16u * e));
-            if (v != 0) dst[e] = v;
-        }
-    };
-    // the lane moves on to a later chunk: the one it leaves reaches up to its end inside the lane's range
-    auto leave = [&]() {
-        if (cur != shared_first) store8(cur, acc);
-        else first = acc;
-    };
+    // Slots are counted from the unit the group takes over in: none of its lanes starts before that.
+    const uint32_t grp_slot = __builtin_amdgcn_readfirstlane(gp.units * 64u);
+    int16_t* const grp_coef = coef + (size_t)grp_slot;
+    WriteChunk chunk = chunk_start(unit * 64u + state_z(xprev) - grp_slot);
     auto store = [&](uint32_t k, uint32_t at, int16_t v) {
-        const uint32_t ck = k * 16u + (at >> 2);
-        if (ck != cur) {
-            leave();
-            acc = 0ull;
-            cur = ck;
-        }
-        acc |= (uint64_t)(uint16_t)v << ((at & 3u) * 16u);
+        chunk_value(chunk, k * 64u + at - grp_slot, v, [&](uint32_t slot, uint64_t a) { *reinterpret_cast<uint64_t*>(grp_coef + (size_t)slot) = a; });
     };
     WriteLane l;
     l.unit = unit;
@@ -1711,13 +1866,8 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     if (TILE && tiled) {
         if (valid && unit < total) {
             start();
-            uint16_t* const tile = reinterpret_cast<uint16_t*>(tile16);
-            const uint32_t tile_first = (uint32_t)tile_a;
-            auto gather = [&](uint32_t k, uint32_t at, int16_t v) {
-                const uint32_t slot = k * 64u + at - tile_first;
-                if (slot < tile_n) tile[slot] = (uint16_t)v;  // (a damaged stream may leave the range)
-            };
-            write_span(l, limit + org, total, word, tab, rows, gather);
+            // (a damaged stream may leave the tile's range)
+            write_span_device<true>(l, limit + org, total, (uint32_t)tile_a, lds_at(tile16), tile_n, nullptr, chunk);
         }
         __syncthreads();
         // the first and the last word are shared with the neighbouring workgroups
@@ -1733,14 +1883,17 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     } else if (unit < total) {
         start();
         if (restart) write_span_rst(l, limit + org, total, D.restart * D.upm, org, D.upm, row0, word, tab, rows, store, bword, &flags);
-        else write_span(l, limit + org, total, word, tab, rows, store);
+        else if constexpr (STAGED) {
+            write_span_device<false>(l, limit + org, total, grp_slot, 0u, 0u, grp_coef, chunk);
+        } else {
+            write_span(l, limit + org, total, word, tab, rows, store);
+        }
     }
     // (in a workgroup with nothing to decode the lane stays where it was: behind the last unit)
     unit = l.unit;
     const uint32_t z_out = unit < total ? (l.s.S >> 9) & 63u : 0u;
     if (l.seen & kWriteBad) flags |= kStInvalid;
-    if (!tiled && cur != S_chunk && S_low != 0u) put_nonzero(S_chunk, first);  // the first chunk, left behind
-    if (!tiled) put_nonzero(cur, acc);  // the last chunk may be shared with the next lane
+    if (!tiled) chunk_ends(chunk, [&](uint32_t slot, int16_t v) { grp_coef[slot] = v; });
     // all restart markers must have been there (the first lane of the image speaks for it)
     if (RST && D.restart && i == 0u && P.st[ii].markers != D.nint - 1u) flags |= kStInvalid;
     if (P.fold) check_boundaries(P, D, lg, nsub);

@@ -240,10 +240,12 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             uint32_t ua = unit, fa = 0, fb = 0;
             int32_t p0 = d[0], p1 = d[1], p2 = d[2];
             win_init(w, a.p, a.p >> 5, fetch);
-            prime(a, w, sx, S.t.lut.data());
+            bool no_dc_code = false;   // as in sync_vs_plain: what is stored behind it is not compared (the stream is refused)
+            const Lut lut{&S.t, &no_dc_code};
+            prime(a, w, sx, lut);
             auto store_a = [&](uint32_t u, uint32_t at, int16_t v) { sa.push_back({(uint64_t)u * 64 + at, v}); };
-            if (restart) decode_span_write_rst(a, w, limit, ua, total, upi, p0, p1, p2, sx, fetch, S.t.lut.data(), store_a, fa, bword);
-            else decode_span_write(a, w, limit, ua, total, p0, p1, p2, sx, fetch, S.t.lut.data(), store_a, fa);
+            if (restart) decode_span_write_rst(a, w, limit, ua, total, upi, p0, p1, p2, sx, fetch, lut, store_a, fa, bword);
+            else decode_span_write(a, w, limit, ua, total, p0, p1, p2, sx, fetch, lut, store_a, fa);
             WriteLane b;
             b.unit = unit;
             b.seen = 0;
@@ -256,9 +258,25 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             const uint32_t u = (b.s.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
             WriteLane want = b;
             write_predictors(want, (S.sched_comp >> (4 * a.u)) & 15, p0, p1, p2);
-            if (sa != sb || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
-                (!restart && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
+            no_dc_code = no_dc_code && (fa & kStInvalid);
+            if ((sa != sb && !no_dc_code) || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
+                (!restart && !no_dc_code && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
                 ++bad;
+            // the values in chunks: nothing outside the image, whole chunks only from the lane's first slot on
+            const uint32_t slots = total * 64u, first = unit * 64u + in.z;
+            WriteChunk ch = chunk_start(first);
+            std::map<uint64_t, int> put;
+            auto store1 = [&](uint32_t at, int16_t v) { at < slots ? (void)(put[at] = v) : (void)++bad; };
+            auto store8 = [&](uint32_t at, uint64_t a) {
+                if ((at & 3u) || at > slots - 4u || (at < first && (!restart || chain))) ++bad;
+                else for (uint32_t j = 0; j < 4u; ++j) put[at + j] = (int16_t)(uint16_t)(a >> (16u * j));
+            };
+            for (auto& v : sb) chunk_value(ch, (uint32_t)v.first, (int16_t)v.second, store8);
+            chunk_ends(ch, store1);
+            if (!restart || chain) {   // (from any state a lane may take a unit for the first of an interval, and store it twice)
+                for (auto& v : sb) { bad += v.second != 0 && put[v.first] != v.second; put.erase(v.first); }
+                for (auto& v : put) bad += v.second != 0;
+            }
             *stored += (uint32_t)sb.size();
         }
         if (chain) {
@@ -296,7 +314,8 @@ extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int i
         uint32_t w = t.write.at(peek >> (32u - (is_dc ? kSyncDcK : kSyncAcK)));
         if (w & kSyncEsc) w = t.write.at((sync_escape_at(w, peek) - kBase) / 4);
         const bool inside = !is_dc && lut_adv(e) != 0u && lut_adv(e) != kAdvEob;
-        bad += w != ((e & kSyncStep) | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u));
+        bad += w != ((e & kSyncStep) | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u) |
+                    (lut_adv(e) == 0u ? 0u : is_dc ? 3u << 29 : lut_size(e) ? 1u << 30 : 0u));
         bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != lut_adv(e) || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
     }
     return bad;
