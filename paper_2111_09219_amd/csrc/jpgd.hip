@@ -760,12 +760,12 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.launched = true;
     if (n > 1)
         hipLaunchKernelGGL(k_upload, dim3(up_wgs), dim3(kWG), 0, stream, (const uint4*)c.buf_dev, (uint4*)ws, up_n16);
-    bool big_tiles = false, alone = n == 1 && !any_restart;  // the two image-level scans are only needed beyond 256 tiles / groups
+    bool big_tiles = false, alone = n == 1 && !any_restart;  // the two image-level scans are only needed beyond kSumMax tiles / groups
     c.big_groups = false;
     for (int i = 0; i < n; ++i) {
         alone = alone && pl.img[i].ntiles <= (uint32_t)kAloneTiles;
-        big_tiles = big_tiles || pl.img[i].ntiles > (uint32_t)kWG;
-        c.big_groups = c.big_groups || pl.img[i].ngrp_max > (uint32_t)kWG;
+        big_tiles = big_tiles || pl.img[i].ntiles > (uint32_t)kSumMax;
+        c.big_groups = c.big_groups || pl.img[i].ngrp_max > (uint32_t)kSumMax;
     }
     if (alone) {
         LAUNCH(JPGD_K_UNSTUFF_SCATTER, k_unstuff_scatter<true>, pl.tiles + P.up_wgs, kWG, 0);
@@ -1095,7 +1095,7 @@ extern "C" int jpgd_unstuff(const uint8_t* d_in, size_t n, uint8_t* d_out, size_
     P.img0 = d;
     P.logL = 10;
     hipLaunchKernelGGL(k_unstuff_count, dim3(tiles), dim3(kWG), 0, stream, P);
-    if (tiles > (uint32_t)kWG) hipLaunchKernelGGL(k_unstuff_scan, dim3(1), dim3(kWG), 0, stream, P);
+    if (tiles > (uint32_t)kSumMax) hipLaunchKernelGGL(k_unstuff_scan, dim3(1), dim3(kWG), 0, stream, P);
     hipLaunchKernelGGL(k_unstuff_scatter<false>, dim3(tiles), dim3(kWG), 0, stream, P);
     HIP_OK(hipGetLastError());
     HIP_OK(hipMemcpyAsync(c->verdict, ws + off_state, sizeof(ImgState), hipMemcpyDeviceToHost, stream));

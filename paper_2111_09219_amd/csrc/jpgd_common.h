@@ -170,6 +170,11 @@ struct Status {
 };
 
 constexpr int kUnstuffTile = 4096;  // bytes per workgroup of the unstuff kernels (256 lanes x 16 bytes)
+// Images of up to this many unstuff tiles, or groups of 256 subsequences, need no kernel for the prefix over them: every
+// workgroup of the kernel behind sums what lies before its own, up to kSumRun per lane, whose loads travel together.  With 256
+// for the line instead of 1024 (one a lane) those kernels and the gaps around them took 5 us of a 4963x7013 gray scan's call
+// twice, and 4 of a 3001x2003 4:2:2 one's once.  Beyond, the sums every workgroup makes would grow with the square of the image.
+constexpr int kSumRun = 4, kSumMax = 256 * kSumRun;
 // Write kernel with the output gathered in LDS: calls of at most one workgroup for every other CU (two calls in flight
 // shall not wait for each other's LDS), subsequences of up to 256 bits (of longer ones a workgroup covers more
 // coefficients than fit), and at most this much room for them: 1024 data units.

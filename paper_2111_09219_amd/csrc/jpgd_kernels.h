@@ -19,7 +19,7 @@ struct Params {
     const uint8_t* scans;
     uint8_t* stream;        // unstuffed streams, image i at img[i].stream_off
     uint32_t* tile_cnt;     // per unstuff tile: bytes removed in it (low half) and restart markers met in it (high
-                            // half), then (in place, images of more than 256 tiles) bytes removed before it
+                            // half), then (in place, images of more than kSumMax tiles) bytes removed before it
     SInfo* sinfo;
     int4* grp_tot;          // per group of kWG subsequences: (units, dc0, dc1, dc2) totals
     int4* grp_pref;         // exclusive prefix of grp_tot inside the image
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scan(Params P) {
     __shared__ uint32_t scratch[8];
     const uint32_t ii = blockIdx.x;
     const ImgDesc D = image_desc_uniform(P, ii);
-    if (D.ntiles <= (uint32_t)kWG) return;  // images of up to 256 tiles: the scatter kernel sums the counts itself
+    if (D.ntiles <= (uint32_t)kSumMax) return;  // (the scatter kernel sums the counts itself)
     // every lane takes a run of consecutive tiles: sum, one scan over the 256 sums, then the prefixes inside the run
     // (one pair of barriers in all; a loop of 256-tile scans was measured at 0.7 microseconds per step)
     uint32_t* cnt = P.tile_cnt + D.tile0;
@@ -519,9 +519,9 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
     const uint8_t* scan = P.scans + D.scan_off;
     uint8_t* out = P.stream + D.stream_off;
     const uint32_t pos = lt * (uint32_t)kUnstuffTile + threadIdx.x * 16u;
-    // bytes removed before this tile: from the scan kernel, or, for images of up to 256 tiles, summed here
-    const bool few_tiles = !ALONE && D.ntiles <= (uint32_t)kWG;
-    uint32_t raw = 0u, before = 0u, nbytes = 0u;
+    // bytes removed before this tile: from the scan kernel, or, for images of up to kSumMax tiles, summed here
+    const bool few_tiles = !ALONE && D.ntiles <= (uint32_t)kSumMax;
+    uint32_t raw = 0u, more[kSumRun - 1] = {0u}, before = 0u, nbytes = 0u;
     if (ALONE) {
         clear_group_total(P, D, lt);
 #pragma unroll 4
@@ -535,6 +535,11 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
         }
     } else if (few_tiles) {
         if (threadIdx.x < D.ntiles) raw = P.tile_cnt[D.tile0 + threadIdx.x];
+        if (D.ntiles > (uint32_t)kWG) {
+#pragma unroll
+            for (uint32_t k = 1; k < (uint32_t)kSumRun; ++k)
+                if (k * kWG + threadIdx.x < D.ntiles) more[k - 1u] = P.tile_cnt[D.tile0 + k * kWG + threadIdx.x];
+        }
     } else {
         before = P.tile_cnt[wg];
         nbytes = P.st[ii].nbytes;
@@ -547,8 +552,19 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
         before = wave_incl_scan(before);
         if ((threadIdx.x & 63u) == 63u) scratch[8u + wave] = before;
     } else if (few_tiles) {
-        const uint32_t v = raw & 0xFFFFu;
-        const uint32_t all = wave_incl_scan(v), prior = wave_incl_scan(threadIdx.x < lt ? v : 0u), marks = wave_incl_scan(raw >> 16);
+        uint32_t all = raw & 0xFFFFu, prior = threadIdx.x < lt ? raw & 0xFFFFu : 0u, marks = raw >> 16;
+        if (D.ntiles > (uint32_t)kWG) {
+#pragma unroll
+            for (uint32_t k = 1; k < (uint32_t)kSumRun; ++k) {
+                const uint32_t v = more[k - 1u] & 0xFFFFu;
+                all += v;
+                prior += k * kWG + threadIdx.x < lt ? v : 0u;
+                marks += more[k - 1u] >> 16;
+            }
+        }
+        all = wave_incl_scan(all);
+        prior = wave_incl_scan(prior);
+        marks = wave_incl_scan(marks);
         if ((threadIdx.x & 63u) == 63u) {
             scratch[4u + wave] = all;
             scratch[8u + wave] = prior;
@@ -1679,7 +1695,7 @@ __global__ __launch_bounds__(kWG) void k_group_scan(Params P) {
     __shared__ uint32_t scratch[20];
     const uint32_t ii = blockIdx.x;
     const ImgDesc D = image_desc_uniform(P, ii);
-    if (D.ngrp_max <= (uint32_t)kWG) return;  // images of up to 256 groups: the write kernel sums the totals itself
+    if (D.ngrp_max <= (uint32_t)kSumMax) return;  // (the write kernel sums the totals itself)
     const uint32_t ngrp = (P.st[ii].nsub + kWG - 1u) / kWG;
     // as in k_unstuff_scan: a run of consecutive groups per lane, one scan over the 256 joined runs
     const int4* tot = P.grp_tot + D.grp0;
@@ -1744,10 +1760,18 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         mine = rec[i];
         if (i > 0u) xprev = rec[i - 1u].x;
     }
-    const bool few_groups = D.ngrp_max <= (uint32_t)kWG;
-    int4 before = make_int4(0, 0, 0, 0);
+    const bool few_groups = D.ngrp_max <= (uint32_t)kSumMax;
+    int4 before = make_int4(0, 0, 0, 0), more[kSumRun - 1];  // totals of a run of consecutive groups per lane
+    const uint32_t per = (lg + (uint32_t)kWG - 1u) / (uint32_t)kWG;
     if (few_groups) {
-        if (t < lg) before = P.grp_tot[D.grp0 + t];
+        if (t * per < lg) before = P.grp_tot[D.grp0 + t * per];
+        if (per > 1u) {
+#pragma unroll
+            for (uint32_t k = 1; k < (uint32_t)kSumRun; ++k) {
+                more[k - 1u] = make_int4(0, 0, 0, 0);
+                if (k < per && t * per + k < lg) more[k - 1u] = P.grp_tot[D.grp0 + t * per + k];
+            }
+        }
     } else {
         before = P.grp_pref[wg];
     }
@@ -1767,13 +1791,20 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     // plus the group's prefix.  Both sums of a scan without restart intervals take lane-to-lane moves and the barrier
     // that ends the staging; the segmented join of the others takes four more barriers.  The states the group's first
     // subsequence starts from and its last one ends in travel the same way.
-    Seg gp = seg_zero(), grp_tot = seg_zero(), ex = seg_zero();
+    Seg gp = seg_zero(), grp_tot = seg_zero(), ex = seg_zero(), run = seg_zero();
     const uint32_t wave = t >> 6;
+    if (few_groups) {
+        run = seg_unpack(before);
+        if (per > 1u) {
+#pragma unroll
+            for (uint32_t k = 1; k < (uint32_t)kSumRun; ++k) run = seg_join(run, seg_unpack(more[k - 1u]));
+        }
+    }
     if (t == 0u) scratch[32] = xprev;
     if (t == nloc - 1u) scratch[33] = mine.x;
     if (D.restart == 0u) {
         const Seg inc = wave_incl_sums(seg_of_record(mine));
-        const Seg bef = few_groups ? wave_incl_sums(seg_unpack(before)) : seg_zero();  // (zero from lane lg on)
+        const Seg bef = few_groups ? wave_incl_sums(run) : seg_zero();
         if ((t & 63u) == 63u) {
             put_sums(scratch + wave * 8u, inc);
             put_sums(scratch + wave * 8u + 4u, bef);
@@ -1794,7 +1825,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
         ex.d0 += inc.d0 - own.d0; ex.d1 += inc.d1 - own.d1; ex.d2 += inc.d2 - own.d2;
     } else {
         restart = __syncthreads_or(seen != 0u) != 0;
-        if (few_groups) wg_excl_segscan(seg_unpack(before), scratch, &gp);  // (zero from lane lg on: the identity of the join)
+        if (few_groups) wg_excl_segscan(run, scratch, &gp);  // (zero, the identity of the join, where nothing is left)
         else gp = seg_unpack(before);
         ex = seg_join(gp, wg_excl_segscan(seg_of_record(mine), scratch, &grp_tot));
     }
