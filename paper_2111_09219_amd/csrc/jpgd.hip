@@ -726,14 +726,14 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     P.pix_per_wg = pl.pix_per_wg;
     // Wavefronts per workgroup of the intra-sequence kernel: as many as the CU's 32 slots allow beside the other
     // workgroups it will hold (LDS, or the size of the grid, decides how many those are), at most 16; more than
-    // 8 only pay when a round is long (measured: 16 instead of 8 gains 5 % at 1024 bits, nothing at 128).  Calls
-    // with restart intervals stay at four: their kernel needs twice the registers.
+    // 8 only pay when a round is long (measured: 16 instead of 8 gains 5 % at 1024 bits, 1 to 2 % at 256, nothing at 128).  Calls
+    // with restart intervals have a few less: their kernel needs more registers.
     uint32_t sync_waves = (uint32_t)(kWG / 64);
     {
-        const uint32_t slots = any_restart ? 20u : 32u;  // the kernel for restart intervals needs 92 registers: 5 per SIMD
+        const uint32_t slots = any_restart ? 28u : 32u;  // the kernel for restart intervals needs 66 to 69 registers: 7 per SIMD
         const uint32_t by_lds = (uint32_t)(160u * 1024u / c.lds_sync), by_grid = (pl.seqs + 255u) / 256u;
         const uint32_t per_cu = by_lds < by_grid ? (by_lds ? by_lds : 1u) : by_grid;
-        const uint32_t most = pl.L >= 512u ? (uint32_t)kSyncWavesMax : 8u;
+        const uint32_t most = pl.L >= 256u ? (uint32_t)kSyncWavesMax : 8u;
         while (sync_waves * 2u <= most && sync_waves * 2u * per_cu <= slots) sync_waves *= 2u;
     }
     P.sync_waves = sync_waves;

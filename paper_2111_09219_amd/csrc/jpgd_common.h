@@ -49,22 +49,23 @@ constexpr int kPairBytes = kLutL1;
 constexpr int kMaxPairs = kMaxSlots / 2;
 constexpr int kLutSetEntries = kMaxSlots * kLutEntries + kMaxPairs * kPairBytes / 2;
 
-// Intra-sequence synchronisation: with at most one and a half chains per wavefront of the workgroup still running,
-// each chain is decoded by a whole wavefront.  Measured on 1920x1088 4:4:4 (128-bit subsequences) and on 4096x4096
-// and 15360x8640 4:2:0 (1024 bits): with four wavefronts 4 to 8 chains are within noise of each other and 16 is
-// slower than never doing it on the large images; with eight wavefronts 12 is best, with sixteen 24.
-constexpr uint32_t kCoopMax = 6u;  // for the kWG / 64 wavefronts that hold the lanes
-// In the second kernel of a split synchronisation (four wavefronts): two more.  Measured per call on the 15360x8640 image for 4, 6,
-// 8, 10 and 12 chains: 2.29, 2.28, 2.25, 2.29, 2.31 ms.
+// Intra-sequence synchronisation: with at most one chain per wavefront of the workgroup still running, each chain is
+// decoded by a whole wavefront.  Calls for 1 / 2 / 3 / 4 / 5 / 6 / 8 / 12 chains per four wavefronts, us: 4096x4096 476 /
+// 450 / 443 / 444 / 446 / 451 / 465 / 489, 24 images of 2047x1535 454 / 445 / 430 / 422 / 424 / 431 / 436 / 459, batch of
+// 256 367 / 357 / 353 / 344 / 345 / 349 / 349 / 352, 3001x2003 with restart intervals 171 / 167 / 163 / 160 / 160 / 161 /
+// 160 / 161.
+constexpr uint32_t kCoopMax = 4u;  // for the kWG / 64 wavefronts that hold the lanes
+// In the second kernel of a split synchronisation (four wavefronts): twice as many.  Measured per call on the 15360x8640 image
+// for 4, 6, 8 and 24 chains: 1.90, 1.89, 1.88, 2.11 ms.
 constexpr uint32_t kTailCoopMax = 8u;
 // The workgroup may have more wavefronts than those: the others do nothing but take chains in these rounds, so
 // that fewer chains share a wavefront (a CU has 32 wavefront slots and a sequence's tail leaves most of them idle).
 constexpr int kSyncWavesMax = 16;
 // Intra-sequence synchronisation as two kernels: calls with at least this many sequences (twice what the chip holds
 // at a time with 1024-bit subsequences), and the number of running chains at which a sequence changes kernel
-// (48 and 64 are within a percent of each other on the 15360x8640 image; 100 and more lose the gain).
+// (15360x8640 with 24 / 48 / 56 / 63 / 100: 1.93 / 1.88 / 1.86 / 1.86 / 1.88 ms a call).
 constexpr int kSplitMinSeqs = 1536;
-constexpr uint32_t kHandoff = 48u;
+constexpr uint32_t kHandoff = 56u;
 // Inter-sequence kernel: a workgroup with at most this many boundaries to decode from walks them with the whole
 // wavefront, one after the other (the walk takes about half the time of a lane's loop per subsequence).
 constexpr int kInterCoopMax = 2;
