@@ -1042,9 +1042,9 @@ __device__ __forceinline__ void sync_span_device(SyncLane& l, uint32_t limit, in
 // write_span (jpgd_lane.h, which says what every value is) as the kernels run it where the stream lies in LDS and the image
 // has no restart intervals; in assembly for the reasons given at sync_span_device.  Entry and first predictor change places
 // from one step to the next, so that neither has to be copied; lanes without a value are switched off for the store instead of
-// branched around.  Calls with the compiler's loop / with this one (us, each against the same older tree beside it): 24 images
-// of 2047x1535 419 / 405, batch of 256 395 / 375, 15360x8640 1877 / 1750, eight of 1600x1200 1116 / 1060, 256x256 gray
-// 56.6 / 53.2.
+// branched around.  Kernel with the compiler's loop / with this one (us): batch of 256 87 / 68, 4096x4096 86 / 66, 15360x8640
+// 368 / 320, 48 frames of 1920x1088 (bound by its stores) 158 / 149, 1920x1088 17 / 14, 256x256 gray 20 / 16.5.  A step takes
+// some 400 cycles with a wavefront or two to a SIMD, 66 vector instructions.
 // Memory: chunk_value, from `out` on, which is where slot0 goes.  A first loop runs until no lane is left in a chunk that it
 // shares with the lane before; the second need not look for it.
 // Tile: every value goes to its place in LDS on its own.  first: place of slot0 there, tile_n: slots there are room for.

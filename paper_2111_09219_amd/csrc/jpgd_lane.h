@@ -504,8 +504,9 @@ JPGD_HD void sync_span(SyncLane& l, uint32_t limit, int64_t& dcacc, Word word, T
 // goes to 64*unit + zig-zag index, DC values un-differenced.  Without branches except around the store itself: a
 // wavefront holds lanes in every kind of symbol at once, so each arm of a branch would be walked anyway.
 // What bounds it is the length of a step in a wavefront that has its SIMD nearly to itself: 680 cycles on the 4096x4096
-// image where the stores are scattered over 64 lines, 450 of them without any store; a loop for the zeros between two
-// values, for stretches of dense units, was 100 more and is gone since the coefficients are always cleared first.
+// image where the stores are scattered over 64 lines, 450 of them without any store (the kernels' assembly, 400 with it:
+// write_span_device); a loop for the zeros between two values, for stretches of dense units, was 100 more and is gone since
+// the coefficients are always cleared first.
 // Kernel before / now, cleared ahead (us): 24 images of 2047x1535 104 / 82, 4963x7013 gray 31 / 21, 1001x667 28 / 23, one
 // 1600x1200 image 46 / 38, 3001x2003 41 / 36; 15360x8640 (cleared here) 412 / 384.
 // The predictors are kept in the order in which the components come next: the current unit's in p0, so that a DC symbol need
