@@ -29,7 +29,8 @@ constexpr int kMaxOverlap = 191;  // warm-up lanes a sequence may borrow from it
 //   bits 5..8   number of value bits that follow the codeword, 0..15
 //   bits 9..14  zig-zag slots the symbol covers: run+1 for a coefficient, 1 for a DC symbol, 16 for
 //               ZRL, 63 for end-of-block (any z >= 1 plus 63 reaches 64 = unit complete), and 0 for
-//               "no codeword starts with these bits" (one bit taken: skip it, state unchanged)
+//               "no codeword starts with these bits" (one bit taken and skipped; in a DC table it counts as the DC
+//               symbol, so that the next one comes from the AC table)
 //   bit 15      0
 //   first-level escape: bit 15 = 1, bits 0..2 = number of further bits that index the second level,
 //               bits 3..10 = half the offset of the subtable inside the second level

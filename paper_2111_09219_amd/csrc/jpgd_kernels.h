@@ -809,11 +809,9 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
         "s_add_u32 %[dcb], %[dcb], %[t]\n"
         "s_add_u32 %[dca], %[dca], %[v]\n"
         "s_and_b32 %[r], %[r], 0x7e1f\n"
-        "s_add_u32 %[S], %[S], %[r]\n"        // the index becomes 1; it stays 0 where no codeword starts
+        "s_add_u32 %[S], %[S], %[r]\n"        // the index becomes 1
         "s_bitcmp1_b32 %[S], 6\n"
         "s_cbranch_scc1 29f\n"
-        "s_cmp_lt_u32 %[S], 0x200\n"
-        "s_cbranch_scc1 20b\n"
         "s_bitcmp1_b32 %[cur], %[kind]\n"
         "s_cbranch_scc0 21b\n"
         // AC symbols of a unit of kind 1

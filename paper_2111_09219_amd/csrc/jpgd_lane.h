@@ -162,7 +162,8 @@ JPGD_HD Step step_and_request(Lane& l, BitWin& w, const Syntax& sx, Fetch fetch,
     s.z = l.z;
     const uint32_t o2 = w.o + s.total;
     s.need = o2 >= 32u;
-    const uint32_t zn = l.z + s.adv;
+    // (bits that start no codeword of a DC table take the DC symbol's slot: sync_entry)
+    const uint32_t zn = l.z + (s.is_dc && !s.esc && s.adv == 0u ? 1u : s.adv);
     s.done = zn >= 64u;
     // off the chain, without branches: when no word is taken the word already held is read again, when the
     // unit does not change its row is
@@ -233,7 +234,7 @@ JPGD_HD void sync_symbol_pair(Lane& l, BitWin& w, int64_t& dcacc, const Syntax& 
     const uint32_t ee = esc ? 0u : e;
     const uint32_t t1 = lut_total(ee), size = lut_size(ee), a1 = lut_adv(ee);
     const bool is_dc = l.z == 0u;
-    const uint32_t zn1 = l.z + a1;
+    const uint32_t zn1 = l.z + (is_dc && !esc && a1 == 0u ? 1u : a1);
     const uint32_t pb = (is_dc || zn1 >= 64u) ? 0u : l.pb;  // (an escape's index has pair byte 0)
     const uint32_t a2c = pb >> 4;
     const uint32_t total = t1 + (pb & 15u);
@@ -325,16 +326,20 @@ constexpr uint32_t kSyncSecond = 0x7E0Fu;      // the same of the second symbol,
 constexpr uint32_t kSyncPairBits = 9u;         // most bits a first symbol with a second one behind it takes
 static_assert(kSyncDcK == kSyncAcK - 1u, "subtables of both kinds are indexed from the last bit of a 10-bit index on");
 
+// Every entry of a DC table covers the one slot of a DC symbol, also where no codeword starts (which takes a bit): the symbol
+// behind it comes from the AC table, and with index 0 the lane's state (position, unit, index) would say otherwise to whoever
+// takes the chain over.  Such bits are met off the true chain, or in a damaged stream.
+constexpr uint32_t kSyncDcSlot = 1u << 9;
 // second-level entry (or first-level one that is no escape) of build_lut, with pair byte pb (0: none)
 JPGD_HD uint32_t sync_entry(uint32_t e, bool is_dc, uint32_t pb) {
     const uint32_t slots = pb >> 4;
-    return (e & kSyncStep) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
+    return (e & kSyncStep) | (is_dc ? kSyncDcSlot : 0u) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
 }
 constexpr uint32_t kWriteInside = 1u << 16, kWriteNoCode = 1u << 17;
 constexpr int32_t kWriteValue = 1 << 30, kWriteDc = 3 << 29;
 JPGD_HD uint32_t write_entry(uint32_t e, bool is_dc) {
     const uint32_t slots = lut_adv(e), size = lut_size(e);
-    return (e & kSyncStep) | (size << 20) | (slots == 0u ? kWriteNoCode : !is_dc && slots != kAdvEob ? kWriteInside : 0u) |
+    return (e & kSyncStep) | (is_dc ? kSyncDcSlot : 0u) | (size << 20) | (slots == 0u ? kWriteNoCode : !is_dc && slots != kAdvEob ? kWriteInside : 0u) |
            (uint32_t)(slots == 0u ? 0 : is_dc ? kWriteDc : size != 0u ? kWriteValue : 0);
 }
 // either, as the tables of the pass need it

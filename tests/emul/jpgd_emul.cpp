@@ -197,9 +197,8 @@ void coop_span_sync(uint32_t& p, uint32_t& u, uint32_t& z, uint32_t& nb, int64_t
                 uint32_t r = entry(dc_slot, S);
                 if (r & 0x8000u) r = coop_resolve(lut, dc_slot, r, peek[S]);
                 dc += (int64_t)symbol_value(peek[S], lut_total(r), lut_size(r)) * (int64_t)(1u << ((cur >> 10) & 31u));
-                S += coop_step(r);
+                S += coop_step(r) | 0x200u;
                 if (S & 0x40u) break;
-                if ((S >> 9) == 0u) continue;
             }
             for (;;) {
                 S += coop_step(entry(ac_slot, S & 63u));
@@ -279,7 +278,7 @@ void sync_intra(Emul& E) {
             active[t] = t + 1 < t1;
             tt[t] = t + 1;
         }
-        uint32_t rounds = 0;
+        uint32_t rounds = 0, waves_used = kWG / 64;
         for (;;) {
             bool any = false;
             for (uint32_t t = 0; t < (uint32_t)kWG; ++t) any = any || active[t];
@@ -288,6 +287,9 @@ void sync_intra(Emul& E) {
             uint32_t now = 0;
             for (uint32_t t = 0; t < (uint32_t)kWG; ++t) now += active[t] ? 1u : 0u;
             const bool coop = im.nslots <= 4u && now <= (restart ? std::min(g_coop_max, g_sync_waves) : g_coop_max);  // stays true once it is
+            // the chains move together where that frees a wavefront; in between a lane goes on with its own
+            const bool packed = ((now + 63u) >> 6) < waves_used;
+            if (packed) waves_used = (now + 63u) >> 6;
             uint32_t unit_word[64];
             for (uint32_t lane = 0; lane < 64; ++lane) unit_word[lane] = coop_unit_word(E.sx, lane);
             for (uint32_t t = 0; t < (uint32_t)kWG; ++t) {
@@ -318,8 +320,10 @@ void sync_intra(Emul& E) {
                 }
                 l[t].nb = 0;
                 dcacc[t] = 0;
-                win_init(bw[t], l[t].p, (l[t].p >> 5) - first_word, fetch);  // a chain moved to another lane restarts its window
-                prime(l[t], bw[t], E.sx, im.lut.data());
+                if (packed) {  // a chain moved to another lane starts there from its state
+                    win_init(bw[t], l[t].p, (l[t].p >> 5) - first_word, fetch);
+                    prime(l[t], bw[t], E.sx, im.lut.data());
+                }
                 uint32_t limit = ((uint32_t)(base + (int32_t)tt[t]) + 1) << logL;
                 uint32_t crossed = 0;
                 if (restart) decode_span_sync_rst(l[t], bw[t], limit, dcacc[t], crossed, E.sx, fetch, im.lut.data(), bword);

@@ -67,15 +67,10 @@ struct Scan {
     uint32_t sched_comp = 0;
 };
 
-// build_lut's tables for the plain lanes; remembers whether an entry of a DC table stood for "no codeword"
+// build_lut's tables for the plain lanes
 struct Lut {
     const Tables* t;
-    bool* no_dc_code;
-    uint32_t operator[](uint32_t k) const {
-        const uint32_t e = t->lut.at(k);
-        if (k < t->ndc * (uint32_t)kLutEntries && !lut_esc(e) && lut_adv(e) == 0u) *no_dc_code = true;
-        return e;
-    }
+    uint32_t operator[](uint32_t k) const { return t->lut.at(k); }
 };
 
 constexpr uint32_t kBase = 176, kRow0 = 48;   // where the tables and the rows start
@@ -130,8 +125,6 @@ int open_scan(const uint8_t* file, size_t len, Scan& S) {
 
 // `tries` random states, each decoded over `spans` subsequences of L bits by both: mismatches in state, unit count, DC sums or
 // "an interval began".  org: added to the positions the lanes of sync_span see (a multiple of 32).  *compared: spans compared.
-// Where bits start no codeword of a DC table (only off the true chain of an intact file) the next entry comes from the AC
-// table, and the plain lane adds that symbol's value to its DC sums: from there on the sums are not compared.
 extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32_t tries, uint32_t spans, uint32_t org,
                              uint32_t seed, uint32_t* compared) {
     Scan S;
@@ -156,8 +149,7 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
     *compared = 0;
     for (uint32_t k = 0; k < tries; ++k) {
         const uint32_t nsub = (S.nbits + L - 1) / L, i0 = rnd(nsub);
-        bool no_dc_code = false;
-        const Lut lut{&S.t, &no_dc_code};
+        const Lut lut{&S.t};
         Lane a;
         BitWin w;
         a.p = i0 * L + (rnd(4) ? rnd(31) : 0u);
@@ -182,7 +174,7 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
             }
             ++*compared;
             const uint32_t u = (b.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.S >> 9) & 63u;
-            if (sync_pos(b) - org != a.p || u != a.u || z != a.z || a.nb != b.nb || (da != db && !no_dc_code) || ca != cb) { ++bad; break; }
+            if (sync_pos(b) - org != a.p || u != a.u || z != a.z || a.nb != b.nb || da != db || ca != cb) { ++bad; break; }
         }
     }
     return bad;
@@ -240,8 +232,7 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             uint32_t ua = unit, fa = 0, fb = 0;
             int32_t p0 = d[0], p1 = d[1], p2 = d[2];
             win_init(w, a.p, a.p >> 5, fetch);
-            bool no_dc_code = false;   // as in sync_vs_plain: what is stored behind it is not compared (the stream is refused)
-            const Lut lut{&S.t, &no_dc_code};
+            const Lut lut{&S.t};
             prime(a, w, sx, lut);
             auto store_a = [&](uint32_t u, uint32_t at, int16_t v) { sa.push_back({(uint64_t)u * 64 + at, v}); };
             if (restart) decode_span_write_rst(a, w, limit, ua, total, upi, p0, p1, p2, sx, fetch, lut, store_a, fa, bword);
@@ -258,9 +249,8 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             const uint32_t u = (b.s.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
             WriteLane want = b;
             write_predictors(want, (S.sched_comp >> (4 * a.u)) & 15, p0, p1, p2);
-            no_dc_code = no_dc_code && (fa & kStInvalid);
-            if ((sa != sb && !no_dc_code) || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
-                (!restart && !no_dc_code && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
+            if (sa != sb || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
+                (!restart && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
                 ++bad;
             // the values in chunks: nothing outside the image, whole chunks only from the lane's first slot on
             const uint32_t slots = total * 64u, first = unit * 64u + in.z;
@@ -284,6 +274,50 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             uint32_t crossed = 0;
             if (restart) decode_span_sync_rst(c, cw, limit, dc, crossed, sx, fetch, S.t.lut.data(), bword);
             else decode_span_sync(c, cw, limit, dc, sx, fetch, S.t.lut.data());
+        }
+    }
+    return bad;
+}
+
+// Position, unit and zig-zag index say all about a decoder: a lane that goes on and one that starts from them again, after
+// every single symbol, read and store the same.  From `tries` random states, `symbols` symbols each; *compared: symbols.
+extern "C" int lanes_restarted(const uint8_t* file, size_t len, uint32_t tries, uint32_t symbols, uint32_t seed, uint32_t* compared) {
+    Scan S;
+    const int rc = open_scan(file, len, S);
+    if (rc) return -rc;
+    const uint32_t* words = (const uint32_t*)S.stream.data();
+    auto word = [&](uint32_t b) { return b / 32 < S.stream.size() / 4 ? __builtin_bswap32(words[b / 32]) : 0u; };
+    auto tab = [&](uint32_t k) { return S.t.sync.at((k - kBase) / 4); };
+    auto wtab = [&](uint32_t k) { return S.t.write.at((k - kBase) / 4); };
+    auto rows = [&](uint32_t k) { return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
+    auto wrows = [&](uint32_t k) { return S.wrows[(k - kRow0) / sizeof(SyncRow)]; };
+    const uint32_t upm = S.in.units_per_mcu;
+    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
+    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    auto unit_of = [&](const SyncLane& l) { return (l.row - kRow0) / (uint32_t)sizeof(SyncRow); };
+    int bad = 0;
+    *compared = 0;
+    for (uint32_t k = 0; k < tries; ++k) {
+        SyncLane a, b;
+        WriteLane x, y;
+        const uint32_t p0 = rnd(S.nbits), u0 = rnd(upm), z0 = rnd(2) ? rnd(64) : 0u;
+        sync_start(a, p0, u0, z0, upm, kRow0, word, tab, rows);
+        write_start(x, p0, u0, z0, upm, kRow0, word, wtab, wrows);
+        for (uint32_t i = 0; i < symbols && sync_pos(a) < S.nbits; ++i, ++*compared) {
+            const uint32_t p = sync_pos(a);
+            int64_t da = 0, db = 0;
+            a.nb = b.nb = 0;
+            sync_start(b, p, unit_of(a), (a.S >> 9) & 63u, upm, kRow0, word, tab, rows);
+            sync_span(a, p + 1u, da, word, tab, rows);
+            sync_span(b, p + 1u, db, word, tab, rows);
+            bad += a.S != b.S || sync_pos(a) != sync_pos(b) || a.row != b.row || a.nb != b.nb || da != db;
+            std::vector<std::pair<uint32_t, int>> sx, sy;
+            x.unit = y.unit = x.seen = y.seen = 0u;
+            x.p0 = x.p1 = x.p2 = y.p0 = y.p1 = y.p2 = 0;
+            write_start(y, p, unit_of(x.s), (x.s.S >> 9) & 63u, upm, kRow0, word, wtab, wrows);
+            write_span(x, p + 1u, 2u, word, wtab, wrows, [&](uint32_t u, uint32_t at, int16_t v) { sx.push_back({u * 64u + at, v}); });
+            write_span(y, p + 1u, 2u, word, wtab, wrows, [&](uint32_t u, uint32_t at, int16_t v) { sy.push_back({u * 64u + at, v}); });
+            bad += sx != sy || x.seen != y.seen || x.s.S != a.S || y.s.S != a.S || x.s.row != a.row || sync_pos(x.s) != sync_pos(a);
         }
     }
     return bad;
@@ -314,9 +348,10 @@ extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int i
         uint32_t w = t.write.at(peek >> (32u - (is_dc ? kSyncDcK : kSyncAcK)));
         if (w & kSyncEsc) w = t.write.at((sync_escape_at(w, peek) - kBase) / 4);
         const bool inside = !is_dc && lut_adv(e) != 0u && lut_adv(e) != kAdvEob;
-        bad += w != ((e & kSyncStep) | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u) |
+        const uint32_t slots = is_dc ? 1u : lut_adv(e);   // (a DC table's also where no codeword starts)
+        bad += w != ((e & 31u) | slots << 9 | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u) |
                     (lut_adv(e) == 0u ? 0u : is_dc ? 3u << 29 : lut_size(e) ? 1u << 30 : 0u));
-        bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != lut_adv(e) || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
+        bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != slots || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
     }
     return bad;
 }

@@ -27,6 +27,7 @@ def lanes():
     lib.sync_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, u32, vp]
     lib.write_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, ctypes.c_int, u32, u32, u32, vp]
     lib.sync_table_vs_lut.argtypes = [vp, vp, ctypes.c_int]
+    lib.lanes_restarted.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, vp]
     return lib
 
 
@@ -58,6 +59,25 @@ def test_write_lanes_equal_the_plain_ones(lanes, sub, opt, q, shape, L, ri, org,
     n = ctypes.c_uint32()
     assert lanes.write_vs_plain(data.ctypes.data, data.size, L, 4000, chain, org, total, 3, ctypes.byref(n)) == 0
     assert n.value > 200
+
+
+def _constant_dc(shape):
+    """Data units whose mean is 128: every DC difference is zero, and the optimised DC table has a single codeword."""
+    px = np.random.default_rng(4).normal(0, 20, (shape[0] // 8, 8, shape[1] // 8, 8))
+    px -= px.mean(axis=(1, 3), keepdims=True)
+    return np.clip(np.rint(px + 128), 0, 255).astype(np.uint8).reshape(shape)
+
+
+@pytest.mark.parametrize("sub,opt,q", [("420", False, 92), ("444", True, 75), ("422", True, 98), ("gray", True, 30)])
+def test_position_unit_and_index_say_all_about_a_lane(lanes, sub, opt, q):
+    """Chains move from lane to lane and are compared by these three alone, so nothing else may decide what a lane reads next,
+    also behind bits that start no codeword (in front of a coefficient, or of a DC value, of which a table of one codeword
+    has many)."""
+    px = _constant_dc((160, 200)) if sub == "gray" else small_image(21, 96, 160, sigma=14.0)
+    data = encode_jpeg(px, q, sub, opt).data
+    n = ctypes.c_uint32()
+    assert lanes.lanes_restarted(data.ctypes.data, data.size, 3000, 40, 7, ctypes.byref(n)) == 0
+    assert n.value > 50000
 
 
 def test_tables_hold_what_the_first_ones_hold(lanes):
