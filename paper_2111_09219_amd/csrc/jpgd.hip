@@ -203,18 +203,7 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
             }
         }
         if (u != d.upm) return JPGD_E_ARG;
-        // kinds of data units (component 0 is of kind 0)
-        uint32_t kind[3] = {0, 0, 0}, kinds = 1, slots[2] = {comp_dc[0] | (ndc + comp_ac[0]) << 3, 0};
-        for (uint32_t c = 1; c < in.ncomp; ++c) {
-            const uint32_t mine = comp_dc[c] | (ndc + comp_ac[c]) << 3;
-            uint32_t k = 0;
-            while (k < kinds && k < 2u && slots[k] != mine) ++k;
-            if (k == kinds && kinds++ < 2u) slots[k] = mine;
-            kind[c] = k;
-        }
-        if (kinds == 1) slots[1] = slots[0];
-        d.walk = kinds > 2u ? 0u : 0x80000000u | slots[0] << kWalkSlots | slots[1] << (kWalkSlots + 6u);
-        for (uint32_t k = 0; d.walk && k < d.upm; ++k) d.walk |= kind[(d.sched_comp >> (4 * k)) & 15u] << k;
+        d.walk = walk_word(d.upm, d.sched_dc, d.sched_ac);
         if (i > 0 && same_tables(infos[i - 1], in)) {
             pl.lut_of_img[i] = pl.lut_of_img[i - 1];
         } else {
@@ -243,6 +232,7 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
         if (mode > 2u) return JPGD_E_ARG;
         // (not with restart intervals: their second kernel, with one chain per wavefront at most and single-symbol
         // steps, takes longer than it saves -- 15360x8640 with one interval per MCU row 2.13 against 2.10 ms)
+        // (nor with more than the four tables a baseline file may have)
         const bool can = pl.bmap_words == 0u && pl.lut_slots <= 4u;
         pl.split = can && (mode == 2u || (mode == 0u && L >= 512u && pl.seqs >= (uint32_t)kSplitMinSeqs));
     }

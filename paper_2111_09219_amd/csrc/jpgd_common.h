@@ -143,12 +143,9 @@ struct ImgDesc {
                            // 128 words per unstuff tile plus 128 of slack)
     uint32_t ndc;          // DC tables of this image: slots 0 .. ndc-1; its AC tables follow, AC table k with pair bytes k
     uint32_t sub_words;    // words of subtables of its AC tables in the synchronisation kernels, 10 bits each
-    uint32_t walk;         // data units that share a DC and an AC table are of one kind.  0: there are more than two kinds;
-                           // else bit 31, in bits 0..5 the kind of each unit of the MCU, and from kWalkSlots on, 3 bits
-                           // each, the slots of the DC and the AC table of kind 0 and of kind 1
+    uint32_t walk;         // kinds of data units (walk_word)
     uint32_t pad_;
 };
-constexpr uint32_t kWalkSlots = 6u;
 
 // written by the unstuff kernels
 struct ImgState {

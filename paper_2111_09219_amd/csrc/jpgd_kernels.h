@@ -655,32 +655,29 @@ __global__ __launch_bounds__(kWG) void k_unstuff_scatter(Params P) {
 // instructions, some 30 cycles, and everything else used to be four times that.  So the whole loop over the windows is
 // assembly: the compiler's form of it set and tested flags around every exit, moved the next window's answers from
 // register to register and spent six taken branches a window outside the walk.  Here a window costs 27 instructions and
-// one taken branch, a unit's end and the DC symbol behind it 45 and three.  An image may have two kinds of data units, by
-// their tables (ImgDesc::walk); each kind has its own loop over AC symbols, so that nothing is selected per symbol.
+// one taken branch, a unit's end and the DC symbol behind it 45 and three.  Each kind of data units, by their tables
+// (ImgDesc::walk), has its own loop over AC symbols, so that nothing is selected per symbol.  Two kinds are the usual, and
+// the walk of images with a third is a form of its own, which looks eight instructions longer at a window.
 // Measured, window loop compiled around an assembly walk / this (kernels, us): second kernel of 15360x8640 848 / 705, 24
 // images of 2047x1535 305 / 270, one 1600x1200 image 190 / 158, 256 images of 512x384 213 / 186, 1001x667 89 / 80; a round
-// of 1024 bits with up to 23 chains on 16 wavefronts 28 000 / 19 800 cycles.  (An image with three kinds of units keeps to
-// the lanes.)
+// of 1024 bits with up to 23 chains on 16 wavefronts 28 000 / 19 800 cycles.  Three kinds of units in the lanes throughout / in
+// the walk (calls, us, components with tables 0/0, 1/1 and 0/1): 4096x4096 302 / 239, six of them 687 / 613, one 1600x1200
+// image 292 / 231, 24 of them 406 / 300; with two kinds 239, 611, 232 and 308.
 
-// lane i < upm describes data unit i of the MCU: index of the unit that follows (bits 0..3), the kind of unit (4), and
-// where its DC differences go in the walk's two sums: shift inside the first word (10-14: 0 for component 0, 16 for
-// component 1), or the second word (bit 15, component 2)
-constexpr uint32_t kUwKind = 4u, kUwShift = 10u, kUwSecond = 15u;
+// lane i < upm describes data unit i of the MCU (walk_unit)
 __device__ __forceinline__ uint32_t coop_unit_word(const ImgDesc& D, uint32_t lane) {
-    if (lane >= D.upm) return 0u;
-    const uint32_t next = lane + 1u == D.upm ? 0u : lane + 1u, comp = (D.sched_comp >> (4u * lane)) & 15u;
-    return next | (((D.walk >> lane) & 1u) << kUwKind) | (comp == 2u ? 1u << kUwSecond : comp * 16u << kUwShift);
+    return lane < D.upm ? walk_unit(D.walk, D.sched_comp, D.upm, lane) : 0u;
 }
 
-// Where the tables of the two kinds of units lie: bytes of LDS, the same in every lane.
+// Where the tables of the kinds of units lie: bytes of LDS, the same in every lane.
 struct CoopTables {
-    uint32_t dc0, ac0, dc1, ac1;
+    uint32_t dc0, ac0, dc1, ac1, dc2, ac2;
+    bool three;  // kinds; with fewer, kind 2 repeats kind 0 and is not looked at
 };
 __device__ __forceinline__ CoopTables coop_tables(const ImgDesc& D, uint32_t tab) {
-    const uint32_t walk = __builtin_amdgcn_readfirstlane(D.walk), ndc = __builtin_amdgcn_readfirstlane(D.ndc);
-    auto dc = [&](uint32_t at) { return tab + ((walk >> at) & 7u) * kSyncDcBytes; };
-    auto ac = [&](uint32_t at) { return tab + ndc * kSyncDcBytes + (((walk >> at) & 7u) - ndc) * kSyncAcBytes; };
-    return CoopTables{dc(kWalkSlots), ac(kWalkSlots + 3u), dc(kWalkSlots + 6u), ac(kWalkSlots + 9u)};
+    const uint32_t w = __builtin_amdgcn_readfirstlane(D.walk), ndc = __builtin_amdgcn_readfirstlane(D.ndc);
+    return CoopTables{walk_dc(w, 0u, tab), walk_ac(w, 0u, ndc, tab), walk_dc(w, 1u, tab), walk_ac(w, 1u, ndc, tab),
+                      walk_dc(w, 2u, tab), walk_ac(w, 2u, ndc, tab), ((w >> kWalkThree) & 1u) != 0u};
 }
 
 // What the walk's instructions take for granted of an entry (sync_entry), beside what the lanes do.
@@ -700,9 +697,11 @@ constexpr uint32_t bit_field(uint32_t at, uint32_t bits) { return (bits << 16) |
 // that of component 2.  (Sums that leave 16 bits come out otherwise than from the lanes' loop in the components behind; the
 // sums of a chain that is in step do so only where DC values leave the range of 8-bit samples, and the 15-bit fields
 // of the lanes do not hold those either.)
-__device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, uint32_t& z_io, uint32_t& nb_out, int64_t& dc_out,
-                                               uint32_t limit, uint32_t words, uint32_t unit_word, uint32_t upm,
-                                               const CoopTables& ct) {
+// THREE: the image has three kinds of units (a component with a pair of tables of its own).
+template <bool THREE>
+__device__ __forceinline__ void coop_span_kinds(uint32_t& p_io, uint32_t& u_io, uint32_t& z_io, uint32_t& nb_out, int64_t& dc_out,
+                                                uint32_t limit, uint32_t words, uint32_t unit_word, uint32_t upm,
+                                                const CoopTables& ct) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t p = __builtin_amdgcn_readfirstlane(p_io), u = __builtin_amdgcn_readfirstlane(u_io);
     const uint32_t ws = p & ~63u;
@@ -716,186 +715,201 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
     uint32_t d0, d1, a0, a1, c0, c1, peek, nd0, nd1, na0, na1, npeek, x0, x1;
     uint32_t t, t2, r, r2, v;
     uint64_t all;
-    asm volatile(
-        "s_waitcnt lgkmcnt(0)\n"
-        "ds_read_b32 %[x0], %[at]\n"
-        "ds_read_b32 %[x1], %[at] offset:4\n"
-        "s_bitset1_b32 %[left], 31\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        "s_branch 2f\n"
-        // the next window's answers become this one's
-        "1:\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        "v_mov_b32 %[peek], %[npeek]\n"
-        "v_mov_b32 %[d0], %[nd0]\n"
-        "v_mov_b32 %[d1], %[nd1]\n"
-        "v_mov_b32 %[a0], %[na0]\n"
-        "v_mov_b32 %[a1], %[na1]\n"
-        "v_and_b32 %[c0], 0xfe1f, %[na0]\n"
-        "v_and_b32 %[c1], 0xfe1f, %[na1]\n"
-        // ask for those of the window behind it, and for the words of the one after that
-        "2:\n"
-        "v_alignbit_b32 %[npeek], %[x0], %[x1], %[shift]\n"
-        "v_lshrrev_b32 %[x0], 23, %[npeek]\n"
-        "v_lshrrev_b32 %[x1], 22, %[npeek]\n"
-        "v_lshl_add_u32 %[nd0], %[x0], 2, %[bd0]\n"
-        "v_lshl_add_u32 %[nd1], %[x0], 2, %[bd1]\n"
-        "v_lshl_add_u32 %[na0], %[x1], 2, %[ba0]\n"
-        "v_lshl_add_u32 %[na1], %[x1], 2, %[ba1]\n"
-        "ds_read_b32 %[nd0], %[nd0]\n"
-        "ds_read_b32 %[nd1], %[nd1]\n"
-        "ds_read_b32 %[na0], %[na0]\n"
-        "ds_read_b32 %[na1], %[na1]\n"
-        "ds_read_b32 %[x0], %[at] offset:8\n"
-        "ds_read_b32 %[x1], %[at] offset:12\n"
-        "v_add_u32 %[at], 8, %[at]\n"
-        "s_bitcmp1_b32 %[left], 31\n"   // (the first time round there is no window to walk through yet)
-        "s_cbranch_scc0 3f\n"
-        "s_bitset0_b32 %[left], 31\n"
-        "s_branch 1b\n"
-        "3:\n"
-        "s_cmp_lt_u32 %[S], 0x200\n"
-        "s_cbranch_scc1 20f\n"
-        "s_bitcmp1_b32 %[cur], %[kind]\n"
-        "s_cbranch_scc1 31f\n"
-        // AC symbols of a unit of kind 0, eight in a row
-        "21:\n"
-        ".rept 8\n"
-        "v_readlane_b32 %[t], %[c0], %[S]\n"
-        "s_add_u32 %[S], %[S], %[t]\n"
-        "s_and_b32 %[t2], %[S], 0x18040\n"
-        "s_cbranch_scc1 22f\n"
-        ".endr\n"
-        "s_branch 21b\n"
-        "22:\n"
-        "s_bitcmp1_b32 %[t], 15\n"
-        "s_cbranch_scc1 27f\n"
-        "s_bitcmp1_b32 %[S], 15\n"
-        "s_cbranch_scc0 29f\n"
-        // unit complete
-        "23:\n"
-        "s_add_u32 %[nb], %[nb], 1\n"
-        "s_and_b32 %[S], %[S], 0x7f\n"
-        "s_and_b32 %[t], %[cur], 15\n"
-        "s_bitcmp1_b32 %[S], 6\n"
-        "v_readlane_b32 %[cur], %[uw], %[t]\n"
-        "s_cbranch_scc1 29f\n"
-        // DC symbol at position S (its zig-zag index is 0): entry of the table, its value, the component's sum
-        "20:\n"
-        "v_readlane_b32 %[r], %[d0], %[S]\n"
-        "v_readlane_b32 %[r2], %[d1], %[S]\n"
-        "v_readlane_b32 %[v], %[peek], %[S]\n"
-        "s_bitcmp1_b32 %[cur], %[kind]\n"
-        "s_cselect_b32 %[r], %[r2], %[r]\n"
-        "s_bitcmp1_b32 %[r], 31\n"
-        "s_cbranch_scc1 28f\n"
-        "24:\n"
-        "s_and_b32 %[t], %[r], 31\n"
-        "s_bfe_u32 %[r2], %[r], %[f_size]\n"
-        "s_sub_u32 %[t], 32, %[t]\n"
-        "s_lshl_b32 %[t2], %[r2], 16\n"
-        "s_or_b32 %[t], %[t], %[t2]\n"
-        "s_bfe_i32 %[v], %[v], %[t]\n"        // the value's bits, signed (none: 0)
-        "s_ashr_i32 %[t], %[v], 31\n"
-        "s_lshl_b32 %[t2], -1, %[r2]\n"
-        "s_xor_b32 %[t], %[t], %[t2]\n"
-        "s_add_i32 %[v], %[v], %[t]\n"
-        "s_add_i32 %[v], %[v], 1\n"           // the difference, as in symbol_value
-        "s_bfe_u32 %[t], %[cur], %[f_shift]\n"
-        "s_lshl_b32 %[v], %[v], %[t]\n"
-        "s_bitcmp1_b32 %[cur], %[b_second]\n"
-        "s_cselect_b32 %[t], %[v], 0\n"
-        "s_cselect_b32 %[v], 0, %[v]\n"
-        "s_add_u32 %[dcb], %[dcb], %[t]\n"
-        "s_add_u32 %[dca], %[dca], %[v]\n"
-        "s_and_b32 %[r], %[r], 0x7e1f\n"
-        "s_add_u32 %[S], %[S], %[r]\n"        // the index becomes 1
-        "s_bitcmp1_b32 %[S], 6\n"
-        "s_cbranch_scc1 29f\n"
-        "s_bitcmp1_b32 %[cur], %[kind]\n"
-        "s_cbranch_scc0 21b\n"
-        // AC symbols of a unit of kind 1
-        "31:\n"
-        ".rept 8\n"
-        "v_readlane_b32 %[t], %[c1], %[S]\n"
-        "s_add_u32 %[S], %[S], %[t]\n"
-        "s_and_b32 %[t2], %[S], 0x18040\n"
-        "s_cbranch_scc1 32f\n"
-        ".endr\n"
-        "s_branch 31b\n"
-        "32:\n"
-        "s_bitcmp1_b32 %[t], 15\n"
-        "s_cbranch_scc1 37f\n"
-        "s_bitcmp1_b32 %[S], 15\n"
-        "s_cbranch_scc1 23b\n"
-        // the window ends
-        "29:\n"
-        "s_sub_u32 %[S], %[S], 64\n"          // the same position, seen from the next window
-        "s_sub_u32 %[left], %[left], 1\n"
-        "s_cmp_lg_u32 %[left], 0\n"
-        "s_cbranch_scc1 1b\n"
-        "s_branch 40f\n"
-        // escapes of the AC table of kind 0, of kind 1, of either DC table; the step is taken (again) with what they lead to
-        "27:\n"
-        "s_sub_u32 %[S], %[S], %[t]\n"
-        "v_cmp_gt_i32 vcc, 0, %[a0]\n"
-        "s_and_saveexec_b64 %[all], vcc\n"
-        "v_bfe_u32 %[c0], %[a0], 6, 3\n"
-        "v_sub_u32 %[c1], 23, %[c0]\n"
-        "v_bfe_u32 %[c0], %[peek], %[c1], %[c0]\n"
-        "v_lshrrev_b32 %[a0], 15, %[a0]\n"
-        "v_and_b32 %[a0], 0xfff8, %[a0]\n"
-        "v_lshl_add_u32 %[a0], %[c0], 2, %[a0]\n"
-        "ds_read_b32 %[a0], %[a0]\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        "s_mov_b64 exec, %[all]\n"
-        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
-        "v_and_b32 %[c1], 0xfe1f, %[a1]\n"
-        "s_nop 1\n"
-        "s_branch 21b\n"
-        "37:\n"
-        "s_sub_u32 %[S], %[S], %[t]\n"
-        "v_cmp_gt_i32 vcc, 0, %[a1]\n"
-        "s_and_saveexec_b64 %[all], vcc\n"
-        "v_bfe_u32 %[c1], %[a1], 6, 3\n"
-        "v_sub_u32 %[c0], 23, %[c1]\n"
-        "v_bfe_u32 %[c1], %[peek], %[c0], %[c1]\n"
-        "v_lshrrev_b32 %[a1], 15, %[a1]\n"
-        "v_and_b32 %[a1], 0xfff8, %[a1]\n"
-        "v_lshl_add_u32 %[a1], %[c1], 2, %[a1]\n"
-        "ds_read_b32 %[a1], %[a1]\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        "s_mov_b64 exec, %[all]\n"
-        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
-        "v_and_b32 %[c1], 0xfe1f, %[a1]\n"
-        "s_nop 1\n"
-        "s_branch 31b\n"
-        "28:\n"
-        "s_bfe_u32 %[t], %[r], %[f_n]\n"
-        "s_sub_u32 %[t2], 23, %[t]\n"
-        "s_lshl_b32 %[t], %[t], 16\n"
-        "s_or_b32 %[t], %[t], %[t2]\n"
-        "s_bfe_u32 %[t], %[v], %[t]\n"
-        "s_lshl_b32 %[t], %[t], 2\n"
-        "s_lshr_b32 %[r], %[r], 15\n"
-        "s_and_b32 %[r], %[r], 0xfff8\n"
-        "s_add_u32 %[t], %[t], %[r]\n"
-        "v_mov_b32 %[c0], %[t]\n"
-        "ds_read_b32 %[c0], %[c0]\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        "v_readfirstlane_b32 %[r], %[c0]\n"
-        "v_and_b32 %[c0], 0xfe1f, %[a0]\n"
-        "s_branch 24b\n"
-        "40:\n"
-        "s_waitcnt lgkmcnt(0)\n"
-        : [S] "+&s"(S), [cur] "+&s"(cur), [left] "+&s"(left), [nb] "+&s"(nb), [dca] "+&s"(dc_a), [dcb] "+&s"(dc_b), [at] "+&v"(at),
-          [d0] "=&v"(d0), [d1] "=&v"(d1), [a0] "=&v"(a0), [a1] "=&v"(a1), [c0] "=&v"(c0), [c1] "=&v"(c1), [peek] "=&v"(peek),
-          [nd0] "=&v"(nd0), [nd1] "=&v"(nd1), [na0] "=&v"(na0), [na1] "=&v"(na1), [npeek] "=&v"(npeek), [x0] "=&v"(x0),
-          [x1] "=&v"(x1), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v), [all] "=&s"(all)
-        : [shift] "v"(shift), [uw] "v"(unit_word), [bd0] "s"(ct.dc0), [ba0] "s"(ct.ac0), [bd1] "s"(ct.dc1), [ba1] "s"(ct.ac1),
-          [kind] "i"(kUwKind), [f_size] "i"(bit_field(20u, 4u)), [f_shift] "i"(bit_field(kUwShift, 5u)),
-          [b_second] "i"(kUwSecond), [f_n] "i"(bit_field(6u, 3u))
-        : "vcc", "scc", "memory");
+// AC symbols of a unit of one kind, eight in a row; an escape, the end of the unit, else that of the window
+#define JPGD_WALK_AC(LOOP, EVENT, ESCAPE, C)                                                               \
+    LOOP ":\n"                                                                                             \
+    ".rept 8\n"                                                                                            \
+    "v_readlane_b32 %[t], " C ", %[S]\n"                                                                   \
+    "s_add_u32 %[S], %[S], %[t]\n"                                                                         \
+    "s_and_b32 %[t2], %[S], 0x18040\n"                                                                     \
+    "s_cbranch_scc1 " EVENT "f\n"                                                                          \
+    ".endr\n"                                                                                              \
+    "s_branch " LOOP "b\n"                                                                                 \
+    EVENT ":\n"                                                                                            \
+    "s_bitcmp1_b32 %[t], 15\n"                                                                             \
+    "s_cbranch_scc1 " ESCAPE "f\n"                                                                         \
+    "s_bitcmp1_b32 %[S], 15\n"
+// the escapes of one kind's AC table, followed up in every lane that holds one; the step is taken again with what they lead to
+#define JPGD_WALK_ESCAPE(ESCAPE, LOOP, A, C, OTHER_A, OTHER_C)                                             \
+    ESCAPE ":\n"                                                                                           \
+    "s_sub_u32 %[S], %[S], %[t]\n"                                                                         \
+    "v_cmp_gt_i32 vcc, 0, " A "\n"                                                                         \
+    "s_and_saveexec_b64 %[all], vcc\n"                                                                     \
+    "v_bfe_u32 " C ", " A ", 6, 3\n"                                                                       \
+    "v_sub_u32 " OTHER_C ", 23, " C "\n"                                                                   \
+    "v_bfe_u32 " C ", %[peek], " OTHER_C ", " C "\n"                                                       \
+    "v_lshrrev_b32 " A ", 15, " A "\n"                                                                     \
+    "v_and_b32 " A ", 0xfff8, " A "\n"                                                                     \
+    "v_lshl_add_u32 " A ", " C ", 2, " A "\n"                                                              \
+    "ds_read_b32 " A ", " A "\n"                                                                           \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "s_mov_b64 exec, %[all]\n"                                                                             \
+    "v_and_b32 " C ", 0xfe1f, " A "\n"                                                                     \
+    "v_and_b32 " OTHER_C ", 0xfe1f, " OTHER_A "\n"                                                         \
+    "s_nop 1\n"                                                                                            \
+    "s_branch " LOOP "b\n"
+// THIRD(text): text where there is a third kind
+#define JPGD_WALK(THIRD)                                                                                   \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "ds_read_b32 %[x0], %[at]\n"                                                                           \
+    "ds_read_b32 %[x1], %[at] offset:4\n"                                                                  \
+    "s_bitset1_b32 %[left], 31\n"                                                                          \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "s_branch 2f\n"                                                                                        \
+    /* the next window's answers become this one's */                                                      \
+    "1:\n"                                                                                                 \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "v_mov_b32 %[peek], %[npeek]\n"                                                                        \
+    "v_mov_b32 %[d0], %[nd0]\n"                                                                            \
+    "v_mov_b32 %[d1], %[nd1]\n"                                                                            \
+    "v_mov_b32 %[a0], %[na0]\n"                                                                            \
+    "v_mov_b32 %[a1], %[na1]\n"                                                                            \
+    THIRD("v_mov_b32 %[d2], %[nd2]\n"                                                                      \
+          "v_mov_b32 %[a2], %[na2]\n"                                                                      \
+          "v_and_b32 %[c2], 0xfe1f, %[na2]\n")                                                             \
+    "v_and_b32 %[c0], 0xfe1f, %[na0]\n"                                                                    \
+    "v_and_b32 %[c1], 0xfe1f, %[na1]\n"                                                                    \
+    /* ask for those of the window behind it, and for the words of the one after that */                   \
+    "2:\n"                                                                                                 \
+    "v_alignbit_b32 %[npeek], %[x0], %[x1], %[shift]\n"                                                    \
+    "v_lshrrev_b32 %[x0], 23, %[npeek]\n"                                                                  \
+    "v_lshrrev_b32 %[x1], 22, %[npeek]\n"                                                                  \
+    "v_lshl_add_u32 %[nd0], %[x0], 2, %[bd0]\n"                                                            \
+    "v_lshl_add_u32 %[nd1], %[x0], 2, %[bd1]\n"                                                            \
+    "v_lshl_add_u32 %[na0], %[x1], 2, %[ba0]\n"                                                            \
+    "v_lshl_add_u32 %[na1], %[x1], 2, %[ba1]\n"                                                            \
+    "ds_read_b32 %[nd0], %[nd0]\n"                                                                         \
+    "ds_read_b32 %[nd1], %[nd1]\n"                                                                         \
+    "ds_read_b32 %[na0], %[na0]\n"                                                                         \
+    "ds_read_b32 %[na1], %[na1]\n"                                                                         \
+    THIRD("v_lshl_add_u32 %[nd2], %[x0], 2, %[bd2]\n"                                                      \
+          "v_lshl_add_u32 %[na2], %[x1], 2, %[ba2]\n"                                                      \
+          "ds_read_b32 %[nd2], %[nd2]\n"                                                                   \
+          "ds_read_b32 %[na2], %[na2]\n")                                                                  \
+    "ds_read_b32 %[x0], %[at] offset:8\n"                                                                  \
+    "ds_read_b32 %[x1], %[at] offset:12\n"                                                                 \
+    "v_add_u32 %[at], 8, %[at]\n"                                                                          \
+    "s_bitcmp1_b32 %[left], 31\n"   /* (the first time round there is no window to walk through yet) */    \
+    "s_cbranch_scc0 3f\n"                                                                                  \
+    "s_bitset0_b32 %[left], 31\n"                                                                          \
+    "s_branch 1b\n"                                                                                        \
+    "3:\n"                                                                                                 \
+    "s_cmp_lt_u32 %[S], 0x200\n"                                                                           \
+    "s_cbranch_scc1 20f\n"                                                                                 \
+    THIRD("s_bitcmp1_b32 %[cur], %[kind] + 1\n"                                                            \
+          "s_cbranch_scc1 41f\n")                                                                          \
+    "s_bitcmp1_b32 %[cur], %[kind]\n"                                                                      \
+    "s_cbranch_scc1 31f\n"                                                                                 \
+    JPGD_WALK_AC("21", "22", "27", "%[c0]")                                                                \
+    "s_cbranch_scc0 29f\n"                                                                                 \
+    /* unit complete */                                                                                    \
+    "23:\n"                                                                                                \
+    "s_add_u32 %[nb], %[nb], 1\n"                                                                          \
+    "s_and_b32 %[S], %[S], 0x7f\n"                                                                         \
+    "s_and_b32 %[t], %[cur], 15\n"                                                                         \
+    "s_bitcmp1_b32 %[S], 6\n"                                                                              \
+    "v_readlane_b32 %[cur], %[uw], %[t]\n"                                                                 \
+    "s_cbranch_scc1 29f\n"                                                                                 \
+    /* DC symbol at position S (its zig-zag index is 0): entry of the table, its value, the component's sum */ \
+    "20:\n"                                                                                                \
+    "v_readlane_b32 %[r], %[d0], %[S]\n"                                                                   \
+    "v_readlane_b32 %[r2], %[d1], %[S]\n"                                                                  \
+    "v_readlane_b32 %[v], %[peek], %[S]\n"                                                                 \
+    "s_bitcmp1_b32 %[cur], %[kind]\n"                                                                      \
+    "s_cselect_b32 %[r], %[r2], %[r]\n"                                                                    \
+    THIRD("v_readlane_b32 %[r2], %[d2], %[S]\n"                                                            \
+          "s_bitcmp1_b32 %[cur], %[kind] + 1\n"                                                            \
+          "s_cselect_b32 %[r], %[r2], %[r]\n")                                                             \
+    "s_bitcmp1_b32 %[r], 31\n"                                                                             \
+    "s_cbranch_scc1 28f\n"                                                                                 \
+    "24:\n"                                                                                                \
+    "s_and_b32 %[t], %[r], 31\n"                                                                           \
+    "s_bfe_u32 %[r2], %[r], %[f_size]\n"                                                                   \
+    "s_sub_u32 %[t], 32, %[t]\n"                                                                           \
+    "s_lshl_b32 %[t2], %[r2], 16\n"                                                                        \
+    "s_or_b32 %[t], %[t], %[t2]\n"                                                                         \
+    "s_bfe_i32 %[v], %[v], %[t]\n"        /* the value's bits, signed (none: 0) */                         \
+    "s_ashr_i32 %[t], %[v], 31\n"                                                                          \
+    "s_lshl_b32 %[t2], -1, %[r2]\n"                                                                        \
+    "s_xor_b32 %[t], %[t], %[t2]\n"                                                                        \
+    "s_add_i32 %[v], %[v], %[t]\n"                                                                         \
+    "s_add_i32 %[v], %[v], 1\n"           /* the difference, as in symbol_value */                         \
+    "s_bfe_u32 %[t], %[cur], %[f_shift]\n"                                                                 \
+    "s_lshl_b32 %[v], %[v], %[t]\n"                                                                        \
+    "s_bitcmp1_b32 %[cur], %[b_second]\n"                                                                  \
+    "s_cselect_b32 %[t], %[v], 0\n"                                                                        \
+    "s_cselect_b32 %[v], 0, %[v]\n"                                                                        \
+    "s_add_u32 %[dcb], %[dcb], %[t]\n"                                                                     \
+    "s_add_u32 %[dca], %[dca], %[v]\n"                                                                     \
+    "s_and_b32 %[r], %[r], 0x7e1f\n"                                                                       \
+    "s_add_u32 %[S], %[S], %[r]\n"        /* the index becomes 1 */                                        \
+    "s_bitcmp1_b32 %[S], 6\n"                                                                              \
+    "s_cbranch_scc1 29f\n"                                                                                 \
+    THIRD("s_bitcmp1_b32 %[cur], %[kind] + 1\n"                                                            \
+          "s_cbranch_scc1 41f\n")                                                                          \
+    "s_bitcmp1_b32 %[cur], %[kind]\n"                                                                      \
+    "s_cbranch_scc0 21b\n"                                                                                 \
+    JPGD_WALK_AC("31", "32", "37", "%[c1]")                                                                \
+    "s_cbranch_scc1 23b\n"                                                                                 \
+    /* the window ends */                                                                                  \
+    "29:\n"                                                                                                \
+    "s_sub_u32 %[S], %[S], 64\n"          /* the same position, seen from the next window */               \
+    "s_sub_u32 %[left], %[left], 1\n"                                                                      \
+    "s_cmp_lg_u32 %[left], 0\n"                                                                            \
+    "s_cbranch_scc1 1b\n"                                                                                  \
+    "s_branch 40f\n"                                                                                       \
+    THIRD(JPGD_WALK_AC("41", "42", "47", "%[c2]")                                                          \
+          "s_cbranch_scc1 23b\n"                                                                           \
+          "s_branch 29b\n"                                                                                 \
+          JPGD_WALK_ESCAPE("47", "41", "%[a2]", "%[c2]", "%[a0]", "%[c0]"))                                \
+    JPGD_WALK_ESCAPE("27", "21", "%[a0]", "%[c0]", "%[a1]", "%[c1]")                                       \
+    JPGD_WALK_ESCAPE("37", "31", "%[a1]", "%[c1]", "%[a0]", "%[c0]")                                       \
+    /* an escape of a DC table */                                                                          \
+    "28:\n"                                                                                                \
+    "s_bfe_u32 %[t], %[r], %[f_n]\n"                                                                       \
+    "s_sub_u32 %[t2], 23, %[t]\n"                                                                          \
+    "s_lshl_b32 %[t], %[t], 16\n"                                                                          \
+    "s_or_b32 %[t], %[t], %[t2]\n"                                                                         \
+    "s_bfe_u32 %[t], %[v], %[t]\n"                                                                         \
+    "s_lshl_b32 %[t], %[t], 2\n"                                                                           \
+    "s_lshr_b32 %[r], %[r], 15\n"                                                                          \
+    "s_and_b32 %[r], %[r], 0xfff8\n"                                                                       \
+    "s_add_u32 %[t], %[t], %[r]\n"                                                                         \
+    "v_mov_b32 %[c0], %[t]\n"                                                                              \
+    "ds_read_b32 %[c0], %[c0]\n"                                                                           \
+    "s_waitcnt lgkmcnt(0)\n"                                                                               \
+    "v_readfirstlane_b32 %[r], %[c0]\n"                                                                    \
+    "v_and_b32 %[c0], 0xfe1f, %[a0]\n"                                                                     \
+    "s_branch 24b\n"                                                                                       \
+    "40:\n"                                                                                                \
+    "s_waitcnt lgkmcnt(0)\n"
+#define JPGD_WALK_RESULTS                                                                                  \
+    [S] "+&s"(S), [cur] "+&s"(cur), [left] "+&s"(left), [nb] "+&s"(nb), [dca] "+&s"(dc_a), [dcb] "+&s"(dc_b), [at] "+&v"(at), \
+        [d0] "=&v"(d0), [d1] "=&v"(d1), [a0] "=&v"(a0), [a1] "=&v"(a1), [c0] "=&v"(c0), [c1] "=&v"(c1), [peek] "=&v"(peek), \
+        [nd0] "=&v"(nd0), [nd1] "=&v"(nd1), [na0] "=&v"(na0), [na1] "=&v"(na1), [npeek] "=&v"(npeek), [x0] "=&v"(x0), \
+        [x1] "=&v"(x1), [t] "=&s"(t), [t2] "=&s"(t2), [r] "=&s"(r), [r2] "=&s"(r2), [v] "=&s"(v), [all] "=&s"(all)
+#define JPGD_WALK_INPUTS                                                                                   \
+    [shift] "v"(shift), [uw] "v"(unit_word), [bd0] "s"(ct.dc0), [ba0] "s"(ct.ac0), [bd1] "s"(ct.dc1), [ba1] "s"(ct.ac1), \
+        [kind] "i"(kUwKind), [f_size] "i"(bit_field(20u, 4u)), [f_shift] "i"(bit_field(kUwShift, 5u)),    \
+        [b_second] "i"(kUwSecond), [f_n] "i"(bit_field(6u, 3u))
+#define JPGD_NO_THIRD(text)
+#define JPGD_THIRD(text) text
+    if constexpr (THREE) {
+        uint32_t d2, a2, c2, nd2, na2;
+        asm volatile(JPGD_WALK(JPGD_THIRD)
+                     : JPGD_WALK_RESULTS, [d2] "=&v"(d2), [a2] "=&v"(a2), [c2] "=&v"(c2), [nd2] "=&v"(nd2), [na2] "=&v"(na2)
+                     : JPGD_WALK_INPUTS, [bd2] "s"(ct.dc2), [ba2] "s"(ct.ac2)
+                     : "vcc", "scc", "memory");
+    } else {
+        asm volatile(JPGD_WALK(JPGD_NO_THIRD) : JPGD_WALK_RESULTS : JPGD_WALK_INPUTS : "vcc", "scc", "memory");
+    }
+#undef JPGD_WALK_AC
+#undef JPGD_WALK_ESCAPE
+#undef JPGD_WALK
+#undef JPGD_WALK_RESULTS
+#undef JPGD_WALK_INPUTS
+#undef JPGD_NO_THIRD
+#undef JPGD_THIRD
     p_io = limit + (S & 0x7Fu);
     z_io = S >> 9;
     const uint32_t next = cur & 15u;  // of the unit the chain is in now
@@ -903,6 +917,11 @@ __device__ __forceinline__ void coop_span_sync(uint32_t& p_io, uint32_t& u_io, u
     nb_out = nb;
     const int32_t s0 = (int32_t)(int16_t)(dc_a & 0xFFFFu), s1 = (int32_t)(dc_a - (uint32_t)s0) >> 16;
     dc_out = (int64_t)s0 + ((int64_t)s1 << 15) + ((int64_t)(int32_t)dc_b << 30);
+}
+__device__ __forceinline__ void coop_span_sync(uint32_t& p, uint32_t& u, uint32_t& z, uint32_t& nb, int64_t& dc, uint32_t limit,
+                                               uint32_t words, uint32_t unit_word, uint32_t upm, const CoopTables& ct) {
+    if (__builtin_expect(ct.three, false)) coop_span_kinds<true>(p, u, z, nb, dc, limit, words, unit_word, upm, ct);
+    else coop_span_kinds<false>(p, u, z, nb, dc, limit, words, unit_word, upm, ct);
 }
 
 // The words the walk reads, for kernels that do not keep the stream in LDS: those from the window of bit p on, copied to `buf`
@@ -1376,10 +1395,9 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     // that frees a whole wavefront: a chain is (p, u, z, target), everything else is rebuilt from the staged
     // stream, so moving one costs two LDS words.  Between packings a round costs one barrier: the count of
     // running chains goes through one LDS word per wavefront, double-buffered by the parity of the round.
-    // The wavefront-per-chain code does not know more than two kinds of data units.  In a workgroup that sees restart intervals
-    // a chain may fall back to a single lane for a round (below): at most one chain per wavefront then, so that
+    // In a workgroup that sees restart intervals a chain may fall back to a single lane for a round (below): at most one chain per wavefront then, so that
     // such rounds never take longer than the packed ones they replace.
-    const uint32_t coop_max = D.walk == 0u ? 0u : (restart ? min(P.coop_max, P.sync_waves) : P.coop_max);
+    const uint32_t coop_max = restart ? min(P.coop_max, P.sync_waves) : P.coop_max;
     uint32_t coop_n = 0u;
     for (uint32_t round = 0u;; ++round) {
         const uint64_t bal = __ballot(active);
@@ -1588,7 +1606,7 @@ __global__ __launch_bounds__(64) void k_sync_inter(Params P) {
     // the slowest of them.  With few in this workgroup, each is walked by the whole wavefront, one after the other
     // (same results as the lane's loop below; the wavefront's decoder does not know restart intervals).
     const uint64_t workers = __ballot(work);
-    if (!D.restart && D.walk != 0u && __popcll(workers) <= kInterCoopMax) {
+    if (!D.restart && __popcll(workers) <= kInterCoopMax) {
         const uint32_t lane = threadIdx.x;
         const uint32_t unit_word = coop_unit_word(D, lane);
         const uint32_t u_upm = __builtin_amdgcn_readfirstlane(D.upm);

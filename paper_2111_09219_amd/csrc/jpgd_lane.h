@@ -669,6 +669,42 @@ JPGD_HD void decode_span_write(Lane& l, BitWin& w, uint32_t limit, uint32_t& uni
     l.p = win_pos(w);
 }
 
+// ---- the walk of a whole wavefront ---------------------------------------------------------------------------
+// What the walk through a single chain (coop_span_sync in jpgd_kernels.h) needs to know of the image's data units.
+//
+// Data units that share a DC and an AC table are of one kind; with a pair of tables per component there are at most three.
+// The word, made by the host: bits 0..11 kind of each unit of the MCU (2 bits each), from kWalkSlots on the slots of the DC
+// and the AC table of kinds 0, 1 and 2 (3 bits each; those of a kind that is not there are kind 0's), bit kWalkThree: there
+// are three.
+constexpr uint32_t kWalkSlots = 12u, kWalkThree = 30u;
+JPGD_HD uint32_t walk_word(uint32_t upm, uint32_t sched_dc, uint32_t sched_ac) {
+    uint32_t word = 0u, kinds = 0u, slots[3] = {0u, 0u, 0u};
+    for (uint32_t u = 0; u < upm; ++u) {
+        const uint32_t mine = ((sched_dc >> (4u * u)) & 15u) | ((sched_ac >> (4u * u)) & 15u) << 3;
+        uint32_t k = 0;
+        while (k < kinds && slots[k] != mine) ++k;
+        if (k == kinds) slots[kinds++] = mine;
+        word |= k << (2u * u);
+    }
+    for (uint32_t k = 0; k < 3u; ++k) word |= slots[k < kinds ? k : 0u] << (kWalkSlots + 6u * k);
+    return word | (kinds == 3u ? 1u << kWalkThree : 0u);
+}
+
+// Data unit u of the MCU for the walk: index of the unit that follows (bits 0..3), its kind (4..5), and where its DC
+// differences go in the walk's two sums: shift inside the first word (10..14: 0 for component 0, 16 for component 1), or the
+// second word (bit 15, component 2)
+constexpr uint32_t kUwKind = 4u, kUwShift = 10u, kUwSecond = 15u;
+JPGD_HD uint32_t walk_unit(uint32_t walk, uint32_t sched_comp, uint32_t upm, uint32_t u) {
+    const uint32_t next = u + 1u == upm ? 0u : u + 1u, comp = (sched_comp >> (4u * u)) & 15u;
+    return next | (((walk >> (2u * u)) & 3u) << kUwKind) | (comp == 2u ? 1u << kUwSecond : comp * 16u << kUwShift);
+}
+
+// Where the tables of kind k lie; tab: byte at which the tables begin.
+JPGD_HD uint32_t walk_dc(uint32_t walk, uint32_t k, uint32_t tab) { return tab + ((walk >> (kWalkSlots + 6u * k)) & 7u) * kSyncDcBytes; }
+JPGD_HD uint32_t walk_ac(uint32_t walk, uint32_t k, uint32_t ndc, uint32_t tab) {
+    return tab + ndc * kSyncDcBytes + (((walk >> (kWalkSlots + 6u * k + 3u)) & 7u) - ndc) * kSyncAcBytes;
+}
+
 // ---- restart intervals -------------------------------------------------------------------------------
 // A scan with restart intervals (DRI) is a chain of independently coded intervals: each ends with up to seven
 // 1-bits of padding and a marker RSTm, and the next starts byte-aligned with the DC predictors at zero.  The

@@ -3,8 +3,10 @@
 // never calls it.
 //
 // Build: g++ -O2 -std=c++17 -shared -fPIC -o libjpgd_sync.so jpgd_sync.cpp ../../paper_2111_09219_amd/csrc/jpgd_parse.cpp
+#include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <utility>
 #include <vector>
@@ -13,6 +15,7 @@
 #include "../../paper_2111_09219_amd/csrc/jpgd_common.h"
 #include "../../paper_2111_09219_amd/csrc/jpgd_lane.h"
 #include "../../paper_2111_09219_amd/csrc/jpgd_lut.h"
+#include "jpgd_walk.h"
 
 using namespace jpgd;
 
@@ -64,7 +67,7 @@ struct Scan {
     uint32_t nbits = 0;
     UnitRow rows[8];
     SyncRow srows[8], wrows[8];
-    uint32_t sched_comp = 0;
+    uint32_t sched_comp = 0, walk = 0;
 };
 
 // build_lut's tables for the plain lanes
@@ -105,6 +108,7 @@ int open_scan(const uint8_t* file, size_t len, Scan& S) {
         S.wrows[k].dcmul = ((sched_comp >> (4 * k)) & 15) != ((sched_comp >> (4 * ((k + 1) % u))) & 15) ? 1u : 0u;
     }
     S.sched_comp = sched_comp;
+    S.walk = walk_word(u, sched_dc, sched_ac);
     const uint8_t* p = file + in.scan_offset;
     S.bmap.assign(in.scan_bytes / 32 + 80, 0);
     for (size_t k = 0; k < in.scan_bytes; ++k) {
@@ -318,6 +322,44 @@ extern "C" int lanes_restarted(const uint8_t* file, size_t len, uint32_t tries, 
             write_span(x, p + 1u, 2u, word, wtab, wrows, [&](uint32_t u, uint32_t at, int16_t v) { sx.push_back({u * 64u + at, v}); });
             write_span(y, p + 1u, 2u, word, wtab, wrows, [&](uint32_t u, uint32_t at, int16_t v) { sy.push_back({u * 64u + at, v}); });
             bad += sx != sy || x.seen != y.seen || x.s.S != a.S || y.s.S != a.S || x.s.row != a.row || sync_pos(x.s) != sync_pos(a);
+        }
+    }
+    return bad;
+}
+
+// The walk of a whole wavefront from `tries` random states over `spans` subsequences of L bits against sync_span: mismatches in
+// state, unit count and DC sums (where those fit the fields they are kept in).  *kinds: of data units.
+extern "C" int walk_vs_lanes(const uint8_t* file, size_t len, uint32_t L, uint32_t tries, uint32_t spans, uint32_t seed,
+                             uint32_t* compared, uint32_t* kinds) {
+    Scan S;
+    const int rc = open_scan(file, len, S);
+    if (rc) return -rc;
+    const uint32_t* words = (const uint32_t*)S.stream.data();
+    auto word = [&](uint32_t b) { return b / 32 < S.stream.size() / 4 ? __builtin_bswap32(words[b / 32]) : 0u; };
+    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.sync.at((k - kBase) / 4); };
+    auto rows = [&](uint32_t k) { return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
+    const uint32_t upm = S.in.units_per_mcu;
+    const Walk w = make_walk(S.walk, S.sched_comp, upm, S.t.ndc, kBase);
+    *kinds = 0;
+    for (uint32_t u = 0; u < upm; ++u) *kinds = std::max(*kinds, ((S.walk >> (2u * u)) & 3u) + 1u);
+    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
+    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    int bad = 0;
+    *compared = 0;
+    for (uint32_t k = 0; k < tries; ++k) {
+        const uint32_t nsub = (S.nbits + L - 1) / L, i0 = rnd(nsub);
+        uint32_t p = i0 * L + (rnd(4) ? rnd(31) : 0u), u = rnd(upm), z = rnd(3) ? rnd(64) : 0u;
+        SyncLane b;
+        sync_start(b, p, u, z, upm, kRow0, word, tab, rows);
+        for (uint32_t i = i0; i < i0 + spans && i < nsub; ++i, ++*compared) {
+            uint32_t nb;
+            int64_t da, db = 0;
+            int32_t exact[3];
+            b.nb = 0;
+            walk_span(p, u, z, nb, da, exact, (i + 1) * L, w, word, tab);
+            sync_span(b, (i + 1) * L, db, word, tab, rows);
+            const bool fits = std::abs(exact[0]) < 16384 && std::abs(exact[1]) < 16384 && std::abs(exact[2]) < 16384;
+            if (p != sync_pos(b) || u != (b.row - kRow0) / sizeof(SyncRow) || z != ((b.S >> 9) & 63u) || nb != b.nb || (fits && da != db)) { ++bad; break; }
         }
     }
     return bad;

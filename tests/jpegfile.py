@@ -144,3 +144,79 @@ def relabelled_as_1x2(data: np.ndarray) -> np.ndarray:
             assert b[at + 11] == 0x21
             b[at + 11] = 0x12
     return np.frombuffer(bytes(b), np.uint8).copy()
+
+
+def written_with_tables(enc, td, ta) -> np.ndarray:
+    """The scan of an encoded three-component file (workloads.EncodedJpeg with its coefficients, without restart intervals,
+    typical tables) written once more with other tables: component c takes DC table td[c] and AC table ta[c], where 0 and 1
+    are the file's own and 2 and 3 copies of 1.  The same coefficients."""
+    b = np.asarray(enc.data, np.uint8).tobytes()
+    tabs, sos_at, sampling = {}, None, None
+    for at, mk, ln in _segments(b):
+        if mk == 0xC4:
+            j = at + 4
+            while j < at + 2 + ln:
+                n = sum(b[j + 1:j + 17])
+                tabs[(b[j] >> 4, b[j] & 15)] = (b[j + 1:j + 17], b[j + 17:j + 17 + n])
+                j += 17 + n
+        if mk == 0xC0:
+            sampling = b[at + 11]
+        if mk == 0xDA:
+            sos_at = at
+    extra = b""
+    for cls in (0, 1):
+        for tid in (2, 3):
+            tabs[(cls, tid)] = tabs[(cls, 1)]
+            if tid in (td, ta)[cls]:
+                extra += dht(cls, tid, *tabs[(cls, tid)])
+    luma = (sampling >> 4) * (sampling & 15)
+    coef = enc.coef.astype(np.int64)
+    n = coef.shape[0]
+    comp = np.tile([0] * luma + [1, 2], n // (luma + 2))
+    unit_diff = np.zeros(n, np.int64)
+    for c in range(3):
+        unit_diff[comp == c] = np.diff(coef[comp == c, 0], prepend=0)
+    # symbols in order: unit, zig-zag index, runs of sixteen zeros in front of a coefficient
+    uu, zz = np.nonzero(coef[:, 1:])
+    zz = zz + 1
+    first = np.diff(uu, prepend=-1) != 0
+    run = zz - np.where(first, 0, np.concatenate([[0], zz[:-1]])) - 1
+    zrl = run >> 4
+    last = np.zeros(n, np.int64)
+    np.maximum.at(last, uu, zz)
+    eob = np.flatnonzero(last < 63)
+    of = np.repeat(np.arange(uu.size), zrl)          # coefficient that a run of sixteen belongs to
+    nth = np.arange(of.size) - np.repeat(np.cumsum(zrl) - zrl, zrl)
+    unit = np.concatenate([np.arange(n), uu, uu[of], eob])
+    order = np.concatenate([np.zeros(n, np.int64), zz * 8 + 7, zz[of] * 8 + nth, np.full(eob.size, 64 * 8)])
+    value = np.concatenate([unit_diff, coef[uu, zz], np.zeros(of.size + eob.size, np.int64)])
+    cls = np.concatenate([np.zeros(n, np.int64), np.ones(uu.size + of.size + eob.size, np.int64)])
+    size = np.where(value == 0, 0, np.floor(np.log2(np.maximum(np.abs(value), 1))).astype(np.int64) + 1)
+    symbol = np.concatenate([size[:n], (run & 15) << 4, np.full(of.size, 0xF0), np.zeros(eob.size, np.int64)])
+    symbol[n:n + uu.size] |= size[n:n + uu.size]
+    table = np.where(cls == 0, np.asarray(td)[comp[unit]], np.asarray(ta)[comp[unit]])
+    code, length = np.zeros((2, 4, 256), np.int64), np.zeros((2, 4, 256), np.int64)
+    for (k, tid), (bits, vals) in tabs.items():
+        next_code, at = 0, 0
+        for ln in range(1, 17):
+            for v in vals[at:at + bits[ln - 1]]:
+                code[k, tid, v], length[k, tid, v] = next_code, ln
+                next_code += 1
+            at += bits[ln - 1]
+            next_code <<= 1
+    k = np.lexsort((order, unit))
+    cls, table, symbol, value, size = cls[k], table[k], symbol[k], value[k], size[k]
+    assert (length[cls, table, symbol] > 0).all()
+    word = (code[cls, table, symbol] << size) | np.where(value < 0, value + (1 << size) - 1, value)
+    total = length[cls, table, symbol] + size
+    end = np.cumsum(total)
+    bits = np.ones(int(end[-1] + 7) // 8 * 8, np.uint8)
+    for j in range(int(total.max())):
+        on = total > j
+        bits[(end - total + j)[on]] = (word[on] >> (total[on] - 1 - j)) & 1
+    raw = np.packbits(bits)
+    scan = np.insert(raw, np.flatnonzero(raw == 0xFF) + 1, 0).astype(np.uint8)
+    head = bytearray(b[:sos_at] + extra + b[sos_at:enc.scan_offset])
+    for c in range(3):
+        head[sos_at + len(extra) + 6 + 2 * c] = td[c] << 4 | ta[c]
+    return np.concatenate([np.frombuffer(bytes(head), np.uint8), scan, np.array([0xFF, 0xD9], np.uint8)])

@@ -361,9 +361,9 @@ def test_randomised_calls_in_the_regime_of_many_inter_sequence_rounds():
 
 
 def test_six_tables_and_1x2_sampling():
-    """A file whose components each have a DC and an AC table of their own (six tables: the rounds with one
-    wavefront per chain, which know four, stay off) and a file with luma sampled 1x2; alone, and both in one call
-    with an ordinary file between them (the table sets differ from image to image)."""
+    """A file whose components each have a DC and an AC table of their own (six tables, three kinds of data units) and a
+    file with luma sampled 1x2; alone, and both in one call with an ordinary file between them (the table sets differ
+    from image to image)."""
     px = small_image(5, 397, 531, sigma=9.0)
     plain = encode_jpeg(px, 90, "444", False).data
     six = jf.with_tables_of_its_own_for_the_third_component(plain)

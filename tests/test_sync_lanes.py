@@ -7,6 +7,7 @@ import subprocess
 import numpy as np
 import pytest
 
+import jpegfile as jf
 from oracle import OracleImage
 from workloads import encode_jpeg, small_image
 
@@ -18,7 +19,7 @@ EMUL_DIR = os.path.join(ROOT, "tests", "emul")
 def lanes():
     lib_path, src = os.path.join(EMUL_DIR, "libjpgd_sync.so"), os.path.join(EMUL_DIR, "jpgd_sync.cpp")
     csrc = os.path.join(ROOT, "paper_2111_09219_amd", "csrc")
-    deps = [src] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
+    deps = [src, os.path.join(EMUL_DIR, "jpgd_walk.h")] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
     if not os.path.exists(lib_path) or any(os.path.getmtime(d) > os.path.getmtime(lib_path) for d in deps):
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", lib_path, src,
                                os.path.join(csrc, "jpgd_parse.cpp")])
@@ -27,6 +28,7 @@ def lanes():
     lib.sync_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, u32, vp]
     lib.write_vs_plain.argtypes = [vp, ctypes.c_size_t, u32, u32, ctypes.c_int, u32, u32, u32, vp]
     lib.sync_table_vs_lut.argtypes = [vp, vp, ctypes.c_int]
+    lib.walk_vs_lanes.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, u32, vp, vp]
     lib.lanes_restarted.argtypes = [vp, ctypes.c_size_t, u32, u32, u32, vp]
     return lib
 
@@ -78,6 +80,23 @@ def test_position_unit_and_index_say_all_about_a_lane(lanes, sub, opt, q):
     n = ctypes.c_uint32()
     assert lanes.lanes_restarted(data.ctypes.data, data.size, 3000, 40, 7, ctypes.byref(n)) == 0
     assert n.value > 50000
+
+
+# tables of the three components and the kinds of data units they make: one pair, two, a component with a pair of its own in four
+# tables (which are all a baseline file may have; also one class with three of them) and in six
+PAIRINGS = [((0, 0, 0), (1, 1, 1), 1), ((0, 1, 1), (0, 1, 1), 2), ((0, 1, 0), (0, 1, 1), 3), ((1, 1, 0), (0, 1, 1), 3),
+            ((0, 0, 0), (0, 1, 2), 3), ((0, 1, 2), (1, 1, 1), 3), ((0, 1, 2), (0, 1, 2), 3), ((0, 1, 0), (0, 1, 0), 2)]
+
+
+@pytest.mark.parametrize("td,ta,kinds", PAIRINGS)
+@pytest.mark.parametrize("sub,q,L", [("420", 90, 128), ("444", 60, 1024), ("422", 97, 256)])
+def test_walk_equals_the_lanes_for_every_pairing_of_tables(lanes, td, ta, kinds, sub, q, L):
+    """The walk of a whole wavefront knows the image's data units by the word the host makes of them; whatever tables the
+    components share, it must take the symbols a lane takes."""
+    data = jf.written_with_tables(encode_jpeg(small_image(33, 96, 144, sigma=16.0), q, sub), td, ta)
+    n, k = ctypes.c_uint32(), ctypes.c_uint32()
+    assert lanes.walk_vs_lanes(data.ctypes.data, data.size, L, 1500, 4, 5, ctypes.byref(n), ctypes.byref(k)) == 0
+    assert n.value > 1000 and k.value == kinds
 
 
 def test_tables_hold_what_the_first_ones_hold(lanes):
