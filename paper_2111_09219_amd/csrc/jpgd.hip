@@ -230,8 +230,9 @@ int make_plan(const jpgd_info* infos, int n, const jpgd_config* cfg, Plan& pl) {
     {
         const uint32_t mode = cfg ? cfg->sync_split : 0u;
         if (mode > 2u) return JPGD_E_ARG;
-        // (not with restart intervals: their second kernel, with one chain per wavefront at most and single-symbol
-        // steps, takes longer than it saves -- 15360x8640 with one interval per MCU row 2.13 against 2.10 ms)
+        // (not with restart intervals, which end most chains early and leave those whose stretch meets one to a single lane:
+        // calls in one kernel / in two, 15360x8640 with an interval per MCU row 2.24 / 2.25 to 2.34 ms, per 50 rows 2.75 /
+        // 3.05, per 16 MCUs 2.54 / 2.54, eight images of 4096x4096 per row 1.02 / 1.03, per 16 rows 0.84 / 0.86)
         // (nor with more than the four tables a baseline file may have)
         const bool can = pl.bmap_words == 0u && pl.lut_slots <= 4u;
         pl.split = can && (mode == 2u || (mode == 0u && L >= 512u && pl.seqs >= (uint32_t)kSplitMinSeqs));
