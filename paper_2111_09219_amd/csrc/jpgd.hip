@@ -294,8 +294,7 @@ struct jpgd_call {
     Params P;
     hipStream_t stream = nullptr;
     uint8_t* ws = nullptr;
-    bool want_pixels = false, staged = false, big_groups = false;
-    int variant = 0;
+    bool want_pixels = false, big_groups = false;
     size_t lds_sync = 0, lds_write = 0, lds_inter = 0;
     uint32_t tmask = 0, max_rounds = 0, rounds = 0, redo = 0;
     std::vector<Timed> timed;
@@ -480,23 +479,12 @@ int wait_verdict(Call& c) {
     return JPGD_OK;
 }
 
-// subsequences of up to this many bits are staged in LDS by the sync and write kernels
-// (JPGD_STAGED_MAX_BITS overrides it for tuning runs)
-uint32_t staged_max_bits() {
-    static const uint32_t v = [] {
-        const char* e = getenv("JPGD_STAGED_MAX_BITS");
-        return e ? (uint32_t)atoi(e) : 2048u;
-    }();
-    return v;
-}
-#define kStagedMaxL staged_max_bits()
-
 // with restart intervals the kernels also keep the interval-start bitmap of the staged bytes: one bit per byte
 size_t lds_bitmap_bytes(uint32_t L, bool restart) {
     return restart && L <= (uint32_t)kBitmapLdsMaxL ? ((size_t)(kWG * (L / 32) + 4 + 7) / 8 + 2) * 4 : 0;
 }
 size_t lds_sync_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
-    uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + kSyncPadWords : kSyncWavesMax * kCoopBufWords;
+    const uint32_t nwords = kWG * (L / 32) + kSyncPadWords;
     return (size_t)tab_bytes + kSyncFixedWords * 4 + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
 }
 // the second of the two synchronisation kernels keeps the tables and the records, not the stream
@@ -505,8 +493,7 @@ size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + (kSyncFix
 constexpr uint32_t kSyncTabMax = kMaxPairs * (kSyncDcBytes + kSyncAcBytes) + kMaxPairs * 4 * (1022u + kLutL2);
 static_assert(kSyncTabMax <= 8u << 13, "an escape has 13 bits for its subtable");
 size_t lds_write_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
-    uint32_t nwords = L <= kStagedMaxL ? kWG * (L / 32) + 4 : 4;
-    return (size_t)tab_bytes + (size_t)nwords * 4 + lds_bitmap_bytes(L, restart);
+    return (size_t)tab_bytes + (size_t)(kWG * (L / 32) + 4) * 4 + lds_bitmap_bytes(L, restart);
 }
 
 // The write kernel that gathers its output in LDS is granted the most it may ever ask for, so that calls of different
@@ -516,7 +503,8 @@ constexpr size_t kLdsTiledMax = 160 * 1024 - 2048;
 static_assert(2u * (kSyncDcBytes + kSyncAcBytes + 4u * kLutL2) + (kWG * (kTileMaxL / 32) + 4) * 4 + kTileBytes <= kLdsTiledMax, "with the kernel's static LDS on one CU");
 
 // dynamic LDS beyond the default limit has to be requested per kernel and device; remember what was granted
-size_t g_lds_granted[kMaxDevices][9];
+enum { kLdsSync, kLdsSyncRst, kLdsHead, kLdsInter, kLdsWrite, kLdsTile, kLdsKernels };
+size_t g_lds_granted[kMaxDevices][kLdsKernels];
 int grant_lds(int dev, int which, const void* kernel, size_t bytes) {
     if (bytes <= 48 * 1024) return JPGD_OK;
     std::lock_guard<std::mutex> lock(g_mu);
@@ -566,9 +554,8 @@ int launch_scan(Call& c, bool totals) {
 }
 
 int launch_write(Call& c) {
-    if (c.P.tile_bytes) LAUNCH(JPGD_K_WRITE, (k_write<true, true>), c.pl.grps, kWG, c.P.tile_off + c.P.tile_bytes);
-    else if (c.staged) LAUNCH(JPGD_K_WRITE, (k_write<true, false>), c.pl.grps, kWG, c.lds_write);
-    else LAUNCH(JPGD_K_WRITE, (k_write<false, false>), c.pl.grps, kWG, c.lds_write);
+    if (c.P.tile_bytes) LAUNCH(JPGD_K_WRITE, k_write<true>, c.pl.grps, kWG, c.P.tile_off + c.P.tile_bytes);
+    else LAUNCH(JPGD_K_WRITE, k_write<false>, c.pl.grps, kWG, c.lds_write);
     return JPGD_OK;
 }
 
@@ -616,7 +603,6 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.stream = stream;
     c.ws = (uint8_t*)d_workspace;
     const bool any_restart = pl.bmap_words != 0u;
-    c.staged = pl.L <= kStagedMaxL;
     rc = call_reserve(c, pl.h.upload_bytes + 16);
     if (rc) return rc;
     uint8_t* up = c.buf;
@@ -665,22 +651,19 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     c.lds_inter = tab_bytes;
     const uint32_t tile_off = (uint32_t)((c.lds_write + 15u) & ~(size_t)15u);
     uint32_t tile_bytes = 0u;
-    if (c.staged && !any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups)
+    if (!any_restart && pl.L <= (uint32_t)kTileMaxL && pl.grps <= (uint32_t)kTileMaxGroups)
         for (int i = 0; i < n; ++i) {
             const uint32_t room = tile_room(infos[i].total_units, infos[i].scan_bytes, pl.L);
             if (room > tile_bytes) tile_bytes = room;
         }
     if (tile_bytes > kLdsTiledMax - tile_off) tile_bytes = (uint32_t)(kLdsTiledMax - tile_off) & ~15u;
     if (c.lds_sync > 150 * 1024) return JPGD_E_ARG;
-    // the variants of the intra-sequence kernel: stream staged in LDS or not, call with or without restart intervals
-    c.variant = (c.staged ? 0 : 1) + (any_restart ? 2 : 0);
-    const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
-                                         (const void*)k_sync_intra<true, true>, (const void*)k_sync_intra<false, true>};
-    if ((rc = grant_lds(c.device, c.variant, sync_kernels[c.variant], c.lds_sync)) ||
-        (rc = grant_lds(c.device, c.staged ? 4 : 5, c.staged ? (const void*)k_write<true, false> : (const void*)k_write<false, false>, c.lds_write)) ||
-        (tile_bytes && (rc = grant_lds(c.device, 7, (const void*)k_write<true, true>, kLdsTiledMax))) ||
-        (rc = grant_lds(c.device, 8, (const void*)k_sync_inter, c.lds_inter)) ||
-        (pl.split && c.staged && (rc = grant_lds(c.device, 6, (const void*)k_sync_head<true, false>, c.lds_sync))))
+    if ((rc = any_restart ? grant_lds(c.device, kLdsSyncRst, (const void*)k_sync_intra<true>, c.lds_sync)
+                          : grant_lds(c.device, kLdsSync, (const void*)k_sync_intra<false>, c.lds_sync)) ||
+        (rc = grant_lds(c.device, kLdsWrite, (const void*)k_write<false>, c.lds_write)) ||
+        (tile_bytes && (rc = grant_lds(c.device, kLdsTile, (const void*)k_write<true>, kLdsTiledMax))) ||
+        (rc = grant_lds(c.device, kLdsInter, (const void*)k_sync_inter, c.lds_inter)) ||
+        (pl.split && (rc = grant_lds(c.device, kLdsHead, (const void*)k_sync_head, c.lds_sync))))
         return rc;
     uint8_t* ws = c.ws;
     // The parameter block goes from the pinned buffer into the workspace: for a batch by a kernel of its own (the
@@ -771,17 +754,14 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
         // first kernel: until at most kHandoff chains of a sequence are left; second kernel: the rest, four
         // wavefronts per sequence, the chains from kTailCoopMax down one per wavefront
         P.handoff = kHandoff;
-        if (c.staged) LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_head<true, false>), pl.seqs, kWG, c.lds_sync);
-        else LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_head<false, false>), pl.seqs, kWG, c.lds_sync);
+        LAUNCH(JPGD_K_SYNC_INTRA, k_sync_head, pl.seqs, kWG, c.lds_sync);
         P.sync_waves = (uint32_t)(kWG / 64);
         P.coop_max = kTailCoopMax;
-        LAUNCH(JPGD_K_SYNC_TAIL, (k_sync_tail<false>), pl.seqs, kWG, lds_tail_bytes(tab_bytes));
-    } else
-    switch (c.variant) {
-        case 0: LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_intra<true, false>), pl.seqs, 64u * P.sync_waves, c.lds_sync); break;
-        case 1: LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_intra<false, false>), pl.seqs, 64u * P.sync_waves, c.lds_sync); break;
-        case 2: LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_intra<true, true>), pl.seqs, 64u * P.sync_waves, c.lds_sync); break;
-        default: LAUNCH(JPGD_K_SYNC_INTRA, (k_sync_intra<false, true>), pl.seqs, 64u * P.sync_waves, c.lds_sync); break;
+        LAUNCH(JPGD_K_SYNC_TAIL, k_sync_tail, pl.seqs, kWG, lds_tail_bytes(tab_bytes));
+    } else if (any_restart) {
+        LAUNCH(JPGD_K_SYNC_INTRA, k_sync_intra<true>, pl.seqs, 64u * P.sync_waves, c.lds_sync);
+    } else {
+        LAUNCH(JPGD_K_SYNC_INTRA, k_sync_intra<false>, pl.seqs, 64u * P.sync_waves, c.lds_sync);
     }
     // Everything is launched in one go, write pass and pixels included: nearly every call is settled by one
     // inter-sequence round, and the host need not hear from the GPU in between.
@@ -951,16 +931,13 @@ extern "C" int jpgd_init(void) {
     c->fixed = true;
     // Dynamic LDS of the kernels as the fixed-size entry point may need it (one image, any subsequence size): asked for
     // here, so that the entry point itself changes no attribute of a function.
-    const void* const sync_kernels[4] = {(const void*)k_sync_intra<true, false>, (const void*)k_sync_intra<false, false>,
-                                         (const void*)k_sync_intra<true, true>, (const void*)k_sync_intra<false, true>};
-    for (int v = 0; v < 4; ++v)
-        if ((rc = grant_lds(dev, v, sync_kernels[v], lds_sync_bytes(2048u, kSyncTabMax, v >= 2)))) break;
-    if (!rc) rc = grant_lds(dev, 6, (const void*)k_sync_head<true, false>, lds_sync_bytes(2048u, kSyncTabMax, false));
-    if (!rc) rc = grant_lds(dev, 4, (const void*)k_write<true, false>, lds_write_bytes(2048u, kSyncTabMax, true));
-    if (!rc) rc = grant_lds(dev, 5, (const void*)k_write<false, false>, lds_write_bytes(2048u, kSyncTabMax, true));
-    if (!rc) rc = grant_lds(dev, 7, (const void*)k_write<true, true>, kLdsTiledMax);
-    if (!rc) rc = grant_lds(dev, 8, (const void*)k_sync_inter, kSyncTabMax);
-    if (rc) return rc;
+    if ((rc = grant_lds(dev, kLdsSync, (const void*)k_sync_intra<false>, lds_sync_bytes(2048u, kSyncTabMax, false))) ||
+        (rc = grant_lds(dev, kLdsSyncRst, (const void*)k_sync_intra<true>, lds_sync_bytes(2048u, kSyncTabMax, true))) ||
+        (rc = grant_lds(dev, kLdsHead, (const void*)k_sync_head, lds_sync_bytes(2048u, kSyncTabMax, false))) ||
+        (rc = grant_lds(dev, kLdsWrite, (const void*)k_write<false>, lds_write_bytes(2048u, kSyncTabMax, true))) ||
+        (rc = grant_lds(dev, kLdsTile, (const void*)k_write<true>, kLdsTiledMax)) ||
+        (rc = grant_lds(dev, kLdsInter, (const void*)k_sync_inter, kSyncTabMax)))
+        return rc;
     {
         std::lock_guard<std::mutex> lock(g_mu);
         g_calls.push_back(c);

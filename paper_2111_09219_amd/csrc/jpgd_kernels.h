@@ -1056,8 +1056,8 @@ __device__ __forceinline__ void sync_span_device(SyncLane& l, uint32_t limit, in
 #undef JPGD_SPAN_CLOBBERS
 }
 
-// write_span (jpgd_lane.h, which says what every value is) as the kernels run it where the stream lies in LDS and the image
-// has no restart intervals; in assembly for the reasons given at sync_span_device.  Entry and first predictor change places
+// write_span (jpgd_lane.h, which says what every value is) as the kernels run it in workgroups that see no start of a restart
+// interval; in assembly for the reasons given at sync_span_device.  Entry and first predictor change places
 // from one step to the next, so that neither has to be copied; lanes without a value are switched off for the store instead of
 // branched around.  Kernel with the compiler's loop / with this one (us): batch of 256 87 / 68, 4096x4096 86 / 66, 15360x8640
 // 368 / 320, 48 frames of 1920x1088 (bound by its stores) 158 / 149, 1920x1088 17 / 14, 256x256 gray 20 / 16.5.  A step takes
@@ -1255,9 +1255,7 @@ __device__ __forceinline__ void clear_coefficients(const Params& P, const ImgDes
 // Workgroup w of an image covers the kWG subsequences base .. base+kWG-1, base = w*seq_len - overlap, and
 // publishes the records of the last seq_len of them; the first `overlap` lanes only warm the chain up.
 
-// STAGED: the workgroup's stretch of the stream is copied to LDS first (small subsequences); otherwise lanes
-// read their words from global memory, one refill ahead, which leaves LDS to the tables and lets more
-// workgroups share a CU (large subsequences).
+// The workgroup's stretch of the stream is copied to LDS first, but in the second kernel below.
 // RST: the call has images with restart intervals.  Calls without get a kernel with none of that code in it (the
 // intra-sequence kernel was measured 3 % slower on plain streams with it: registers and code layout).
 // PHASE: kSyncAll = the whole of it in one kernel.  For calls with many more sequences than the chip holds at a time
@@ -1272,9 +1270,10 @@ constexpr uint32_t kHandWords = 4u * kWG;  // per sequence: 3 x kWG record words
 constexpr uint32_t kSyncFixedWords = 7u * kWG / 2u;  // of LDS: records and chains
 constexpr uint32_t kSyncPadWords = 12u;   // behind the stream in LDS: what lanes, and the walk of a whole wavefront, look at
 static_assert(kHandoff < kWG, "chains and their number in kWG words");
-template <bool STAGED, bool RST, int PHASE>
+template <bool RST, int PHASE>
 __device__ __forceinline__ void sync_intra_body(const Params& P) {
-    static_assert(PHASE != kSyncTail || !STAGED, "the second kernel reads the stream from memory");
+    constexpr bool STAGED = PHASE != kSyncTail;  // the second kernel reads the stream from memory
+    static_assert(STAGED || !RST, "the second kernel has no room for a bitmap of interval starts");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     const uint32_t wg = blockIdx.x;
     const uint32_t ii = find_image(P, wg, &ImgDesc::seq0);
@@ -1308,7 +1307,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     stage_tables<false>(P, D, lds_raw, &dc_fill);
     if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
     // scans with restart intervals: the bitmap of interval starts, for the bytes staged above
-    uint32_t* bm_s = strm + (STAGED ? kWG * wps + kSyncPadWords : (uint32_t)kSyncWavesMax * kCoopBufWords);
+    uint32_t* bm_s = strm + kWG * wps + kSyncPadWords;
     const uint32_t bm_k0 = first_word >> 3;
     uint32_t seen = 0u;
     const bool bm_lds = (1u << P.logL) <= (uint32_t)kBitmapLdsMaxL;
@@ -1550,17 +1549,16 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
     if (t == 0u) P.warm_x[wg] = (P.overlap > 0u && P.overlap - 1u >= t0) ? rec[P.overlap - 1u] & 0xFFFFu : 0xFFFFFFFFu;
 }
 
-template <bool STAGED, bool RST>
-__global__ __launch_bounds__(64 * kSyncWavesMax) void k_sync_intra(Params P) {
-    sync_intra_body<STAGED, RST, kSyncAll>(P);
-}
-template <bool STAGED, bool RST>
-__global__ __launch_bounds__(kWG) void k_sync_head(Params P) {
-    sync_intra_body<STAGED, RST, kSyncHead>(P);
-}
 template <bool RST>
+__global__ __launch_bounds__(64 * kSyncWavesMax) void k_sync_intra(Params P) {
+    sync_intra_body<RST, kSyncAll>(P);
+}
+// (calls with restart intervals are not split)
+__global__ __launch_bounds__(kWG) void k_sync_head(Params P) {
+    sync_intra_body<false, kSyncHead>(P);
+}
 __global__ __launch_bounds__(kWG) void k_sync_tail(Params P) {
-    sync_intra_body<false, RST, kSyncTail>(P);
+    sync_intra_body<false, kSyncTail>(P);
 }
 
 // ---- synchronisation, inter-sequence (paper, Algorithm 3, second loop) ------------------------------
@@ -1741,9 +1739,8 @@ __global__ __launch_bounds__(kWG) void k_clear_coefficients(Params P) {
 // fit P.tile_bytes of LDS they are gathered there, value by value, and leave as full lines at the end: such a call
 // waits for its slowest lane, and a lane that only stores into LDS takes a quarter fewer instructions per symbol;
 // nothing is cleared in memory beforehand.
-template <bool STAGED, bool TILE>
+template <bool TILE>
 __global__ __launch_bounds__(kWG) void k_write(Params P) {
-    static_assert(STAGED || !TILE);
     constexpr bool RST = !TILE;  // (a variant without the restart code, as for k_sync_intra, was measured 2 % slower)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
     __shared__ uint32_t scratch[36];
@@ -1791,10 +1788,10 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     } else {
         before = P.grp_pref[wg];
     }
-    if (STAGED) stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
+    stage_stream(P.stream + D.stream_off, first_word, nwords, strm);
     __syncthreads();
     stage_tables<true>(P, D, lds_raw, &dc_fill);
-    uint32_t* bm_s = strm + (STAGED ? kWG * wps + 4u : 4u);
+    uint32_t* bm_s = strm + kWG * wps + 4u;
     const uint32_t bm_k0 = first_word >> 3;
     uint32_t seen = 0u;
     const bool bm_lds = (1u << P.logL) <= (uint32_t)kBitmapLdsMaxL;
@@ -1882,10 +1879,9 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     }
     if (!tiled && !valid) return;
 
-    const uint32_t* gwords = reinterpret_cast<const uint32_t*>(P.stream + D.stream_off) + first_word;
     // The lanes' bits: as in the synchronisation kernels.
-    const uint32_t org = (STAGED ? 8u * lds_at(strm) : 0u) - (first_word << 5);
-    auto word = [&](uint32_t b) { return STAGED ? lds_word(b >> 3) : __builtin_bswap32(gwords[b >> 5]); };
+    const uint32_t org = 8u * lds_at(strm) - (first_word << 5);
+    auto word = [&](uint32_t b) { return lds_word(b >> 3); };
     auto tab = [&](uint32_t k) { return lds_word(k); };
     const uint32_t row0 = lds_at(rows_s);
     auto rows = [&](uint32_t k) { return lds_row(k); };
@@ -1930,11 +1926,7 @@ __global__ __launch_bounds__(kWG) void k_write(Params P) {
     } else if (unit < total) {
         start();
         if (restart) write_span_rst(l, limit + org, total, D.restart * D.upm, org, D.upm, row0, word, tab, rows, store, bword, &flags);
-        else if constexpr (STAGED) {
-            write_span_device<false>(l, limit + org, total, grp_slot, 0u, 0u, grp_coef, chunk);
-        } else {
-            write_span(l, limit + org, total, word, tab, rows, store);
-        }
+        else write_span_device<false>(l, limit + org, total, grp_slot, 0u, 0u, grp_coef, chunk);
     }
     // (in a workgroup with nothing to decode the lane stays where it was: behind the last unit)
     unit = l.unit;
