@@ -491,7 +491,11 @@ size_t lds_sync_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
 size_t lds_tail_bytes(uint32_t tab_bytes) { return (size_t)tab_bytes + (kSyncFixedWords + kWG / 64 * kCoopBufWords) * 4; }
 // most bytes that any image's tables take there
 constexpr uint32_t kSyncTabMax = kMaxPairs * (kSyncDcBytes + kSyncAcBytes) + kMaxPairs * 4 * (1022u + kLutL2);
-static_assert(kSyncTabMax <= 8u << 13, "an escape has 13 bits for its subtable");
+// Static LDS that a synchronisation or write kernel has in front of its tables, at most: rows of the data units, sums, the
+// words of a single chain.
+constexpr uint32_t kLdsStatic = 2048u;
+static_assert(8u * sizeof(SyncRow) + 36u * 4u + 4u + kCoopBufWords * 4u <= kLdsStatic, "k_sync_inter and k_write together");
+static_assert(kLdsStatic + kSyncTabMax <= 8u << 13, "an escape has 13 bits for the byte of LDS, in eights, at which its subtable lies");
 size_t lds_write_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
     return (size_t)tab_bytes + (size_t)(kWG * (L / 32) + 4) * 4 + lds_bitmap_bytes(L, restart);
 }
@@ -499,7 +503,7 @@ size_t lds_write_bytes(uint32_t L, uint32_t tab_bytes, bool restart) {
 // The write kernel that gathers its output in LDS is granted the most it may ever ask for, so that calls of different
 // sizes do not each change its attribute.  (With an image of six tables that are full of long codes there is not the most
 // room behind them.)
-constexpr size_t kLdsTiledMax = 160 * 1024 - 2048;
+constexpr size_t kLdsTiledMax = 160 * 1024 - kLdsStatic;
 static_assert(2u * (kSyncDcBytes + kSyncAcBytes + 4u * kLutL2) + (kWG * (kTileMaxL / 32) + 4) * 4 + kTileBytes <= kLdsTiledMax, "with the kernel's static LDS on one CU");
 
 // dynamic LDS beyond the default limit has to be requested per kernel and device; remember what was granted

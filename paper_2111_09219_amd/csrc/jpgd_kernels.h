@@ -947,6 +947,19 @@ __device__ __forceinline__ uint32_t coop_words(uint32_t* buf, uint32_t p, uint32
 // Measured against the compiler's loop: 15360x8640 head 622 -> 573 us and tail 705 -> 661, eight calls of 1600x1200 160 ->
 // 149, 1001x753 83 -> 77, 3001x2003 with restart intervals 91 -> 89; a lane round of 4096x4096 (L = 1024) 33.5k -> 28.3k
 // cycles.
+// Rules for whoever moves an instruction, here, in write_span_device and in the walk above.  The compiler does not look into the
+// block, and nothing but these makes the results right:
+//  * between a vector compare (or v_addc, v_mad_i64) and a vector instruction that reads the mask it wrote, VCC or a pair of
+//    scalar registers, stand two instructions, or s_nop 1: without them the old mask may be read.  Scalar instructions and
+//    branches on such a mask wait by themselves;
+//  * between a vector instruction and a v_readlane of the register it wrote stands one; a v_readlane's lane never comes from a
+//    scalar register that a vector instruction wrote;
+//  * an LDS or memory instruction's address and 8 bytes of data may be overwritten right behind it, what it loads may be read
+//    only behind a wait.  LDS answers in order, so lgkmcnt(n) waits until all but the last n requests are answered: the
+//    order entry, word, row (and the store, in the tile) is what the counts count.  What the surrounding code has still
+//    outstanding makes them wait longer, never less.  Instructions with no lane on count like others;
+//  * v56..v63 are the block's own (clobbers): rows arrive in v60..v63, behind the row's wait and before the next request for
+//    one v60 and v61 are free; nothing may be outstanding to any register when the block ends.
 // `ahead` is asked for when the window may have moved on and looked at a step later.  STAGED: big-endian words in LDS; else
 // the stream in memory, bytes swapped when the word is used.
 template <bool STAGED>
@@ -1284,6 +1297,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
 
     // A record: the state after the subsequence (16 bits, pack_state), completed units (15 bits) and "an interval began"
     // (bit 31), the DC sums of components 0 and 1, that of component 2.
+    static_assert(kMaxSubseqBits / 2u + 1u < 1u << 15, "a unit takes two symbols, of one bit at least; the first may have begun before the subsequence");
     uint32_t* rec = reinterpret_cast<uint32_t*>(lds_raw + P.tab_bytes);
     uint32_t* pdc01 = rec + kWG;
     uint16_t* pdc2 = reinterpret_cast<uint16_t*>(pdc01 + kWG);
