@@ -522,8 +522,8 @@ def test_tables_change_between_calls():
 
 
 def test_output_buffers_need_not_be_cleared():
-    """The write pass clears the coefficients itself, group by group: stale values of an earlier, different image
-    in the same buffers must not survive (flat image after a busy one, so most slots have to become zero)."""
+    """Whichever kernel clears the coefficients, stale values of an earlier, different image in the same buffers must not
+    survive (flat image after a busy one, so most slots have to become zero)."""
     busy = encode_jpeg(small_image(21, 256, 384, sigma=60), 98, "444").data
     flat = encode_jpeg(np.full((256, 384, 3), 117, np.uint8), 98, "444").data
     sparse = encode_jpeg(small_image(22, 256, 384, sigma=0.0, shapes=3), 50, "444").data
@@ -590,10 +590,9 @@ def test_synchronisation_split_in_two_kernels():
 
 
 def test_dense_and_sparse_stretches_in_one_image():
-    """The write pass treats a workgroup's stretch of the output in one of two ways: where data units are dense the
-    lanes lay down the zeros of their own ranges, where they are sparse the workgroup clears its stretch first.
-    Images that switch between the two (flat and noise halves like configs[4], noise stripes, every subsequence
-    size), into buffers full of stale values: every slot must end up defined, zeros included."""
+    """Images with data units of a few bits beside ones with a value in nearly every slot (flat and noise halves, noise
+    stripes), every subsequence size, into buffers full of stale values: every slot must end up defined, zeros included.
+    (Calls small enough that the output is gathered in LDS, where it fits, or cleared by the synchronisation kernels.)"""
     rng = np.random.default_rng(55)
     imgs = []
     h, w = 203, 333
@@ -728,9 +727,13 @@ def test_large_image_with_restart_intervals_and_small_subsequences():
 @pytest.mark.slow
 def test_config5_flat_and_random_halves():
     """Full size: 15360x8640, in the launch configuration the bench times.  Every coefficient and every pixel of
-    the frame is compared with the oracle."""
+    the frame is compared with the oracle.  The buffers start full of stale values: beyond 320 MB of coefficients the write
+    pass clears its own stretches."""
     data = config_jpeg(5).data
-    batch, rep = _decode([data])
+    batch = J.prepare_batch([data])
+    batch.d_coef.fill_(0x7777)
+    batch.d_pixels.fill_(0x5A)
+    batch.decode()
     _check_image(batch, 0, data)
 
 
