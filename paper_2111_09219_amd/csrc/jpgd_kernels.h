@@ -1500,7 +1500,7 @@ __device__ __forceinline__ void sync_intra_body(const Params& P) {
                 int64_t cdc = 0;
                 const uint32_t limit = (uint32_t)(u_base + (int32_t)ctt + 1) << P.logL;
                 // The wavefront's decoder does not know the rules of restart intervals.  A chain whose stretch holds
-                // no interval start does not need them (decode_span_sync_rst is the plain loop then); one whose
+                // no interval start does not need them (sync_span_rst is sync_span then); one whose
                 // stretch does is decoded by a single lane for this round.
                 uint32_t crossed = 0u;
                 uint32_t B = kNoBoundary;

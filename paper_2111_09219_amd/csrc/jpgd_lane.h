@@ -1,102 +1,22 @@
 // What one lane does: decode JPEG syntax elements from an arbitrary bit position and decoder state
 // (paper, Algorithm 2 "decode_subsequence" and the function decode_next_symbol it calls).
-// Host/device code: the kernels inline it, and a host build of the same functions is exercised
-// on the CPU by the test suite.
+// Host/device code.  The lanes' inner loops (sync_span, write_span) are written out in assembly in jpgd_kernels.h; what stands
+// here says what every value in them is, and is what the tests of the CPU-only run hold to plain decoders.  Everything
+// else - how the tables are laid out, how a lane starts, restart intervals, chunks of coefficients - is what the kernels inline.
 //
-// The loop is software-pipelined by hand.  One symbol depends on the previous one through a short
-// chain -- table entry -> code + value length -> shifted window -> next table index -> LDS read -- and a
-// lone wavefront spends most of its time waiting on that chain.  So the table entry of the NEXT
-// symbol is requested as soon as the current entry has been unpacked, and everything that is not on
-// the chain (DC sums, unit bookkeeping, stores, fetching stream words) is done while that read is in
-// flight.  A codeword longer than the first-level index is resolved as an iteration of its own that
-// consumes no bits, so the common path has no second dependent read.
+// One symbol depends on the previous one through a short chain: table entry -> code and value length -> shifted window -> next
+// table index -> LDS read.  A lone wavefront spends most of its time on that chain, so the entry of the next symbol is asked
+// for as soon as the one in hand has been taken apart, and everything else (DC sums, unit bookkeeping, stores, stream words) is
+// done while that read is in flight.  A codeword longer than the first-level index is resolved as a step of its own that
+// takes no bits, so the common path has no second dependent read.
+//
+// Decoder state of the paper, (p, n, c, z): c is refined to the data unit inside the MCU (two decoders inside different
+// luminance units of a 4:2:0 MCU agree on the component but not on what follows) and n kept as completed data units (see
+// SInfo).
 #pragma once
 #include "jpgd_common.h"
 
 namespace jpgd {
-
-// What a lane needs to know about one data unit of the MCU: where the tables of its symbols are, which
-// DC sum it feeds, and which unit follows.  One row per data unit, 16 bytes, read as a whole.
-struct alignas(16) UnitRow {
-    uint32_t tb_ac;       // first entry of the unit's AC table inside the LUT array
-    uint32_t tb_dc_next;  // first entry of the DC table of the unit that follows
-    uint32_t dcmul;       // 1 << (15 * component): the component's field of the packed DC sums
-    uint32_t next;        // index of the unit that follows
-};
-
-// sched_*: 4 bits per data unit (see ImgDesc)
-JPGD_HD UnitRow make_unit_row(uint32_t u, uint32_t upm, uint32_t sched_dc, uint32_t sched_ac, uint32_t sched_comp) {
-    UnitRow r;
-    const uint32_t un = u + 1u == upm ? 0u : u + 1u;
-    r.tb_ac = ((sched_ac >> (4u * u)) & 15u) * (uint32_t)kLutEntries;
-    r.tb_dc_next = ((sched_dc >> (4u * un)) & 15u) * (uint32_t)kLutEntries;
-    r.dcmul = 1u << (15u * ((sched_comp >> (4u * u)) & 15u));
-    r.next = un;
-    return r;
-}
-
-// Decoder state of the paper, (p, n, c, z), with c refined to the data unit inside the MCU
-// (two decoders inside different luminance units of a 4:2:0 MCU agree on the component but
-// not on what follows) and n kept as completed data units (see SInfo).
-struct Lane {
-    uint32_t p;    // bit position in the unstuffed stream of the next syntax element (kept by the window inside the
-                   // decode loops, written back when they end)
-    uint32_t u;    // data unit inside the MCU
-    uint32_t z;    // zig-zag index of the next coefficient (0 = a DC symbol is next)
-    uint32_t nb;   // data units completed since the counter was last cleared
-    // pipeline registers (prime)
-    uint32_t e;    // table entry already read for the symbol at p (possibly a first-level escape)
-    uint32_t base; // table that entry came from
-    // synchronisation pass with two symbols per step (decode_span_sync_pairs)
-    uint32_t pb;   // pair byte read for the symbol at p, as if that symbol came from unit u's AC table
-};
-
-// Window on the stream: two consecutive big-endian words and the offset of the next unread bit in the
-// first; `peek` is the 32 bits that start there (a codeword has at most 16 bits, its value at most 16).
-struct BitWin {
-    uint32_t hi, lo;
-    uint32_t o;      // 0..31
-    uint32_t peek;
-    uint32_t next;   // cursor of the word held in `ahead`, in the units of the Fetch functor; hi is word next - 2
-    uint32_t ahead;  // the word after `lo`, fetched one refill early so that its latency is hidden
-    uint32_t origin; // bit position in the stream of the word with cursor 0
-};
-
-// bit position of the next unread bit
-JPGD_HD uint32_t win_pos(const BitWin& w) { return w.origin + ((w.next - 2u) << 5) + w.o; }
-// the window has reached bit `limit` (a multiple of 32) as soon as its cursor `next` has reached this value
-JPGD_HD uint32_t win_stop(const BitWin& w, uint32_t limit) { return ((limit - w.origin) >> 5) + 2u; }
-
-// per-image constants of the scan syntax
-struct Syntax {
-    const UnitRow* rows;  // one per data unit of the MCU
-    uint32_t upm;         // units per MCU
-    const uint32_t* pair_of_unit = nullptr;  // per data unit: offset of its AC table's pair bytes (kernels that use them)
-};
-
-JPGD_HD uint32_t win_peek(const BitWin& w) {
-    return (uint32_t)(((((uint64_t)w.hi << 32) | (uint64_t)w.lo) << w.o) >> 32);
-}
-
-// `cursor` addresses the 32-bit word that holds bit p
-template <class Fetch>
-JPGD_HD void win_init(BitWin& w, uint32_t p, uint32_t cursor, Fetch fetch) {
-    w.hi = fetch(cursor);
-    w.lo = fetch(cursor + 1u);
-    w.o = p & 31u;
-    w.peek = win_peek(w);
-    w.next = cursor + 2u;
-    w.ahead = fetch(w.next);
-    w.origin = (p & ~31u) - (cursor << 5);
-}
-
-// Starts the pipeline: after (p, u, z) and the window are set, read the entry of the symbol at p.
-template <class LutPtr>
-JPGD_HD void prime(Lane& l, const BitWin& w, const Syntax& sx, LutPtr lut) {
-    const uint32_t tb_dc = sx.rows[l.u == 0u ? sx.upm - 1u : l.u - 1u].tb_dc_next;
-    l.base = l.z == 0u ? tb_dc : sx.rows[l.u].tb_ac;
-    l.e = lut[l.base + (w.peek >> (32 - kLutK))];
-}
 
 // The value bits are the last `size` of the `total` bits a symbol takes; "signed ones' complement" (paper,
 // Section 2): a leading 1 means the bits are the value itself, a leading 0 means value = bits - (2^size - 1);
@@ -128,180 +48,22 @@ JPGD_HD void dc_unpack(int64_t acc, int32_t& d0, int32_t& d1, int32_t& d2) {
     d2 = (int32_t)acc;
 }
 
-// One step of the pipeline, shared by both passes.  Unpacks the entry in hand, moves the window and
-// (z, u) past the symbol, and requests the entry of the next symbol (or, for an escape, the second-level
-// entry of the same symbol).  What the passes do with the symbol itself comes after, in the shadow of
-// that request.
-struct Step {
-    uint32_t peek;   // window as the symbol saw it
-    uint32_t total, size, adv;  // bits taken, value bits among them, zig-zag slots covered
-    bool esc;        // first-level escape: nothing was consumed, the state did not change
-    bool is_dc;
-    bool done;       // the symbol completed its data unit
-    bool need;       // the window moved on by a word
-    uint32_t z;      // zig-zag index the symbol started at
-    uint32_t dcmul;  // of the data unit the symbol belongs to
-};
-
-// The row of the current unit is read at the top of the step and used at its end (which table the next entry comes
-// from); the next stream word is asked for in the middle and used in the next step; the table entry is asked for
-// last and is what the next step starts with.  Nothing but the entry and the window is carried from step to step
-// in registers.
-template <class Fetch, class LutPtr>
-JPGD_HD Step step_and_request(Lane& l, BitWin& w, const Syntax& sx, Fetch fetch, LutPtr lut) {
-    Step s;
-    const UnitRow old = sx.rows[l.u];
-    const uint32_t e = l.e;
-    s.peek = w.peek;
-    s.esc = lut_esc(e);
-    const uint32_t ee = s.esc ? 0u : e;
-    s.total = lut_total(ee);  // at most 31
-    s.size = lut_size(ee);
-    s.adv = lut_adv(ee);
-    s.is_dc = l.z == 0u;
-    s.z = l.z;
-    const uint32_t o2 = w.o + s.total;
-    s.need = o2 >= 32u;
-    // (bits that start no codeword of a DC table take the DC symbol's slot: sync_entry)
-    const uint32_t zn = l.z + (s.is_dc && !s.esc && s.adv == 0u ? 1u : s.adv);
-    s.done = zn >= 64u;
-    // off the chain, without branches: when no word is taken the word already held is read again, when the
-    // unit does not change its row is
-    w.next += s.need ? 1u : 0u;
-    const uint32_t ahead = fetch(w.next);
-    l.u = s.done ? old.next : l.u;
-    s.dcmul = old.dcmul;
-    l.nb += s.done ? 1u : 0u;
-    // window past the symbol
-    w.o = o2 & 31u;
-    w.hi = s.need ? w.lo : w.hi;
-    w.lo = s.need ? w.ahead : w.lo;
-    w.ahead = ahead;
-    w.peek = win_peek(w);
-    l.z = s.done ? 0u : zn;
-    // request: next symbol from the DC table of the next unit or the AC table of this one; an escape asks
-    // the second level of the table it came from
-    uint32_t base2 = s.done ? old.tb_dc_next : old.tb_ac;
-#if defined(__HIP_DEVICE_COMPILE__)
-    // (Only the arm for ordinary entries below uses base2, and the compiler would move the read of the row into that
-    // arm and wait for it there; this keeps the read at the top of the step.)
-    asm volatile("" : "+v"(base2));
-#endif
-    const uint32_t nb2 = lut_esc_bits(e);
-    const uint32_t sub = (uint32_t)kLutL1 + lut_esc_offset(e) + ((s.peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u));
-    const uint32_t idx = s.esc ? l.base + sub : base2 + (w.peek >> (32 - kLutK));
-    l.base = s.esc ? l.base : base2;
-    l.e = lut[idx];
-    return s;
-}
-
-// One symbol of the synchronisation pass (write = false in Algorithm 2): state, count of completed units
-// (inside step_and_request) and the per-component sums of DC differences.
-template <class Fetch, class LutPtr>
-JPGD_HD void sync_symbol(Lane& l, BitWin& w, int64_t& dcacc, const Syntax& sx, Fetch fetch, LutPtr lut) {
-    const Step s = step_and_request(l, w, sx, fetch, lut);
-    const int32_t v = symbol_value(s.peek, s.total, s.size);
-    const int32_t mul = s.is_dc ? (int32_t)s.dcmul : 0;
-    dcacc += (int64_t)v * (int64_t)mul;
-}
-
-// Synchronisation pass: decode while the next symbol starts before `limit`.  The lane must have been primed.
-template <class Fetch, class LutPtr>
-JPGD_HD void decode_span_sync(Lane& l, BitWin& w, uint32_t limit, int64_t& dcacc, const Syntax& sx, Fetch fetch,
-                              LutPtr lut) {
-    const uint32_t stop = win_stop(w, limit);
-    while (w.next < stop) sync_symbol(l, w, dcacc, sx, fetch, lut);
-    l.p = win_pos(w);
-}
-
-// ---- two symbols per step ---------------------------------------------------------------------------------
-// (The kernels' lanes take two symbols per step from tables of their own, sync_span below.  decode_span_sync,
-// decode_span_sync_pairs and decode_span_sync_rst say the same on the tables of jpgd_lut.h; the host walk-through runs
-// them, and sync_span is held to them.)
-// The synchronisation pass needs the state, the unit count and the DC sums, not the coefficients.  So where the
-// first-level index of an AC symbol also holds the whole codeword of the AC symbol after it, one step may take
-// both: the pair byte of that index (build_pairs) says how many bits the second symbol takes and how many slots it
-// covers.  The second symbol is taken only if the first one is an AC symbol that leaves its data unit open (the
-// second then belongs to the same unit and the same table); the step is exactly two steps of sync_symbol.
-template <class Fetch, class LutPtr, class PairPtr>
-JPGD_HD void sync_symbol_pair(Lane& l, BitWin& w, int64_t& dcacc, const Syntax& sx, Fetch fetch, LutPtr lut,
-                              PairPtr pairs) {
-    const UnitRow row = sx.rows[l.u];
-    const uint32_t pair = sx.pair_of_unit[l.u];
-    const uint32_t e = l.e;
-    const uint32_t peek = w.peek;
-    const bool esc = lut_esc(e);
-    const uint32_t ee = esc ? 0u : e;
-    const uint32_t t1 = lut_total(ee), size = lut_size(ee), a1 = lut_adv(ee);
-    const bool is_dc = l.z == 0u;
-    const uint32_t zn1 = l.z + (is_dc && !esc && a1 == 0u ? 1u : a1);
-    const uint32_t pb = (is_dc || zn1 >= 64u) ? 0u : l.pb;  // (an escape's index has pair byte 0)
-    const uint32_t a2c = pb >> 4;
-    const uint32_t total = t1 + (pb & 15u);
-    const uint32_t zn = zn1 + a2c;
-    const bool done = zn >= 64u || a2c == 15u;  // 15: the second symbol is end-of-block
-    const uint32_t o2 = w.o + total;  // at most 31 + 20 + 15
-    const bool need = o2 >= 32u;
-    w.next += need ? 1u : 0u;
-    const uint32_t ahead = fetch(w.next);
-    l.nb += done ? 1u : 0u;
-    w.o = o2 & 31u;
-    w.hi = need ? w.lo : w.hi;
-    w.lo = need ? w.ahead : w.lo;
-    w.ahead = ahead;
-    w.peek = win_peek(w);
-    l.z = done ? 0u : zn;
-    l.u = done ? row.next : l.u;
-    uint32_t base2 = done ? row.tb_dc_next : row.tb_ac;
-#if defined(__HIP_DEVICE_COMPILE__)
-    // (Only the arm for ordinary entries below uses base2, and the compiler would move the read of the row into that
-    // arm and wait for it there; this keeps the read at the top of the step.)
-    asm volatile("" : "+v"(base2));
-#endif
-    const uint32_t nb2 = lut_esc_bits(e);
-    const uint32_t sub = (uint32_t)kLutL1 + lut_esc_offset(e) + ((peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u));
-    const uint32_t i1 = w.peek >> (32 - kLutK);
-    const uint32_t idx = esc ? l.base + sub : base2 + i1;
-    l.base = esc ? l.base : base2;
-    l.e = lut[idx];
-    // asked as if the next symbol came from the AC table of the unit just left: if the unit is complete the next
-    // symbol is a DC symbol and the byte is not looked at
-    l.pb = pairs[pair + i1];
-    const int32_t v = symbol_value(peek, t1, size);
-    dcacc += (int64_t)v * (int64_t)(is_dc ? (int32_t)row.dcmul : 0);
-}
-
-// The synchronisation pass with pairs.  A second symbol must start before `limit` like any other: pairs are taken
-// while the step starts at least 32 bits before it (a first symbol with a pair byte has at most 20 bits), single
-// symbols from there on.  The lane must have been primed; sx.pair_of_unit must be set.
-template <class Fetch, class LutPtr, class PairPtr>
-JPGD_HD void decode_span_sync_pairs(Lane& l, BitWin& w, uint32_t limit, int64_t& dcacc, const Syntax& sx, Fetch fetch,
-                                    LutPtr lut, PairPtr pairs) {
-    const uint32_t stop = win_stop(w, limit);
-    l.pb = pairs[sx.pair_of_unit[l.u] + (w.peek >> (32 - kLutK))];
-#if defined(__HIP_DEVICE_COMPILE__)
-    // (Keeps the compiler from merging this read with the one at the end of a step into a single read at the top of
-    // the loop, where every step would wait for it: the byte is asked for one step ahead, like the table entry.)
-    asm volatile("" : "+v"(l.pb));
-#endif
-    while (w.next + 1u < stop) sync_symbol_pair(l, w, dcacc, sx, fetch, lut, pairs);
-    while (w.next < stop) sync_symbol(l, w, dcacc, sx, fetch, lut);
-    l.p = win_pos(w);
-}
-
 // ---- the lanes of the synchronisation pass -----------------------------------------------------------------
-// The same walk as decode_span_sync, on tables laid out for it in LDS (SyncTables): a 32-bit entry per first-level index
-// says at once what its symbol takes, what the symbol behind it takes where the index holds that one's whole codeword
-// too (build_pairs), and how many value bits a DC symbol has.  Position and zig-zag index are one register that an entry
-// is added to.
+// write = false in Algorithm 2: state, count of completed units and sums of DC differences, on tables laid out for it in LDS.  A
+// 32-bit entry per first-level index says at once what its symbol takes, what the symbol behind it takes where the index
+// holds that one's whole codeword too (build_pairs), and how many value bits a DC symbol has.  Position and zig-zag index
+// are one register that an entry is added to.
+// The pass needs no coefficients, so one step may take two symbols: the second only behind an AC symbol that leaves its unit
+// open (it belongs to the same unit and table then), and only where it starts before the end of the subsequence, like any
+// other.  Such a step is exactly two steps of one symbol.
 //
 // What bounds it: a lane's next look-up waits for the one before (about 130 cycles of LDS), and behind that for the
 // instructions between an entry's arrival and the next request, 4 cycles each; with several wavefronts on a SIMD, for
 // all instructions of a step.  So the words on the way from entry to request are kept few, everything else stands behind
 // the request, and an escape (a codeword longer than the index) is followed up without a branch, which would cost a
-// lone wavefront more than the instructions it skips: 46 vector instructions and three LDS reads a step where
-// sync_symbol_pair takes 62 and five, two thirds of them in front of the request.
-// Measured, decode_span_sync_pairs / this (kernels, us): 15360x8640 first kernel 697 / 611, second 890 / 848; 256 images of
+// lone wavefront more than the instructions it skips: 46 vector instructions and three LDS reads a step.  On the 16-bit
+// entries of build_lut with pair bytes beside them a step took 62 and five, two thirds of them in front of the request.
+// Measured, on those / on these (kernels, us): 15360x8640 first kernel 697 / 611, second 890 / 848; 256 images of
 // 512x384 240 / 213; 24 images of 2047x1535 337 / 305; one 1001x667 image 104 / 89; 3001x2003 with an interval per MCU row
 // (single symbols before) 122 / 97.
 //
@@ -630,45 +392,6 @@ JPGD_HD void chunk_ends(const WriteChunk& c, Store1 store1) {
     }
 }
 
-// One symbol of the write pass (write = true in Algorithm 2): every non-zero coefficient goes to
-// 64*unit + zig-zag index, DC values un-differenced.  `unit` is the index of the data unit being decoded,
-// pred0..2 the DC predictors; `flags` collects kSt* bits.  Without branches except around the store itself:
-// a wavefront holds lanes in every kind of symbol at once, so each arm of a branch would be walked anyway.
-template <class Fetch, class LutPtr, class Store>
-JPGD_HD void write_symbol(Lane& l, BitWin& w, uint32_t& unit, int32_t& pred0, int32_t& pred1, int32_t& pred2,
-                          const Syntax& sx, Fetch fetch, LutPtr lut, Store store, uint32_t& flags) {
-    const Step s = step_and_request(l, w, sx, fetch, lut);
-    const bool comp0 = s.dcmul == 1u, comp1 = s.dcmul == (1u << 15);
-    // An escape comes out as value 0, size 0, no slot; bits that start no codeword as value 0, size 0, one bit, no
-    // slot: neither changes a predictor or passes the test of the store below.
-    const int32_t value = symbol_value(s.peek, s.total, s.size);
-    const bool dc = s.is_dc;
-    const int32_t pred = (comp0 ? pred0 : (comp1 ? pred1 : pred2)) + value;
-    pred0 = dc && comp0 ? pred : pred0;
-    pred1 = dc && comp1 ? pred : pred1;
-    pred2 = dc && !comp0 && !comp1 ? pred : pred2;
-    // where the symbol ends: a coefficient sits in the last slot it covers (after its run of zeros); a DC symbol ends
-    // in slot 0, or, if it covers none, before it
-    const uint32_t zn = s.z + s.adv;
-    const uint32_t at = zn - 1u;
-    if ((dc || s.size != 0u) && at < 64u) store(unit, at, (int16_t)(dc ? pred : value));  // (a DC symbol of size 0 still yields the predictor)
-    // no codeword starts with these bits; or a coefficient or a run of sixteen zeros (not end-of-block,
-    // which may be coded anywhere) that runs past the end of the unit
-    const bool bad = (s.adv == 0u && !s.esc) || (zn > 64u && s.adv != kAdvEob);
-    flags |= bad ? kStInvalid : 0u;
-    unit += s.done ? 1u : 0u;
-}
-
-// Write pass: the same walk as the synchronisation pass, up to the image's last data unit.
-template <class Fetch, class LutPtr, class Store>
-JPGD_HD void decode_span_write(Lane& l, BitWin& w, uint32_t limit, uint32_t& unit, uint32_t total_units,
-                               int32_t& pred0, int32_t& pred1, int32_t& pred2, const Syntax& sx, Fetch fetch,
-                               LutPtr lut, Store store, uint32_t& flags) {
-    const uint32_t stop = win_stop(w, limit);
-    while (w.next < stop && unit < total_units) write_symbol(l, w, unit, pred0, pred1, pred2, sx, fetch, lut, store, flags);
-    l.p = win_pos(w);
-}
-
 // ---- the walk of a whole wavefront ---------------------------------------------------------------------------
 // What the walk through a single chain (coop_span_sync in jpgd_kernels.h) needs to know of the image's data units.
 //
@@ -738,73 +461,13 @@ JPGD_HD uint32_t next_boundary(uint32_t from_bit, uint32_t end_bit, BWord bword)
     }
 }
 
-// the window moves to bit B (a multiple of 8) and the decoder starts a fresh MCU there
-template <class Fetch, class LutPtr>
-JPGD_HD void move_to_interval(Lane& l, BitWin& w, uint32_t B, const Syntax& sx, Fetch fetch, LutPtr lut) {
-    l.z = 0u;
-    l.u = 0u;
-    win_init(w, B, (B - w.origin) >> 5, fetch);
-    prime(l, w, sx, lut);
-}
-
-// after a symbol: has the decoder reached the padding in front of the interval that starts at B, or passed B?
-JPGD_HD bool at_interval_end(const BitWin& w, uint32_t pos, uint32_t B) {
-    if (pos >= B) return true;
-    const uint32_t r = B - pos;
-    return r <= 7u && (~w.peek >> (32u - r)) == 0u;
-}
-
-// Where the fast part of a span ends when the next interval starts at B: a symbol that starts before `calm` ends more
-// than 7 bits before B (it has at most 31 bits), so nothing has to be checked on the way there.  As a window cursor.
-JPGD_HD uint32_t calm_stop(const BitWin& w, uint32_t B, uint32_t limit) {
-    uint32_t calm = limit;
-    if (B != kNoBoundary) {
-        const uint32_t c = B >= 40u ? (B - 39u) & ~31u : 0u;
-        calm = c < limit ? c : limit;
-    }
-    return calm > w.origin ? win_stop(w, calm) : 0u;
-}
-
-// Synchronisation pass over a stream with restart intervals.  `crossed` is set when a symbol of this span
-// started an interval (dcacc then holds the sums since the last such symbol).
-// A fast loop up to the neighbourhood of the next interval start, then a careful loop.  (The single loop of the
-// write pass below was measured here too: the overflow rounds are a chain of dependent symbols in a lone
-// wavefront, and the extra tests per symbol cost them more -- 4096x4096 with one interval per MCU row: 0.93
-// against 0.78 ms -- than walking a span twice costs the few wavefronts that meet an interval start.)
-template <class Fetch, class LutPtr, class BWord>
-JPGD_HD void decode_span_sync_rst(Lane& l, BitWin& w, uint32_t limit, int64_t& dcacc, uint32_t& crossed, const Syntax& sx,
-                                  Fetch fetch, LutPtr lut, BWord bword) {
-    uint32_t from = win_pos(w);
-    for (;;) {
-        const uint32_t B = next_boundary(from, limit + 64u, bword);
-        const uint32_t stop = calm_stop(w, B, limit);
-        while (w.next < stop) sync_symbol(l, w, dcacc, sx, fetch, lut);
-        if (B == kNoBoundary) break;
-        uint32_t pos = win_pos(w);
-        bool next_interval = false;
-        while (pos < limit) {
-            if (pos == B) {  // this symbol starts the interval
-                dcacc = 0;
-                crossed = 1u;
-                from = B + 1u;
-                next_interval = true;
-                break;
-            }
-            sync_symbol(l, w, dcacc, sx, fetch, lut);
-            pos = win_pos(w);
-            if (at_interval_end(w, pos, B)) {
-                move_to_interval(l, w, B, sx, fetch, lut);
-                pos = B;
-            }
-        }
-        if (!next_interval) break;
-    }
-    l.p = win_pos(w);
-}
-
-// The same over a stream with restart intervals (rules: decode_span_sync_rst below, which this follows step by step).
-// Boundaries are positions in the image's stream: a position there plus `org` is a bit of `word`.  start(p): sync_start at
-// bit p with u = z = 0; span(limit): sync_span.
+// Synchronisation pass over a stream with restart intervals.  `crossed` is set when a symbol of this span started an interval
+// (dcacc then holds the sums since the last such symbol).  Boundaries are positions in the image's stream: a position there
+// plus `org` is a bit of `word`.  start(p): sync_start at bit p with u = z = 0; span(limit): sync_span.
+// A fast loop up to the neighbourhood of the next interval start, then a careful one of single symbols.  (The single loop of
+// the write pass below was measured here too: the overflow rounds are a chain of dependent symbols in a lone wavefront, and
+// the extra tests per symbol cost them more -- 4096x4096 with one interval per MCU row: 0.93 against 0.78 ms -- than walking
+// a span twice costs the few wavefronts that meet an interval start.)
 template <class Start, class Span, class BWord>
 JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t& crossed, uint32_t org, Start start, Span span,
                            BWord bword) {
@@ -839,8 +502,14 @@ JPGD_HD void sync_span_rst(SyncLane& l, uint32_t limit, int64_t& dcacc, uint32_t
     }
 }
 
-// The write pass's lanes over a stream with restart intervals (rules: decode_span_write_rst below).  `org` as in
-// sync_span_rst; *flags: kStInvalid where an interval starts at another unit than it should.
+// Write pass over a stream with restart intervals: the predictors return to zero where an interval starts.  `org` as in
+// sync_span_rst.  An interval holds units_per_interval data units (all but the last of the scan): a start reached at any
+// other unit count means damaged data and is flagged (kStInvalid in *flags).
+// One loop for all lanes: a lane near an interval start does its checks before and after the same write_step the others
+// execute.  With a fast loop and a careful loop one after the other, a wavefront in which a few lanes meet an interval
+// start walks its span up to three times (the fast loop for the others, the careful one, the fast one again for what
+// follows the start); the write kernel, whose wavefronts all have full spans to decode, is a third faster this way on
+// streams with one interval per MCU row.
 template <class Word, class Tab, class Row, class Store, class BWord>
 JPGD_HD void write_span_rst(WriteLane& l, uint32_t limit, uint32_t total_units, uint32_t units_per_interval, uint32_t org,
                             uint32_t upm, uint32_t row0, Word word, Tab tab, Row rows, Store store, BWord bword, uint32_t* flags) {
@@ -868,40 +537,6 @@ JPGD_HD void write_span_rst(WriteLane& l, uint32_t limit, uint32_t total_units, 
             pos = B;
         }
     }
-}
-
-// Write pass over a stream with restart intervals: the predictors return to zero where an interval starts.
-// An interval holds units_per_interval data units (all but the last of the scan): a start reached at any
-// other unit count means damaged data and is flagged.
-// One loop for all lanes: a lane near an interval start does its checks before and after the same write_symbol the
-// others execute.  With a fast loop and a careful loop one after the other, a wavefront in which a few lanes meet
-// an interval start walks its span up to three times (the fast loop for the others, the careful one, the fast
-// one again for what follows the start); the write kernel, whose wavefronts all have full spans to decode, is a
-// third faster this way on streams with one interval per MCU row.
-template <class Fetch, class LutPtr, class Store, class BWord>
-JPGD_HD void decode_span_write_rst(Lane& l, BitWin& w, uint32_t limit, uint32_t& unit, uint32_t total_units,
-                                   uint32_t units_per_interval, int32_t& pred0, int32_t& pred1, int32_t& pred2,
-                                   const Syntax& sx, Fetch fetch, LutPtr lut, Store store, uint32_t& flags, BWord bword) {
-    uint32_t B = next_boundary(win_pos(w), limit + 64u, bword);
-    uint32_t stop = calm_stop(w, B, limit);
-    while (unit < total_units) {
-        const bool near = w.next >= stop;
-        if (near) {
-            if (B == kNoBoundary) break;
-            const uint32_t pos = win_pos(w);
-            if (pos >= limit) break;
-            if (pos == B) {
-                pred0 = pred1 = pred2 = 0;
-                if (unit % units_per_interval != 0u) flags |= kStInvalid;
-                B = next_boundary(B + 1u, limit + 64u, bword);
-                stop = calm_stop(w, B, limit);
-                continue;
-            }
-        }
-        write_symbol(l, w, unit, pred0, pred1, pred2, sx, fetch, lut, store, flags);
-        if (near && at_interval_end(w, win_pos(w), B)) move_to_interval(l, w, B, sx, fetch, lut);
-    }
-    l.p = win_pos(w);
 }
 
 }  // namespace jpgd

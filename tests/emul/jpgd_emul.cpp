@@ -1,5 +1,6 @@
-// Host walk-through of the decoder's kernels: the same lane code (jpgd_lane.h, jpgd_lut.h, jpgd_idct.h)
-// and the same index arithmetic as jpgd_kernels.h, with workgroups and lanes run one after another.
+// Host walk-through of the decoder's kernels: the lanes on the kernels' tables (sync_span, write_span and their _rst forms of
+// jpgd_lane.h, which the kernels have in assembly), the walk of a whole wavefront (jpgd_walk.h) and the same index arithmetic
+// as jpgd_kernels.h, with workgroups and lanes run one after another.
 // It exists so that the CPU-only test run can check the host logic (tables, lane decoder, record
 // packing, padded staging layout, scan, write, pixel arithmetic) before anything reaches a GPU.
 // It is test code: the library never calls it and it is not a fallback for the GPU path.
@@ -11,11 +12,9 @@
 #include <algorithm>
 #include <vector>
 
-#include "../../include/jpgd.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_common.h"
 #include "../../paper_2111_09219_amd/csrc/jpgd_idct.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_lane.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_lut.h"
+#include "jpgd_tables.h"
+#include "jpgd_walk.h"
 
 using namespace jpgd;
 
@@ -28,47 +27,15 @@ uint32_t pack_dc2(int64_t acc) { int32_t a, b, c; dc_unpack(acc, a, b, c); retur
 
 struct Image {
     jpgd_info in;
-    uint32_t sched_dc = 0, sched_ac = 0, sched_comp = 0, nslots = 0;
-    std::vector<uint16_t> lut;
-    std::vector<uint8_t> pairs;    // pair bytes of the AC tables, AC table k at k * kPairBytes
-    uint32_t pair_of_unit[8] = {0};
+    Layout y;
     std::vector<uint8_t> stream;  // unstuffed + zero slack
     std::vector<uint32_t> bmap;   // restart intervals: one bit per unstuffed byte, set at the first byte of an interval
     uint32_t nbytes = 0, nsub = 0, markers = 0;
 };
 
 int prepare(const uint8_t* file, size_t len, Image& im) {
-    int rc = jpgd_parse(file, len, &im.in);
-    if (rc) return rc;
-    const jpgd_info& in = im.in;
-    uint32_t dc_ids[3], ac_ids[3], ndc = 0, nac = 0, cdc[3], cac[3];
-    for (uint32_t c = 0; c < in.ncomp; ++c) {
-        uint32_t k;
-        for (k = 0; k < ndc && dc_ids[k] != in.td[c]; ++k) {}
-        if (k == ndc) dc_ids[ndc++] = in.td[c];
-        cdc[c] = k;
-        for (k = 0; k < nac && ac_ids[k] != in.ta[c]; ++k) {}
-        if (k == nac) ac_ids[nac++] = in.ta[c];
-        cac[c] = k;
-    }
-    im.nslots = ndc + nac;
-    im.lut.assign((size_t)im.nslots * kLutEntries, 0);
-    im.pairs.assign((size_t)nac * kPairBytes, 0);
-    uint32_t u = 0;
-    for (uint32_t c = 0; c < in.ncomp; ++c) {
-        uint32_t nu = (in.ncomp == 1) ? 1u : (c == 0 ? (uint32_t)in.hsamp[0] * in.vsamp[0] : 1u);
-        for (uint32_t k = 0; k < nu; ++k, ++u) {
-            im.sched_dc |= cdc[c] << (4 * u);
-            im.sched_ac |= (ndc + cac[c]) << (4 * u);
-            im.sched_comp |= c << (4 * u);
-            im.pair_of_unit[u] = cac[c] * (uint32_t)kPairBytes;
-        }
-        if (!build_lut(in.dht_bits[0][in.td[c]], in.dht_vals[0][in.td[c]], true, &im.lut[(size_t)cdc[c] * kLutEntries]) ||
-            !build_lut(in.dht_bits[1][in.ta[c]], in.dht_vals[1][in.ta[c]], false, &im.lut[(size_t)(ndc + cac[c]) * kLutEntries]))
-            return JPGD_E_TABLE;
-        build_pairs(&im.lut[(size_t)(ndc + cac[c]) * kLutEntries], &im.pairs[(size_t)cac[c] * kPairBytes]);
-    }
-    return JPGD_OK;
+    const int rc = jpgd_parse(file, len, &im.in);
+    return rc ? rc : make_layout(im.in, im.y);
 }
 
 // the two unstuff kernels, tile by tile and lane by lane
@@ -124,109 +91,15 @@ struct Emul {
     uint32_t logL, H, seq_len;
     std::vector<SInfo> sinfo;
     std::vector<uint32_t> warm;  // per sequence: the state its records continue (0xFFFFFFFF = none)
-    UnitRow rows[8];
-    Syntax sx;
+    Walk walk;
     uint32_t inter_changed = 0, rounds_max = 0, flags = 0, pending = 0;
 };
 
-// The wavefront-per-chain decoder of jpgd_kernels.h (coop_unit_word, coop_span_sync) with its 64 lanes run
-// one after another: the same table words, the same 64-word stretch held by the lanes, the same four answers
-// per lane, the same grid of windows and the same walk through them (the kernel asks for the next window's
-// answers ahead of time and follows up the escapes of all lanes at the first one the chain meets; here each is
-// followed up when the chain meets it, which gives the same entries).
 uint32_t g_coop_max = kCoopMax;  // as the library sets it for four wavefronts; the tests also run with 0 (never), 8 and 64
 uint32_t g_sync_waves = kWG / 64;  // wavefronts per workgroup (the library launches 4, 8 or 16)
 
-uint32_t coop_unit_word(const Syntax& sx, uint32_t lane) {
-    if (lane >= sx.upm) return 0u;
-    const UnitRow r = sx.rows[lane];
-    return (r.tb_ac / (uint32_t)kLutEntries) | ((r.tb_dc_next / (uint32_t)kLutEntries) << 3) | (r.next << 6) |
-           (((uint32_t)__builtin_ffs((int)r.dcmul) - 1u) << 10);
-}
-
-uint32_t coop_resolve(const uint16_t* lut, uint32_t slot, uint32_t e, uint32_t peek) {
-    const uint32_t nb2 = lut_esc_bits(e);
-    return lut[slot * (uint32_t)kLutEntries + (uint32_t)kLutL1 + lut_esc_offset(e) +
-               ((peek >> (32 - kLutK - nb2)) & ((1u << nb2) - 1u))];
-}
-
-uint32_t coop_step(uint32_t e) { return (e & 0x8000u) ? 0x10000u : ((e & 0x7E00u) | std::max(e & 31u, 1u)); }
-
-template <class Fetch>
-void coop_span_sync(uint32_t& p, uint32_t& u, uint32_t& z, uint32_t& nb, int64_t& dc, uint32_t limit, uint32_t org_word,
-                    uint32_t nwords, const uint32_t unit_word[64], uint32_t upm, uint32_t nslots, Fetch fetch,
-                    const uint16_t* lut) {
-    nb = 0;
-    dc = 0;
-    uint32_t cur = unit_word[u];
-    uint32_t ac_slot = cur & 7u;
-    uint32_t dc_slot = (unit_word[u == 0u ? upm - 1u : u - 1u] >> 3) & 7u;
-    uint32_t w0 = 0, held[64];
-    bool have = false;
-    if (p >= limit) return;
-    // windows of 64 bit positions on a 64-bit grid of the stream (a subsequence is a whole number of them); the
-    // chain enters a window where the last symbol of the window before ended
-    uint32_t ws = p & ~63u;
-    uint32_t S = (p - ws) | (z << 9);
-    for (;; ws += 64u) {
-        uint32_t wb = (ws >> 5) - w0;
-        if (!have || wb + 2u > 63u) {
-            w0 = ws >> 5;
-            for (uint32_t lane = 0; lane < 64; ++lane) {
-                const uint32_t c = w0 - org_word + lane;
-                held[lane] = c < nwords ? fetch(c) : 0u;
-            }
-            wb = 0;
-            have = true;
-        }
-        uint32_t peek[64], e01[64], e23[64];
-        for (uint32_t lane = 0; lane < 64; ++lane) {
-            const uint32_t off = lane >> 5;
-            const uint32_t hi = held[wb + off], lo = held[wb + off + 1u];
-            peek[lane] = (uint32_t)(((((uint64_t)hi << 32) | (uint64_t)lo) << (lane & 31u)) >> 32);
-            const uint32_t idx = peek[lane] >> (32 - kLutK);
-            uint32_t e[4];
-            for (uint32_t s = 0; s < 4u; ++s) e[s] = lut[std::min(s, nslots - 1u) * (uint32_t)kLutEntries + idx];
-            e01[lane] = e[0] | (e[1] << 16);
-            e23[lane] = e[2] | (e[3] << 16);
-        }
-        auto entry = [&](uint32_t slot, uint32_t j) { return ((slot & 2u) ? e23[j] : e01[j]) >> ((slot & 1u) << 4); };
-        if ((S & 0x7Fu) >= 64u) abort();  // a symbol has at most 31 bits: the chain enters within the window
-        for (;;) {
-            if ((S >> 9) == 0u) {
-                uint32_t r = entry(dc_slot, S);
-                if (r & 0x8000u) r = coop_resolve(lut, dc_slot, r, peek[S]);
-                dc += (int64_t)symbol_value(peek[S], lut_total(r), lut_size(r)) * (int64_t)(1u << ((cur >> 10) & 31u));
-                S += coop_step(r) | 0x200u;
-                if (S & 0x40u) break;
-            }
-            for (;;) {
-                S += coop_step(entry(ac_slot, S & 63u));
-                if ((S & 0x18040u) == 0u) continue;
-                if (S & 0x10000u) {
-                    S &= 0xFFFFu;
-                    const uint32_t j = S & 63u;
-                    S += coop_step(coop_resolve(lut, ac_slot, entry(ac_slot, j), peek[j]));
-                    if ((S & 0x8040u) == 0u) continue;
-                }
-                break;
-            }
-            if (S & 0x8000u) {
-                ++nb;
-                S &= 0x7Fu;
-                u = (cur >> 6) & 15u;
-                dc_slot = (cur >> 3) & 7u;
-                cur = unit_word[u];
-                ac_slot = cur & 7u;
-            }
-            if (S & 0x40u) break;
-        }
-        if (ws + 64u >= limit) break;
-        S -= 64u;  // the same position, seen from the next window
-    }
-    p = ws + (S & 0x7Fu);
-    z = S >> 9;
-}
+constexpr uint32_t kStreamAt = 4096;  // byte of LDS at which the stream lies
+constexpr uint32_t kPadWords = 12;     // behind it, for what the walk looks at
 
 void sync_intra(Emul& E) {
     const Image& im = E.im;
@@ -240,12 +113,18 @@ void sync_intra(Emul& E) {
         const uint32_t t0 = (uint32_t)((int32_t)first - base);
         const uint32_t t1 = std::min<uint32_t>(kWG, (uint32_t)((int32_t)nsub - base));
         const uint32_t first_word = first * wps, nwords = (t1 - t0) * wps + 4;
-        strm.assign(nwords, 0xDEADBEEF);
+        strm.assign(nwords + kPadWords, 0xDEADBEEF);
         for (uint32_t r = 0; r < nwords; ++r) strm[r] = bswap(words[first_word + r]);
-        auto fetch = [&](uint32_t c) {
-            if (c >= nwords) abort();  // a lane read outside the staged window
-            return strm[c];
+        // the lanes' bits count from where the stream lies in LDS
+        const uint32_t org = 8 * kStreamAt - (first_word << 5);
+        auto staged = [&](uint32_t b, uint32_t n) {
+            if ((b & 31) || b / 32 - kStreamAt / 4 >= n) abort();  // a lane looked outside the staged stretch
+            return strm[b / 32 - kStreamAt / 4];
         };
+        auto word = [&](uint32_t b) { return staged(b, nwords); };
+        auto walk_word_at = [&](uint32_t p) { return staged(p + org, nwords + kPadWords); };
+        auto tab = [&](uint32_t k) { return im.y.sync_entry_at(k); };
+        auto rows = [&](uint32_t k) { return im.y.sync_row_at(k); };
         // the part of the bitmap the kernel stages with these words
         const bool restart = im.in.restart_interval != 0;
         const uint32_t bm_k0 = first_word >> 3, bm_n = ((first_word + nwords + 7) >> 3) - bm_k0 + 1;
@@ -254,85 +133,73 @@ void sync_intra(Emul& E) {
             return im.bmap[k];
         };
         uint32_t sw[kWG], pnb[kWG], pdc01[kWG], pdc2[kWG];
-        Lane l[kWG];
-        BitWin bw[kWG];
-        int64_t dcacc[kWG];
+        SyncLane l[kWG];
         bool active[kWG];
-        uint32_t tt[kWG];
+        uint32_t tt[kWG], chain[kWG] = {0};  // chain: state in front of its target, once chains have a wavefront each
+        auto start_of = [&](uint32_t k) { return (uint32_t)(base + (int32_t)k) << logL; };
+        auto state_of = [&](const SyncLane& a, uint32_t end) { return pack_state(sync_pos(a) - org - end, (a.S >> 9) & 63u, im.y.unit_of_row(a.row)); };
+        auto start = [&](SyncLane& a, uint32_t p, uint32_t u, uint32_t z) { sync_start(a, p + org, u, z, im.y.upm, kRow0, word, tab, rows); };
+        auto decode = [&](SyncLane& a, uint32_t limit, int64_t& dc, uint32_t& crossed) {
+            a.nb = 0;
+            if (restart)
+                sync_span_rst(a, limit + org, dc, crossed, org, [&](uint32_t p) { sync_start(a, p, 0u, 0u, im.y.upm, kRow0, word, tab, rows); },
+                              [&](uint32_t to) { sync_span(a, to, dc, word, tab, rows); }, bword);
+            else sync_span(a, limit + org, dc, word, tab, rows);
+        };
+        auto put_record = [&](uint32_t k, uint32_t x, uint32_t nb, uint32_t crossed, int64_t dc) {
+            if (nb > 0x7FFFu) abort();  // records in LDS have 15 bits for the units
+            sw[k] = x; pnb[k] = nb | (crossed << 31); pdc01[k] = pack_dc01(dc); pdc2[k] = pack_dc2(dc);
+        };
         for (uint32_t t = 0; t < (uint32_t)kWG; ++t) {
             active[t] = false;
             if (t < t0 || t >= t1) continue;
-            uint32_t i = (uint32_t)(base + (int32_t)t);
-            l[t].p = i << logL; l[t].u = 0; l[t].z = 0; l[t].nb = 0;
-            dcacc[t] = 0;
-            win_init(bw[t], l[t].p, (l[t].p >> 5) - first_word, fetch);
-            prime(l[t], bw[t], E.sx, im.lut.data());
-            uint32_t limit = (i + 1) << logL;
+            int64_t dc = 0;
             uint32_t crossed = 0;
-            if (restart) decode_span_sync_rst(l[t], bw[t], limit, dcacc[t], crossed, E.sx, fetch, im.lut.data(), bword);
-            else decode_span_sync_pairs(l[t], bw[t], limit, dcacc[t], E.sx, fetch, im.lut.data(), im.pairs.data());
-            sw[t] = pack_state(l[t].p - limit, l[t].z, l[t].u);
-            pnb[t] = l[t].nb | (crossed << 31);
-            pdc01[t] = pack_dc01(dcacc[t]);
-            pdc2[t] = pack_dc2(dcacc[t]);
+            start(l[t], start_of(t), 0, 0);
+            decode(l[t], start_of(t + 1), dc, crossed);
+            put_record(t, state_of(l[t], start_of(t + 1)), l[t].nb, crossed, dc);
             active[t] = t + 1 < t1;
             tt[t] = t + 1;
         }
         uint32_t rounds = 0, waves_used = kWG / 64;
+        bool coop = false;
         for (;;) {
-            bool any = false;
-            for (uint32_t t = 0; t < (uint32_t)kWG; ++t) any = any || active[t];
-            if (!any) break;
-            ++rounds;
             uint32_t now = 0;
             for (uint32_t t = 0; t < (uint32_t)kWG; ++t) now += active[t] ? 1u : 0u;
-            const bool coop = im.nslots <= 4u && now <= (restart ? std::min(g_coop_max, g_sync_waves) : g_coop_max);  // stays true once it is
+            if (!now) break;
+            ++rounds;
+            if (!coop && now <= (restart ? std::min(g_coop_max, g_sync_waves) : g_coop_max)) {
+                coop = true;  // from here on a wavefront per chain
+                for (uint32_t t = 0; t < (uint32_t)kWG; ++t)
+                    if (active[t]) chain[t] = state_of(l[t], start_of(tt[t]));
+            }
             // the chains move together where that frees a wavefront; in between a lane goes on with its own
-            const bool packed = ((now + 63u) >> 6) < waves_used;
+            const bool packed = !coop && ((now + 63u) >> 6) < waves_used;
             if (packed) waves_used = (now + 63u) >> 6;
-            uint32_t unit_word[64];
-            for (uint32_t lane = 0; lane < 64; ++lane) unit_word[lane] = coop_unit_word(E.sx, lane);
             for (uint32_t t = 0; t < (uint32_t)kWG; ++t) {
                 if (!active[t]) continue;
-                if (coop) {
-                    const uint32_t limit = ((uint32_t)(base + (int32_t)tt[t]) + 1) << logL;
-                    uint32_t nb, crossed = 0;
-                    // a chain whose stretch holds an interval start is decoded by one lane with the interval rules
-                    if (!restart || next_boundary(l[t].p, limit + 64u, bword) == kNoBoundary) {
-                        coop_span_sync(l[t].p, l[t].u, l[t].z, nb, dcacc[t], limit, first_word, nwords, unit_word, E.sx.upm,
-                                       im.nslots, fetch, im.lut.data());
-                    } else {
-                        l[t].nb = 0;
-                        dcacc[t] = 0;
-                        win_init(bw[t], l[t].p, (l[t].p >> 5) - first_word, fetch);
-                        prime(l[t], bw[t], E.sx, im.lut.data());
-                        decode_span_sync_rst(l[t], bw[t], limit, dcacc[t], crossed, E.sx, fetch, im.lut.data(), bword);
-                        nb = l[t].nb;
-                    }
-                    uint32_t x = pack_state(l[t].p - limit, l[t].z, l[t].u);
-                    bool synced = x == sw[tt[t]];
-                    sw[tt[t]] = x; pnb[tt[t]] = nb | (crossed << 31);
-                    pdc01[tt[t]] = pack_dc01(dcacc[t]);
-                    pdc2[tt[t]] = pack_dc2(dcacc[t]);
-                    ++tt[t];
-                    active[t] = !synced && tt[t] < t1;
-                    continue;
+                const uint32_t limit = start_of(tt[t] + 1);
+                int64_t dc = 0;
+                uint32_t x, nb, crossed = 0;
+                if (packed) {
+                    const uint32_t m = state_of(l[t], start_of(tt[t]));
+                    start(l[t], start_of(tt[t]) + state_prel(m), state_u(m), state_z(m));
                 }
-                l[t].nb = 0;
-                dcacc[t] = 0;
-                if (packed) {  // a chain moved to another lane starts there from its state
-                    win_init(bw[t], l[t].p, (l[t].p >> 5) - first_word, fetch);
-                    prime(l[t], bw[t], E.sx, im.lut.data());
+                uint32_t p = start_of(tt[t]) + state_prel(chain[t]), u = state_u(chain[t]), z = state_z(chain[t]);
+                // (a chain whose stretch holds an interval start is decoded by one lane with the interval rules)
+                if (coop && (!restart || next_boundary(p, limit + 64u, bword) == kNoBoundary)) {
+                    int32_t exact[3];
+                    walk_span(p, u, z, nb, dc, exact, limit, E.walk, walk_word_at, tab);
+                    x = pack_state(p - limit, z, u);
+                } else {
+                    if (coop) start(l[t], p, u, z);
+                    decode(l[t], limit, dc, crossed);
+                    x = state_of(l[t], limit);
+                    nb = l[t].nb;
                 }
-                uint32_t limit = ((uint32_t)(base + (int32_t)tt[t]) + 1) << logL;
-                uint32_t crossed = 0;
-                if (restart) decode_span_sync_rst(l[t], bw[t], limit, dcacc[t], crossed, E.sx, fetch, im.lut.data(), bword);
-                else decode_span_sync_pairs(l[t], bw[t], limit, dcacc[t], E.sx, fetch, im.lut.data(), im.pairs.data());
-                uint32_t x = pack_state(l[t].p - limit, l[t].z, l[t].u);
-                bool synced = x == sw[tt[t]];
-                sw[tt[t]] = x; pnb[tt[t]] = l[t].nb | (crossed << 31);
-                pdc01[tt[t]] = pack_dc01(dcacc[t]);
-                pdc2[tt[t]] = pack_dc2(dcacc[t]);
+                const bool synced = x == sw[tt[t]];
+                put_record(tt[t], x, nb, crossed, dc);
+                chain[t] = x;
                 ++tt[t];
                 active[t] = !synced && tt[t] < t1;
             }
@@ -350,7 +217,9 @@ void sync_inter(Emul& E) {
     const Image& im = E.im;
     const uint32_t nsub = im.nsub, logL = E.logL;
     const uint32_t* words = (const uint32_t*)im.stream.data();
-    auto fetch = [&](uint32_t w) { return bswap(words[w]); };
+    auto word = [&](uint32_t b) { return b / 32 < im.stream.size() / 4 ? bswap(words[b / 32]) : 0u; };
+    auto tab = [&](uint32_t k) { return im.y.sync_entry_at(k); };
+    auto rows = [&](uint32_t k) { return im.y.sync_row_at(k); };
     auto bword = [&](uint32_t k) { return im.bmap[k]; };
     const bool restart = im.in.restart_interval != 0;
     E.inter_changed = 0;
@@ -358,30 +227,42 @@ void sync_inter(Emul& E) {
     // its boundary when the kernel starts, whatever another lane does to that record later in the same round.
     std::vector<uint32_t> seen;
     for (uint32_t b = 0; (uint64_t)(b + 1) * E.seq_len < nsub; ++b) seen.push_back(E.sinfo[(b + 1) * E.seq_len - 1].x);
+    const std::vector<uint32_t> at_start = E.warm;
     for (uint32_t b = 0;; ++b) {
         uint64_t gfirst = (uint64_t)(b + 1) * E.seq_len;
         if (gfirst >= nsub) break;
         uint32_t g = (uint32_t)gfirst, gend = std::min(nsub, g + E.seq_len);
         uint32_t x0 = seen[b];
         if (E.warm[b + 1] == x0) continue;  // the two sequences already form one chain
-        Lane l;
-        BitWin w;
-        l.p = (g << logL) + state_prel(x0); l.z = state_z(x0); l.u = state_u(x0);
-        win_init(w, l.p, l.p >> 5, fetch);
-        prime(l, w, E.sx, im.lut.data());
+        // few of the 64 boundaries of a workgroup to decode from: the wavefront walks them one after the other
+        uint32_t workers = 0;
+        for (uint32_t k = b & ~63u; k < std::min<uint32_t>((b & ~63u) + 64u, (uint32_t)seen.size()); ++k) workers += at_start[k + 1] != seen[k];
+        const bool walks = !restart && workers <= (uint32_t)kInterCoopMax;
+        uint32_t p = (g << logL) + state_prel(x0), u = state_u(x0), z = state_z(x0);
+        SyncLane l;
+        sync_start(l, p, u, z, im.y.upm, kRow0, word, tab, rows);
         bool first = true;
         for (;;) {
-            l.nb = 0;
-            int64_t dcacc = 0;
-            uint32_t limit = (g + 1) << logL;
-            uint32_t crossed = 0;
-            if (restart) decode_span_sync_rst(l, w, limit, dcacc, crossed, E.sx, fetch, im.lut.data(), bword);
-            else decode_span_sync(l, w, limit, dcacc, E.sx, fetch, im.lut.data());
-            SInfo r = {pack_state(l.p - limit, l.z, l.u), l.nb | (crossed << 31), pack_dc01(dcacc), pack_dc2(dcacc)};
-            bool synced = r.x == E.sinfo[g].x;
+            int64_t dc = 0;
+            const uint32_t limit = (g + 1) << logL;
+            uint32_t crossed = 0, nb, x;
+            if (walks) {
+                int32_t exact[3];
+                walk_span(p, u, z, nb, dc, exact, limit, E.walk, word, tab);
+                x = pack_state(p - limit, z, u);
+            } else {
+                l.nb = 0;
+                if (restart)
+                    sync_span_rst(l, limit, dc, crossed, 0u, [&](uint32_t q) { sync_start(l, q, 0u, 0u, im.y.upm, kRow0, word, tab, rows); },
+                                  [&](uint32_t to) { sync_span(l, to, dc, word, tab, rows); }, bword);
+                else sync_span(l, limit, dc, word, tab, rows);
+                nb = l.nb;
+                x = pack_state(sync_pos(l) - limit, (l.S >> 9) & 63u, im.y.unit_of_row(l.row));
+            }
+            const bool synced = x == E.sinfo[g].x;
             if (first && !synced) E.inter_changed++;
             first = false;
-            E.sinfo[g] = r;
+            E.sinfo[g] = SInfo{x, nb | (crossed << 31), pack_dc01(dc), pack_dc2(dc)};
             ++g;
             if (synced || g >= gend) break;
         }
@@ -413,14 +294,13 @@ void scan_and_write(Emul& E, int16_t* coef) {
         const uint32_t first_word = i0 * wps, nwords = nloc * wps + 4;
         strm.assign(nwords, 0xDEADBEEF);
         for (uint32_t r = 0; r < nwords; ++r) strm[r] = bswap(words[first_word + r]);
-        auto fetch = [&](uint32_t c) {
-            if (c >= nwords) abort();
-            return strm[c];
+        const uint32_t org = 8 * kStreamAt - (first_word << 5);
+        auto word = [&](uint32_t b) {
+            if ((b & 31) || b / 32 - kStreamAt / 4 >= nwords) abort();
+            return strm[b / 32 - kStreamAt / 4];
         };
-        auto store = [&](uint32_t k, uint32_t at, int16_t v) {
-            if (k >= total || at > 63) abort();
-            coef[(size_t)k * 64 + at] = v;
-        };
+        auto tab = [&](uint32_t k) { return im.y.write_entry_at(k); };
+        auto rows = [&](uint32_t k) { return im.y.write_row_at(k); };
         const bool restart = im.in.restart_interval != 0;
         const uint32_t bm_k0 = first_word >> 3, bm_n = ((first_word + nwords + 7) >> 3) - bm_k0 + 1;
         auto bword = [&](uint32_t k) {
@@ -442,29 +322,44 @@ void scan_and_write(Emul& E, int16_t* coef) {
                 coef[k] = 0;
             }
         }
+        const uint32_t grp_slot = unit0 * 64u;
         for (uint32_t t = 0; t < nloc; ++t) {
             const uint32_t i = i0 + t;
             const SInfo mine = E.sinfo[i];
             const uint32_t xprev = i ? E.sinfo[i - 1].x : 0u;
-            Lane l;
-            BitWin w;
-            l.p = (i << logL) + state_prel(xprev); l.z = state_z(xprev); l.u = state_u(xprev); l.nb = 0;
-            int32_t p0 = (int16_t)pred[0], p1 = (int16_t)pred[1], p2 = (int16_t)pred[2];
-            uint32_t unit = unit0, flags = 0;
-            if (unit < total && unit % im.in.units_per_mcu != l.u) flags |= kStUnit;
+            const uint32_t u_in = state_u(xprev), z_in = state_z(xprev);
+            uint32_t flags = 0;
+            if (unit0 < total && unit0 % im.in.units_per_mcu != u_in) flags |= kStUnit;
             const uint32_t limit = (i + 1) << logL;
-            if (unit < total) {
-                win_init(w, l.p, (l.p >> 5) - first_word, fetch);
-                prime(l, w, E.sx, im.lut.data());
-                if (restart) decode_span_write_rst(l, w, limit, unit, total, im.in.restart_interval * im.in.units_per_mcu, p0, p1, p2, E.sx, fetch, im.lut.data(), store, flags, bword);
-                else decode_span_write(l, w, limit, unit, total, p0, p1, p2, E.sx, fetch, im.lut.data(), store, flags);
+            WriteLane l;
+            l.unit = unit0;
+            l.seen = 0;
+            write_predictors(l, im.y.component(u_in), (int16_t)pred[0], (int16_t)pred[1], (int16_t)pred[2]);
+            // the values leave in chunks of four slots, counted from the first unit of the group
+            WriteChunk chunk = chunk_start(unit0 * 64u + z_in - grp_slot);
+            auto put = [&](uint32_t slot, int16_t v) {
+                if ((uint64_t)grp_slot + slot >= (uint64_t)total * 64) abort();
+                coef[(size_t)grp_slot + slot] = v;
+            };
+            auto store8 = [&](uint32_t slot, uint64_t v) { for (uint32_t k = 0; k < 4; ++k) put(slot + k, (int16_t)(uint16_t)(v >> (16 * k))); };
+            auto store = [&](uint32_t k, uint32_t at, int16_t v) {
+                if (k >= total || at > 63) abort();
+                chunk_value(chunk, k * 64u + at - grp_slot, v, store8);
+            };
+            if (unit0 < total) {
+                write_start(l, (i << logL) + state_prel(xprev) + org, u_in, z_in, im.y.upm, kRow0, word, tab, rows);
+                if (restart) write_span_rst(l, limit + org, total, im.in.restart_interval * im.in.units_per_mcu, org, im.y.upm, kRow0, word, tab, rows, store, bword, &flags);
+                else write_span(l, limit + org, total, word, tab, rows, store);
             }
+            if (l.seen & kWriteBad) flags |= kStInvalid;
+            chunk_ends(chunk, put);
             if (restart && i == 0) {
                 const uint64_t mcus = (uint64_t)im.in.mcus_x * im.in.mcus_y;
                 if (im.markers != (uint32_t)((mcus + im.in.restart_interval - 1) / im.in.restart_interval) - 1) flags |= kStInvalid;
             }
-            if (unit < total) {
-                if (l.p < limit || pack_state(l.p - limit, l.z, l.u) != mine.x) flags |= kStMismatch;
+            if (l.unit < total) {
+                const uint32_t p = sync_pos(l.s) - org;
+                if (p < limit || pack_state(p - limit, (l.s.S >> 9) & 63u, im.y.unit_of_row(l.s.row)) != mine.x) flags |= kStMismatch;
                 if (i == nsub - 1) flags |= kStShort;
             }
             E.flags |= flags;
@@ -488,7 +383,7 @@ void pixels(const Emul& E, const int16_t* coef_all, uint8_t* pix) {
             const uint32_t m0 = run * M, nm = std::min(M, in.mcus_x - m0), nblk = nm * upm;
             const int16_t* coef = coef_all + ((size_t)mrow * in.mcus_x + m0) * upm * 64;
             for (uint32_t k = 0; k < nblk; ++k) {
-                uint32_t comp = (E.im.sched_comp >> ((k % upm) * 4)) & 15u;
+                uint32_t comp = E.im.y.component(k % upm);
                 for (uint32_t zi = 0; zi < 64; ++zi)
                     blk[k * 72 + (zz[zi] >> 3) * 9 + (zz[zi] & 7)] = (float)coef[k * 64 + zi] * (float)in.qt[in.tq[comp]][zi];
             }
@@ -533,11 +428,7 @@ extern "C" int emul_decode(const uint8_t* file, size_t len, uint32_t L, uint32_t
     while ((1u << E.logL) < L) ++E.logL;
     E.H = H;
     E.seq_len = kWG - H;
-    for (uint32_t u = 0; u < E.im.in.units_per_mcu; ++u)
-        E.rows[u] = make_unit_row(u, E.im.in.units_per_mcu, E.im.sched_dc, E.im.sched_ac, E.im.sched_comp);
-    E.sx.rows = E.rows;
-    E.sx.upm = E.im.in.units_per_mcu;
-    E.sx.pair_of_unit = E.im.pair_of_unit;
+    E.walk = make_walk(E.im.y.walk, E.im.y.sched_comp, E.im.y.upm, E.im.y.t.ndc, kBase);
     unstuff(file + E.im.in.scan_offset, (uint32_t)E.im.in.scan_bytes, E.logL, E.im);
     E.sinfo.assign(E.im.nsub, SInfo{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu});
     const uint32_t nseq = (E.im.nsub + E.seq_len - 1) / E.seq_len;
@@ -595,7 +486,7 @@ extern "C" int emul_build_lut(const uint8_t* bits, const uint8_t* vals, int is_d
 // pair bytes of an AC table built by jpgd_lut.h (lut: the table's kLutEntries entries)
 extern "C" void emul_build_pairs(const uint16_t* lut, uint8_t* pairs) { build_pairs(lut, pairs); }
 
-// The synchronisation pass with two symbols per step against the one with single symbols, from decoder states that
+// The synchronisation pass with two symbols per step (sync_span) against the one with single symbols, from decoder states that
 // need not lie on the true chain: `nstart` starts at pseudo-random subsequences in pseudo-random states, each
 // followed over `span` subsequences by both decoders (the lanes keep their window from one subsequence to the
 // next, as in the kernel's overflow rounds).  Returns the number of subsequences after which the two disagreed in
@@ -603,23 +494,19 @@ extern "C" void emul_build_pairs(const uint16_t* lut, uint8_t* pairs) { build_pa
 // stats[1] = steps of the pair decoder over the same stretches.
 extern "C" int emul_pairs_vs_single(const uint8_t* file, size_t len, uint32_t L, uint32_t nstart, uint32_t span,
                                     uint32_t seed, uint32_t* stats) {
-    Emul E;
-    int rc = prepare(file, len, E.im);
-    if (rc) return -1;
-    Image& im = E.im;
-    if (im.in.restart_interval) return -1;
-    E.logL = 0;
-    while ((1u << E.logL) < L) ++E.logL;
-    for (uint32_t u = 0; u < im.in.units_per_mcu; ++u)
-        E.rows[u] = make_unit_row(u, im.in.units_per_mcu, im.sched_dc, im.sched_ac, im.sched_comp);
-    E.sx.rows = E.rows;
-    E.sx.upm = im.in.units_per_mcu;
-    E.sx.pair_of_unit = im.pair_of_unit;
-    unstuff(file + im.in.scan_offset, (uint32_t)im.in.scan_bytes, E.logL, im);
+    Image im;
+    if (prepare(file, len, im) || im.in.restart_interval) return -1;
+    uint32_t logL = 0;
+    while ((1u << logL) < L) ++logL;
+    unstuff(file + im.in.scan_offset, (uint32_t)im.in.scan_bytes, logL, im);
     const uint32_t* words = (const uint32_t*)im.stream.data();
-    uint32_t steps[2] = {0u, 0u};
-    int which = 0;
-    auto fetch = [&](uint32_t w) { ++steps[which]; return bswap(words[w]); };  // one fetch per step (plus three per window)
+    uint32_t steps = 0;
+    auto at = [&](uint32_t k) { return k < im.stream.size() / 4 ? bswap(words[k]) : 0u; };
+    auto word = [&](uint32_t b) { ++steps; return at(b / 32); };  // one word per step (and up to three where a lane starts)
+    auto tab = [&](uint32_t k) { return im.y.sync_entry_at(k); };
+    auto rows = [&](uint32_t k) { return im.y.sync_row_at(k); };
+    auto single = plain_scan(im.y.units, im.y.upm, im.y.t.lut.data(),
+                             [&](uint32_t p) { return (uint32_t)((((uint64_t)at(p / 32) << 32 | at(p / 32 + 1)) << (p & 31u)) >> 32); });
     uint64_t rng = 0x9E3779B97F4A7C15ull ^ seed;
     auto next = [&]() { rng ^= rng << 13; rng ^= rng >> 7; rng ^= rng << 17; return (uint32_t)(rng >> 16); };
     int bad = 0;
@@ -627,22 +514,19 @@ extern "C" int emul_pairs_vs_single(const uint8_t* file, size_t len, uint32_t L,
     for (uint32_t k = 0; k < nstart; ++k) {
         const uint32_t i0 = next() % (im.nsub - 1u);
         const uint32_t prel = next() % 32u, z = next() % 64u, u = next() % im.in.units_per_mcu;
-        Lane a, b;
-        BitWin wa, wb;
-        a.p = (i0 << E.logL) + prel; a.z = z; a.u = u; a.nb = 0;
-        b = a;
-        which = 0; win_init(wa, a.p, a.p >> 5, fetch); prime(a, wa, E.sx, im.lut.data());
-        which = 1; win_init(wb, b.p, b.p >> 5, fetch); prime(b, wb, E.sx, im.lut.data());
+        PlainLane a = {(i0 << logL) + prel, u, z, 0u};
+        SyncLane b;
+        sync_start(b, a.p, u, z, im.y.upm, kRow0, word, tab, rows);
         for (uint32_t i = i0; i < std::min(im.nsub, i0 + span); ++i) {
-            const uint32_t limit = (i + 1u) << E.logL;
+            const uint32_t limit = (i + 1u) << logL;
             int64_t da = 0, db = 0;
             a.nb = b.nb = 0;
-            which = 0; decode_span_sync(a, wa, limit, da, E.sx, fetch, im.lut.data());
-            which = 1; decode_span_sync_pairs(b, wb, limit, db, E.sx, fetch, im.lut.data(), im.pairs.data());
-            if (a.p != b.p || a.u != b.u || a.z != b.z || a.nb != b.nb || da != db) { ++bad; break; }
+            single.sync(a, limit, da);
+            sync_span(b, limit, db, word, tab, rows);
+            if (a.p != sync_pos(b) || a.u != im.y.unit_of_row(b.row) || a.z != ((b.S >> 9) & 63u) || a.nb != b.nb || da != db) { ++bad; break; }
         }
     }
-    stats[0] = steps[0];
-    stats[1] = steps[1];
+    stats[0] = single.symbols;
+    stats[1] = steps;
     return bad;
 }

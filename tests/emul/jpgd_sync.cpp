@@ -1,6 +1,5 @@
-// Host build of the kernels' lanes (sync_span, write_span and their _rst forms) on tables laid out as the kernels lay them out
-// in LDS, beside the plain lanes that decode symbol by symbol from the tables of jpgd_lut.h.  Test code: the library
-// never calls it.
+// Host build of the kernels' lanes (sync_span, write_span and their _rst forms) and of the walk on tables laid out as the kernels
+// lay them out in LDS, beside the plain lanes of jpgd_plain.h.  Test code: the library never calls it.
 //
 // Build: g++ -O2 -std=c++17 -shared -fPIC -o libjpgd_sync.so jpgd_sync.cpp ../../paper_2111_09219_amd/csrc/jpgd_parse.cpp
 #include <stdlib.h>
@@ -11,104 +10,34 @@
 #include <utility>
 #include <vector>
 
-#include "../../include/jpgd.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_common.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_lane.h"
-#include "../../paper_2111_09219_amd/csrc/jpgd_lut.h"
+#include "jpgd_tables.h"
 #include "jpgd_walk.h"
 
 using namespace jpgd;
 
 namespace {
 
-struct Tables {
-    std::vector<uint16_t> lut;       // build_lut, DC slots first
-    std::vector<uint32_t> sync;      // the kernels' layout: synchronisation pass,
-    std::vector<uint32_t> write;     // write pass
-    uint32_t ndc = 0, nslots = 0;
-    uint32_t words[6] = {0};         // sync_sub_words
-};
-
-// as stage_tables fills them, DC subtables in the order of their entries
-template <bool WRITE>
-bool lay_out(Tables& t, uint32_t base, std::vector<uint32_t>& out) {
-    const uint32_t nac = t.nslots - t.ndc;
-    std::vector<uint8_t> pairs(kPairBytes);
-    uint32_t sub = t.ndc * kSyncDcBytes + nac * kSyncAcBytes, all = 0;
-    for (uint32_t s = 0; s < t.nslots; ++s) all += t.words[s] = sync_sub_words(&t.lut[s * kLutEntries], s < t.ndc);
-    out.assign(sub / 4 + all, 0xDEADBEEFu);
-    for (uint32_t a = 0; a < nac; ++a) {
-        const uint16_t* lut = &t.lut[(t.ndc + a) * kLutEntries];
-        build_pairs(lut, pairs.data());
-        for (uint32_t i = 0; i < (uint32_t)kLutL1; ++i)
-            out[(t.ndc * kSyncDcBytes + a * kSyncAcBytes) / 4 + i] = sync_ac_entry<WRITE>(i, lut[i], pairs[i], base + sub);
-        for (uint32_t k = 0; k < t.words[t.ndc + a]; ++k) out[sub / 4 + k] = pass_entry<WRITE>(lut[kLutL1 + k], false, 0u);
-        sub += 4u * t.words[t.ndc + a];
-    }
-    for (uint32_t s = 0; s < t.ndc; ++s) {
-        const uint16_t* lut = &t.lut[s * kLutEntries];
-        for (uint32_t i = 0; i < 1u << kSyncDcK; ++i) {
-            const uint32_t a = lut[2 * i], b = lut[2 * i + 1], n = sync_dc_sub(a, b);
-            uint32_t& e = out[s * kSyncDcBytes / 4 + i];
-            if (n == 0xFFFFFFFFu) { e = sync_dc_direct<WRITE>(a); continue; }
-            e = sync_escape(n + 1u, base + sub);
-            for (uint32_t j = 0; j < 2u << n; ++j, sub += 4)
-                out.at(sub / 4) = sync_dc_sub_entry<WRITE>(a, b, n, j, lut + kLutL1);
-        }
-    }
-    return sub / 4 == out.size();
-}
-
 struct Scan {
     jpgd_info in;
-    Tables t;
+    Layout y;
     std::vector<uint8_t> stream;
     std::vector<uint32_t> bmap;
     uint32_t nbits = 0;
-    UnitRow rows[8];
-    SyncRow srows[8], wrows[8];
-    uint32_t sched_comp = 0, walk = 0;
+
+    uint32_t word(uint32_t k) const { return k < stream.size() / 4 ? __builtin_bswap32(((const uint32_t*)stream.data())[k]) : 0u; }
+    uint32_t peek(uint32_t p) const { return (uint32_t)(((((uint64_t)word(p >> 5) << 32) | word((p >> 5) + 1u)) << (p & 31u)) >> 32); }
 };
 
-// build_lut's tables for the plain lanes
-struct Lut {
-    const Tables* t;
-    uint32_t operator[](uint32_t k) const { return t->lut.at(k); }
+struct Random {
+    uint64_t r;
+    explicit Random(uint32_t seed) : r(seed * 2654435761ull + 88172645463325252ull) {}
+    uint32_t operator()(uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); }
 };
-
-constexpr uint32_t kBase = 176, kRow0 = 48;   // where the tables and the rows start
 
 int open_scan(const uint8_t* file, size_t len, Scan& S) {
-    const int rc = jpgd_parse(file, len, &S.in);
-    if (rc) return rc;
+    int rc = jpgd_parse(file, len, &S.in);
+    if (rc || (rc = make_layout(S.in, S.y))) return rc;
     const jpgd_info& in = S.in;
-    uint32_t slot_dc[3], slot_ac[3];
-    std::map<uint32_t, uint32_t> dc, ac;
-    for (uint32_t c = 0; c < in.ncomp; ++c) slot_dc[c] = dc.emplace(in.td[c], (uint32_t)dc.size()).first->second;
-    for (uint32_t c = 0; c < in.ncomp; ++c) slot_ac[c] = ac.emplace(in.ta[c], (uint32_t)ac.size()).first->second;
-    S.t.ndc = (uint32_t)dc.size();
-    S.t.nslots = (uint32_t)(dc.size() + ac.size());
-    S.t.lut.assign(S.t.nslots * kLutEntries, 0);
-    for (auto& d : dc) if (!build_lut(in.dht_bits[0][d.first], in.dht_vals[0][d.first], true, &S.t.lut[d.second * kLutEntries])) return JPGD_E_TABLE;
-    for (auto& a : ac) if (!build_lut(in.dht_bits[1][a.first], in.dht_vals[1][a.first], false, &S.t.lut[(S.t.ndc + a.second) * kLutEntries])) return JPGD_E_TABLE;
-    if (!lay_out<false>(S.t, kBase, S.t.sync) || !lay_out<true>(S.t, kBase, S.t.write)) return JPGD_E_TABLE;
-    uint32_t sched_dc = 0, sched_ac = 0, sched_comp = 0, u = 0;
-    for (uint32_t c = 0; c < in.ncomp; ++c)
-        for (uint32_t k = 0, nu = in.ncomp == 3 && c == 0 ? (uint32_t)in.hsamp[0] * in.vsamp[0] : 1u; k < nu; ++k, ++u) {
-            sched_dc |= slot_dc[c] << (4 * u);
-            sched_ac |= (S.t.ndc + slot_ac[c]) << (4 * u);
-            sched_comp |= c << (4 * u);
-        }
-    for (uint32_t k = 0; k < u; ++k) {
-        S.rows[k] = make_unit_row(k, u, sched_dc, sched_ac, sched_comp);
-        S.srows[k] = SyncRow{kBase + S.t.ndc * kSyncDcBytes + (((sched_ac >> (4 * k)) & 15) - S.t.ndc) * kSyncAcBytes,
-                             kBase + ((sched_dc >> (4 * ((k + 1) % u))) & 15) * kSyncDcBytes, S.rows[k].dcmul,
-                             kRow0 + S.rows[k].next * (uint32_t)sizeof(SyncRow)};
-        S.wrows[k] = S.srows[k];
-        S.wrows[k].dcmul = ((sched_comp >> (4 * k)) & 15) != ((sched_comp >> (4 * ((k + 1) % u))) & 15) ? 1u : 0u;
-    }
-    S.sched_comp = sched_comp;
-    S.walk = walk_word(u, sched_dc, sched_ac);
     const uint8_t* p = file + in.scan_offset;
     S.bmap.assign(in.scan_bytes / 32 + 80, 0);
     for (size_t k = 0; k < in.scan_bytes; ++k) {
@@ -134,99 +63,80 @@ extern "C" int sync_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32
     Scan S;
     const int rc = open_scan(file, len, S);
     if (rc) return -rc;
-    const uint32_t* words = (const uint32_t*)S.stream.data();
-    auto fetch = [&](uint32_t c) { return c < S.stream.size() / 4 ? __builtin_bswap32(words[c]) : 0u; };
     auto word = [&](uint32_t b) {
         if ((b & 31u) || b - org > S.nbits + 4096u) __builtin_trap();
-        return fetch((b - org) >> 5);
+        return S.word((b - org) >> 5);
     };
-    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.sync.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { if (k < kRow0 || k % sizeof(SyncRow) || (k - kRow0) / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
+    auto tab = [&](uint32_t k) { return S.y.sync_entry_at(k); };
+    auto rows = [&](uint32_t k) { return S.y.sync_row_at(k); };
     auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
-    Syntax sx;
-    sx.rows = S.rows;
-    sx.upm = S.in.units_per_mcu;
+    auto plain = plain_scan(S.y.units, S.y.upm, S.y.t.lut.data(), [&](uint32_t p) { return S.peek(p); });
     const bool restart = S.in.restart_interval != 0;
-    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
-    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    Random rnd(seed);
     int bad = 0;
     *compared = 0;
     for (uint32_t k = 0; k < tries; ++k) {
         const uint32_t nsub = (S.nbits + L - 1) / L, i0 = rnd(nsub);
-        const Lut lut{&S.t};
-        Lane a;
-        BitWin w;
+        PlainLane a;
         a.p = i0 * L + (rnd(4) ? rnd(31) : 0u);
         if (a.p >= S.nbits || (org >> 31 && a.p + org >= org)) continue;   // (a negative org: the stretch starts at bit -org)
-        a.u = rnd(sx.upm); a.z = rnd(3) ? rnd(64) : 0u;
+        a.u = rnd(S.y.upm); a.z = rnd(3) ? rnd(64) : 0u;
         SyncLane b;
-        win_init(w, a.p, a.p >> 5, fetch);
-        prime(a, w, sx, lut);
-        sync_start(b, a.p + org, a.u, a.z, sx.upm, kRow0, word, tab, rows);
+        sync_start(b, a.p + org, a.u, a.z, S.y.upm, kRow0, word, tab, rows);
         for (uint32_t i = i0; i < i0 + spans && i < nsub; ++i) {
             const uint32_t limit = (i + 1) * L;
             int64_t da = 0, db = 0;
             uint32_t ca = 0, cb = 0;
             a.nb = b.nb = 0;
             if (restart) {
-                decode_span_sync_rst(a, w, limit, da, ca, sx, fetch, lut, bword);
-                sync_span_rst(b, limit + org, db, cb, org, [&](uint32_t p) { sync_start(b, p, 0u, 0u, sx.upm, kRow0, word, tab, rows); },
+                plain.sync_rst(a, limit, da, ca, bword);
+                sync_span_rst(b, limit + org, db, cb, org, [&](uint32_t p) { sync_start(b, p, 0u, 0u, S.y.upm, kRow0, word, tab, rows); },
                               [&](uint32_t to) { sync_span(b, to, db, word, tab, rows); }, bword);
             } else {
-                decode_span_sync(a, w, limit, da, sx, fetch, lut);
+                plain.sync(a, limit, da);
                 sync_span(b, limit + org, db, word, tab, rows);
             }
             ++*compared;
-            const uint32_t u = (b.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.S >> 9) & 63u;
-            if (sync_pos(b) - org != a.p || u != a.u || z != a.z || a.nb != b.nb || da != db || ca != cb) { ++bad; break; }
+            if (sync_pos(b) - org != a.p || S.y.unit_of_row(b.row) != a.u || ((b.S >> 9) & 63u) != a.z || a.nb != b.nb || da != db || ca != cb) { ++bad; break; }
         }
     }
     return bad;
 }
 
 // The write pass's lanes from `tries` states: what they store, unit, position, state, predictors and flags must be those of
-// decode_span_write (_rst).  States: random ones, and with `chain` those the true chain passes through (both flag
-// nothing there).  Predictors are compared in scans without intervals: a lane that has moved to the start of one has yet to
-// clear them.  total: units after which they stop (0: all of the image).
+// the plain ones.  States: random ones, and with `chain` those the true chain passes through (both flag nothing there).
+// Predictors are compared in scans without intervals: a lane that has moved to the start of one has yet to clear them.
+// total: units after which they stop (0: all of the image).
 extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint32_t tries, int chain, uint32_t org, uint32_t total,
                               uint32_t seed, uint32_t* stored) {
     Scan S;
     const int rc = open_scan(file, len, S);
     if (rc) return -rc;
-    const uint32_t* words = (const uint32_t*)S.stream.data();
-    auto fetch = [&](uint32_t c) { return c < S.stream.size() / 4 ? __builtin_bswap32(words[c]) : 0u; };
     auto word = [&](uint32_t b) {
         if ((b & 31u) || b - org > S.nbits + 4096u) __builtin_trap();
-        return fetch((b - org) >> 5);
+        return S.word((b - org) >> 5);
     };
-    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.write.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { if (k < kRow0 || k % sizeof(SyncRow) || (k - kRow0) / sizeof(SyncRow) >= S.in.units_per_mcu) __builtin_trap(); return S.wrows[(k - kRow0) / sizeof(SyncRow)]; };
+    auto tab = [&](uint32_t k) { return S.y.write_entry_at(k); };
+    auto rows = [&](uint32_t k) { return S.y.write_row_at(k); };
     auto bword = [&](uint32_t k) { return k < S.bmap.size() ? S.bmap[k] : 0u; };
-    Syntax sx;
-    sx.rows = S.rows;
-    const uint32_t upm = sx.upm = S.in.units_per_mcu;
+    auto plain = plain_scan(S.y.units, S.y.upm, S.y.t.lut.data(), [&](uint32_t p) { return S.peek(p); });
+    const uint32_t upm = S.y.upm;
     const bool restart = S.in.restart_interval != 0;
     const uint32_t upi = S.in.restart_interval * upm;
-    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
-    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    Random rnd(seed);
     int bad = 0;
     *stored = 0;
-    Lane c;   // the true chain
-    BitWin cw;
-    c.p = c.u = c.z = c.nb = 0;
-    win_init(cw, 0, 0, fetch);
-    prime(c, cw, sx, S.t.lut.data());
+    PlainLane c = {0u, 0u, 0u, 0u};   // the true chain
     const uint32_t nsub = (S.nbits + L - 1) / L;
     if (!total) total = S.in.total_units;
     for (uint32_t k = 0; k < tries && (!chain || k < nsub); ++k) {
         const uint32_t i = chain ? k : rnd(nsub), limit = (i + 1) * L;
-        Lane a;
-        BitWin w;
+        PlainLane a;
         a.p = chain ? c.p : i * L + rnd(31);
         a.u = chain ? c.u : rnd(upm);
         a.z = chain ? c.z : rnd(3) ? rnd(64) : 0u;
         a.nb = 0;
-        const Lane in = a;
+        const PlainLane in = a;
         // (no lane starts in the padding in front of an interval)
         const bool padding = restart && next_boundary(a.p, a.p + 8u, bword) != kNoBoundary && next_boundary(a.p, a.p + 8u, bword) > a.p;
         if (a.p < S.nbits && !(org >> 31 && a.p + org >= org) && !padding) {
@@ -234,25 +144,22 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
             const int32_t d[3] = {(int32_t)rnd(4096) - 2048, (int32_t)rnd(4096) - 2048, (int32_t)rnd(4096) - 2048};
             std::vector<std::pair<uint64_t, int>> sa, sb;
             uint32_t ua = unit, fa = 0, fb = 0;
-            int32_t p0 = d[0], p1 = d[1], p2 = d[2];
-            win_init(w, a.p, a.p >> 5, fetch);
-            const Lut lut{&S.t};
-            prime(a, w, sx, lut);
+            int32_t pred[3] = {d[0], d[1], d[2]};
             auto store_a = [&](uint32_t u, uint32_t at, int16_t v) { sa.push_back({(uint64_t)u * 64 + at, v}); };
-            if (restart) decode_span_write_rst(a, w, limit, ua, total, upi, p0, p1, p2, sx, fetch, lut, store_a, fa, bword);
-            else decode_span_write(a, w, limit, ua, total, p0, p1, p2, sx, fetch, lut, store_a, fa);
+            if (restart) plain.write_rst(a, limit, ua, total, upi, pred, store_a, fa, bword);
+            else plain.write(a, limit, ua, total, pred, store_a, fa);
             WriteLane b;
             b.unit = unit;
             b.seen = 0;
             auto store_b = [&](uint32_t u, uint32_t at, int16_t v) { if (at > 63u) __builtin_trap(); sb.push_back({(uint64_t)u * 64 + at, v}); };
-            write_predictors(b, (S.sched_comp >> (4 * in.u)) & 15, d[0], d[1], d[2]);
+            write_predictors(b, S.y.component(in.u), d[0], d[1], d[2]);
             write_start(b, in.p + org, in.u, in.z, upm, kRow0, word, tab, rows);
             if (restart) write_span_rst(b, limit + org, total, upi, org, upm, kRow0, word, tab, rows, store_b, bword, &fb);
             else write_span(b, limit + org, total, word, tab, rows, store_b);
             if (b.seen & kWriteBad) fb |= kStInvalid;
-            const uint32_t u = (b.s.row - kRow0) / (uint32_t)sizeof(SyncRow), z = (b.s.S >> 9) & 63u;
+            const uint32_t u = S.y.unit_of_row(b.s.row), z = (b.s.S >> 9) & 63u;
             WriteLane want = b;
-            write_predictors(want, (S.sched_comp >> (4 * a.u)) & 15, p0, p1, p2);
+            write_predictors(want, S.y.component(a.u), pred[0], pred[1], pred[2]);
             if (sa != sb || ua != b.unit || fa != fb || sync_pos(b.s) - org != a.p || u != a.u || z != a.z || (chain && fa) ||
                 (!restart && (want.p0 != b.p0 || want.p1 != b.p1 || want.p2 != b.p2)))
                 ++bad;
@@ -276,8 +183,8 @@ extern "C" int write_vs_plain(const uint8_t* file, size_t len, uint32_t L, uint3
         if (chain) {
             int64_t dc = 0;
             uint32_t crossed = 0;
-            if (restart) decode_span_sync_rst(c, cw, limit, dc, crossed, sx, fetch, S.t.lut.data(), bword);
-            else decode_span_sync(c, cw, limit, dc, sx, fetch, S.t.lut.data());
+            if (restart) plain.sync_rst(c, limit, dc, crossed, bword);
+            else plain.sync(c, limit, dc);
         }
     }
     return bad;
@@ -289,16 +196,14 @@ extern "C" int lanes_restarted(const uint8_t* file, size_t len, uint32_t tries, 
     Scan S;
     const int rc = open_scan(file, len, S);
     if (rc) return -rc;
-    const uint32_t* words = (const uint32_t*)S.stream.data();
-    auto word = [&](uint32_t b) { return b / 32 < S.stream.size() / 4 ? __builtin_bswap32(words[b / 32]) : 0u; };
-    auto tab = [&](uint32_t k) { return S.t.sync.at((k - kBase) / 4); };
-    auto wtab = [&](uint32_t k) { return S.t.write.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
-    auto wrows = [&](uint32_t k) { return S.wrows[(k - kRow0) / sizeof(SyncRow)]; };
-    const uint32_t upm = S.in.units_per_mcu;
-    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
-    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
-    auto unit_of = [&](const SyncLane& l) { return (l.row - kRow0) / (uint32_t)sizeof(SyncRow); };
+    auto word = [&](uint32_t b) { return S.word(b >> 5); };
+    auto tab = [&](uint32_t k) { return S.y.sync_entry_at(k); };
+    auto wtab = [&](uint32_t k) { return S.y.write_entry_at(k); };
+    auto rows = [&](uint32_t k) { return S.y.sync_row_at(k); };
+    auto wrows = [&](uint32_t k) { return S.y.write_row_at(k); };
+    const uint32_t upm = S.y.upm;
+    Random rnd(seed);
+    auto unit_of = [&](const SyncLane& l) { return S.y.unit_of_row(l.row); };
     int bad = 0;
     *compared = 0;
     for (uint32_t k = 0; k < tries; ++k) {
@@ -334,16 +239,14 @@ extern "C" int walk_vs_lanes(const uint8_t* file, size_t len, uint32_t L, uint32
     Scan S;
     const int rc = open_scan(file, len, S);
     if (rc) return -rc;
-    const uint32_t* words = (const uint32_t*)S.stream.data();
-    auto word = [&](uint32_t b) { return b / 32 < S.stream.size() / 4 ? __builtin_bswap32(words[b / 32]) : 0u; };
-    auto tab = [&](uint32_t k) { if (k < kBase || (k & 3u)) __builtin_trap(); return S.t.sync.at((k - kBase) / 4); };
-    auto rows = [&](uint32_t k) { return S.srows[(k - kRow0) / sizeof(SyncRow)]; };
-    const uint32_t upm = S.in.units_per_mcu;
-    const Walk w = make_walk(S.walk, S.sched_comp, upm, S.t.ndc, kBase);
+    auto word = [&](uint32_t b) { return S.word(b >> 5); };
+    auto tab = [&](uint32_t k) { return S.y.sync_entry_at(k); };
+    auto rows = [&](uint32_t k) { return S.y.sync_row_at(k); };
+    const uint32_t upm = S.y.upm;
+    const Walk w = make_walk(S.y.walk, S.y.sched_comp, upm, S.y.t.ndc, kBase);
     *kinds = 0;
-    for (uint32_t u = 0; u < upm; ++u) *kinds = std::max(*kinds, ((S.walk >> (2u * u)) & 3u) + 1u);
-    uint64_t r = seed * 2654435761ull + 88172645463325252ull;
-    auto rnd = [&](uint32_t n) { r ^= r << 13; r ^= r >> 7; r ^= r << 17; return (uint32_t)(r % n); };
+    for (uint32_t u = 0; u < upm; ++u) *kinds = std::max(*kinds, ((S.y.walk >> (2u * u)) & 3u) + 1u);
+    Random rnd(seed);
     int bad = 0;
     *compared = 0;
     for (uint32_t k = 0; k < tries; ++k) {
@@ -359,7 +262,7 @@ extern "C" int walk_vs_lanes(const uint8_t* file, size_t len, uint32_t L, uint32
             walk_span(p, u, z, nb, da, exact, (i + 1) * L, w, word, tab);
             sync_span(b, (i + 1) * L, db, word, tab, rows);
             const bool fits = std::abs(exact[0]) < 16384 && std::abs(exact[1]) < 16384 && std::abs(exact[2]) < 16384;
-            if (p != sync_pos(b) || u != (b.row - kRow0) / sizeof(SyncRow) || z != ((b.S >> 9) & 63u) || nb != b.nb || (fits && da != db)) { ++bad; break; }
+            if (p != sync_pos(b) || u != S.y.unit_of_row(b.row) || z != ((b.S >> 9) & 63u) || nb != b.nb || (fits && da != db)) { ++bad; break; }
         }
     }
     return bad;

@@ -72,7 +72,7 @@ void walk_span(uint32_t& p, uint32_t& u, uint32_t& z, uint32_t& nb, int64_t& dc,
     const uint32_t next = cur & 15u;
     u = next == 0u ? w.upm - 1u : next - 1u;
     const int32_t s0 = (int32_t)(int16_t)(dc_a & 0xFFFFu), s1 = (int32_t)(dc_a - (uint32_t)s0) >> 16;
-    dc = (int64_t)s0 + ((int64_t)s1 << 15) + ((int64_t)(int32_t)dc_b << 30);
+    dc = (int64_t)s0 + (int64_t)s1 * (1 << 15) + (int64_t)(int32_t)dc_b * (1 << 30);
 }
 
 }  // namespace jpgd

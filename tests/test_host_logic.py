@@ -148,7 +148,7 @@ def emul():
     lib_path = os.path.join(EMUL_DIR, "libjpgd_emul.so")
     src = os.path.join(EMUL_DIR, "jpgd_emul.cpp")
     csrc = os.path.join(ROOT, "paper_2111_09219_amd", "csrc")
-    deps = [src] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
+    deps = [src] + [os.path.join(EMUL_DIR, f) for f in os.listdir(EMUL_DIR) if f.endswith(".h")] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
     if not os.path.exists(lib_path) or any(os.path.getmtime(d) > os.path.getmtime(lib_path) for d in deps):
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", lib_path, src,
                                os.path.join(csrc, "jpgd_parse.cpp")])
@@ -358,7 +358,7 @@ def test_host_walkthrough_reproduces_oracle(emul, sub, opt, q, shape, L, H, coop
     try:
         rc, coef, pix, sinfo, stream, stats, o = _emul_run(emul, data, L, H)
     finally:
-        emul.emul_set_coop_max(6)   # the library's value (kCoopMax)
+        emul.emul_set_coop_max(4)   # the library's value for four wavefronts (kCoopMax)
     assert rc == 0 and stats[3] == 0
     assert np.array_equal(stream, o.unstuffed())
     ref = o.coefficients()
@@ -381,8 +381,7 @@ def test_host_walkthrough_reproduces_oracle(emul, sub, opt, q, shape, L, H, coop
 
 def test_host_walkthrough_six_tables_and_1x2_sampling(emul):
     """Layouts the encoder of the workloads does not write, made by header surgery: a file whose three components
-    each have tables of their own (six tables: more than the wavefront-per-chain rounds handle, so they stay
-    off), and a file whose luma is sampled 1x2 (two luma units one above the other in the MCU)."""
+    each have tables of their own (six tables, three kinds of data units), and a file whose luma is sampled 1x2 (two luma units one above the other in the MCU)."""
     px = small_image(5, 197, 331, sigma=9.0)
     plain = encode_jpeg(px, 90, "444", False).data
     six = jf.with_tables_of_its_own_for_the_third_component(plain)
@@ -434,12 +433,12 @@ def test_host_walkthrough_with_restart_intervals(emul, sub, opt, q, shape, L, H,
     data = encode_jpeg(px, q, sub, opt, restart_interval=ri).data
     # with the switch at 64 chains and a wavefront for each of up to 16 chains many overflow rounds run one wavefront
     # per chain, which hands chains whose stretch holds an interval start to a single lane
-    emul.emul_set_coop_max(64 if ri in (2, 7, 1000) else 6)
+    emul.emul_set_coop_max(64 if ri in (2, 7, 1000) else 4)
     emul.emul_set_sync_waves(16 if ri in (2, 7, 1000) else 4)
     try:
         rc, coef, pix, sinfo, stream, stats, o = _emul_run(emul, data, L, H)
     finally:
-        emul.emul_set_coop_max(6)
+        emul.emul_set_coop_max(4)
         emul.emul_set_sync_waves(4)
     assert rc == 0 and stats[3] == 0
     assert o.restart_interval == ri
@@ -511,14 +510,14 @@ def test_host_walkthrough_survives_random_damage(emul, sub, opt, ri):
                 continue
             bad[pos] = v
         L, H = [(128, 16), (256, 0), (1024, 32)][trial % 3]
-        emul.emul_set_coop_max([6, 64, 0][trial % 3])
+        emul.emul_set_coop_max([4, 64, 0][trial % 3])
         try:
             try:
                 rc, coef, pix, sinfo, stream, stats, o = _emul_run(emul, bad, L, H)
             except OracleError:
                 continue                         # the oracle's parser already refuses the file
         finally:
-            emul.emul_set_coop_max(6)
+            emul.emul_set_coop_max(4)
         assert rc in (0, -6)
         if rc == 0:
             try:

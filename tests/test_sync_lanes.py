@@ -19,7 +19,7 @@ EMUL_DIR = os.path.join(ROOT, "tests", "emul")
 def lanes():
     lib_path, src = os.path.join(EMUL_DIR, "libjpgd_sync.so"), os.path.join(EMUL_DIR, "jpgd_sync.cpp")
     csrc = os.path.join(ROOT, "paper_2111_09219_amd", "csrc")
-    deps = [src, os.path.join(EMUL_DIR, "jpgd_walk.h")] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
+    deps = [src] + [os.path.join(EMUL_DIR, f) for f in os.listdir(EMUL_DIR) if f.endswith(".h")] + [os.path.join(csrc, f) for f in os.listdir(csrc)]
     if not os.path.exists(lib_path) or any(os.path.getmtime(d) > os.path.getmtime(lib_path) for d in deps):
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", lib_path, src,
                                os.path.join(csrc, "jpgd_parse.cpp")])
