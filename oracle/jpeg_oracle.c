@@ -381,7 +381,7 @@ typedef struct { int64_t p; int u, z; } orc_state;
  * DC table when z == 0, else the AC table of the unit's component (Section 4.1).
  * Rules where the paper is silent (they matter only for decoders that are not yet
  * synchronised, or corrupt input): no matching codeword -> consume one bit, which in front
- * of a DC value takes that value's slot too (z becomes 1), else leave the state; AC symbol with zero size and run not in {0,15} -> end of block;
+ * of a DC value takes that value's slot and the next (z becomes 2), else leave the state; AC symbol with zero size and run not in {0,15} -> end of block;
  * z running past 63 -> unit complete.
  */
 static void step(const orc_image* im, bitrd* r, orc_state* s, orc_symbol* sym) {
@@ -394,7 +394,7 @@ static void step(const orc_image* im, bitrd* r, orc_state* s, orc_symbol* sym) {
     int advance; /* zig-zag slots covered */
     if (s->z == 0) {
         int t = read_symbol(r, &im->huff[0][in->td[c]]);
-        if (t < 0) { sym->kind = 3; sym->length = 1; s->p += 1; s->z = 1; return; }
+        if (t < 0) { sym->kind = 3; sym->length = 1; s->p += 1; s->z = 2; return; }
         sym->size = t > 16 ? 16 : t; /* DC symbols are plain sizes; valid streams use 0..11 */
         sym->value = extend(read_bits(r, sym->size), sym->size);
         advance = 1;

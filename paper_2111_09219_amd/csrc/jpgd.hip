@@ -708,7 +708,7 @@ int enqueue_call(Call& c, int n, const jpgd_info* infos, const uint8_t* d_scans,
     // with restart intervals have a few less: their kernel needs more registers.
     uint32_t sync_waves = (uint32_t)(kWG / 64);
     {
-        const uint32_t slots = any_restart ? 28u : 32u;  // the kernel for restart intervals needs 66 to 69 registers: 7 per SIMD
+        const uint32_t slots = any_restart ? 28u : 32u;  // the kernel for restart intervals needs 66 registers: 7 per SIMD
         const uint32_t by_lds = (uint32_t)(160u * 1024u / c.lds_sync), by_grid = (pl.seqs + 255u) / 256u;
         const uint32_t per_cu = by_lds < by_grid ? (by_lds ? by_lds : 1u) : by_grid;
         const uint32_t most = pl.L >= 256u ? (uint32_t)kSyncWavesMax : 8u;

@@ -842,7 +842,7 @@ __device__ __forceinline__ void coop_span_kinds(uint32_t& p_io, uint32_t& u_io, 
     "s_add_u32 %[dcb], %[dcb], %[t]\n"                                                                     \
     "s_add_u32 %[dca], %[dca], %[v]\n"                                                                     \
     "s_and_b32 %[r], %[r], 0x7e1f\n"                                                                       \
-    "s_add_u32 %[S], %[S], %[r]\n"        /* the index becomes 1 */                                        \
+    "s_add_u32 %[S], %[S], %[r]\n"        /* the index becomes 1 (2 where no codeword starts) */             \
     "s_bitcmp1_b32 %[S], 6\n"                                                                              \
     "s_cbranch_scc1 29f\n"                                                                                 \
     THIRD("s_bitcmp1_b32 %[cur], %[kind] + 1\n"                                                            \

@@ -88,21 +88,18 @@ constexpr uint32_t kSyncSecond = 0x7E0Fu;      // the same of the second symbol,
 constexpr uint32_t kSyncPairBits = 9u;         // most bits a first symbol with a second one behind it takes
 static_assert(kSyncDcK == kSyncAcK - 1u, "subtables of both kinds are indexed from the last bit of a 10-bit index on");
 
-// Every entry of a DC table covers the one slot of a DC symbol, also where no codeword starts (which takes a bit): the symbol
-// behind it comes from the AC table, and with index 0 the lane's state (position, unit, index) would say otherwise to whoever
-// takes the chain over.  Such bits are met off the true chain, or in a damaged stream.
-constexpr uint32_t kSyncDcSlot = 1u << 9;
 // second-level entry (or first-level one that is no escape) of build_lut, with pair byte pb (0: none)
 JPGD_HD uint32_t sync_entry(uint32_t e, bool is_dc, uint32_t pb) {
     const uint32_t slots = pb >> 4;
-    return (e & kSyncStep) | (is_dc ? kSyncDcSlot : 0u) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
+    return (e & kSyncStep) | (is_dc ? lut_size(e) << 20 : ((pb & 15u) | ((slots == 15u ? kAdvEob : slots) << 9)) << 16);
 }
 constexpr uint32_t kWriteInside = 1u << 16, kWriteNoCode = 1u << 17;
 constexpr int32_t kWriteValue = 1 << 30, kWriteDc = 3 << 29;
 JPGD_HD uint32_t write_entry(uint32_t e, bool is_dc) {
     const uint32_t slots = lut_adv(e), size = lut_size(e);
-    return (e & kSyncStep) | (is_dc ? kSyncDcSlot : 0u) | (size << 20) | (slots == 0u ? kWriteNoCode : !is_dc && slots != kAdvEob ? kWriteInside : 0u) |
-           (uint32_t)(slots == 0u ? 0 : is_dc ? kWriteDc : size != 0u ? kWriteValue : 0);
+    const bool coded = is_dc ? slots == 1u : slots != 0u;
+    return (e & kSyncStep) | (size << 20) | (!coded ? kWriteNoCode : !is_dc && slots != kAdvEob ? kWriteInside : 0u) |
+           (uint32_t)(!coded ? 0 : is_dc ? kWriteDc : size != 0u ? kWriteValue : 0);
 }
 // either, as the tables of the pass need it
 template <bool WRITE>
@@ -143,7 +140,7 @@ JPGD_HD uint32_t sync_dc_sub_entry(uint32_t a, uint32_t b, uint32_t n, uint32_t 
     return pass_entry<WRITE>(l2[lut_esc_offset(e) + ((j & ((1u << n) - 1u)) >> (n - k))], true, 0u);
 }
 template <bool WRITE = false>
-JPGD_HD uint32_t sync_dc_direct(uint32_t a) { return pass_entry<WRITE>(lut_esc(a) ? 1u : a, true, 0u); }
+JPGD_HD uint32_t sync_dc_direct(uint32_t a) { return pass_entry<WRITE>(lut_esc(a) ? kDcNoCode : a, true, 0u); }
 
 // Words of subtables that a table of build_lut needs in this layout (at most 1022).
 inline uint32_t sync_sub_words(const uint16_t* lut, bool is_dc) {

@@ -56,10 +56,10 @@ inline bool build_lut(const uint8_t bits[16], const uint8_t* vals, bool is_dc, u
                 if (maxlen[prefix] < len) maxlen[prefix] = (uint8_t)len;
             }
         }
-    // second level: entries 0 and 1 are the shared "no codeword" record (one bit, nothing else), then one
+    // second level: entries 0 and 1 are the shared "no codeword" record, then one
     // subtable per escaping prefix; subtables hold 2, 4, .. 64 entries, so every offset is even
     uint16_t* l2 = out + kLutL1;
-    const uint16_t invalid = 1u;
+    const uint16_t invalid = (uint16_t)(is_dc ? kDcNoCode : 1u);
     for (int i = 0; i < kLutL2; ++i) l2[i] = invalid;
     uint32_t used = 2;
     uint32_t suboff[kLutL1];

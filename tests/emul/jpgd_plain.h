@@ -45,8 +45,8 @@ struct PlainScan {
             e = lut[table + (uint32_t)kLutL1 + lut_esc_offset(e) + ((bits >> (32 - kLutK - n)) & ((1u << n) - 1u))];
         }
         s.size = lut_size(e);
-        s.coded = lut_adv(e) != 0u;
-        s.slots = s.coded ? lut_adv(e) : s.is_dc ? 1u : 0u;
+        s.slots = lut_adv(e);
+        s.coded = s.is_dc ? s.slots == 1u : s.slots != 0u;
         s.value = symbol_value(bits, lut_total(e), s.size);
         l.p += lut_total(e);
         l.z += s.slots;

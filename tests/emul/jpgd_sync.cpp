@@ -293,9 +293,10 @@ extern "C" int sync_table_vs_lut(const uint8_t* bits, const uint8_t* vals, int i
         uint32_t w = t.write.at(peek >> (32u - (is_dc ? kSyncDcK : kSyncAcK)));
         if (w & kSyncEsc) w = t.write.at((sync_escape_at(w, peek) - kBase) / 4);
         const bool inside = !is_dc && lut_adv(e) != 0u && lut_adv(e) != kAdvEob;
-        const uint32_t slots = is_dc ? 1u : lut_adv(e);   // (a DC table's also where no codeword starts)
-        bad += w != ((e & 31u) | slots << 9 | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (lut_adv(e) == 0u ? kWriteNoCode : 0u) |
-                    (lut_adv(e) == 0u ? 0u : is_dc ? 3u << 29 : lut_size(e) ? 1u << 30 : 0u));
+        const uint32_t slots = lut_adv(e);
+        const bool coded = is_dc ? slots == 1u : slots != 0u;
+        bad += (is_dc && slots != 1u && slots != 2u) || w != ((e & 31u) | slots << 9 | lut_size(e) << 20 | (inside ? kWriteInside : 0u) | (coded ? 0u : kWriteNoCode) |
+                    (!coded ? 0u : is_dc ? 3u << 29 : lut_size(e) ? 1u << 30 : 0u));
         bad += (s & 31u) != lut_total(e) || ((s >> 9) & 63u) != slots || ((s >> 20) & 15u) != (is_dc ? lut_size(e) : 0u) || (s & 0x81E0u);
     }
     return bad;
